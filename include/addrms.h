@@ -445,7 +445,7 @@ int addrms_rstd_probe(const double* ss, int64_t n, int64_t N, float eps, float* 
  *   n                      0 .. 2^32-1 (the counters are 32 bits wide; more is INVALID_ARG)
  *   counts_out             device, 16-byte aligned; receives the verdict
  *   stream                 a hipStream_t passed as void*; NULL = the default stream
- * Blocking: allocates a buffer of per-workgroup partial counts (16 bytes per 4096 elements, at most 64 KiB),
+ * Blocking: allocates a buffer of per-workgroup partial counts (16 bytes per workgroup, at most 8 KiB),
  * runs the two kernels of the gate on `stream`, waits for them and frees the buffer.  The counts are exact and
  * cost the same whether nothing or everything disagrees (no atomics). */
 typedef struct addrms_gate_counts {
@@ -459,11 +459,11 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
 
 /* addrms_gate_probe for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments and the same verdict in counts_out, but the
- * per-workgroup partial counts live in a 64 KiB array that is part of the library's device code (one copy per GPU,
+ * per-workgroup partial counts live in an 8 KiB array that is part of the library's device code (one copy per GPU,
  * held until the process ends), so this call allocates nothing, frees nothing and does not wait: both kernels
  * are only enqueued on `stream`, and counts_out is valid once the stream has reached them.  Nothing in it is a
  * memset, so a capturing caller records two kernel nodes.  n beyond 2^32-1 is INVALID_ARG as above (the array
- * itself never limits n: a launch uses at most 4096 slots whatever n is).  Every call on a GPU shares that GPU's
+ * itself never limits n: a launch uses at most 512 slots whatever n is).  Every call on a GPU shares that GPU's
  * array: calls that may overlap in time on one GPU (different streams, concurrent graphs) race on it and must be
  * serialised by the caller; calls on one stream are ordered and safe. */
 int addrms_gate_probe_noalloc(const void* y, const void* y_ref, const void* residual, const void* residual_ref,

@@ -30,7 +30,7 @@ using namespace addrms_host;
 // code object, one copy per GPU, so the entry point needs no allocation.  Host code never
 // uses this name as an address; it asks the runtime for the device address once per device
 // (gate_scratch_on_current_device) and passes that pointer around.
-constexpr int kGateScratchSlots = 4096;
+constexpr int kGateScratchSlots = 512;
 static __device__ __align__(256) unsigned scratch[kGateScratchSlots * 4];
 
 namespace {
@@ -238,105 +238,165 @@ __global__ void fill_kernel(void* p, long long n, uint32_t seed, float lo, float
 //   out[0] = residual elements that differ, out[1] = y elements beyond tol,
 //   out[2] = largest y distance seen, out[3] = 0.
 // Every slot that is read was written by the same call, so the buffer needs no clearing.
-constexpr int kGateBlock = 256;
-constexpr int kGateMaxGrid = kGateScratchSlots;          // slots of 4 counters each
+//
+// Bound by HBM reads (four streams, nothing written), so a thread takes 16 bytes of y and
+// of its reference at a time (8 or 4 elements) and the matching elements of the residual
+// pair, with all loads of a piece issued before the first is used; the arithmetic is about
+// ten 32-bit operations per element, a quarter of what the reads leave room for.  Tensors
+// are only element-aligned here, so the vector type says so.  134 MB (4096 x 4096 bf16): the
+// first stage takes 21.8 us (6.2 TB/s; 24.6 with ordinary loads and 1024 workgroups, 30.6 with
+// one element per access), the second 4 (6.1 over 4096 slots).
+constexpr int kGateBlock = 512;
+constexpr int kGateMaxGrid = kGateScratchSlots;          // slots of 4 counters each: two workgroups per CU, all of the wave slots
 constexpr size_t kGateScratchBytes = static_cast<size_t>(kGateMaxGrid) * 4 * sizeof(unsigned);
 constexpr long long kGateMaxElems = 0xffffffffll;        // the counters are 32 bits wide
 
-template <int ES>
-__device__ __forceinline__ long long ordered_bits(const void* p, long long i)
+template <int ES> struct gate_piece;                     // 16 bytes at element alignment
+template <> struct gate_piece<2> { typedef addrms::u32x4 type __attribute__((aligned(2))); };
+template <> struct gate_piece<4> { typedef addrms::u32x4 type __attribute__((aligned(4))); };
+
+template <typename P> __device__ __forceinline__ addrms::u32x4 gate_load(const char* p)
 {
-    if constexpr (ES == 4) {
-        const uint32_t u = static_cast<const uint32_t*>(p)[i];
-        const long long mag = u & 0x7fffffffu;
-        return (u >> 31) ? -mag : mag;
-    } else {
-        const uint32_t u = static_cast<const uint16_t*>(p)[i];
-        const long long mag = u & 0x7fffu;
-        return (u >> 15) ? -mag : mag;
-    }
+    return __builtin_nontemporal_load(reinterpret_cast<const P*>(p));      // read once
 }
+
+// Distance in units in the last place of two bit patterns (sign and magnitude; the zeros are one value).
+template <int ES>
+__device__ __forceinline__ unsigned ulp_distance(unsigned a, unsigned b)
+{
+    constexpr unsigned kSign = ES == 4 ? 0x80000000u : 0x8000u, kMag = kSign - 1u;
+    const unsigned ma = a & kMag, mb = b & kMag;
+    // same sign: difference of the magnitudes; opposite signs: their sum, which fits 32 bits
+    return ((a ^ b) & kSign) ? ma + mb : (ma > mb ? ma - mb : mb - ma);
+}
+template <int ES>
+__device__ __forceinline__ void gate_count_y(unsigned a, unsigned b, unsigned tol, unsigned& bad, unsigned& most)
+{
+    const unsigned d = ulp_distance<ES>(a, b);
+    bad += d > tol;
+    most = d > most ? d : most;
+}
+// Sum (or largest) over the 64 lanes of a wave, in every lane.
+template <bool MAX, int STEP>
+__device__ __forceinline__ unsigned gate_fold(unsigned v)
+{
+    const unsigned o = addrms::lane_partner<STEP>(v);
+    return MAX ? (o > v ? o : v) : v + o;
+}
+template <bool MAX>
+__device__ __forceinline__ unsigned gate_wave(unsigned v)
+{
+    v = gate_fold<MAX, 1>(v); v = gate_fold<MAX, 2>(v); v = gate_fold<MAX, 4>(v);
+    v = gate_fold<MAX, 8>(v); v = gate_fold<MAX, 16>(v); return gate_fold<MAX, 32>(v);
+}
+// The three counts of a workgroup, valid in thread 0.
+__device__ __forceinline__ void gate_block(unsigned& rbad, unsigned& ybad, unsigned& ymax)
+{
+    __shared__ unsigned red[3][kGateBlock / 64];
+    rbad = gate_wave<false>(rbad); ybad = gate_wave<false>(ybad); ymax = gate_wave<true>(ymax);
+    if ((threadIdx.x & 63u) == 0u) {
+        red[0][threadIdx.x >> 6] = rbad; red[1][threadIdx.x >> 6] = ybad; red[2][threadIdx.x >> 6] = ymax;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < kGateBlock / 64; ++w) {
+            rbad += red[0][w]; ybad += red[1][w];
+            ymax = red[2][w] > ymax ? red[2][w] : ymax;
+        }
+}
+
 template <int XB, int RB>
-__global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(const void* y, const void* y_ref, const void* r,
-                                                                   const void* r_ref, long long n, unsigned tol,
+__global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(const char* y, const char* y_ref, const char* r,
+                                                                   const char* r_ref, long long n, unsigned tol,
                                                                    unsigned* partial)
 {
-    __shared__ unsigned red[3][kGateBlock];
+    using YP = typename gate_piece<XB>::type;
+    using RP = typename gate_piece<RB>::type;
+    constexpr int E = 16 / XB, RPP = E * RB / 16;        // elements per piece; residual pieces beside it
     unsigned rbad = 0, ybad = 0, ymax = 0;
-    const long long step = static_cast<long long>(gridDim.x) * kGateBlock;
-    for (long long i = static_cast<long long>(blockIdx.x) * kGateBlock + threadIdx.x; i < n; i += step) {
-        if constexpr (RB == 4) rbad += static_cast<const uint32_t*>(r)[i] != static_cast<const uint32_t*>(r_ref)[i];
-        else rbad += static_cast<const uint16_t*>(r)[i] != static_cast<const uint16_t*>(r_ref)[i];
-        long long d = ordered_bits<XB>(y, i) - ordered_bits<XB>(y_ref, i);
-        if (d < 0) d = -d;
-        const unsigned du = d > 0xffffffffll ? 0xffffffffu : static_cast<unsigned>(d);
-        ybad += du > tol;
-        ymax = du > ymax ? du : ymax;
-    }
-    red[0][threadIdx.x] = rbad; red[1][threadIdx.x] = ybad; red[2][threadIdx.x] = ymax;
-    __syncthreads();
-    for (int half = kGateBlock / 2; half > 0; half >>= 1) {
-        if (static_cast<int>(threadIdx.x) < half) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + half];
-            red[1][threadIdx.x] += red[1][threadIdx.x + half];
-            const unsigned o = red[2][threadIdx.x + half];
-            if (o > red[2][threadIdx.x]) red[2][threadIdx.x] = o;
+    const unsigned pieces = static_cast<unsigned>(n / E), step = gridDim.x * kGateBlock;
+    for (unsigned long long p = blockIdx.x * kGateBlock + threadIdx.x; p < pieces; p += step) {
+        const addrms::u32x4 a = gate_load<YP>(y + p * 16), b = gate_load<YP>(y_ref + p * 16);
+        addrms::u32x4 ra[RPP], rb[RPP];
+#pragma unroll
+        for (int k = 0; k < RPP; ++k) {
+            ra[k] = gate_load<RP>(r + (p * RPP + k) * 16);
+            rb[k] = gate_load<RP>(r_ref + (p * RPP + k) * 16);
         }
-        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (XB == 4) {
+                gate_count_y<4>(a[j], b[j], tol, ybad, ymax);
+            } else {
+                gate_count_y<2>(a[j] & 0xffffu, b[j] & 0xffffu, tol, ybad, ymax);
+                gate_count_y<2>(a[j] >> 16, b[j] >> 16, tol, ybad, ymax);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < RPP; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const unsigned d = ra[k][j] ^ rb[k][j];
+                if constexpr (RB == 4) rbad += d != 0u;
+                else rbad += ((d & 0xffffu) != 0u) + ((d >> 16) != 0u);
+            }
     }
-    if (threadIdx.x == 0) {
-        unsigned* slot = partial + 4 * static_cast<size_t>(blockIdx.x);
-        slot[0] = red[0][0]; slot[1] = red[1][0]; slot[2] = red[2][0]; slot[3] = 0u;
+    // the last n % E elements, one per thread of the first workgroup
+    const long long i = static_cast<long long>(pieces) * E + threadIdx.x;
+    if (blockIdx.x == 0 && i < n) {
+        if constexpr (XB == 4) gate_count_y<4>(reinterpret_cast<const uint32_t*>(y)[i], reinterpret_cast<const uint32_t*>(y_ref)[i], tol, ybad, ymax);
+        else gate_count_y<2>(reinterpret_cast<const uint16_t*>(y)[i], reinterpret_cast<const uint16_t*>(y_ref)[i], tol, ybad, ymax);
+        if constexpr (RB == 4) rbad += reinterpret_cast<const uint32_t*>(r)[i] != reinterpret_cast<const uint32_t*>(r_ref)[i];
+        else rbad += reinterpret_cast<const uint16_t*>(r)[i] != reinterpret_cast<const uint16_t*>(r_ref)[i];
     }
+    gate_block(rbad, ybad, ymax);
+    if (threadIdx.x == 0)
+        reinterpret_cast<addrms::u32x4*>(partial)[blockIdx.x] = addrms::u32x4{rbad, ybad, ymax, 0u};
 }
 // One workgroup.  accumulate != 0 folds the new counts into what `out` already holds
 // (a second comparison graded into the same verdict).
 __global__ __launch_bounds__(kGateBlock) void gate_finish_kernel(const unsigned* partial, int nslots, unsigned* out,
                                                                   int accumulate)
 {
-    __shared__ unsigned red[3][kGateBlock];
     unsigned a = 0, b = 0, c = 0;
-    for (int s = threadIdx.x; s < nslots; s += kGateBlock) {
-        a += partial[4 * s]; b += partial[4 * s + 1];
-        const unsigned m = partial[4 * s + 2];
-        c = m > c ? m : c;
-    }
-    red[0][threadIdx.x] = a; red[1][threadIdx.x] = b; red[2][threadIdx.x] = c;
-    __syncthreads();
-    for (int half = kGateBlock / 2; half > 0; half >>= 1) {
-        if (static_cast<int>(threadIdx.x) < half) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + half];
-            red[1][threadIdx.x] += red[1][threadIdx.x + half];
-            const unsigned o = red[2][threadIdx.x + half];
-            if (o > red[2][threadIdx.x]) red[2][threadIdx.x] = o;
+#pragma unroll
+    for (int k = 0; k < kGateMaxGrid / kGateBlock; ++k) {
+        const int s = k * kGateBlock + static_cast<int>(threadIdx.x);
+        if (s < nslots) {
+            const addrms::u32x4 v = reinterpret_cast<const addrms::u32x4*>(partial)[s];
+            a += v.x; b += v.y;
+            c = v.z > c ? v.z : c;
         }
-        __syncthreads();
     }
+    gate_block(a, b, c);
     if (threadIdx.x == 0) {
         if (accumulate) {
-            out[0] += red[0][0]; out[1] += red[1][0];
-            if (red[2][0] > out[2]) out[2] = red[2][0];
+            out[0] += a; out[1] += b;
+            if (c > out[2]) out[2] = c;
         } else {
-            out[0] = red[0][0]; out[1] = red[1][0]; out[2] = red[2][0]; out[3] = 0u;
+            *reinterpret_cast<addrms::u32x4*>(out) = addrms::u32x4{a, b, c, 0u};
         }
     }
 }
 
-int gate_grid(long long n)
+// Workgroups of the first stage for n elements of xb bytes: a piece per thread until the chip is full.
+int gate_grid(long long n, int xb)
 {
-    const long long per_wg = static_cast<long long>(kGateBlock) * 16;     // at least 16 elements per thread
+    const long long per_wg = static_cast<long long>(kGateBlock) * (16 / xb);
     return static_cast<int>(std::max<long long>(1, std::min<long long>(kGateMaxGrid, (n + per_wg - 1) / per_wg)));
 }
 
 // Both stages of the gate on `stream`: xb/rb are the element sizes of the y and residual
-// streams, `partial` holds at least gate_grid(n) slots, `out` four counters.  Asynchronous.
+// streams, `partial` holds at least gate_grid(n, xb) slots, `out` four counters.  Asynchronous.
 int launch_gate(const void* y, const void* y_ref, const void* r, const void* r_ref, long long n, int xb, int rb,
                 unsigned tol, unsigned* partial, unsigned* out, bool accumulate, hipStream_t stream)
 {
-    const dim3 block(kGateBlock), grid(static_cast<unsigned>(gate_grid(n)));
-    if (xb == 2 && rb == 2) hipLaunchKernelGGL((gate_partial_kernel<2, 2>), grid, block, 0, stream, y, y_ref, r, r_ref, n, tol, partial);
-    else if (xb == 2) hipLaunchKernelGGL((gate_partial_kernel<2, 4>), grid, block, 0, stream, y, y_ref, r, r_ref, n, tol, partial);
-    else hipLaunchKernelGGL((gate_partial_kernel<4, 4>), grid, block, 0, stream, y, y_ref, r, r_ref, n, tol, partial);
+    const dim3 block(kGateBlock), grid(static_cast<unsigned>(gate_grid(n, xb)));
+    const char *py = static_cast<const char*>(y), *pyr = static_cast<const char*>(y_ref);
+    const char *pr = static_cast<const char*>(r), *prr = static_cast<const char*>(r_ref);
+    if (xb == 2 && rb == 2) hipLaunchKernelGGL((gate_partial_kernel<2, 2>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, partial);
+    else if (xb == 2) hipLaunchKernelGGL((gate_partial_kernel<2, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, partial);
+    else hipLaunchKernelGGL((gate_partial_kernel<4, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, partial);
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(gate_finish_kernel, dim3(1), block, 0, stream, partial, static_cast<int>(grid.x), out, accumulate ? 1 : 0);
     HIP_TRY(hipGetLastError());
@@ -1119,7 +1179,7 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (n == 0) { HIP_TRY(hipMemsetAsync(counts_out, 0, sizeof *counts_out, s)); HIP_TRY(hipStreamSynchronize(s)); return ADDRMS_OK; }
     unsigned* partial = nullptr;
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&partial), static_cast<size_t>(gate_grid(n)) * 4 * sizeof(unsigned)));
+    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&partial), static_cast<size_t>(gate_grid(n, x_bytes(dtype))) * 4 * sizeof(unsigned)));
     st = launch_gate(y, y_ref, residual, residual_ref, n, x_bytes(dtype), r_bytes(dtype), tol, partial,
                      reinterpret_cast<unsigned*>(counts_out), false, s);
     const hipError_t e = hipStreamSynchronize(s);
