@@ -24,7 +24,8 @@ extern "C" {
 #endif
 
 /* One asynchronous launch.  All pointers device; outputs must not overlap inputs.
- * rows == 0 is a no-op.  cfg: host; NULL = specialised table, else default. */
+ * rows == 0 is a no-op.  cfg: host; NULL = specialised table, else a kernel and launch shape
+ * chosen for the problem outside the knob grid (same results; the default cfg where it does not apply). */
 int mergestates_run(const void* v_a, const float* s_a, const void* v_b, const float* s_b,
                     void* v_out, float* s_out, int64_t rows, int64_t d, int dtype,
                     const addrms_cfg* cfg, void* stream);

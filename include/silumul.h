@@ -24,7 +24,8 @@ extern "C" {
 #endif
 
 /* One asynchronous launch.  x: device, [M, 2d]; out: device, [M, d], must not overlap x.
- * M == 0 is a no-op.  cfg: host; NULL = specialised table, else the default cfg.
+ * M == 0 is a no-op.  cfg: host; NULL = specialised table, else a kernel and launch shape
+ * chosen for the problem outside the knob grid (same results; the default cfg where it does not apply).
  * stream: hipStream_t as void*.  Never synchronises, never allocates. */
 int silumul_run(const void* x, void* out, int64_t M, int64_t d, int dtype, const addrms_cfg* cfg, void* stream);
 

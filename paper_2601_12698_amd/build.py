@@ -123,12 +123,14 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
         if force or not _newer(obj, src, *hdrs, *gen):
             _run(["hipcc", "-x", "c++", *HOST_FLAGS, *INCLUDES, "-c", src, "-o", obj])
         objs.append(obj)
-    src = os.path.join(CSRC, "addrms_runtime.hip")
-    obj = os.path.join(BUILD, "addrms_runtime.o")
-    if force or not _newer(obj, src, os.path.join(CSRC, "addrms_kernel.h"), os.path.join(CSRC, "silumul_kernel.h"),
-                           os.path.join(CSRC, "mergestates_kernel.h"), *hdrs, *gen):
-        _run(["hipcc", *DEVICE_FLAGS, *INCLUDES, "-c", src, "-o", obj])
-    objs.append(obj)
+    dev_hdrs = [os.path.join(CSRC, f) for f in ("addrms_kernel.h", "silumul_kernel.h", "mergestates_kernel.h",
+                                                 "direct_kernel.h", "addrms_direct.h")]
+    for name in ("addrms_runtime.hip", "addrms_direct.hip"):
+        src = os.path.join(CSRC, name)
+        obj = os.path.join(BUILD, name[:-4] + ".o")
+        if force or not _newer(obj, src, *dev_hdrs, *hdrs, *gen):
+            _run(["hipcc", *DEVICE_FLAGS, *INCLUDES, "-c", src, "-o", obj])
+        objs.append(obj)
     tmp = LIB + f".{os.getpid()}.tmp"
     _run(["hipcc", "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *objs])
     os.replace(tmp, LIB)

@@ -1,0 +1,26 @@
+// Launches without a configuration (kernels in direct_kernel.h, rules in addrms_direct.hip).
+#pragma once
+#include <stdint.h>
+
+#include "addrms_internal.h"
+
+namespace addrms_host {
+
+// A launch that is ready but for the pointers.
+struct DirectPlan {
+    const void* fn = nullptr;
+    unsigned grid = 0, block_x = 0, block_y = 1, lds = 0;
+    unsigned units = 0, total = 0, mul = 0, shift = 0;      // flat operators: see direct_kernel.h
+};
+
+// The kernel and shape for a problem that the grid's default configuration covers, or false: the default
+// configuration runs.  *_align: the tensors' bases or-ed together.
+bool direct_silumul_plan(int64_t M, int64_t d, int dtype, uintptr_t x_align, uintptr_t out_align, DirectPlan* out);
+bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_align, DirectPlan* out);
+
+// hipError_t of the launch.
+int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream);
+int direct_launch_mergestates(const DirectPlan& p, const void* va, const float* sa, const void* vb, const float* sb, void* vo,
+                              float* so, void* stream);
+
+}  // namespace addrms_host

@@ -1,0 +1,122 @@
+// Launches without a configuration: which kernel of direct_kernel.h a problem takes, and in
+// what shape.
+#include <hip/hip_runtime.h>
+
+#include "addrms_direct.h"
+#include "direct_kernel.h"
+
+using namespace addrms;
+
+namespace {
+
+template <int DT, int POL, bool RAG>
+__global__ __launch_bounds__(kFlatThreads) void silumul_flat(const char* x, char* out, uint32_t d, uint32_t units,
+                                                             uint32_t total, FlatDiv fd)
+{
+    silumul_flat_body<DT, POL, RAG>(x, out, d, units, total, fd);
+}
+template <int DT, int POL>
+__global__ __launch_bounds__(kFlatThreads) void mergestates_flat(const char* va, const float* sa, const char* vb,
+                                                                 const float* sb, char* vo, float* so, uint32_t units,
+                                                                 uint32_t total, FlatDiv fd)
+{
+    mergestates_flat_body<DT, POL>(va, sa, vb, sb, vo, so, units, total, fd);
+}
+
+template <int DT> const void* silumul_fn1(int pol, bool rag)
+{
+    if (rag) return pol == POL_NT ? reinterpret_cast<const void*>(&silumul_flat<DT, POL_NT, true>)
+                                  : reinterpret_cast<const void*>(&silumul_flat<DT, POL_WT, true>);
+    return pol == POL_NT ? reinterpret_cast<const void*>(&silumul_flat<DT, POL_NT, false>)
+                         : reinterpret_cast<const void*>(&silumul_flat<DT, POL_WT, false>);
+}
+const void* silumul_fn(int dtype, int pol, bool rag)
+{
+    switch (dtype) {
+    case DT_BF16: return silumul_fn1<DT_BF16>(pol, rag);
+    case DT_FP16: return silumul_fn1<DT_FP16>(pol, rag);
+    case DT_FP32: return silumul_fn1<DT_FP32>(pol, rag);
+    default: return nullptr;
+    }
+}
+template <int DT> const void* mergestates_fn1(int pol)
+{
+    return pol == POL_NT ? reinterpret_cast<const void*>(&mergestates_flat<DT, POL_NT>)
+                         : reinterpret_cast<const void*>(&mergestates_flat<DT, POL_WT>);
+}
+
+// Write-through stores up to this many bytes of output, non-temporal ones beyond: three eighths of the
+// memory-side cache, so that the output is still there when the next kernel reads it.  Measured on buffers
+// that a program cycles through (three sets) / on buffers from HBM, write-through against non-temporal, in us:
+//   silu_and_mul  5.5 MB of traffic  2.3 / 3.0 against 2.9 / 2.8      49 MB   8.6 / 9.9 against 9.3 / 9.8
+//               270 MB, 90 MB out   39.5 / 43.2 against 42.0 / 42.5  344 MB, 115 MB out  57.2 / 56.9 against 55.9 / 56.0
+//              1057 MB, 352 MB out   171 / 170 against 168 / 166
+//   merge_attn_states  38 MB  7.4 / 8.6 against 7.6 / 8.3   24 MB  5.3 / 6.3 against 5.1 / 5.8
+int64_t write_through_max() { return addrms_host::hw().last_level_cache_bytes / 8 * 3; }
+
+void set_flat(addrms_host::DirectPlan* out, int64_t pieces, int64_t units, int64_t total)
+{
+    out->grid = static_cast<unsigned>((pieces + kFlatThreads - 1) / kFlatThreads);
+    out->block_x = kFlatThreads;
+    out->units = static_cast<unsigned>(units);
+    out->total = static_cast<unsigned>(total);
+    uint32_t l = 0;
+    while ((1ll << l) < units) ++l;                           // ceil(log2 units)
+    out->mul = static_cast<unsigned>(((1ull << (31 + l)) + static_cast<uint64_t>(units) - 1) / static_cast<uint64_t>(units));
+    out->shift = l - 1;
+}
+constexpr int64_t kFlatMax = 1ll << 31;                       // positions the flat kernels divide exactly
+
+}  // namespace
+
+namespace addrms_host {
+
+bool direct_silumul_plan(int64_t M, int64_t d, int dtype, uintptr_t x_align, uintptr_t out_align, DirectPlan* out)
+{
+    const int es = x_bytes(dtype), vec = 16 / es;
+    const bool rag = d % vec != 0;
+    if (d < 2 * vec || M >= kFlatMax / d) return false;       // rows of one piece have no division; 32-bit positions
+    if (out_align % 16 != 0 || (!rag && x_align % 16 != 0)) return false;
+    out->fn = silumul_fn(dtype, M * d * es <= write_through_max() ? POL_WT : POL_NT, rag);
+    if (!out->fn) return false;
+    if (rag) set_flat(out, (M * d + vec - 1) / vec, d, M * d);
+    else set_flat(out, M * (d / vec), d / vec, M * (d / vec));
+    return true;
+}
+
+// Below 4 MB of traffic the row kernels' ordinary loads are as fast (2000 x 80 bf16: 2.3 us against 2.5): the launch
+// is all there is.
+bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_align, DirectPlan* out)
+{
+    constexpr int64_t kSmall = 4 << 20;
+    const int vec = 16 / x_bytes(dtype);
+    if (d % vec != 0 || d < 2 * vec || rows >= kFlatMax / d || v_align % 16 != 0) return false;
+    if (algorithmic_bytes(OP_MERGE, rows, d, dtype) < kSmall) return false;
+    const int pol = rows * d * x_bytes(dtype) <= write_through_max() ? POL_WT : POL_NT;
+    out->fn = dtype == DT_BF16 ? mergestates_fn1<DT_BF16>(pol) : mergestates_fn1<DT_FP16>(pol);
+    set_flat(out, rows * (d / vec), d / vec, rows * (d / vec));
+    return true;
+}
+
+static int go(const DirectPlan& p, void** args, void* stream)
+{
+    return static_cast<int>(hipLaunchKernel(p.fn, dim3(p.grid), dim3(p.block_x, p.block_y), args, p.lds,
+                                            static_cast<hipStream_t>(stream)));
+}
+int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream)
+{
+    uint32_t ud = static_cast<uint32_t>(d), units = p.units, total = p.total;
+    FlatDiv fd{p.mul, p.shift};
+    void* args[] = {&x, &out, &ud, &units, &total, &fd};
+    return go(p, args, stream);
+}
+int direct_launch_mergestates(const DirectPlan& p, const void* va, const float* sa, const void* vb, const float* sb, void* vo,
+                              float* so, void* stream)
+{
+    uint32_t units = p.units, total = p.total;
+    FlatDiv fd{p.mul, p.shift};
+    void* args[] = {&va, &sa, &vb, &sb, &vo, &so, &units, &total, &fd};
+    return go(p, args, stream);
+}
+
+}  // namespace addrms_host

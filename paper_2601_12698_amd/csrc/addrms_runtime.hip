@@ -10,6 +10,7 @@
 #include <mutex>
 #include <vector>
 
+#include "addrms_direct.h"
 #include "addrms_internal.h"
 #include "mergestates.h"
 #include "mergestates_kernel.h"
@@ -117,13 +118,38 @@ int launch_mergestates(const Feas& f, const addrms_cfg& c, const void* va, const
     return launch_instance(f, c, rows, OP_MERGE, args, stream);
 }
 
-int resolve_cfg(const addrms_cfg* cfg, int64_t M, int64_t N, int dtype, addrms_cfg* out, int op = OP_ADDRMS)
+// *untuned (may be NULL): true if neither the caller nor the table names a configuration.
+int resolve_cfg(const addrms_cfg* cfg, int64_t M, int64_t N, int dtype, addrms_cfg* out, int op = OP_ADDRMS, bool* untuned = nullptr)
 {
+    if (untuned) *untuned = false;
     if (cfg) { *out = *cfg; return ADDRMS_OK; }
     if (table_lookup(M, N, dtype, out, op) == ADDRMS_OK) return ADDRMS_OK;
     std::string why;
     const int st = default_cfg(N, dtype, out, &why, op);
+    if (untuned) *untuned = st == ADDRMS_OK;
     return st == ADDRMS_OK ? st : fail(st, "%s", why.c_str());
+}
+
+uintptr_t bits(const void* p) { return reinterpret_cast<uintptr_t>(p); }
+
+// Launches without a configuration: the default one has been checked against the problem (f, c) and stands in where
+// the direct kernels do not cover it.
+int launch_untuned_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out, int64_t M, int64_t d, int dtype,
+                           hipStream_t stream)
+{
+    DirectPlan p;
+    if (!direct_silumul_plan(M, d, dtype, bits(x), bits(out), &p)) return launch_silumul(f, c, x, out, M, d, stream);
+    HIP_TRY(static_cast<hipError_t>(direct_launch_silumul(p, x, out, d, stream)));
+    return ADDRMS_OK;
+}
+int launch_untuned_mergestates(const Feas& f, const addrms_cfg& c, const void* va, const float* sa, const void* vb,
+                               const float* sb, void* vo, float* so, int64_t rows, int64_t d, int dtype, hipStream_t stream)
+{
+    DirectPlan p;
+    if (!direct_mergestates_plan(rows, d, dtype, bits(va) | bits(vb) | bits(vo), &p))
+        return launch_mergestates(f, c, va, sa, vb, sb, vo, so, rows, d, stream);
+    HIP_TRY(static_cast<hipError_t>(direct_launch_mergestates(p, va, sa, vb, sb, vo, so, stream)));
+    return ADDRMS_OK;
 }
 
 // ---- probe and harness kernels ---------------------------------------------------
@@ -428,6 +454,7 @@ struct Harness {
     char* pool = nullptr;
     char *x0 = nullptr, *r0 = nullptr, *yref = nullptr, *rref = nullptr, *w = nullptr;
     std::vector<char*> xs, rs;
+    bool untuned = false;     // measure what a call without a configuration launches
     unsigned* counts = nullptr;
     hipStream_t stream = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -601,6 +628,7 @@ struct SiluHarness {
     char* pool = nullptr;
     char *ref = nullptr;
     std::vector<char*> ins, outs;
+    bool untuned = false;     // measure what a call without a configuration launches
     unsigned* counts = nullptr;
     hipStream_t stream = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -674,7 +702,8 @@ struct SiluHarness {
         int set = 0;
         for (int i = 0; i < warmup + reps; ++i) {
             if (i == warmup) HIP_TRY(hipEventRecord(ev0, stream));
-            const int st = launch_silumul(f, c, ins[set], outs[set], M, d, stream);
+            const int st = untuned ? launch_untuned_silumul(f, c, ins[set], outs[set], M, d, dtype, stream)
+                                   : launch_silumul(f, c, ins[set], outs[set], M, d, stream);
             if (st != ADDRMS_OK) return st;
             set = (set + 1) % nsets;
         }
@@ -699,6 +728,7 @@ struct MergeHarness {
     float* sref = nullptr;
     struct Set { char *va, *vb, *vo; float *sa, *sb, *so; };
     std::vector<Set> sets;
+    bool untuned = false;     // measure what a call without a configuration launches
     unsigned* counts = nullptr;
     hipStream_t stream = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -754,7 +784,8 @@ struct MergeHarness {
     }
     int run_set(const Feas& f, const addrms_cfg& c, const Set& s, char* vo, float* so)
     {
-        return launch_mergestates(f, c, s.va, s.sa, s.vb, s.sb, vo, so, rows, d, stream);
+        return untuned ? launch_untuned_mergestates(f, c, s.va, s.sa, s.vb, s.sb, vo, so, rows, d, dtype, stream)
+                       : launch_mergestates(f, c, s.va, s.sa, s.vb, s.sb, vo, so, rows, d, stream);
     }
     int make_reference(const addrms_cfg& c)
     {
@@ -920,10 +951,12 @@ template <class H> int measure_on_device(const addrms_cfg* cfg, int64_t M, int64
     int st = check_op_shape(H::kOp, M, N, dtype, "measuring");
     if (st != ADDRMS_OK) return st;
     addrms_cfg c{};
-    st = resolve_cfg(cfg, M, N, dtype, &c, H::kOp);
+    bool untuned = false;
+    st = resolve_cfg(cfg, M, N, dtype, &c, H::kOp, &untuned);
     if (st != ADDRMS_OK) return st;
     std::lock_guard<std::mutex> lock(g_tune_mu);
     H h;
+    h.untuned = untuned;
     st = h.init(M, N, dtype, eps, rotate != 0);
     if (st != ADDRMS_OK) return st;
     st = h.measure(c, warmup, reps, mean_us);
@@ -1215,13 +1248,15 @@ int silumul_run(const void* x, void* out, int64_t M, int64_t d, int dtype, const
     if (M > (1ll << 31) - 1) return fail(ADDRMS_ERR_INVALID_ARG, "M=%lld exceeds the 2^31-1 row limit", (long long)M);
     if (!dispatch_consistent()) return fail(ADDRMS_ERR_INVALID_ARG, "library was built with inconsistent kernel tables");
     addrms_cfg c{};
-    const int st = resolve_cfg(cfg, M, d, dtype, &c, OP_SILUMUL);
+    bool untuned = false;
+    const int st = resolve_cfg(cfg, M, d, dtype, &c, OP_SILUMUL, &untuned);
     if (st != ADDRMS_OK) return st;
     const Feas f = check_cfg(c, M, d, dtype, OP_SILUMUL);
     if (f.status != ADDRMS_OK) return fail(f.status, "%s", f.reason.c_str());
     const int al = c.vec * x_bytes(dtype);
     if (!aligned(x, al) || !aligned(out, al))
         return fail(ADDRMS_ERR_MISALIGNED, "x and out must be %d-byte aligned for vec=%d", al, c.vec);
+    if (untuned) return launch_untuned_silumul(f, c, x, out, M, d, dtype, static_cast<hipStream_t>(stream));
     return launch_silumul(f, c, x, out, M, d, static_cast<hipStream_t>(stream));
 }
 
@@ -1286,13 +1321,15 @@ int mergestates_run(const void* v_a, const float* s_a, const void* v_b, const fl
     if (rows > (1ll << 31) - 1) return fail(ADDRMS_ERR_INVALID_ARG, "rows=%lld exceeds the 2^31-1 limit", (long long)rows);
     if (!dispatch_consistent()) return fail(ADDRMS_ERR_INVALID_ARG, "library was built with inconsistent kernel tables");
     addrms_cfg c{};
-    const int st = resolve_cfg(cfg, rows, d, dtype, &c, OP_MERGE);
+    bool untuned = false;
+    const int st = resolve_cfg(cfg, rows, d, dtype, &c, OP_MERGE, &untuned);
     if (st != ADDRMS_OK) return st;
     const Feas f = check_cfg(c, rows, d, dtype, OP_MERGE);
     if (f.status != ADDRMS_OK) return fail(f.status, "%s", f.reason.c_str());
     const int al = c.vec * x_bytes(dtype);
     if (!aligned(v_a, al) || !aligned(v_b, al) || !aligned(v_out, al) || !aligned(s_a, 4) || !aligned(s_b, 4) || !aligned(s_out, 4))
         return fail(ADDRMS_ERR_MISALIGNED, "v_a, v_b and v_out must be %d-byte aligned for vec=%d, scores 4-byte aligned", al, c.vec);
+    if (untuned) return launch_untuned_mergestates(f, c, v_a, s_a, v_b, s_b, v_out, s_out, rows, d, dtype, static_cast<hipStream_t>(stream));
     return launch_mergestates(f, c, v_a, s_a, v_b, s_b, v_out, s_out, rows, d, static_cast<hipStream_t>(stream));
 }
 

@@ -1,0 +1,93 @@
+"""Calls that name no configuration and have none in the table take kernels of their own, chosen by the problem.
+They must give what the default configuration gives, bit for bit (same arithmetic, element by element), touch
+nothing beside their outputs, and leave to the default configuration what they do not cover."""
+import pytest
+import torch
+
+from paper_2601_12698_amd import binding as B
+from paper_2601_12698_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+PAD = 64            # canary elements on either side of an output
+
+
+@pytest.fixture(autouse=True)
+def _empty_table():
+    B.addrms_table_clear()
+
+
+def bits(t):
+    return t.view(torch.int16 if t.element_size() == 2 else torch.int32)
+
+
+def guarded(numel, dtype, off=0):
+    """A tensor of numel elements, off elements past an aligned address, and a check that its surroundings are untouched."""
+    buf = torch.full((numel + 2 * PAD + off,), 42.0, dtype=dtype, device="cuda")
+    view = buf[PAD + off:PAD + off + numel]
+
+    def intact():
+        return bool((buf[:PAD + off] == 42.0).all()) and bool((buf[PAD + off + numel:] == 42.0).all())
+    return view, intact
+
+
+def normal(shape, dtype, seed, std=1.5):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    t = (torch.randn(shape, generator=g, device="cuda") * std).to(dtype)
+    t.view(-1)[0] = float("inf")
+    t.view(-1)[t.numel() // 2] = -float("inf")
+    return t
+
+
+SILU = [("bf16", 1, 16), ("bf16", 3, 17), ("bf16", 1, 23), ("fp16", 5, 1000), ("fp16", 7, 1001), ("fp32", 3, 9), ("fp32", 2, 8),
+        ("fp32", 11, 1003), ("bf16", 33, 2056), ("bf16", 2, 8191), ("bf16", 2000, 4099), ("bf16", 6500, 8200), ("fp16", 6500, 8190),
+        ("bf16", 4, 15), ("fp32", 1, 28672)]
+
+
+@pytest.mark.parametrize("dtype,M,d", SILU)
+def test_gated_activation(dtype, M, d):
+    """Pieces of 16 bytes: rows shorter than two of them, rows that end inside one, an output that ends inside one, and
+    outputs on both sides of the size where the store policy changes."""
+    t = W.x_torch_dtype(dtype)
+    x = normal((M, 2 * d), t, d)
+    want = torch.empty((M, d), dtype=t, device="cuda")
+    B.silumul_run(x, want, M, d, dtype, B.silumul_default_cfg(d, dtype))
+    got, intact = guarded(M * d, t)
+    B.silumul_run(x, got, M, d, dtype)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(got), bits(want).view(-1)) and intact()
+
+
+@pytest.mark.parametrize("off", [1, 2, 4])
+def test_gated_activation_with_bases_that_are_not_16_byte_aligned(off):
+    """Odd d: one-element accesses were always accepted at any element; even so with the input alone off, and refused as
+    before where the default configuration's access does not fit the base."""
+    M, d = 9, 1001
+    buf = normal((2 * M * d + 8,), torch.bfloat16, 5)
+    x = buf[off:off + 2 * M * d]
+    want = torch.empty((M, d), dtype=torch.bfloat16, device="cuda")
+    B.silumul_run(x, want, M, d, "bf16", B.silumul_default_cfg(d, "bf16"))
+    for out_off in (0, off):
+        got, intact = guarded(M * d, torch.bfloat16, out_off)
+        B.silumul_run(x, got, M, d, "bf16")
+        torch.cuda.synchronize()
+        assert torch.equal(bits(got), bits(want).view(-1)) and intact()
+    with pytest.raises(B.AddrmsError) as e:
+        B.silumul_run(buf[off:off + 2 * 8 * 1000], got[:8 * 1000], 8, 1000, "bf16")
+    assert e.value.status == B.ERR_MISALIGNED
+
+
+@pytest.mark.parametrize("dtype,rows,d", [("bf16", 30000, 64), ("fp16", 20011, 128), ("bf16", 9001, 192), ("bf16", 24576, 256),
+                                          ("fp16", 7003, 1000), ("bf16", 250_000, 256), ("fp16", 3, 128), ("bf16", 60000, 72),
+                                          ("bf16", 40000, 100)])
+def test_merge_of_attention_states(dtype, rows, d):
+    t = W.x_torch_dtype(dtype)
+    va, vb = normal((rows, d), t, 1), normal((rows, d), t, 2)
+    sa, sb = normal((rows,), torch.float32, 3, 3.0).nan_to_num(posinf=80.0, neginf=-80.0), \
+        normal((rows,), torch.float32, 4, 3.0).nan_to_num(posinf=80.0, neginf=-80.0)
+    vw, sw = torch.empty_like(va), torch.empty_like(sa)
+    B.mergestates_run(va, sa, vb, sb, vw, sw, rows, d, dtype, B.mergestates_default_cfg(d, dtype))
+    vo, vok = guarded(rows * d, t)
+    so, sok = guarded(rows, torch.float32)
+    B.mergestates_run(va, sa, vb, sb, vo, so, rows, d, dtype)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(vo), bits(vw).view(-1)) and torch.equal(bits(so), bits(sw)) and vok() and sok()
