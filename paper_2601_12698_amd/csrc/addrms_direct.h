@@ -15,10 +15,12 @@ struct DirectPlan {
 
 // The kernel and shape for a problem that the grid's default configuration covers, or false: the default
 // configuration runs.  *_align: the tensors' bases or-ed together.
+bool direct_addrms_plan(int64_t M, int64_t N, int dtype, DirectPlan* out);
 bool direct_silumul_plan(int64_t M, int64_t d, int dtype, uintptr_t x_align, uintptr_t out_align, DirectPlan* out);
 bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_align, DirectPlan* out);
 
 // hipError_t of the launch.
+int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream);
 int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream);
 int direct_launch_mergestates(const DirectPlan& p, const void* va, const float* sa, const void* vb, const float* sb, void* vo,
                               float* so, void* stream);

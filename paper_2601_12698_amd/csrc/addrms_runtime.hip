@@ -134,6 +134,14 @@ uintptr_t bits(const void* p) { return reinterpret_cast<uintptr_t>(p); }
 
 // Launches without a configuration: the default one has been checked against the problem (f, c) and stands in where
 // the direct kernels do not cover it.
+int launch_untuned_addrms(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, float eps, int64_t M, int64_t N,
+                          int dtype, hipStream_t stream)
+{
+    DirectPlan p;
+    if (!direct_addrms_plan(M, N, dtype, &p)) return launch(f, c, x, r, w, eps, M, N, stream);
+    HIP_TRY(static_cast<hipError_t>(direct_launch_addrms(p, x, r, w, eps, M, N, stream)));
+    return ADDRMS_OK;
+}
 int launch_untuned_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out, int64_t M, int64_t d, int dtype,
                            hipStream_t stream)
 {
@@ -512,7 +520,11 @@ struct Harness {
         if (pool) (void)hipFree(pool);
     }
 
-    int run_on(const addrms_cfg& c, const Feas& f, int set) { return launch(f, c, xs[set], rs[set], w, eps, M, N, stream); }
+    int run_on(const addrms_cfg& c, const Feas& f, int set)
+    {
+        if (untuned) return launch_untuned_addrms(f, c, xs[set], rs[set], w, eps, M, N, dtype, stream);
+        return launch(f, c, xs[set], rs[set], w, eps, M, N, stream);
+    }
 
     int make_reference(const addrms_cfg& c)
     {
@@ -990,7 +1002,8 @@ int addrms_run(void* x, void* residual, const void* weight, float eps, int64_t M
     if (M > (1ll << 31) - 1) return fail(ADDRMS_ERR_INVALID_ARG, "M=%lld exceeds the 2^31-1 row limit", (long long)M);
     if (!dispatch_consistent()) return fail(ADDRMS_ERR_INVALID_ARG, "library was built with inconsistent kernel tables");
     addrms_cfg c{};
-    int st = resolve_cfg(cfg, M, N, dtype, &c);
+    bool untuned = false;
+    int st = resolve_cfg(cfg, M, N, dtype, &c, OP_ADDRMS, &untuned);
     if (st != ADDRMS_OK) return st;
     const Feas f = check_cfg(c, M, N, dtype);
     if (f.status != ADDRMS_OK) return fail(f.status, "%s", f.reason.c_str());
@@ -998,6 +1011,7 @@ int addrms_run(void* x, void* residual, const void* weight, float eps, int64_t M
     if (!aligned(x, xa) || !aligned(weight, xa) || !aligned(residual, ra))
         return fail(ADDRMS_ERR_MISALIGNED, "x and weight must be %d-byte aligned and residual %d-byte aligned for vec=%d",
                     xa, ra, c.vec);
+    if (untuned) return launch_untuned_addrms(f, c, x, residual, weight, eps, M, N, dtype, static_cast<hipStream_t>(stream));
     return launch(f, c, x, residual, weight, eps, M, N, static_cast<hipStream_t>(stream));
 }
 
@@ -1054,10 +1068,12 @@ int addrms_measure_stats(const addrms_cfg* cfg, int64_t M, int64_t N, int dtype,
         return fail(ADDRMS_ERR_INVALID_ARG, "need M, N > 0, 0 < reps <= 100000 and warmup >= 0");
     if (!dispatch_consistent()) return fail(ADDRMS_ERR_INVALID_ARG, "library was built with inconsistent kernel tables");
     addrms_cfg c{};
-    int st = resolve_cfg(cfg, M, N, dtype, &c);
+    bool untuned = false;
+    int st = resolve_cfg(cfg, M, N, dtype, &c, OP_ADDRMS, &untuned);
     if (st != ADDRMS_OK) return st;
     std::lock_guard<std::mutex> lock(g_tune_mu);
     Harness h;
+    h.untuned = untuned;
     st = h.init(M, N, dtype, eps, rotate != 0);
     if (st != ADDRMS_OK) return st;
     memset(out, 0, sizeof *out);

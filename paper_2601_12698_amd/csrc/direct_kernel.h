@@ -58,6 +58,113 @@ __device__ __forceinline__ void st_stream(char* base, uint32_t off, const raw_t<
     }
 }
 
+// ---- add + RMSNorm ---------------------------------------------------------------------------
+// A workgroup per row (several for rows shorter than a wave), a thread holds CPT chunks of VEC
+// elements from the loads to the stores.  Same arithmetic as addrms_body, bit for bit.  HBM-bound:
+// all loads of a thread are issued before the first value is used (in two batches beyond 32
+// values), and a row is spread over as many threads as there are pieces, up to 1024, so that a
+// thread has few and the row arrives early: of the 1 to 8 chunks per thread tried on 40 shapes
+// the fewest were the fastest on all but four, by 2-8 % against twice as many.  DEFER (more than
+// one chunk): both streams written after the row sum, 1-3 % there.
+// Default of the knob grid -> here, us: 16 x 4096 bf16 3.1 -> 2.5, 256 x 5120 4.1 -> 3.5,
+// 512 x 8192 8.3 -> 6.3, 4096 x 4096 21.5 -> 20.1, 20000 x 5120 152 -> 130 (6.3 TB/s),
+// 32768 x 7168 340 -> 304, 2048 x 8192 fp32 56.4 -> 45.3, 900 x 28672 fp16 44.3 -> 39.8.
+template <int DT, int VEC, int CPT, int POL, bool DEFER>
+__device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* __restrict__ rp,
+                                                   const void* __restrict__ wp, float eps, double inv_n, int64_t M,
+                                                   int32_t N)
+{
+    using T = dt_traits<DT>;
+    constexpr int XB = T::XB, RB = T::RB;
+    constexpr int UNR = VEC * CPT <= 32 ? CPT : (CPT + 1) / 2;
+    constexpr bool BF = T::BF;
+    extern __shared__ double lds[];
+
+    const uint32_t tpr = blockDim.x, rpw = blockDim.y;
+    const uint32_t lane = threadIdx.x, ry = threadIdx.y;
+    const RowAddr ra = row_addr<XB, RB>(xp, rp, blockIdx.x, rpw, ry, M, N);
+    const char* wbase = static_cast<const char*>(wp);
+    const uint32_t nlast = static_cast<uint32_t>(N) - VEC;
+    const uint32_t col0 = lane * VEC, stride = tpr * VEC;
+
+    float h[CPT][VEC];
+    double acc = 0.0;
+#pragma unroll
+    for (int g = 0; g < CPT; g += UNR) {
+        raw_t<XB * VEC> xv[UNR];
+        raw_t<RB * VEC> rv[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            if (g + u < CPT) {
+                const uint32_t col = col0 + static_cast<uint32_t>(g + u) * stride;
+                const uint32_t colc = col < nlast ? col : nlast;      // idle lanes re-read valid data
+                ld_stream<POL, XB * VEC, 16>(ra.xbase, (ra.rowoff + colc) * XB, xv[u]);
+                ld_stream<POL, RB * VEC, 16>(ra.rbase, (ra.rowoff + colc) * RB, rv[u]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            if (g + u < CPT) {
+                const int c = g + u;
+                const uint32_t col = col0 + static_cast<uint32_t>(c) * stride;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e)
+                    h[c][e] = get_elem<XB, BF>(xv[u], e) + get_elem<RB, BF && RB == 2>(rv[u], e);
+                if (ra.row_ok && col <= nlast) {
+                    if constexpr (!DEFER) {
+                        raw_t<RB * VEC> out;
+                        pack_vec<RB, BF, VEC>(h[c], out);
+                        st_stream<POL, RB * VEC>(ra.rbase, (ra.rowoff + col) * RB, out);
+                    }
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) {
+                        const double hd = static_cast<double>(h[c][e]);
+                        acc = __builtin_fma(hd, hd, acc);
+                    }
+                }
+            }
+        }
+        if (g + UNR < CPT) __builtin_amdgcn_sched_barrier(0);
+    }
+    raw_t<XB * VEC> wv[CPT];
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const uint32_t col = col0 + static_cast<uint32_t>(c) * stride;
+        const uint32_t colc = col < nlast ? col : nlast;
+        ld_stream<POL_CACHED, XB * VEC, 16>(wbase, colc * XB, wv[c]);
+    }
+
+    const double ss = row_sum(acc, RED_WAVE, tpr, lane, ry, lds);
+    const float rstd = rsqrt_to_f32(__builtin_fma(ss, inv_n, static_cast<double>(eps)));
+
+    if constexpr (DEFER) {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            const uint32_t col = col0 + static_cast<uint32_t>(c) * stride;
+            if (ra.row_ok && col <= nlast) {
+                raw_t<RB * VEC> out;
+                pack_vec<RB, BF, VEC>(h[c], out);
+                st_stream<POL, RB * VEC>(ra.rbase, (ra.rowoff + col) * RB, out);
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const uint32_t col = col0 + static_cast<uint32_t>(c) * stride;
+        float y[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const float t = h[c][e] * rstd;
+            y[e] = t * get_elem<XB, BF>(wv[c], e);
+        }
+        if (ra.row_ok && col <= nlast) {
+            raw_t<XB * VEC> out;
+            pack_vec<XB, BF, VEC>(y, out);
+            st_stream<POL, XB * VEC>(ra.xbase, (ra.rowoff + col) * XB, out);
+        }
+    }
+}
+
 // ---- elementwise operators over the output as one flat array -----------------------------------
 // silu_and_mul and merge_attn_states have no reduction, so nothing ties a workgroup to a row: the
 // output is a flat array of 16-byte pieces, piece p goes to one lane, and its row is p divided by

@@ -91,3 +91,39 @@ def test_merge_of_attention_states(dtype, rows, d):
     B.mergestates_run(va, sa, vb, sb, vo, so, rows, d, dtype)
     torch.cuda.synchronize()
     assert torch.equal(bits(vo), bits(vw).view(-1)) and torch.equal(bits(so), bits(sw)) and vok() and sok()
+
+
+def norm_inputs(M, N, dtype, seed, off=0):
+    x, xok = guarded(M * N, W.x_torch_dtype(dtype), off)
+    r, rok = guarded(M * N, W.r_torch_dtype(dtype), off)
+    x.copy_(normal((M * N,), x.dtype, seed))
+    r.copy_(normal((M * N,), r.dtype, seed + 1))
+    w = torch.rand(N + off, generator=torch.Generator(device="cuda").manual_seed(seed + 2), device="cuda").to(x.dtype)[off:]
+    return x, xok, r, rok, w
+
+
+def check_norm(M, N, dtype, off=0):
+    x, xok, r, rok, w = norm_inputs(M, N, dtype, N, off)
+    xw, rw = x.clone(), r.clone()
+    if off:                                                       # the clones start at an aligned address
+        xw, rw = torch.cat([xw[:off], xw])[off:], torch.cat([rw[:off], rw])[off:]
+    B.addrms_run(xw, rw, w, 1e-6, M, N, dtype, B.addrms_default_cfg(N, dtype))
+    B.addrms_run(x, r, w, 1e-6, M, N, dtype)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(r), bits(rw)) and torch.equal(bits(x), bits(xw)) and xok() and rok()
+
+
+# N in pieces of 16 bytes (8 or 4 elements): half a wave and one more, whole waves and one more, one piece per thread
+# at its limit and beyond, the most a thread holds; M around the rows of a workgroup; sizes on both sides of the store
+# policy's two limits (16 and 96 MB)
+NORM = [("bf16", 1, 136), ("bf16", 7, 256), ("bf16", 8, 264), ("fp16", 5, 512), ("fp16", 3, 520), ("bf16", 2, 8192),
+        ("bf16", 3, 8200), ("fp16", 2, 16384), ("fp16", 2, 24584), ("bf16", 2, 32768), ("fp32", 3, 68), ("fp32", 5, 132),
+        ("fp32", 2, 4096), ("fp32", 2, 4100), ("fp32", 2, 16388), ("fp32", 2, 24580), ("fp32", 1, 32768),
+        ("fp16_res32", 3, 72), ("fp16_res32", 9, 1000), ("fp16_res32", 3, 1004), ("fp16_res32", 2, 20484),
+        ("fp16_res32", 2, 32764), ("bf16", 4096, 1024), ("bf16", 4095, 1024), ("bf16", 6144, 4096), ("bf16", 6145, 4096),
+        ("fp32", 700, 3584), ("fp16_res32", 5000, 2880)]
+
+
+@pytest.mark.parametrize("dtype,M,N", NORM)
+def test_norm(dtype, M, N):
+    check_norm(M, N, dtype)
