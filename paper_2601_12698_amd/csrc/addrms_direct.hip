@@ -2,6 +2,8 @@
 // what shape.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "addrms_direct.h"
 #include "direct_kernel.h"
 
@@ -9,11 +11,11 @@ using namespace addrms;
 
 namespace {
 
-template <int DT, int VEC, int CPT, int POL>
+template <int DT, int VEC, int CPT, int POL, bool RAG>
 __global__ __launch_bounds__(1024) void addrms_direct(void* x, void* r, const void* w, float eps, double inv_n,
                                                       long long M, int N)
 {
-    addrms_direct_body<DT, VEC, CPT, POL, (CPT > 1)>(x, r, w, eps, inv_n, M, N);
+    addrms_direct_body<DT, VEC, CPT, POL, RAG, (CPT > 1)>(x, r, w, eps, inv_n, M, N);
 }
 template <int DT, int POL, bool RAG>
 __global__ __launch_bounds__(kFlatThreads) void silumul_flat(const char* x, char* out, uint32_t d, uint32_t units,
@@ -32,35 +34,37 @@ __global__ __launch_bounds__(kFlatThreads) void mergestates_flat(const char* va,
 // Elements per thread and access: 16 bytes of the residual, and of x too unless the residual is wider.
 constexpr int direct_vec(int dtype) { return dtype == DT_BF16 || dtype == DT_FP16 ? 8 : 4; }
 
-template <int DT, int CPT> const void* addrms_fn2(int pol)
+template <int DT, int CPT> const void* addrms_fn2(int pol, bool rag)
 {
     constexpr int VEC = direct_vec(DT);
-    return pol == POL_NT ? reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_NT>)
-                         : reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_WT>);
+    if (rag) return pol == POL_NT ? reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_NT, true>)
+                                  : reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_WT, true>);
+    return pol == POL_NT ? reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_NT, false>)
+                         : reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_WT, false>);
 }
 // At most 32 values per thread: a workgroup of 1024 threads leaves each 128 registers.
-template <int DT> const void* addrms_fn1(int cpt, int pol)
+template <int DT> const void* addrms_fn1(int cpt, int pol, bool rag)
 {
     switch (cpt) {
-    case 1: return addrms_fn2<DT, 1>(pol);
-    case 2: return addrms_fn2<DT, 2>(pol);
-    case 3: return addrms_fn2<DT, 3>(pol);
-    case 4: return addrms_fn2<DT, 4>(pol);
+    case 1: return addrms_fn2<DT, 1>(pol, rag);
+    case 2: return addrms_fn2<DT, 2>(pol, rag);
+    case 3: return addrms_fn2<DT, 3>(pol, rag);
+    case 4: return addrms_fn2<DT, 4>(pol, rag);
     default: break;
     }
     if constexpr (direct_vec(DT) == 4) {
-        if (cpt == 5 || cpt == 6) return addrms_fn2<DT, 6>(pol);
-        if (cpt == 7 || cpt == 8) return addrms_fn2<DT, 8>(pol);
+        if (cpt == 5 || cpt == 6) return addrms_fn2<DT, 6>(pol, rag);
+        if (cpt == 7 || cpt == 8) return addrms_fn2<DT, 8>(pol, rag);
     }
     return nullptr;
 }
-const void* addrms_fn(int dtype, int cpt, int pol)
+const void* addrms_fn(int dtype, int cpt, int pol, bool rag)
 {
     switch (dtype) {
-    case DT_BF16: return addrms_fn1<DT_BF16>(cpt, pol);
-    case DT_FP16: return addrms_fn1<DT_FP16>(cpt, pol);
-    case DT_FP16_RES32: return addrms_fn1<DT_FP16_RES32>(cpt, pol);
-    case DT_FP32: return addrms_fn1<DT_FP32>(cpt, pol);
+    case DT_BF16: return addrms_fn1<DT_BF16>(cpt, pol, rag);
+    case DT_FP16: return addrms_fn1<DT_FP16>(cpt, pol, rag);
+    case DT_FP16_RES32: return addrms_fn1<DT_FP16_RES32>(cpt, pol, rag);
+    case DT_FP32: return addrms_fn1<DT_FP32>(cpt, pol, rag);
     default: return nullptr;
     }
 }
@@ -115,25 +119,42 @@ constexpr int64_t kFlatMax = 1ll << 31;                       // positions the f
 
 namespace addrms_host {
 
-// Threads per row: one per piece up to 1024, then as few pieces per thread as that allows, in equal shares.
+// Ragged rows up to 96 MB take three pieces per thread and two rows per workgroup, so that fewer waves repeat what a
+// row costs before and after its pieces (2047 x 4095 fp16 12.9 us against 14.0 with one piece per thread, 5000 x 1001
+// fp32 15.5 against 16.0, 300 x 10001 bf16 7.4 against 8.2 with two); beyond, one is as good or better (9000 x 6150
+// bf16 76.4-79.7 us against 78.1-78.9).
 // Store policy: as above, but non-temporal below 16 MB of x and residual, where the caches of the XCDs hold most of it
-// anyway and a write-through store only waits longer (16 x 4096 bf16 2.5 us against 2.7, 1024 x 2048 3.8 against 4.1).
-bool direct_addrms_plan(int64_t M, int64_t N, int dtype, DirectPlan* out)
+// anyway and a write-through store only waits longer (16 x 4096 bf16 2.5 us against 2.7, 1024 x 2048 3.8 against 4.1),
+// and for rows with single elements, whose partly written lines a write-through store sends out at once (2047 x 4095
+// fp16 12.9 us and from HBM 13.5 against 13.3 and 15.9).
+// Ragged walk: where a vector access does not divide the row, unless all of it is under 1 MB and the default
+// configuration's accesses are at least two elements wide (40 x 1030 bf16 3.3 us against 3.2); and where rows are whole
+// vectors but not whole lines, from 16 MB on (below, 1000 x 1000 bf16 3.6 us against 3.5).
+bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, DirectPlan* out)
 {
-    constexpr int64_t kWriteThroughMin = 16 << 20;
-    const int vec = direct_vec(dtype);
-    const int64_t pieces = N / vec;
-    if (N % vec != 0 || pieces <= 16 || pieces > 8192) return false;
-    const int64_t bytes = M * N * (x_bytes(dtype) + r_bytes(dtype));
-    const int pol = bytes >= kWriteThroughMin && bytes <= write_through_max() ? POL_WT : POL_NT;
-    const int64_t cpt = (pieces + 1023) / 1024;
-    out->fn = addrms_fn(dtype, static_cast<int>(cpt), pol);
+    constexpr int64_t kWriteThroughMin = 16 << 20, kRaggedMin = 1 << 20;
+    const int vec = direct_vec(dtype), xb = x_bytes(dtype), rb = r_bytes(dtype);
+    const int64_t bytes = M * N * (xb + rb);
+    const bool split = N % vec != 0;                                                  // rows have single elements
+    const bool rag = split || ((N * xb) % kLineBytes != 0 && bytes >= kWriteThroughMin && N >= 128 * vec);
+    if (split && ((x / xb) % vec != (r / rb) % vec || (bytes < kRaggedMin && default_vec > 1))) return false;
+    const int line = kLineBytes / xb;                                                 // elements
+    const int64_t pieces = (N + (rag ? line - 1 : 0) + vec - 1) / vec;                // a ragged row begins anywhere in a line
+    if (N < 16 * vec || pieces > 8192) return false;
+    const int pol = bytes >= kWriteThroughMin && bytes <= write_through_max() && !split ? POL_WT : POL_NT;
+    // threads per row: one per piece up to 1024, then as few pieces per thread as that allows, in equal shares; three
+    // pieces per thread and two rows per workgroup for ragged rows
+    const bool thick = rag && bytes <= write_through_max();
+    int64_t cpt = std::max<int64_t>((pieces + 1023) / 1024, thick ? 3 : 1);
+    int64_t tpr = (pieces + cpt - 1) / cpt;
+    tpr = tpr <= 32 ? 32 : (tpr + 63) / 64 * 64;
+    cpt = (pieces + tpr - 1) / tpr;
+    out->fn = addrms_fn(dtype, static_cast<int>(cpt), pol, rag);
     if (!out->fn) return false;
-    const int64_t share = (pieces + cpt - 1) / cpt;
-    out->block_x = share <= 32 ? 32u : static_cast<unsigned>((share + 63) / 64 * 64);
-    out->block_y = share <= 32 ? 2u : 1u;
+    out->block_x = static_cast<unsigned>(tpr);
+    out->block_y = tpr == 32 || (thick && tpr <= 256 && M >= 512) ? 2u : 1u;
     out->grid = static_cast<unsigned>((M + out->block_y - 1) / out->block_y);
-    out->lds = out->block_x > 64 ? 16u * 8u : 0u;              // one fp64 sum per wave
+    out->lds = tpr > 64 ? out->block_y * 16u * 8u : 0u;        // one fp64 sum per wave
     return true;
 }
 

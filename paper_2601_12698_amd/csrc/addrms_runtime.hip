@@ -138,7 +138,7 @@ int launch_untuned_addrms(const Feas& f, const addrms_cfg& c, void* x, void* r, 
                           int dtype, hipStream_t stream)
 {
     DirectPlan p;
-    if (!direct_addrms_plan(M, N, dtype, &p)) return launch(f, c, x, r, w, eps, M, N, stream);
+    if (!direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(r), &p)) return launch(f, c, x, r, w, eps, M, N, stream);
     HIP_TRY(static_cast<hipError_t>(direct_launch_addrms(p, x, r, w, eps, M, N, stream)));
     return ADDRMS_OK;
 }

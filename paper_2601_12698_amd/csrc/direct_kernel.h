@@ -8,6 +8,13 @@
 // kernel of the program looks for its input.  Write-through stores (sc1) go to the memory
 // side as they are issued and stay there.  Which one a problem takes is decided by what it
 // writes (write_through_max in addrms_direct.hip has both sides measured).
+//
+// Ragged rows (RAG).  A row length that VEC does not divide used to mean accesses as narrow
+// as one element, and one that 128 bytes do not divide waves whose lines are shared with the
+// waves beside them.  Here the walk of a row begins at the cache line its first element lies
+// in, so that every wave covers whole lines; the pieces of VEC elements inside the row go to
+// the lanes, and the fewer than 2 * VEC elements before its first and after its last whole
+// piece to the first lanes, one each.
 #pragma once
 #include <type_traits>
 
@@ -69,7 +76,10 @@ __device__ __forceinline__ void st_stream(char* base, uint32_t off, const raw_t<
 // Default of the knob grid -> here, us: 16 x 4096 bf16 3.1 -> 2.5, 256 x 5120 4.1 -> 3.5,
 // 512 x 8192 8.3 -> 6.3, 4096 x 4096 21.5 -> 20.1, 20000 x 5120 152 -> 130 (6.3 TB/s),
 // 32768 x 7168 340 -> 304, 2048 x 8192 fp32 56.4 -> 45.3, 900 x 28672 fp16 44.3 -> 39.8.
-template <int DT, int VEC, int CPT, int POL, bool DEFER>
+// Ragged: 2047 x 4095 fp16 18.6 -> 12.9 (buffers from HBM 27.4 -> 13.5), 9000 x 6150 bf16 95.5 ->
+// 77, 300 x 10001 9.3 -> 7.5, 8192 x 1000 fp16+fp32 18.2 -> 17.4 (from HBM 23.5 -> 20.8); the single
+// elements cost the first 0.7 us and weights at odd addresses 0.4 of what an aligned row would not.
+template <int DT, int VEC, int CPT, int POL, bool RAG, bool DEFER>
 __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* __restrict__ rp,
                                                    const void* __restrict__ wp, float eps, double inv_n, int64_t M,
                                                    int32_t N)
@@ -84,11 +94,31 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     const RowAddr ra = row_addr<XB, RB>(xp, rp, blockIdx.x, rpw, ry, M, N);
     const char* wbase = static_cast<const char*>(wp);
-    const uint32_t nlast = static_cast<uint32_t>(N) - VEC;
-    const uint32_t col0 = lane * VEC, stride = tpr * VEC;
+    // Ragged: `into` elements of the row's first cache line belong to the row before it; `head` elements precede the
+    // row's first whole piece, which is a whole piece of both streams (the host checked that they have the same phase).
+    constexpr int32_t LINE = 128 / XB;
+    const int32_t into = RAG ? static_cast<int32_t>((static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ra.xbase)) / XB + ra.rowoff) % LINE) : 0;
+    const int32_t head = RAG ? (LINE - into) % VEC : 0;
+    const int32_t nv = RAG ? head + (N - head) / VEC * VEC : N;
+    const int32_t nlast = nv - VEC;
+    const int32_t col0 = static_cast<int32_t>(lane) * VEC - into, stride = static_cast<int32_t>(tpr) * VEC;
+    const uint32_t tcol = static_cast<int32_t>(lane) < head ? lane : static_cast<uint32_t>(nv - head) + lane;   // this lane's single element
+    const bool tail = RAG && tcol < static_cast<uint32_t>(N);
+    auto in_row = [=](int32_t col) { return RAG ? static_cast<uint32_t>(col) <= static_cast<uint32_t>(nlast) : col <= nlast; };
+    auto clamped = [=](int32_t col) {            // idle lanes re-read valid data
+        const int32_t c = RAG && col < head ? head : col;
+        return static_cast<uint32_t>(c < nlast ? c : nlast);
+    };
 
-    float h[CPT][VEC];
+    float h[CPT][VEC], ht = 0.0f;
+    raw_t<XB> xt{}, wt{};
+    raw_t<RB> rt{};
     double acc = 0.0;
+    if (tail) {
+        ld_raw<XB, true>(ra.xbase + static_cast<uint64_t>((ra.rowoff + tcol) * XB), xt);
+        ld_raw<RB, true>(ra.rbase + static_cast<uint64_t>((ra.rowoff + tcol) * RB), rt);
+        ld_raw<XB, false>(wbase + static_cast<uint64_t>(tcol * XB), wt);
+    }
 #pragma unroll
     for (int g = 0; g < CPT; g += UNR) {
         raw_t<XB * VEC> xv[UNR];
@@ -96,8 +126,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             if (g + u < CPT) {
-                const uint32_t col = col0 + static_cast<uint32_t>(g + u) * stride;
-                const uint32_t colc = col < nlast ? col : nlast;      // idle lanes re-read valid data
+                const uint32_t colc = clamped(col0 + (g + u) * stride);
                 ld_stream<POL, XB * VEC, 16>(ra.xbase, (ra.rowoff + colc) * XB, xv[u]);
                 ld_stream<POL, RB * VEC, 16>(ra.rbase, (ra.rowoff + colc) * RB, rv[u]);
             }
@@ -106,11 +135,11 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
         for (int u = 0; u < UNR; ++u) {
             if (g + u < CPT) {
                 const int c = g + u;
-                const uint32_t col = col0 + static_cast<uint32_t>(c) * stride;
+                const int32_t col = col0 + c * stride;
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
                     h[c][e] = get_elem<XB, BF>(xv[u], e) + get_elem<RB, BF && RB == 2>(rv[u], e);
-                if (ra.row_ok && col <= nlast) {
+                if (ra.row_ok && in_row(col)) {
                     if constexpr (!DEFER) {
                         raw_t<RB * VEC> out;
                         pack_vec<RB, BF, VEC>(h[c], out);
@@ -126,12 +155,16 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
         }
         if (g + UNR < CPT) __builtin_amdgcn_sched_barrier(0);
     }
+    if (tail) {
+        ht = get_elem<XB, BF>(xt, 0) + get_elem<RB, BF && RB == 2>(rt, 0);
+        const double hd = static_cast<double>(ht);
+        acc = __builtin_fma(hd, hd, acc);
+    }
     raw_t<XB * VEC> wv[CPT];
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-        const uint32_t col = col0 + static_cast<uint32_t>(c) * stride;
-        const uint32_t colc = col < nlast ? col : nlast;
-        ld_stream<POL_CACHED, XB * VEC, 16>(wbase, colc * XB, wv[c]);
+        const uint32_t colc = clamped(col0 + c * stride);
+        ld_stream<POL_CACHED, XB * VEC, RAG ? XB : 16>(wbase, colc * XB, wv[c]);
     }
 
     const double ss = row_sum(acc, RED_WAVE, tpr, lane, ry, lds);
@@ -140,8 +173,8 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
     if constexpr (DEFER) {
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
-            const uint32_t col = col0 + static_cast<uint32_t>(c) * stride;
-            if (ra.row_ok && col <= nlast) {
+            const int32_t col = col0 + c * stride;
+            if (ra.row_ok && in_row(col)) {
                 raw_t<RB * VEC> out;
                 pack_vec<RB, BF, VEC>(h[c], out);
                 st_stream<POL, RB * VEC>(ra.rbase, (ra.rowoff + col) * RB, out);
@@ -150,18 +183,29 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
     }
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-        const uint32_t col = col0 + static_cast<uint32_t>(c) * stride;
+        const int32_t col = col0 + c * stride;
         float y[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
             const float t = h[c][e] * rstd;
             y[e] = t * get_elem<XB, BF>(wv[c], e);
         }
-        if (ra.row_ok && col <= nlast) {
+        if (ra.row_ok && in_row(col)) {
             raw_t<XB * VEC> out;
             pack_vec<XB, BF, VEC>(y, out);
             st_stream<POL, XB * VEC>(ra.xbase, (ra.rowoff + col) * XB, out);
         }
+    }
+    if (tail && ra.row_ok) {
+        float f[1] = {ht};
+        raw_t<RB> rout;
+        pack_vec<RB, BF, 1>(f, rout);
+        st_raw<RB, true>(ra.rbase + static_cast<uint64_t>((ra.rowoff + tcol) * RB), rout);
+        const float t = ht * rstd;
+        f[0] = t * get_elem<XB, BF>(wt, 0);
+        raw_t<XB> yout;
+        pack_vec<XB, BF, 1>(f, yout);
+        st_raw<XB, true>(ra.xbase + static_cast<uint64_t>((ra.rowoff + tcol) * XB), yout);
     }
 }
 

@@ -127,3 +127,43 @@ NORM = [("bf16", 1, 136), ("bf16", 7, 256), ("bf16", 8, 264), ("fp16", 5, 512), 
 @pytest.mark.parametrize("dtype,M,N", NORM)
 def test_norm(dtype, M, N):
     check_norm(M, N, dtype)
+
+
+# rows that 16 bytes do not divide (every remainder), that lines do not divide, that begin at every element of a line,
+# with as many pieces as threads and one more, and the longest ones; under 1 MB with a default access of two elements
+RAGGED = [("bf16", 67, 129), ("bf16", 66, 131), ("fp16", 130, 255), ("fp16", 9, 1001), ("fp16", 9, 1003), ("bf16", 9, 1005),
+          ("bf16", 9, 1007), ("bf16", 700, 1030), ("bf16", 600, 1020), ("bf16", 5, 449), ("bf16", 5, 450), ("fp32", 70, 65),
+          ("fp32", 35, 67), ("fp32", 9, 1001), ("fp32", 300, 1002), ("fp32", 3, 4067), ("fp32", 3, 4069), ("fp16_res32", 65, 67),
+          ("fp16_res32", 9, 1001), ("fp16_res32", 9, 4033), ("fp16_res32", 9, 4035), ("bf16", 40, 1030), ("bf16", 3, 8129),
+          ("bf16", 3, 8131), ("fp16", 2, 16385), ("fp16", 2, 32705), ("fp16", 2, 32707), ("fp32", 2, 32737), ("fp32", 2, 32739),
+          ("fp16_res32", 2, 32705), ("bf16", 4500, 1000), ("fp16_res32", 3000, 1000), ("fp32", 2200, 1004), ("bf16", 9000, 6150)]
+
+
+@pytest.mark.parametrize("dtype,M,N", RAGGED)
+def test_norm_of_ragged_rows(dtype, M, N):
+    check_norm(M, N, dtype)
+
+
+@pytest.mark.parametrize("dtype", W.DTYPES)
+@pytest.mark.parametrize("off", [1, 2, 3, 5])
+def test_norm_of_ragged_rows_from_any_element(dtype, off):
+    check_norm(17, 1001, dtype, off)
+
+
+def test_norm_of_ragged_rows_whose_streams_begin_at_different_elements():
+    M, N = 17, 1001
+    x, xok, r, rok, w = norm_inputs(M, N, "bf16", 7, 1)
+    r2, r2ok = guarded(M * N, torch.bfloat16, 0)
+    r2.copy_(r)
+    xw, rw = x.clone(), r.clone()
+    B.addrms_run(xw, rw, w, 1e-6, M, N, "bf16", B.addrms_default_cfg(N, "bf16"))
+    B.addrms_run(x, r2, w, 1e-6, M, N, "bf16")
+    torch.cuda.synchronize()
+    assert torch.equal(bits(r2), bits(rw)) and torch.equal(bits(x), bits(xw)) and xok() and r2ok()
+
+
+def test_norm_refuses_bases_the_default_configuration_refuses():
+    x, _, r, _, w = norm_inputs(8, 1000, "bf16", 7, 1)
+    with pytest.raises(B.AddrmsError) as e:
+        B.addrms_run(x, r, w, 1e-6, 8, 1000, "bf16")
+    assert e.value.status == B.ERR_MISALIGNED
