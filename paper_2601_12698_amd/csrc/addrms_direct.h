@@ -10,6 +10,8 @@ namespace addrms_host {
 struct DirectPlan {
     const void* fn = nullptr;
     unsigned grid = 0, block_x = 0, block_y = 1, lds = 0;
+    bool long_row = false;                                  // rows beyond the registers: units = chunks parked in LDS
+    unsigned long_index = 0;                                // ... and which of those kernels
     unsigned units = 0, total = 0, mul = 0, shift = 0;      // flat operators: see direct_kernel.h
 };
 

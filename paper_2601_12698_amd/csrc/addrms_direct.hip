@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 
 #include "addrms_direct.h"
 #include "direct_kernel.h"
@@ -16,6 +17,15 @@ __global__ __launch_bounds__(1024) void addrms_direct(void* x, void* r, const vo
                                                       long long M, int N)
 {
     addrms_direct_body<DT, VEC, CPT, POL, RAG, (CPT > 1)>(x, r, w, eps, inv_n, M, N);
+}
+// Workgroups of 1024 threads leave each 128 registers: 48 values of the row stay there.  (512 threads with 144 values
+// each: 204 us against 210 on 1024 x 131072 bf16, but 68 against 58 on 300 x 110592 and 27 against 20 on 8 x 123776.)
+constexpr int kLongThreads = 1024, kLongRegValues = 48;
+template <int DT, int VEC, int POL, bool RAG>
+__global__ __launch_bounds__(kLongThreads) void addrms_long(void* x, void* r, const void* w, float eps, double inv_n, int N,
+                                                            unsigned lds_chunks)
+{
+    addrms_long_body<DT, VEC, kLongRegValues / VEC, 2, POL, RAG>(x, r, w, eps, inv_n, N, lds_chunks);
 }
 template <int DT, int POL, bool RAG>
 __global__ __launch_bounds__(kFlatThreads) void silumul_flat(const char* x, char* out, uint32_t d, uint32_t units,
@@ -65,6 +75,25 @@ const void* addrms_fn(int dtype, int cpt, int pol, bool rag)
     case DT_FP16: return addrms_fn1<DT_FP16>(cpt, pol, rag);
     case DT_FP16_RES32: return addrms_fn1<DT_FP16_RES32>(cpt, pol, rag);
     case DT_FP32: return addrms_fn1<DT_FP32>(cpt, pol, rag);
+    default: return nullptr;
+    }
+}
+
+template <int DT> const void* addrms_long_fn1(int pol, bool rag)
+{
+    constexpr int VEC = direct_vec(DT);
+    if (rag) return pol == POL_NT ? reinterpret_cast<const void*>(&addrms_long<DT, VEC, POL_NT, true>)
+                                  : reinterpret_cast<const void*>(&addrms_long<DT, VEC, POL_CACHED, true>);
+    return pol == POL_NT ? reinterpret_cast<const void*>(&addrms_long<DT, VEC, POL_NT, false>)
+                         : reinterpret_cast<const void*>(&addrms_long<DT, VEC, POL_CACHED, false>);
+}
+const void* addrms_long_fn(int dtype, int pol, bool rag)
+{
+    switch (dtype) {
+    case DT_BF16: return addrms_long_fn1<DT_BF16>(pol, rag);
+    case DT_FP16: return addrms_long_fn1<DT_FP16>(pol, rag);
+    case DT_FP16_RES32: return addrms_long_fn1<DT_FP16_RES32>(pol, rag);
+    case DT_FP32: return addrms_long_fn1<DT_FP32>(pol, rag);
     default: return nullptr;
     }
 }
@@ -119,6 +148,27 @@ constexpr int64_t kFlatMax = 1ll << 31;                       // positions the f
 
 namespace addrms_host {
 
+// Rows that 32 values per thread of 1024 do not hold.  Ordinary loads and stores up to the size that the memory-side
+// cache keeps (230 x 86912 bf16, 80 MB: 26.6 us against 31.6 with non-temporal ones; 8 x 123776 16.5 against 20.8),
+// non-temporal beyond (1024 x 131072 bf16 210 us against 245).
+static bool direct_addrms_long_plan(int64_t M, int64_t N, int dtype, DirectPlan* out)
+{
+    const int vec = direct_vec(dtype), xb = x_bytes(dtype);
+    const bool rag = (N * xb) % kLineBytes != 0, nt = M * N * (xb + r_bytes(dtype)) > write_through_max();
+    const int64_t span = static_cast<int64_t>(kLongThreads) * vec, slot = span * 4;             // elements, LDS bytes per chunk
+    const int64_t need = (N + (rag ? kLineBytes / xb - 1 : 0) + span - 1) / span;
+    const int64_t fit = (hw().lds_bytes_per_cu - 128) / slot;                                   // behind one fp64 sum per wave
+    out->units = static_cast<unsigned>(std::min(fit, std::max<int64_t>(0, need - kLongRegValues / vec)));
+    out->fn = addrms_long_fn(dtype, nt ? POL_NT : POL_CACHED, rag);
+    if (!out->fn) return false;
+    out->long_index = static_cast<unsigned>(dtype) * 4u + (nt ? 2u : 0u) + (rag ? 1u : 0u);
+    out->block_x = kLongThreads;
+    out->grid = static_cast<unsigned>(M);
+    out->lds = 128u + out->units * static_cast<unsigned>(slot);
+    out->long_row = true;
+    return true;
+}
+
 // Ragged rows up to 96 MB take three pieces per thread and two rows per workgroup, so that fewer waves repeat what a
 // row costs before and after its pieces (2047 x 4095 fp16 12.9 us against 14.0 with one piece per thread, 5000 x 1001
 // fp32 15.5 against 16.0, 300 x 10001 bf16 7.4 against 8.2 with two); beyond, one is as good or better (9000 x 6150
@@ -140,7 +190,8 @@ bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintpt
     if (split && ((x / xb) % vec != (r / rb) % vec || (bytes < kRaggedMin && default_vec > 1))) return false;
     const int line = kLineBytes / xb;                                                 // elements
     const int64_t pieces = (N + (rag ? line - 1 : 0) + vec - 1) / vec;                // a ragged row begins anywhere in a line
-    if (N < 16 * vec || pieces > 8192) return false;
+    if (N < 16 * vec) return false;
+    if (pieces * vec > 32 * 1024) return direct_addrms_long_plan(M, N, dtype, out);
     const int pol = bytes >= kWriteThroughMin && bytes <= write_through_max() && !split ? POL_WT : POL_NT;
     // threads per row: one per piece up to 1024, then as few pieces per thread as that allows, in equal shares; three
     // pieces per thread and two rows per workgroup for ragged rows
@@ -187,6 +238,15 @@ bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_ali
 
 static int go(const DirectPlan& p, void** args, void* stream)
 {
+    if (p.lds > 64u * 1024u) {                                 // beyond the default limit: once per kernel, as launch_instance
+        static std::atomic<uint64_t> allowed{0};               // one bit per long-row kernel
+        const uint64_t bit = 1ull << p.long_index;
+        if (!(allowed.load(std::memory_order_acquire) & bit)) {
+            const hipError_t e = hipFuncSetAttribute(p.fn, hipFuncAttributeMaxDynamicSharedMemorySize, hw().lds_bytes_per_cu);
+            if (e != hipSuccess) return static_cast<int>(e);
+            allowed.fetch_or(bit, std::memory_order_acq_rel);
+        }
+    }
     return static_cast<int>(hipLaunchKernel(p.fn, dim3(p.grid), dim3(p.block_x, p.block_y), args, p.lds,
                                             static_cast<hipStream_t>(stream)));
 }
@@ -195,6 +255,11 @@ int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, f
     double inv_n = 1.0 / static_cast<double>(N);
     long long m = M;
     int n = static_cast<int>(N);
+    if (p.long_row) {
+        unsigned lds_chunks = p.units;
+        void* args[] = {&x, &r, &w, &eps, &inv_n, &n, &lds_chunks};
+        return go(p, args, stream);
+    }
     void* args[] = {&x, &r, &w, &eps, &inv_n, &m, &n};
     return go(p, args, stream);
 }

@@ -65,6 +65,78 @@ __device__ __forceinline__ void st_stream(char* base, uint32_t off, const raw_t<
     }
 }
 
+// The columns of one row as a workgroup's lanes walk them: lane `lane` of `tpr` takes the VEC elements from
+// col0 + c * stride on, for c = 0, 1, ...  Ragged: `into` elements of the row's first cache line belong to the row
+// before it; `head` elements precede the row's first whole piece, which is a whole piece of both streams (the host
+// checked that they have the same phase), and lane i of the first ones has the single element `single`.
+template <int XB, int VEC, bool RAG>
+struct RowWalk {
+    static constexpr int32_t LINE = 128 / XB;
+    int32_t into, head, nlast, col0, stride;
+    uint32_t single;
+    bool has_single;
+    __device__ __forceinline__ RowWalk(const char* xbase, uint32_t rowoff, int32_t N, uint32_t lane, uint32_t tpr)
+    {
+        into = RAG ? static_cast<int32_t>((static_cast<uint32_t>(reinterpret_cast<uintptr_t>(xbase)) / XB + rowoff) % LINE) : 0;
+        head = RAG ? (LINE - into) % VEC : 0;
+        const int32_t nv = RAG ? head + (N - head) / VEC * VEC : N;       // end of the last whole piece
+        nlast = nv - VEC;
+        col0 = static_cast<int32_t>(lane) * VEC - into;
+        stride = static_cast<int32_t>(tpr) * VEC;
+        single = static_cast<int32_t>(lane) < head ? lane : static_cast<uint32_t>(nv - head) + lane;
+        has_single = RAG && single < static_cast<uint32_t>(N);
+    }
+    __device__ __forceinline__ bool in_row(int32_t col) const
+    {
+        return RAG ? static_cast<uint32_t>(col) <= static_cast<uint32_t>(nlast) : col <= nlast;
+    }
+    __device__ __forceinline__ uint32_t clamped(int32_t col) const         // idle lanes re-read valid data
+    {
+        const int32_t c = RAG && col < head ? head : col;
+        return static_cast<uint32_t>(c < nlast ? c : nlast);
+    }
+};
+// A lane's single element from the loads to the stores (nothing where rows are not ragged).
+template <int DT, bool RAG>
+struct SingleElement {
+    using T = dt_traits<DT>;
+    static constexpr int XB = T::XB, RB = T::RB;
+    raw_t<XB> x{}, w{};
+    raw_t<RB> r{};
+    float h = 0.0f;
+    __device__ __forceinline__ void load(const char* xrow, const char* rrow, const char* wbase, uint32_t at, bool mine)
+    {
+        if (RAG && mine) {
+            ld_raw<XB, true>(xrow + static_cast<uint64_t>(at * XB), x);
+            ld_raw<RB, true>(rrow + static_cast<uint64_t>(at * RB), r);
+            ld_raw<XB, false>(wbase + static_cast<uint64_t>(at * XB), w);
+        }
+    }
+    __device__ __forceinline__ double add(double acc)                      // 0 where a lane has none
+    {
+        if constexpr (RAG) {
+            h = get_elem<XB, T::BF>(x, 0) + get_elem<RB, T::BF && RB == 2>(r, 0);
+            const double hd = static_cast<double>(h);
+            acc = __builtin_fma(hd, hd, acc);
+        }
+        return acc;
+    }
+    __device__ __forceinline__ void store(char* xrow, char* rrow, uint32_t at, bool mine, float rstd) const
+    {
+        if (RAG && mine) {
+            float f[1] = {h};
+            raw_t<RB> rout;
+            pack_vec<RB, T::BF, 1>(f, rout);
+            st_raw<RB, true>(rrow + static_cast<uint64_t>(at * RB), rout);
+            const float t = h * rstd;
+            f[0] = t * get_elem<XB, T::BF>(w, 0);
+            raw_t<XB> yout;
+            pack_vec<XB, T::BF, 1>(f, yout);
+            st_raw<XB, true>(xrow + static_cast<uint64_t>(at * XB), yout);
+        }
+    }
+};
+
 // ---- add + RMSNorm ---------------------------------------------------------------------------
 // A workgroup per row (several for rows shorter than a wave), a thread holds CPT chunks of VEC
 // elements from the loads to the stores.  Same arithmetic as addrms_body, bit for bit.  HBM-bound:
@@ -94,31 +166,14 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     const RowAddr ra = row_addr<XB, RB>(xp, rp, blockIdx.x, rpw, ry, M, N);
     const char* wbase = static_cast<const char*>(wp);
-    // Ragged: `into` elements of the row's first cache line belong to the row before it; `head` elements precede the
-    // row's first whole piece, which is a whole piece of both streams (the host checked that they have the same phase).
-    constexpr int32_t LINE = 128 / XB;
-    const int32_t into = RAG ? static_cast<int32_t>((static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ra.xbase)) / XB + ra.rowoff) % LINE) : 0;
-    const int32_t head = RAG ? (LINE - into) % VEC : 0;
-    const int32_t nv = RAG ? head + (N - head) / VEC * VEC : N;
-    const int32_t nlast = nv - VEC;
-    const int32_t col0 = static_cast<int32_t>(lane) * VEC - into, stride = static_cast<int32_t>(tpr) * VEC;
-    const uint32_t tcol = static_cast<int32_t>(lane) < head ? lane : static_cast<uint32_t>(nv - head) + lane;   // this lane's single element
-    const bool tail = RAG && tcol < static_cast<uint32_t>(N);
-    auto in_row = [=](int32_t col) { return RAG ? static_cast<uint32_t>(col) <= static_cast<uint32_t>(nlast) : col <= nlast; };
-    auto clamped = [=](int32_t col) {            // idle lanes re-read valid data
-        const int32_t c = RAG && col < head ? head : col;
-        return static_cast<uint32_t>(c < nlast ? c : nlast);
-    };
+    char *xrow = ra.xbase + static_cast<uint64_t>(ra.rowoff * XB), *rrow = ra.rbase + static_cast<uint64_t>(ra.rowoff * RB);
+    const RowWalk<XB, VEC, RAG> rw(ra.xbase, ra.rowoff, N, lane, tpr);
+    const int32_t col0 = rw.col0, stride = rw.stride;
 
-    float h[CPT][VEC], ht = 0.0f;
-    raw_t<XB> xt{}, wt{};
-    raw_t<RB> rt{};
+    float h[CPT][VEC];
     double acc = 0.0;
-    if (tail) {
-        ld_raw<XB, true>(ra.xbase + static_cast<uint64_t>((ra.rowoff + tcol) * XB), xt);
-        ld_raw<RB, true>(ra.rbase + static_cast<uint64_t>((ra.rowoff + tcol) * RB), rt);
-        ld_raw<XB, false>(wbase + static_cast<uint64_t>(tcol * XB), wt);
-    }
+    SingleElement<DT, RAG> one;
+    one.load(xrow, rrow, wbase, rw.single, rw.has_single);
 #pragma unroll
     for (int g = 0; g < CPT; g += UNR) {
         raw_t<XB * VEC> xv[UNR];
@@ -126,7 +181,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             if (g + u < CPT) {
-                const uint32_t colc = clamped(col0 + (g + u) * stride);
+                const uint32_t colc = rw.clamped(col0 + (g + u) * stride);
                 ld_stream<POL, XB * VEC, 16>(ra.xbase, (ra.rowoff + colc) * XB, xv[u]);
                 ld_stream<POL, RB * VEC, 16>(ra.rbase, (ra.rowoff + colc) * RB, rv[u]);
             }
@@ -139,7 +194,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
                     h[c][e] = get_elem<XB, BF>(xv[u], e) + get_elem<RB, BF && RB == 2>(rv[u], e);
-                if (ra.row_ok && in_row(col)) {
+                if (ra.row_ok && rw.in_row(col)) {
                     if constexpr (!DEFER) {
                         raw_t<RB * VEC> out;
                         pack_vec<RB, BF, VEC>(h[c], out);
@@ -155,15 +210,11 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
         }
         if (g + UNR < CPT) __builtin_amdgcn_sched_barrier(0);
     }
-    if (tail) {
-        ht = get_elem<XB, BF>(xt, 0) + get_elem<RB, BF && RB == 2>(rt, 0);
-        const double hd = static_cast<double>(ht);
-        acc = __builtin_fma(hd, hd, acc);
-    }
+    acc = one.add(acc);
     raw_t<XB * VEC> wv[CPT];
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-        const uint32_t colc = clamped(col0 + c * stride);
+        const uint32_t colc = rw.clamped(col0 + c * stride);
         ld_stream<POL_CACHED, XB * VEC, RAG ? XB : 16>(wbase, colc * XB, wv[c]);
     }
 
@@ -174,7 +225,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
             const int32_t col = col0 + c * stride;
-            if (ra.row_ok && in_row(col)) {
+            if (ra.row_ok && rw.in_row(col)) {
                 raw_t<RB * VEC> out;
                 pack_vec<RB, BF, VEC>(h[c], out);
                 st_stream<POL, RB * VEC>(ra.rbase, (ra.rowoff + col) * RB, out);
@@ -190,23 +241,196 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
             const float t = h[c][e] * rstd;
             y[e] = t * get_elem<XB, BF>(wv[c], e);
         }
-        if (ra.row_ok && in_row(col)) {
+        if (ra.row_ok && rw.in_row(col)) {
             raw_t<XB * VEC> out;
             pack_vec<XB, BF, VEC>(y, out);
             st_stream<POL, XB * VEC>(ra.xbase, (ra.rowoff + col) * XB, out);
         }
     }
-    if (tail && ra.row_ok) {
-        float f[1] = {ht};
-        raw_t<RB> rout;
-        pack_vec<RB, BF, 1>(f, rout);
-        st_raw<RB, true>(ra.rbase + static_cast<uint64_t>((ra.rowoff + tcol) * RB), rout);
-        const float t = ht * rstd;
-        f[0] = t * get_elem<XB, BF>(wt, 0);
-        raw_t<XB> yout;
-        pack_vec<XB, BF, 1>(f, yout);
-        st_raw<XB, true>(ra.xbase + static_cast<uint64_t>((ra.rowoff + tcol) * XB), yout);
+    one.store(xrow, rrow, rw.single, rw.has_single && ra.row_ok, rstd);
+}
+
+// ---- add + RMSNorm, rows beyond the registers ---------------------------------------------------
+// The walk of addrms_hybrid_body (its comment has the three parts: registers, parked in LDS, read
+// twice) for one row per workgroup, with the store policy of the size, ragged rows, and the weights
+// of the register part fetched before the row sum, so that its stores are the first to follow it
+// (1-3 % against fetching each behind the stores before it).  Bound by one workgroup filling a CU:
+// it reads its row, then writes it, and nothing else runs there meanwhile.  Write-through stores
+// lose here (1024 x 131072 bf16 234 us against 211): the next loads wait for their acknowledgement.
+// Default of the knob grid -> here, us: 1024 x 131072 bf16 248 -> 210, 2048 x 65536 221 -> 198,
+// 4096 x 40960 264 -> 232, 300 x 110592 77 -> 58, 230 x 86912 fp32 87 -> 59, 500 x 200000 fp32
+// 408 -> 356, 230 x 86912 bf16 35 -> 26; ragged rows, which were read one to four elements at a
+// time: 300 x 33333 bf16 41 -> 22, 700 x 99991 240 -> 113, 100 x 180001 113 -> 39.
+template <int DT, int VEC, int CPT, int UNR, int POL, bool RAG>
+__device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __restrict__ rp,
+                                                 const void* __restrict__ wp, float eps, double inv_n, int32_t N,
+                                                 uint32_t lds_chunks)
+{
+    using T = dt_traits<DT>;
+    constexpr int XB = T::XB, RB = T::RB;
+    constexpr bool BF = T::BF;
+    extern __shared__ double lds[];
+
+    const uint32_t tpr = blockDim.x, lane = threadIdx.x;
+    char* xbase = static_cast<char*>(xp) + static_cast<int64_t>(blockIdx.x) * N * XB;
+    char* rbase = static_cast<char*>(rp) + static_cast<int64_t>(blockIdx.x) * N * RB;
+    const char* wbase = static_cast<const char*>(wp);
+    const RowWalk<XB, VEC, RAG> rw(xbase, 0u, N, lane, tpr);
+    const int32_t col0 = rw.col0, stride = rw.stride;
+    const int32_t need = (N + (RAG ? 128 / XB - 1 : 0) + stride - 1) / stride;    // chunks per thread
+    const int32_t parked = static_cast<int32_t>(lds_chunks), streamed = CPT + parked;
+    float* cache = reinterpret_cast<float*>(lds + 16) + lane * VEC;                // behind one fp64 slot per wave
+
+    float h[CPT][VEC];
+    double acc = 0.0;
+    auto load = [&](int32_t col, raw_t<XB * VEC>& x, raw_t<RB * VEC>& r) {
+        const uint32_t c = rw.clamped(col);
+        ld_stream<POL, XB * VEC, 16>(xbase, c * XB, x);
+        ld_stream<POL, RB * VEC, 16>(rbase, c * RB, r);
+    };
+    auto weight = [&](int32_t col, raw_t<XB * VEC>& w) {
+        ld_stream<POL_CACHED, XB * VEC, RAG ? XB : 16>(wbase, rw.clamped(col) * XB, w);
+    };
+    auto sum = [&](const raw_t<XB * VEC>& x, const raw_t<RB * VEC>& r, float (&s)[VEC]) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) s[e] = get_elem<XB, BF>(x, e) + get_elem<RB, BF && RB == 2>(r, e);
+    };
+    auto square = [&](const float (&s)[VEC]) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const double hd = static_cast<double>(s[e]);
+            acc = __builtin_fma(hd, hd, acc);
+        }
+    };
+    auto put_residual = [&](int32_t col, const float (&s)[VEC]) {
+        raw_t<RB * VEC> out;
+        pack_vec<RB, BF, VEC>(s, out);
+        st_stream<POL, RB * VEC>(rbase, static_cast<uint32_t>(col) * RB, out);
+    };
+    auto put_y = [&](int32_t col, const float (&s)[VEC], const raw_t<XB * VEC>& w, float rstd) {
+        float y[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const float t = s[e] * rstd;
+            y[e] = t * get_elem<XB, BF>(w, e);
+        }
+        raw_t<XB * VEC> out;
+        pack_vec<XB, BF, VEC>(y, out);
+        st_stream<POL, XB * VEC>(xbase, static_cast<uint32_t>(col) * XB, out);
+    };
+
+    SingleElement<DT, RAG> one;
+    one.load(xbase, rbase, wbase, rw.single, rw.has_single);
+    // ---- register part
+#pragma unroll
+    for (int g = 0; g < CPT; g += UNR) {
+        raw_t<XB * VEC> xv[UNR];
+        raw_t<RB * VEC> rv[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) load(col0 + (g + u) * stride, xv[u], rv[u]);
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const int32_t col = col0 + (g + u) * stride;
+            sum(xv[u], rv[u], h[g + u]);
+            if (rw.in_row(col)) {
+                put_residual(col, h[g + u]);
+                square(h[g + u]);
+            }
+        }
+        if (g + UNR < CPT) __builtin_amdgcn_sched_barrier(0);
     }
+    // ---- LDS part
+    for (int32_t c0 = 0; c0 < parked; c0 += UNR) {
+        raw_t<XB * VEC> xv[UNR];
+        raw_t<RB * VEC> rv[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) load(col0 + (CPT + c0 + u) * stride, xv[u], rv[u]);
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const int32_t col = col0 + (CPT + c0 + u) * stride;
+            if (c0 + u < parked) {
+                float s[VEC];
+                sum(xv[u], rv[u], s);
+                if (rw.in_row(col)) {
+                    put_residual(col, s);
+                    square(s);
+                }
+                float* slot = cache + static_cast<uint32_t>(c0 + u) * (tpr * VEC);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) slot[e] = s[e];
+            }
+        }
+    }
+    // ---- part that is read twice, first time: the sum only (ordinary loads: the second asks for the same lines)
+    for (int32_t c0 = streamed; c0 < need; c0 += UNR) {
+        raw_t<XB * VEC> xv[UNR];
+        raw_t<RB * VEC> rv[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const uint32_t c = rw.clamped(col0 + (c0 + u) * stride);
+            ld_raw<XB * VEC>(xbase + static_cast<uint64_t>(c * XB), xv[u]);
+            ld_raw<RB * VEC>(rbase + static_cast<uint64_t>(c * RB), rv[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            float s[VEC];
+            sum(xv[u], rv[u], s);
+            if (rw.in_row(col0 + (c0 + u) * stride)) square(s);
+        }
+    }
+    acc = one.add(acc);
+
+    raw_t<XB * VEC> wreg[CPT];
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) weight(col0 + c * stride, wreg[c]);
+    const double ss = row_sum(acc, RED_WAVE, tpr, lane, 0u, lds);
+    const float rstd = rsqrt_to_f32(__builtin_fma(ss, inv_n, static_cast<double>(eps)));
+
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const int32_t col = col0 + c * stride;
+        if (rw.in_row(col)) put_y(col, h[c], wreg[c], rstd);
+    }
+    // ---- read twice, second time, backwards: what was read last is nearest
+    for (int32_t k = need; k > streamed;) {
+        const int32_t c0 = k - UNR > streamed ? k - UNR : streamed;
+        raw_t<XB * VEC> xv[UNR], wv[UNR];
+        raw_t<RB * VEC> rv[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            load(col0 + (c0 + u) * stride, xv[u], rv[u]);
+            weight(col0 + (c0 + u) * stride, wv[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const int32_t col = col0 + (c0 + u) * stride;
+            if (c0 + u < k && rw.in_row(col)) {
+                float s[VEC];
+                sum(xv[u], rv[u], s);
+                put_residual(col, s);
+                put_y(col, s, wv[u], rstd);
+            }
+        }
+        k = c0;
+    }
+    // ---- LDS part
+    for (int32_t c0 = 0; c0 < parked; c0 += UNR) {
+        raw_t<XB * VEC> wv[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) weight(col0 + (CPT + c0 + u) * stride, wv[u]);
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const int32_t col = col0 + (CPT + c0 + u) * stride;
+            if (c0 + u < parked && rw.in_row(col)) {
+                const float* slot = cache + static_cast<uint32_t>(c0 + u) * (tpr * VEC);
+                float s[VEC];
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) s[e] = slot[e];
+                put_y(col, s, wv[u], rstd);
+            }
+        }
+    }
+    one.store(xbase, rbase, rw.single, rw.has_single, rstd);
 }
 
 // ---- elementwise operators over the output as one flat array -----------------------------------

@@ -167,3 +167,23 @@ def test_norm_refuses_bases_the_default_configuration_refuses():
     with pytest.raises(B.AddrmsError) as e:
         B.addrms_run(x, r, w, 1e-6, 8, 1000, "bf16")
     assert e.value.status == B.ERR_MISALIGNED
+
+
+# rows beyond the registers: the first length that is, one chunk parked in LDS and one left over, as much as LDS holds
+# and more (read twice), whole lines or not; both store policies
+LONG = [("bf16", 2, 32776), ("bf16", 3, 32832), ("fp16", 2, 32707), ("bf16", 2, 49152), ("bf16", 2, 49160), ("fp16", 2, 57344),
+        ("bf16", 2, 81920), ("bf16", 2, 81984), ("bf16", 2, 90113), ("fp16", 2, 131071), ("bf16", 1, 1 << 20), ("fp32", 2, 32772),
+        ("fp32", 2, 32741), ("fp32", 2, 49156), ("fp32", 2, 86016), ("fp32", 2, 86048), ("fp32", 2, 86019), ("fp32", 2, 200001),
+        ("fp16_res32", 2, 32832), ("fp16_res32", 2, 49153), ("fp16_res32", 2, 86020), ("fp16_res32", 2, 100003),
+        ("bf16", 700, 40960), ("bf16", 300, 99991), ("fp32", 150, 100000), ("fp16_res32", 200, 86022)]
+
+
+@pytest.mark.parametrize("dtype,M,N", LONG)
+def test_norm_of_rows_beyond_the_registers(dtype, M, N):
+    check_norm(M, N, dtype)
+
+
+@pytest.mark.parametrize("off", [1, 3])
+def test_norm_of_long_ragged_rows_from_any_element(off):
+    check_norm(3, 40001, "bf16", off)
+    check_norm(3, 90001, "fp32", off)
