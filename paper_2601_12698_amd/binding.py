@@ -314,11 +314,47 @@ def _dtype_id(dtype) -> int:
     return DTYPE_IDS[dtype] if isinstance(dtype, str) else int(dtype)
 
 
-def _stream_ptr(stream, tensor=None) -> Optional[int]:
+def _stream_ptr(stream, tensor) -> Optional[int]:
+    """The stream's handle; without one, of torch's current stream on the tensor's device (the raw handle: a Stream
+    object around it costs 2 us, as much as a launch)."""
     if stream is not None:
         return int(getattr(stream, "cuda_stream", stream))
-    import torch
-    return int(torch.cuda.current_stream(tensor.device if tensor is not None else None).cuda_stream)
+    return _torch().raw_stream(tensor.get_device())
+
+
+class _Torch:
+    """What the calls below ask of torch, looked up once: element types per storage format and the raw current stream."""
+
+    def __init__(self):
+        import torch
+        self.elems = {dt: (getattr(torch, _X_ELEM[dt]), getattr(torch, _R_ELEM[dt])) for dt in _X_ELEM}
+        self.float32 = torch.float32
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        self.raw_stream = raw or (lambda device: int(torch.cuda.current_stream(device).cuda_stream))
+
+
+_torch_facts = None
+
+
+def _torch() -> _Torch:
+    global _torch_facts
+    if _torch_facts is None:
+        _torch_facts = _Torch()
+    return _torch_facts
+
+
+def _format(dtype):
+    """(format id, element type of x, element type of residual)."""
+    dt = _dtype_id(dtype)
+    elems = _torch().elems.get(dt)
+    if elems is None:
+        raise ValueError(f"unknown dtype {dtype!r}")
+    return dt, elems[0], elems[1]
+
+
+def _fits(t, elem, numel) -> bool:
+    """What _expect_device_tensor asks for, without the words."""
+    return t.dtype is elem and t.numel() == numel and t.is_cuda and t.is_contiguous()
 
 
 def _ptr(t) -> int:
@@ -364,14 +400,16 @@ def addrms_algorithmic_bytes(M: int, N: int, dtype) -> int:
 def addrms_run(x, residual, weight, eps: float, M: int, N: int, dtype, cfg: Optional[Cfg] = None,
                stream=None) -> None:
     """In place: residual <- round(x + residual), x <- rmsnorm(x + residual) * weight."""
-    dt = _dtype_id(dtype)
-    if dt not in _X_ELEM:
-        raise ValueError(f"unknown dtype {dtype!r}")
-    _expect_device_tensor("x", x, M * N, _X_ELEM[dt])
-    _expect_device_tensor("residual", residual, M * N, _R_ELEM[dt])
-    _expect_device_tensor("weight", weight, N, _X_ELEM[dt])
-    _check(load().addrms_run(_ptr(x), _ptr(residual), _ptr(weight), float(eps), M, N, _dtype_id(dtype),
-                             byref(cfg) if cfg is not None else None, _stream_ptr(stream, x)))
+    dt, xe, re = _format(dtype)
+    n = M * N
+    if not (_fits(x, xe, n) and _fits(residual, re, n) and _fits(weight, xe, N)):
+        _expect_device_tensor("x", x, n, _X_ELEM[dt])
+        _expect_device_tensor("residual", residual, n, _R_ELEM[dt])
+        _expect_device_tensor("weight", weight, N, _X_ELEM[dt])
+    st = load().addrms_run(x.data_ptr(), residual.data_ptr(), weight.data_ptr(), float(eps), M, N, dt,
+                           byref(cfg) if cfg is not None else None, _stream_ptr(stream, x))
+    if st:
+        _check(st)
 
 
 def addrms_default_cfg(N: int, dtype) -> Cfg:
@@ -675,14 +713,13 @@ class GateCounts(Structure):
 
 
 def _gate_args(y, y_ref, residual, residual_ref, dtype, counts_out):
-    dt = _dtype_id(dtype)
-    if dt not in _X_ELEM:
-        raise ValueError(f"unknown dtype {dtype!r}")
+    dt, xe, re = _format(dtype)
     n = y.numel()
-    _expect_device_tensor("y", y, n, _X_ELEM[dt])
-    _expect_device_tensor("y_ref", y_ref, n, _X_ELEM[dt])
-    _expect_device_tensor("residual", residual, n, _R_ELEM[dt])
-    _expect_device_tensor("residual_ref", residual_ref, n, _R_ELEM[dt])
+    if not (_fits(y, xe, n) and _fits(y_ref, xe, n) and _fits(residual, re, n) and _fits(residual_ref, re, n)):
+        _expect_device_tensor("y", y, n, _X_ELEM[dt])
+        _expect_device_tensor("y_ref", y_ref, n, _X_ELEM[dt])
+        _expect_device_tensor("residual", residual, n, _R_ELEM[dt])
+        _expect_device_tensor("residual_ref", residual_ref, n, _R_ELEM[dt])
     if not counts_out.is_cuda or counts_out.numel() * counts_out.element_size() < 16:
         raise ValueError("counts_out must be a device tensor of at least 16 bytes")
     return n, dt
@@ -710,13 +747,15 @@ def silumul_algorithmic_bytes(M: int, d: int, dtype) -> int:
 
 def silumul_run(x, out, M: int, d: int, dtype, cfg: Optional[Cfg] = None, stream=None) -> None:
     """out[i, j] = silu(x[i, j]) * x[i, d + j]; x is [M, 2d], out is [M, d], both on the device."""
-    dt = _dtype_id(dtype)
-    if dt not in _X_ELEM:
-        raise ValueError(f"unknown dtype {dtype!r}")
-    _expect_device_tensor("x", x, 2 * M * d, _X_ELEM[dt])
-    _expect_device_tensor("out", out, M * d, _X_ELEM[dt])
-    _check(load().silumul_run(_ptr(x), _ptr(out), M, d, _dtype_id(dtype),
-                              byref(cfg) if cfg is not None else None, _stream_ptr(stream, x)))
+    dt, xe, _ = _format(dtype)
+    n = M * d
+    if not (_fits(x, xe, 2 * n) and _fits(out, xe, n)):
+        _expect_device_tensor("x", x, 2 * n, _X_ELEM[dt])
+        _expect_device_tensor("out", out, n, _X_ELEM[dt])
+    st = load().silumul_run(x.data_ptr(), out.data_ptr(), M, d, dt, byref(cfg) if cfg is not None else None,
+                            _stream_ptr(stream, x))
+    if st:
+        _check(st)
 
 
 def silumul_default_cfg(d: int, dtype) -> Cfg:
@@ -820,15 +859,19 @@ def mergestates_algorithmic_bytes(rows: int, d: int, dtype) -> int:
 def mergestates_run(v_a, s_a, v_b, s_b, v_out, s_out, rows: int, d: int, dtype, cfg: Optional[Cfg] = None,
                     stream=None) -> None:
     """Merge two partial attention states; v tensors [rows, d], scores fp32 [rows], all on the device."""
-    dt = _dtype_id(dtype)
-    if dt not in _X_ELEM:
-        raise ValueError(f"unknown dtype {dtype!r}")
-    for name, t in (("v_a", v_a), ("v_b", v_b), ("v_out", v_out)):
-        _expect_device_tensor(name, t, rows * d, _X_ELEM[dt])
-    for name, t in (("s_a", s_a), ("s_b", s_b), ("s_out", s_out)):
-        _expect_device_tensor(name, t, rows, "float32")
-    _check(load().mergestates_run(_ptr(v_a), _ptr(s_a), _ptr(v_b), _ptr(s_b), _ptr(v_out), _ptr(s_out), rows, d,
-                                  _dtype_id(dtype), byref(cfg) if cfg is not None else None, _stream_ptr(stream, v_a)))
+    dt, xe, _ = _format(dtype)
+    n, f32 = rows * d, _torch().float32
+    if not (_fits(v_a, xe, n) and _fits(v_b, xe, n) and _fits(v_out, xe, n) and _fits(s_a, f32, rows) and
+            _fits(s_b, f32, rows) and _fits(s_out, f32, rows)):
+        for name, t in (("v_a", v_a), ("v_b", v_b), ("v_out", v_out)):
+            _expect_device_tensor(name, t, n, _X_ELEM[dt])
+        for name, t in (("s_a", s_a), ("s_b", s_b), ("s_out", s_out)):
+            _expect_device_tensor(name, t, rows, "float32")
+    st = load().mergestates_run(v_a.data_ptr(), s_a.data_ptr(), v_b.data_ptr(), s_b.data_ptr(), v_out.data_ptr(),
+                                s_out.data_ptr(), rows, d, dt, byref(cfg) if cfg is not None else None,
+                                _stream_ptr(stream, v_a))
+    if st:
+        _check(st)
 
 
 def mergestates_default_cfg(d: int, dtype) -> Cfg:

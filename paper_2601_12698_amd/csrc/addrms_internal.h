@@ -114,6 +114,8 @@ std::string cfg_json(const addrms_cfg& c);
 // ---- specialised table -----------------------------------------------------
 int table_lookup(int64_t M, int64_t N, int dtype, addrms_cfg* out, int op = OP_ADDRMS);
 int table_insert(int64_t M, int64_t N, int dtype, const addrms_cfg& cfg, double mean_us, int op);
+// Another number after every change of the table: what was resolved from it before may be stale.
+uint64_t table_generation();
 
 // ---- search ----------------------------------------------------------------
 int run_search(int64_t M, int64_t N, int dtype, const addrms_budget* budget,

@@ -130,33 +130,117 @@ int resolve_cfg(const addrms_cfg* cfg, int64_t M, int64_t N, int dtype, addrms_c
     return st == ADDRMS_OK ? st : fail(st, "%s", why.c_str());
 }
 
-uintptr_t bits(const void* p) { return reinterpret_cast<uintptr_t>(p); }
+// ---- resolved calls -----------------------------------------------------------------
+// What a *_run call decides before it launches depends on its sizes, its configuration (if any), the table and the
+// alignment of its tensors, not on their contents or addresses.  Deciding it takes from 0.8 us to 13 us (a default
+// configuration behind several infeasible ones) beside a launch of 2 us, so each thread keeps its last decisions:
+// 64 of them, looked up by everything they depend on.
+struct Resolved {
+    Feas f;                  // of c, which has passed every check
+    addrms_cfg c{};
+    bool direct = false;     // no configuration named, and the direct kernels cover the problem: p
+    DirectPlan p;
+};
+struct ResolvedKey {
+    int64_t M, N;
+    uint64_t table;          // table_generation(); 0 in an empty slot
+    addrms_cfg cfg;          // zeroes where the call names none
+    int32_t op, dtype, has_cfg;
+    uint32_t low;            // the bases modulo 16: as much of an address as any check or rule asks for
+};
+bool same_key(const ResolvedKey& a, const ResolvedKey& b)
+{
+    return a.M == b.M && a.N == b.N && a.table == b.table && a.op == b.op && a.dtype == b.dtype && a.has_cfg == b.has_cfg &&
+           a.low == b.low && cfg_equal(a.cfg, b.cfg);
+}
 
-// Launches without a configuration: the default one has been checked against the problem (f, c) and stands in where
-// the direct kernels do not cover it.
-int launch_untuned_addrms(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, float eps, int64_t M, int64_t N,
-                          int dtype, hipStream_t stream)
+// Fills and checks one decision.  `misaligned` is the operator's own test of its tensors against a configuration.
+template <class Misaligned, class Plan>
+int resolve_call(const ResolvedKey& k, Resolved* out, Misaligned misaligned, Plan plan)
 {
-    DirectPlan p;
-    if (!direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(r), &p)) return launch(f, c, x, r, w, eps, M, N, stream);
-    HIP_TRY(static_cast<hipError_t>(direct_launch_addrms(p, x, r, w, eps, M, N, stream)));
+    bool untuned = false;
+    int st = resolve_cfg(k.has_cfg ? &k.cfg : nullptr, k.M, k.N, k.dtype, &out->c, k.op, &untuned);
+    if (st != ADDRMS_OK) return st;
+    out->f = check_cfg(out->c, k.M, k.N, k.dtype, k.op);
+    if (out->f.status != ADDRMS_OK) return fail(out->f.status, "%s", out->f.reason.c_str());
+    st = misaligned(out->c);
+    if (st != ADDRMS_OK) return st;
+    out->p = DirectPlan{};
+    out->direct = untuned && plan(out->c, &out->p);
     return ADDRMS_OK;
 }
-int launch_untuned_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out, int64_t M, int64_t d, int dtype,
-                           hipStream_t stream)
+template <class Misaligned, class Plan>
+int find_or_resolve(int op, int64_t M, int64_t N, int dtype, const addrms_cfg* cfg, uint32_t low, const Resolved** out,
+                    Misaligned misaligned, Plan plan)
 {
-    DirectPlan p;
-    if (!direct_silumul_plan(M, d, dtype, bits(x), bits(out), &p)) return launch_silumul(f, c, x, out, M, d, stream);
-    HIP_TRY(static_cast<hipError_t>(direct_launch_silumul(p, x, out, d, stream)));
+    constexpr unsigned kSlots = 64;
+    static thread_local ResolvedKey keys[kSlots];
+    static thread_local Resolved values[kSlots];
+    ResolvedKey k{M, N, table_generation(), cfg ? *cfg : addrms_cfg{}, op, dtype, cfg ? 1 : 0, low};
+    uint64_t h = static_cast<uint64_t>(M) * 0x9e3779b97f4a7c15ull ^ static_cast<uint64_t>(N) * 0xc2b2ae3d27d4eb4full;
+    h ^= (static_cast<uint64_t>(op) << 8 | static_cast<uint64_t>(dtype) << 4 | static_cast<uint64_t>(low) << 16) * 0x165667b19e3779f9ull;
+    if (cfg) h ^= cfg_key(*cfg) * 0x27d4eb2f165667c5ull;
+    const unsigned slot = static_cast<unsigned>(h >> 58);                  // the top six bits
+    static_assert(kSlots == 64, "six bits of the hash");
+    *out = &values[slot];
+    if (same_key(keys[slot], k)) return ADDRMS_OK;
+    keys[slot].table = 0;                                                  // nothing is kept of a call that fails
+    const int st = resolve_call(k, &values[slot], misaligned, plan);
+    if (st == ADDRMS_OK) keys[slot] = k;
+    return st;
+}
+uintptr_t bits(const void* p) { return reinterpret_cast<uintptr_t>(p); }
+uint32_t low4(const void* p, int place) { return static_cast<uint32_t>(bits(p) & 15u) << (4 * place); }
+
+int run_addrms(void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype, const addrms_cfg* cfg, hipStream_t stream)
+{
+    const Resolved* call = nullptr;
+    const int st = find_or_resolve(
+        OP_ADDRMS, M, N, dtype, cfg, low4(x, 0) | low4(r, 1) | low4(w, 2), &call,
+        [=](const addrms_cfg& c) {
+            const int xa = c.vec * x_bytes(dtype), ra = std::min(16, c.vec * r_bytes(dtype));
+            if (aligned(x, xa) && aligned(w, xa) && aligned(r, ra)) return static_cast<int>(ADDRMS_OK);
+            return fail(ADDRMS_ERR_MISALIGNED, "x and weight must be %d-byte aligned and residual %d-byte aligned for vec=%d",
+                        xa, ra, c.vec);
+        },
+        [=](const addrms_cfg& c, DirectPlan* p) { return direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(r), p); });
+    if (st != ADDRMS_OK) return st;
+    if (!call->direct) return launch(call->f, call->c, x, r, w, eps, M, N, stream);
+    HIP_TRY(static_cast<hipError_t>(direct_launch_addrms(call->p, x, r, w, eps, M, N, stream)));
     return ADDRMS_OK;
 }
-int launch_untuned_mergestates(const Feas& f, const addrms_cfg& c, const void* va, const float* sa, const void* vb,
-                               const float* sb, void* vo, float* so, int64_t rows, int64_t d, int dtype, hipStream_t stream)
+int run_silumul(const void* x, void* out, int64_t M, int64_t d, int dtype, const addrms_cfg* cfg, hipStream_t stream)
 {
-    DirectPlan p;
-    if (!direct_mergestates_plan(rows, d, dtype, bits(va) | bits(vb) | bits(vo), &p))
-        return launch_mergestates(f, c, va, sa, vb, sb, vo, so, rows, d, stream);
-    HIP_TRY(static_cast<hipError_t>(direct_launch_mergestates(p, va, sa, vb, sb, vo, so, stream)));
+    const Resolved* call = nullptr;
+    const int st = find_or_resolve(
+        OP_SILUMUL, M, d, dtype, cfg, low4(x, 0) | low4(out, 1), &call,
+        [=](const addrms_cfg& c) {
+            const int al = c.vec * x_bytes(dtype);
+            if (aligned(x, al) && aligned(out, al)) return static_cast<int>(ADDRMS_OK);
+            return fail(ADDRMS_ERR_MISALIGNED, "x and out must be %d-byte aligned for vec=%d", al, c.vec);
+        },
+        [=](const addrms_cfg&, DirectPlan* p) { return direct_silumul_plan(M, d, dtype, bits(x), bits(out), p); });
+    if (st != ADDRMS_OK) return st;
+    if (!call->direct) return launch_silumul(call->f, call->c, x, out, M, d, stream);
+    HIP_TRY(static_cast<hipError_t>(direct_launch_silumul(call->p, x, out, d, stream)));
+    return ADDRMS_OK;
+}
+int run_mergestates(const void* va, const float* sa, const void* vb, const float* sb, void* vo, float* so, int64_t rows,
+                    int64_t d, int dtype, const addrms_cfg* cfg, hipStream_t stream)
+{
+    const Resolved* call = nullptr;
+    const int st = find_or_resolve(
+        OP_MERGE, rows, d, dtype, cfg, low4(va, 0) | low4(vb, 1) | low4(vo, 2) | low4(sa, 3) | low4(sb, 4) | low4(so, 5), &call,
+        [=](const addrms_cfg& c) {
+            const int al = c.vec * x_bytes(dtype);
+            if (aligned(va, al) && aligned(vb, al) && aligned(vo, al) && aligned(sa, 4) && aligned(sb, 4) && aligned(so, 4))
+                return static_cast<int>(ADDRMS_OK);
+            return fail(ADDRMS_ERR_MISALIGNED, "v_a, v_b and v_out must be %d-byte aligned for vec=%d, scores 4-byte aligned", al, c.vec);
+        },
+        [=](const addrms_cfg&, DirectPlan* p) { return direct_mergestates_plan(rows, d, dtype, bits(va) | bits(vb) | bits(vo), p); });
+    if (st != ADDRMS_OK) return st;
+    if (!call->direct) return launch_mergestates(call->f, call->c, va, sa, vb, sb, vo, so, rows, d, stream);
+    HIP_TRY(static_cast<hipError_t>(direct_launch_mergestates(call->p, va, sa, vb, sb, vo, so, stream)));
     return ADDRMS_OK;
 }
 
@@ -522,7 +606,7 @@ struct Harness {
 
     int run_on(const addrms_cfg& c, const Feas& f, int set)
     {
-        if (untuned) return launch_untuned_addrms(f, c, xs[set], rs[set], w, eps, M, N, dtype, stream);
+        if (untuned) return run_addrms(xs[set], rs[set], w, eps, M, N, dtype, nullptr, stream);
         return launch(f, c, xs[set], rs[set], w, eps, M, N, stream);
     }
 
@@ -714,7 +798,7 @@ struct SiluHarness {
         int set = 0;
         for (int i = 0; i < warmup + reps; ++i) {
             if (i == warmup) HIP_TRY(hipEventRecord(ev0, stream));
-            const int st = untuned ? launch_untuned_silumul(f, c, ins[set], outs[set], M, d, dtype, stream)
+            const int st = untuned ? run_silumul(ins[set], outs[set], M, d, dtype, nullptr, stream)
                                    : launch_silumul(f, c, ins[set], outs[set], M, d, stream);
             if (st != ADDRMS_OK) return st;
             set = (set + 1) % nsets;
@@ -796,7 +880,7 @@ struct MergeHarness {
     }
     int run_set(const Feas& f, const addrms_cfg& c, const Set& s, char* vo, float* so)
     {
-        return untuned ? launch_untuned_mergestates(f, c, s.va, s.sa, s.vb, s.sb, vo, so, rows, d, dtype, stream)
+        return untuned ? run_mergestates(s.va, s.sa, s.vb, s.sb, vo, so, rows, d, dtype, nullptr, stream)
                        : launch_mergestates(f, c, s.va, s.sa, s.vb, s.sb, vo, so, rows, d, stream);
     }
     int make_reference(const addrms_cfg& c)
@@ -1001,18 +1085,7 @@ int addrms_run(void* x, void* residual, const void* weight, float eps, int64_t M
     if (!x || !residual || !weight) return fail(ADDRMS_ERR_INVALID_ARG, "x, residual and weight must not be NULL");
     if (M > (1ll << 31) - 1) return fail(ADDRMS_ERR_INVALID_ARG, "M=%lld exceeds the 2^31-1 row limit", (long long)M);
     if (!dispatch_consistent()) return fail(ADDRMS_ERR_INVALID_ARG, "library was built with inconsistent kernel tables");
-    addrms_cfg c{};
-    bool untuned = false;
-    int st = resolve_cfg(cfg, M, N, dtype, &c, OP_ADDRMS, &untuned);
-    if (st != ADDRMS_OK) return st;
-    const Feas f = check_cfg(c, M, N, dtype);
-    if (f.status != ADDRMS_OK) return fail(f.status, "%s", f.reason.c_str());
-    const int xa = c.vec * x_bytes(dtype), ra = std::min(16, c.vec * r_bytes(dtype));
-    if (!aligned(x, xa) || !aligned(weight, xa) || !aligned(residual, ra))
-        return fail(ADDRMS_ERR_MISALIGNED, "x and weight must be %d-byte aligned and residual %d-byte aligned for vec=%d",
-                    xa, ra, c.vec);
-    if (untuned) return launch_untuned_addrms(f, c, x, residual, weight, eps, M, N, dtype, static_cast<hipStream_t>(stream));
-    return launch(f, c, x, residual, weight, eps, M, N, static_cast<hipStream_t>(stream));
+    return run_addrms(x, residual, weight, eps, M, N, dtype, cfg, static_cast<hipStream_t>(stream));
 }
 
 int addrms_tune(int64_t M, int64_t N, int dtype, const addrms_budget* budget, addrms_cfg* out_cfg,
@@ -1263,17 +1336,7 @@ int silumul_run(const void* x, void* out, int64_t M, int64_t d, int dtype, const
     if (!x || !out) return fail(ADDRMS_ERR_INVALID_ARG, "x and out must not be NULL");
     if (M > (1ll << 31) - 1) return fail(ADDRMS_ERR_INVALID_ARG, "M=%lld exceeds the 2^31-1 row limit", (long long)M);
     if (!dispatch_consistent()) return fail(ADDRMS_ERR_INVALID_ARG, "library was built with inconsistent kernel tables");
-    addrms_cfg c{};
-    bool untuned = false;
-    const int st = resolve_cfg(cfg, M, d, dtype, &c, OP_SILUMUL, &untuned);
-    if (st != ADDRMS_OK) return st;
-    const Feas f = check_cfg(c, M, d, dtype, OP_SILUMUL);
-    if (f.status != ADDRMS_OK) return fail(f.status, "%s", f.reason.c_str());
-    const int al = c.vec * x_bytes(dtype);
-    if (!aligned(x, al) || !aligned(out, al))
-        return fail(ADDRMS_ERR_MISALIGNED, "x and out must be %d-byte aligned for vec=%d", al, c.vec);
-    if (untuned) return launch_untuned_silumul(f, c, x, out, M, d, dtype, static_cast<hipStream_t>(stream));
-    return launch_silumul(f, c, x, out, M, d, static_cast<hipStream_t>(stream));
+    return run_silumul(x, out, M, d, dtype, cfg, static_cast<hipStream_t>(stream));
 }
 
 int silumul_default_cfg(int64_t d, int dtype, addrms_cfg* out) { return export_default_cfg(OP_SILUMUL, d, dtype, out); }
@@ -1336,17 +1399,7 @@ int mergestates_run(const void* v_a, const float* s_a, const void* v_b, const fl
     if (!v_a || !s_a || !v_b || !s_b || !v_out || !s_out) return fail(ADDRMS_ERR_INVALID_ARG, "no pointer may be NULL");
     if (rows > (1ll << 31) - 1) return fail(ADDRMS_ERR_INVALID_ARG, "rows=%lld exceeds the 2^31-1 limit", (long long)rows);
     if (!dispatch_consistent()) return fail(ADDRMS_ERR_INVALID_ARG, "library was built with inconsistent kernel tables");
-    addrms_cfg c{};
-    bool untuned = false;
-    const int st = resolve_cfg(cfg, rows, d, dtype, &c, OP_MERGE, &untuned);
-    if (st != ADDRMS_OK) return st;
-    const Feas f = check_cfg(c, rows, d, dtype, OP_MERGE);
-    if (f.status != ADDRMS_OK) return fail(f.status, "%s", f.reason.c_str());
-    const int al = c.vec * x_bytes(dtype);
-    if (!aligned(v_a, al) || !aligned(v_b, al) || !aligned(v_out, al) || !aligned(s_a, 4) || !aligned(s_b, 4) || !aligned(s_out, 4))
-        return fail(ADDRMS_ERR_MISALIGNED, "v_a, v_b and v_out must be %d-byte aligned for vec=%d, scores 4-byte aligned", al, c.vec);
-    if (untuned) return launch_untuned_mergestates(f, c, v_a, s_a, v_b, s_b, v_out, s_out, rows, d, dtype, static_cast<hipStream_t>(stream));
-    return launch_mergestates(f, c, v_a, s_a, v_b, s_b, v_out, s_out, rows, d, static_cast<hipStream_t>(stream));
+    return run_mergestates(v_a, s_a, v_b, s_b, v_out, s_out, rows, d, dtype, cfg, static_cast<hipStream_t>(stream));
 }
 
 int mergestates_default_cfg(int64_t d, int dtype, addrms_cfg* out) { return export_default_cfg(OP_MERGE, d, dtype, out); }

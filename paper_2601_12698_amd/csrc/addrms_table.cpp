@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <atomic>
 #include <map>
 #include <mutex>
 #include <string>
@@ -19,6 +20,8 @@ struct Entry { addrms_cfg cfg; double us; };
 using Key = std::tuple<int, int, int64_t, int64_t>;   // operator, dtype, N, M
 
 static std::mutex g_mu;
+static std::atomic<uint64_t> g_generation{1};         // moves on with every change of the table's content
+uint64_t table_generation() { return g_generation.load(std::memory_order_acquire); }
 static std::map<Key, Entry>& table()
 {
     static std::map<Key, Entry> t;
@@ -51,6 +54,7 @@ int table_insert(int64_t M, int64_t N, int dtype, const addrms_cfg& cfg, double 
     {
         std::lock_guard<std::mutex> lock(g_mu);
         table()[Key(op, dtype, N, M)] = Entry{cfg, mean_us};
+        g_generation.fetch_add(1, std::memory_order_acq_rel);
     }
     if (!g_cache_path.empty()) return addrms_table_save(g_cache_path.c_str());
     return ADDRMS_OK;
@@ -121,6 +125,7 @@ void addrms_table_clear(void)
 {
     std::lock_guard<std::mutex> lock(g_mu);
     table().clear();
+    g_generation.fetch_add(1, std::memory_order_acq_rel);
 }
 
 int addrms_table_save(const char* path)
@@ -204,6 +209,7 @@ int addrms_table_load(const char* path)
     if (!have_magic || !have_arch || !have_version) return fail(ADDRMS_ERR_IO, "%s: header incomplete (format, arch and library lines)", path);
     std::lock_guard<std::mutex> lock(g_mu);
     for (const auto& kv : staged) table()[kv.first] = kv.second;
+    g_generation.fetch_add(1, std::memory_order_acq_rel);
     return ADDRMS_OK;
 }
 
