@@ -12,11 +12,13 @@ using namespace addrms;
 
 namespace {
 
-template <int DT, int VEC, int CPT, int POL, bool RAG>
-__global__ __launch_bounds__(1024) void addrms_direct(void* x, void* r, const void* w, float eps, double inv_n,
-                                                      long long M, int N)
+// MULTI: several rows per workgroup (rpw).  The launch shape travels as arguments: together with the rest they are preloaded
+// into scalar registers, where blockDim would be another load before the first address is known.
+template <int DT, int VEC, int CPT, int POL, bool RAG, bool MULTI>
+__global__ __launch_bounds__(1024) void addrms_direct(void* x, void* r, const void* w, double inv_n, float eps, int N,
+                                                      unsigned tpr, unsigned rpw, long long M)
 {
-    addrms_direct_body<DT, VEC, CPT, POL, RAG, (CPT > 1)>(x, r, w, eps, inv_n, M, N);
+    addrms_direct_body<DT, VEC, CPT, POL, RAG, (CPT > 1), MULTI>(x, r, w, eps, inv_n, N, tpr, rpw, M);
 }
 // Workgroups of 1024 threads leave each 128 registers: 48 values of the row stay there.  (512 threads with 144 values
 // each: 204 us against 210 on 1024 x 131072 bf16, but 68 against 58 on 300 x 110592 and 27 against 20 on 8 x 123776.)
@@ -44,37 +46,39 @@ __global__ __launch_bounds__(kFlatThreads) void mergestates_flat(const char* va,
 // Elements per thread and access: 16 bytes of the residual, and of x too unless the residual is wider.
 constexpr int direct_vec(int dtype) { return dtype == DT_BF16 || dtype == DT_FP16 ? 8 : 4; }
 
-template <int DT, int CPT> const void* addrms_fn2(int pol, bool rag)
+template <int DT, int CPT, bool MULTI> const void* addrms_fn2(int pol, bool rag)
 {
     constexpr int VEC = direct_vec(DT);
-    if (rag) return pol == POL_NT ? reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_NT, true>)
-                                  : reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_WT, true>);
-    return pol == POL_NT ? reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_NT, false>)
-                         : reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_WT, false>);
+    if (rag) return pol == POL_NT ? reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_NT, true, MULTI>)
+                                  : reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_WT, true, MULTI>);
+    return pol == POL_NT ? reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_NT, false, MULTI>)
+                         : reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL_WT, false, MULTI>);
 }
-// At most 32 values per thread: a workgroup of 1024 threads leaves each 128 registers.
-template <int DT> const void* addrms_fn1(int cpt, int pol, bool rag)
+// At most 32 values per thread: a workgroup of 1024 threads leaves each 128 registers.  Rows that share a workgroup have
+// at most three pieces per thread.
+template <int DT> const void* addrms_fn1(int cpt, int pol, bool rag, bool multi)
 {
     switch (cpt) {
-    case 1: return addrms_fn2<DT, 1>(pol, rag);
-    case 2: return addrms_fn2<DT, 2>(pol, rag);
-    case 3: return addrms_fn2<DT, 3>(pol, rag);
-    case 4: return addrms_fn2<DT, 4>(pol, rag);
+    case 1: return multi ? addrms_fn2<DT, 1, true>(pol, rag) : addrms_fn2<DT, 1, false>(pol, rag);
+    case 2: return multi ? addrms_fn2<DT, 2, true>(pol, rag) : addrms_fn2<DT, 2, false>(pol, rag);
+    case 3: return multi ? addrms_fn2<DT, 3, true>(pol, rag) : addrms_fn2<DT, 3, false>(pol, rag);
     default: break;
     }
+    if (multi) return nullptr;
+    if (cpt == 4) return addrms_fn2<DT, 4, false>(pol, rag);
     if constexpr (direct_vec(DT) == 4) {
-        if (cpt == 5 || cpt == 6) return addrms_fn2<DT, 6>(pol, rag);
-        if (cpt == 7 || cpt == 8) return addrms_fn2<DT, 8>(pol, rag);
+        if (cpt == 5 || cpt == 6) return addrms_fn2<DT, 6, false>(pol, rag);
+        if (cpt == 7 || cpt == 8) return addrms_fn2<DT, 8, false>(pol, rag);
     }
     return nullptr;
 }
-const void* addrms_fn(int dtype, int cpt, int pol, bool rag)
+const void* addrms_fn(int dtype, int cpt, int pol, bool rag, bool multi)
 {
     switch (dtype) {
-    case DT_BF16: return addrms_fn1<DT_BF16>(cpt, pol, rag);
-    case DT_FP16: return addrms_fn1<DT_FP16>(cpt, pol, rag);
-    case DT_FP16_RES32: return addrms_fn1<DT_FP16_RES32>(cpt, pol, rag);
-    case DT_FP32: return addrms_fn1<DT_FP32>(cpt, pol, rag);
+    case DT_BF16: return addrms_fn1<DT_BF16>(cpt, pol, rag, multi);
+    case DT_FP16: return addrms_fn1<DT_FP16>(cpt, pol, rag, multi);
+    case DT_FP16_RES32: return addrms_fn1<DT_FP16_RES32>(cpt, pol, rag, multi);
+    case DT_FP32: return addrms_fn1<DT_FP32>(cpt, pol, rag, multi);
     default: return nullptr;
     }
 }
@@ -169,41 +173,44 @@ static bool direct_addrms_long_plan(int64_t M, int64_t N, int dtype, DirectPlan*
     return true;
 }
 
-// Ragged rows up to 96 MB take three pieces per thread and two rows per workgroup, so that fewer waves repeat what a
+// Threads per row: one per piece up to 1024, then as few pieces per thread as that allows, in equal shares: on 40 shapes
+// tried with 1 to 8 the fewest were the fastest, by 2-8 % against twice as many.  Written-through rows of more than 256
+// pieces take at least two, which then are stored in one go after the row sum (256 x 8192 bf16 4.0 us against 4.2 and from
+// HBM 4.4 against 5.6; 512 x 8192 5.8 against 6.5; 4096 x 4096 the same; shorter rows 1-2 % slower).
+// Ragged rows up to 96 MB take three pieces per thread (two where there are no single elements: 8192 x 1000 fp16+fp32
+// 17.1 us against 17.5) and two rows per workgroup, so that fewer waves repeat what a
 // row costs before and after its pieces (2047 x 4095 fp16 12.9 us against 14.0 with one piece per thread, 5000 x 1001
 // fp32 15.5 against 16.0, 300 x 10001 bf16 7.4 against 8.2 with two); beyond, one is as good or better (9000 x 6150
 // bf16 76.4-79.7 us against 78.1-78.9).
-// Store policy: as above, but non-temporal below 16 MB of x and residual, where the caches of the XCDs hold most of it
-// anyway and a write-through store only waits longer (16 x 4096 bf16 2.5 us against 2.7, 1024 x 2048 3.8 against 4.1),
-// and for rows with single elements, whose partly written lines a write-through store sends out at once (2047 x 4095
-// fp16 12.9 us and from HBM 13.5 against 13.3 and 15.9).
+// Store policy: as above, but non-temporal below 512 KB of x and residual, where the launch is all there is and a
+// write-through store only waits longer (16 x 4096 bf16 2.2 us against 2.4; from 1 MB on write-through wins, 64 x 8192
+// 2.9 against 3.4), and for rows with single elements, whose partly written lines a write-through store sends out at
+// once (2047 x 4095 fp16 12.9 us and from HBM 13.5 against 13.3 and 15.9).
 // Ragged walk: where a vector access does not divide the row, unless all of it is under 1 MB and the default
 // configuration's accesses are at least two elements wide (40 x 1030 bf16 3.3 us against 3.2); and where rows are whole
 // vectors but not whole lines, from 16 MB on (below, 1000 x 1000 bf16 3.6 us against 3.5).
 bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, DirectPlan* out)
 {
-    constexpr int64_t kWriteThroughMin = 16 << 20, kRaggedMin = 1 << 20;
+    constexpr int64_t kWriteThroughMin = 512 << 10, kRaggedMin = 1 << 20, kLineWalkMin = 16 << 20;
     const int vec = direct_vec(dtype), xb = x_bytes(dtype), rb = r_bytes(dtype);
     const int64_t bytes = M * N * (xb + rb);
     const bool split = N % vec != 0;                                                  // rows have single elements
-    const bool rag = split || ((N * xb) % kLineBytes != 0 && bytes >= kWriteThroughMin && N >= 128 * vec);
+    const bool rag = split || ((N * xb) % kLineBytes != 0 && bytes >= kLineWalkMin && N >= 128 * vec);
     if (split && ((x / xb) % vec != (r / rb) % vec || (bytes < kRaggedMin && default_vec > 1))) return false;
     const int line = kLineBytes / xb;                                                 // elements
     const int64_t pieces = (N + (rag ? line - 1 : 0) + vec - 1) / vec;                // a ragged row begins anywhere in a line
     if (N < 16 * vec) return false;
     if (pieces * vec > 32 * 1024) return direct_addrms_long_plan(M, N, dtype, out);
     const int pol = bytes >= kWriteThroughMin && bytes <= write_through_max() && !split ? POL_WT : POL_NT;
-    // threads per row: one per piece up to 1024, then as few pieces per thread as that allows, in equal shares; three
-    // pieces per thread and two rows per workgroup for ragged rows
     const bool thick = rag && bytes <= write_through_max();
-    int64_t cpt = std::max<int64_t>((pieces + 1023) / 1024, thick ? 3 : 1);
+    int64_t cpt = std::max<int64_t>((pieces + 1023) / 1024, thick && split ? 3 : thick || (pol == POL_WT && pieces > 256) ? 2 : 1);
     int64_t tpr = (pieces + cpt - 1) / cpt;
     tpr = tpr <= 32 ? 32 : (tpr + 63) / 64 * 64;
     cpt = (pieces + tpr - 1) / tpr;
-    out->fn = addrms_fn(dtype, static_cast<int>(cpt), pol, rag);
-    if (!out->fn) return false;
     out->block_x = static_cast<unsigned>(tpr);
     out->block_y = tpr == 32 || (thick && tpr <= 256 && M >= 512) ? 2u : 1u;
+    out->fn = addrms_fn(dtype, static_cast<int>(cpt), pol, rag, out->block_y > 1);
+    if (!out->fn) return false;
     out->grid = static_cast<unsigned>((M + out->block_y - 1) / out->block_y);
     out->lds = tpr > 64 ? out->block_y * 16u * 8u : 0u;        // one fp64 sum per wave
     return true;
@@ -260,7 +267,8 @@ int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, f
         void* args[] = {&x, &r, &w, &eps, &inv_n, &n, &lds_chunks};
         return go(p, args, stream);
     }
-    void* args[] = {&x, &r, &w, &eps, &inv_n, &m, &n};
+    unsigned tpr = p.block_x, rpw = p.block_y;
+    void* args[] = {&x, &r, &w, &inv_n, &eps, &n, &tpr, &rpw, &m};
     return go(p, args, stream);
 }
 int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream)

@@ -138,33 +138,41 @@ struct SingleElement {
 };
 
 // ---- add + RMSNorm ---------------------------------------------------------------------------
-// A workgroup per row (several for rows shorter than a wave), a thread holds CPT chunks of VEC
-// elements from the loads to the stores.  Same arithmetic as addrms_body, bit for bit.  HBM-bound:
-// all loads of a thread are issued before the first value is used (in two batches beyond 32
-// values), and a row is spread over as many threads as there are pieces, up to 1024, so that a
-// thread has few and the row arrives early: of the 1 to 8 chunks per thread tried on 40 shapes
-// the fewest were the fastest on all but four, by 2-8 % against twice as many.  DEFER (more than
-// one chunk): both streams written after the row sum, 1-3 % there.
-// Default of the knob grid -> here, us: 16 x 4096 bf16 3.1 -> 2.5, 256 x 5120 4.1 -> 3.5,
-// 512 x 8192 8.3 -> 6.3, 4096 x 4096 21.5 -> 20.1, 20000 x 5120 152 -> 130 (6.3 TB/s),
-// 32768 x 7168 340 -> 304, 2048 x 8192 fp32 56.4 -> 45.3, 900 x 28672 fp16 44.3 -> 39.8.
-// Ragged: 2047 x 4095 fp16 18.6 -> 12.9 (buffers from HBM 27.4 -> 13.5), 9000 x 6150 bf16 95.5 ->
-// 77, 300 x 10001 9.3 -> 7.5, 8192 x 1000 fp16+fp32 18.2 -> 17.4 (from HBM 23.5 -> 20.8); the single
+// A workgroup per row (MULTI: several, for rows shorter than a wave and ragged ones), a thread
+// holds CPT chunks of VEC elements from the loads to the stores.  Same arithmetic as addrms_body,
+// bit for bit.  HBM-bound: all loads of a thread are issued before the first value is used (in two
+// batches beyond 32 values), and a row is spread over many threads with few chunks each, so that it
+// arrives early.  DEFER (more than one chunk): both streams written after the row sum, 1-3 % there.
+// With written-through stores and up to two chunks the weights are fetched along with the row, so
+// that nothing is loaded behind a store (400 x 6144 bf16 4.7 -> 4.0 us, 1000 x 4096 fp32 10.3 ->
+// 10.1); with non-temporal ones they are fetched after it (20000 x 5120 126 us, along with it 131).
+// Default of the knob grid -> here, us: 16 x 4096 bf16 3.0 -> 2.2, 64 x 8192 3.9 -> 2.9, 512 x 8192
+// 8.2 -> 5.8, 4096 x 4096 21.2 -> 19.8, 20000 x 5120 152 -> 126 (6.5 TB/s), 32768 x 7168 340 -> 304,
+// 2048 x 8192 fp32 56.4 -> 45.3, 900 x 28672 fp16 44.3 -> 39.8.
+// Ragged: 2047 x 4095 fp16 18.6 -> 12.8 (buffers from HBM 27.0 -> 13.4), 9000 x 6150 bf16 95.5 ->
+// 77, 300 x 10001 9.3 -> 7.5, 8192 x 1000 fp16+fp32 18.2 -> 17.1 (from HBM 23.5 -> 20.1); the single
 // elements cost the first 0.7 us and weights at odd addresses 0.4 of what an aligned row would not.
-template <int DT, int VEC, int CPT, int POL, bool RAG, bool DEFER>
+template <int DT, int VEC, int CPT, int POL, bool RAG, bool DEFER, bool MULTI>
 __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* __restrict__ rp,
-                                                   const void* __restrict__ wp, float eps, double inv_n, int64_t M,
-                                                   int32_t N)
+                                                   const void* __restrict__ wp, float eps, double inv_n, int32_t N,
+                                                   uint32_t tpr, uint32_t rpw, int64_t M)
 {
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
     constexpr int UNR = VEC * CPT <= 32 ? CPT : (CPT + 1) / 2;
-    constexpr bool BF = T::BF;
+    constexpr bool BF = T::BF, EARLY_WEIGHTS = POL == POL_WT && CPT <= 2;
     extern __shared__ double lds[];
 
-    const uint32_t tpr = blockDim.x, rpw = blockDim.y;
-    const uint32_t lane = threadIdx.x, ry = threadIdx.y;
-    const RowAddr ra = row_addr<XB, RB>(xp, rp, blockIdx.x, rpw, ry, M, N);
+    const uint32_t lane = threadIdx.x, ry = MULTI ? threadIdx.y : 0u;
+    RowAddr ra;
+    if constexpr (MULTI) {
+        ra = row_addr<XB, RB>(xp, rp, blockIdx.x, rpw, ry, M, N);
+    } else {
+        ra.xbase = static_cast<char*>(xp) + static_cast<int64_t>(blockIdx.x) * N * XB;
+        ra.rbase = static_cast<char*>(rp) + static_cast<int64_t>(blockIdx.x) * N * RB;
+        ra.rowoff = 0u;
+        ra.row_ok = 1u;
+    }
     const char* wbase = static_cast<const char*>(wp);
     char *xrow = ra.xbase + static_cast<uint64_t>(ra.rowoff * XB), *rrow = ra.rbase + static_cast<uint64_t>(ra.rowoff * RB);
     const RowWalk<XB, VEC, RAG> rw(ra.xbase, ra.rowoff, N, lane, tpr);
@@ -174,6 +182,12 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
     double acc = 0.0;
     SingleElement<DT, RAG> one;
     one.load(xrow, rrow, wbase, rw.single, rw.has_single);
+    raw_t<XB * VEC> wv[CPT];
+    auto load_weights = [&] {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c)
+            ld_stream<POL_CACHED, XB * VEC, RAG ? XB : 16>(wbase, rw.clamped(col0 + c * stride) * XB, wv[c]);
+    };
 #pragma unroll
     for (int g = 0; g < CPT; g += UNR) {
         raw_t<XB * VEC> xv[UNR];
@@ -185,6 +199,10 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
                 ld_stream<POL, XB * VEC, 16>(ra.xbase, (ra.rowoff + colc) * XB, xv[u]);
                 ld_stream<POL, RB * VEC, 16>(ra.rbase, (ra.rowoff + colc) * RB, rv[u]);
             }
+        }
+        if constexpr (EARLY_WEIGHTS) {
+            if (g == 0) load_weights();
+            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
@@ -211,12 +229,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
         if (g + UNR < CPT) __builtin_amdgcn_sched_barrier(0);
     }
     acc = one.add(acc);
-    raw_t<XB * VEC> wv[CPT];
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) {
-        const uint32_t colc = rw.clamped(col0 + c * stride);
-        ld_stream<POL_CACHED, XB * VEC, RAG ? XB : 16>(wbase, colc * XB, wv[c]);
-    }
+    if constexpr (!EARLY_WEIGHTS) load_weights();
 
     const double ss = row_sum(acc, RED_WAVE, tpr, lane, ry, lds);
     const float rstd = rsqrt_to_f32(__builtin_fma(ss, inv_n, static_cast<double>(eps)));
