@@ -16,9 +16,10 @@ struct DirectPlan {
 };
 
 // The kernel and shape for a problem that the grid's default configuration covers, or false: the default
-// configuration runs.  x, r: the tensors' bases, aligned as the default configuration (of default_vec elements per access)
+// configuration runs.  x, r, w: the tensors' bases, aligned as the default configuration (of default_vec elements per access)
 // asks for; *_align: bases or-ed together.
-bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, DirectPlan* out);
+bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, uintptr_t w,
+                        DirectPlan* out);
 bool direct_silumul_plan(int64_t M, int64_t d, int dtype, uintptr_t x_align, uintptr_t out_align, DirectPlan* out);
 bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_align, DirectPlan* out);
 

@@ -155,10 +155,10 @@ namespace addrms_host {
 // Rows that 32 values per thread of 1024 do not hold.  Ordinary loads and stores up to the size that the memory-side
 // cache keeps (230 x 86912 bf16, 80 MB: 26.6 us against 31.6 with non-temporal ones; 8 x 123776 16.5 against 20.8),
 // non-temporal beyond (1024 x 131072 bf16 210 us against 245).
-static bool direct_addrms_long_plan(int64_t M, int64_t N, int dtype, DirectPlan* out)
+static bool direct_addrms_long_plan(int64_t M, int64_t N, int dtype, bool split, DirectPlan* out)
 {
     const int vec = direct_vec(dtype), xb = x_bytes(dtype);
-    const bool rag = (N * xb) % kLineBytes != 0, nt = M * N * (xb + r_bytes(dtype)) > write_through_max();
+    const bool rag = split || (N * xb) % kLineBytes != 0, nt = M * N * (xb + r_bytes(dtype)) > write_through_max();
     const int64_t span = static_cast<int64_t>(kLongThreads) * vec, slot = span * 4;             // elements, LDS bytes per chunk
     const int64_t need = (N + (rag ? kLineBytes / xb - 1 : 0) + span - 1) / span;
     const int64_t fit = (hw().lds_bytes_per_cu - 128) / slot;                                   // behind one fp64 sum per wave
@@ -189,18 +189,20 @@ static bool direct_addrms_long_plan(int64_t M, int64_t N, int dtype, DirectPlan*
 // Ragged walk: where a vector access does not divide the row, unless all of it is under 1 MB and the default
 // configuration's accesses are at least two elements wide (40 x 1030 bf16 3.3 us against 3.2); and where rows are whole
 // vectors but not whole lines, from 16 MB on (below, 1000 x 1000 bf16 3.6 us against 3.5).
-bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, DirectPlan* out)
+// A default configuration with narrower accesses than these admits bases that they do not (86912 fp32: two elements per
+// access): such rows take the ragged walk, whole vectors or not.
+bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, uintptr_t w, DirectPlan* out)
 {
     constexpr int64_t kWriteThroughMin = 512 << 10, kRaggedMin = 1 << 20, kLineWalkMin = 16 << 20;
     const int vec = direct_vec(dtype), xb = x_bytes(dtype), rb = r_bytes(dtype);
     const int64_t bytes = M * N * (xb + rb);
-    const bool split = N % vec != 0;                                                  // rows have single elements
+    const bool split = N % vec != 0 || x % (vec * xb) != 0 || r % (vec * rb) != 0 || w % (vec * xb) != 0;   // single elements
     const bool rag = split || ((N * xb) % kLineBytes != 0 && bytes >= kLineWalkMin && N >= 128 * vec);
     if (split && ((x / xb) % vec != (r / rb) % vec || (bytes < kRaggedMin && default_vec > 1))) return false;
     const int line = kLineBytes / xb;                                                 // elements
     const int64_t pieces = (N + (rag ? line - 1 : 0) + vec - 1) / vec;                // a ragged row begins anywhere in a line
     if (N < 16 * vec) return false;
-    if (pieces * vec > 32 * 1024) return direct_addrms_long_plan(M, N, dtype, out);
+    if (pieces * vec > 32 * 1024) return direct_addrms_long_plan(M, N, dtype, split, out);
     const int pol = bytes >= kWriteThroughMin && bytes <= write_through_max() && !split ? POL_WT : POL_NT;
     const bool thick = rag && bytes <= write_through_max();
     int64_t cpt = std::max<int64_t>((pieces + 1023) / 1024, thick && split ? 3 : thick || (pol == POL_WT && pieces > 256) ? 2 : 1);

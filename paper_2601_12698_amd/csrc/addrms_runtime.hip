@@ -203,7 +203,7 @@ int run_addrms(void* x, void* r, const void* w, float eps, int64_t M, int64_t N,
             return fail(ADDRMS_ERR_MISALIGNED, "x and weight must be %d-byte aligned and residual %d-byte aligned for vec=%d",
                         xa, ra, c.vec);
         },
-        [=](const addrms_cfg& c, DirectPlan* p) { return direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(r), p); });
+        [=](const addrms_cfg& c, DirectPlan* p) { return direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(r), bits(w), p); });
     if (st != ADDRMS_OK) return st;
     if (!call->direct) return launch(call->f, call->c, x, r, w, eps, M, N, stream);
     HIP_TRY(static_cast<hipError_t>(direct_launch_addrms(call->p, x, r, w, eps, M, N, stream)));

@@ -187,3 +187,78 @@ def test_norm_of_rows_beyond_the_registers(dtype, M, N):
 def test_norm_of_long_ragged_rows_from_any_element(off):
     check_norm(3, 40001, "bf16", off)
     check_norm(3, 90001, "fp32", off)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32", "fp16_res32"])
+def test_norm_from_bases_that_only_a_narrow_default_access_fits(dtype):
+    """Rows of whole 16-byte pieces whose default configuration reads two elements at a time (86912: what LDS holds at that
+    width), so that it takes bases no 16-byte access fits; the weights alone may be off, too."""
+    N = 86912
+    assert B.addrms_default_cfg(N, dtype).vec < (8 if dtype == "bf16" else 4)
+    for off in (0, 2, 4, 6):
+        check_norm(3, N, dtype, off)
+    x, xok, r, rok, _ = norm_inputs(3, N, dtype, 1)
+    w = torch.rand(N + 2, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda").to(x.dtype)[2:]
+    xw, rw = x.clone(), r.clone()
+    B.addrms_run(xw, rw, w, 1e-6, 3, N, dtype, B.addrms_default_cfg(N, dtype))
+    B.addrms_run(x, r, w, 1e-6, 3, N, dtype)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(x), bits(xw)) and torch.equal(bits(r), bits(rw)) and xok() and rok()
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_any_form_the_default_configuration_takes(seed):
+    """Sizes, formats and first elements at random: whatever route a call takes, the bits are the default configuration's."""
+    import random
+    rng = random.Random(seed)
+    for _ in range(12):
+        dtype = rng.choice(W.DTYPES)
+        N = int(2 ** rng.uniform(3, 16.5))
+        N = rng.choice((N, N // 8 * 8 or 8, N // 64 * 64 or 64))
+        M = rng.choice((1, 2, 3, 5, 64, 513))
+        M = max(1, min(M, 4_000_000 // N))
+        vec = B.addrms_default_cfg(N, dtype).vec
+        off = rng.choice((0, 0, *(v for v in (1, 2, 4, 8) if v % vec == 0)))
+        print(f"add+RMSNorm {dtype} {M} x {N} from element {off}", flush=True)
+        check_norm(M, N, dtype, off)
+    for _ in range(6):
+        dtype = rng.choice(("bf16", "fp16", "fp32"))
+        d = int(2 ** rng.uniform(3, 13))
+        M = max(1, min(rng.choice((1, 2, 7, 300)), 2_000_000 // d))
+        print(f"gated activation {dtype} {M} x {d}", flush=True)
+        test_gated_activation(dtype, M, d)
+
+
+def test_calls_without_a_configuration_in_a_graph():
+    """Captured once, replayed with other work of the stream in between: every replay starts from the same inputs and
+    must leave what the eager call leaves.  The long rows park 128 KB in LDS, beyond what a launch may ask for by default."""
+    cases = [("bf16", 16, 4096), ("fp16", 300, 1001), ("bf16", 600, 4096), ("bf16", 3, 81920)]
+    state = []
+    for dtype, M, N in cases:
+        x, _, r, _, w = norm_inputs(M, N, dtype, N)
+        state.append((dtype, M, N, x.clone(), r.clone(), w, torch.empty_like(x), torch.empty_like(r)))
+    xs = normal((64, 2 * 1001), torch.bfloat16, 3)
+    out = torch.empty((64, 1001), dtype=torch.bfloat16, device="cuda")
+
+    def body():
+        for dtype, M, N, x0, r0, w, x, r in state:
+            x.copy_(x0)
+            r.copy_(r0)
+            B.addrms_run(x, r, w, 1e-6, M, N, dtype)
+        B.silumul_run(xs, out, 64, 1001, "bf16")
+
+    body()
+    torch.cuda.synchronize()
+    want = [(bits(s[6]).clone(), bits(s[7]).clone()) for s in state] + [(bits(out).clone(), bits(out).clone())]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        body()
+    for _ in range(3):
+        for s in state:
+            s[6].fill_(1.0)
+            s[7].fill_(1.0)
+        out.fill_(1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [(bits(s[6]), bits(s[7])) for s in state] + [(bits(out), bits(out))]
+        assert all(torch.equal(a, c) and torch.equal(b, d) for (a, b), (c, d) in zip(got, want))
