@@ -145,12 +145,15 @@ struct SingleElement {
 // arrives early.  DEFER (more than one chunk): both streams written after the row sum, 1-3 % there.
 // With written-through stores and up to two chunks the weights are fetched along with the row, so
 // that nothing is loaded behind a store (400 x 6144 bf16 4.7 -> 4.0 us, 1000 x 4096 fp32 10.3 ->
-// 10.1); with non-temporal ones they are fetched after it (20000 x 5120 126 us, along with it 131).
+// 10.1); with non-temporal ones they are fetched after it (20000 x 5120 126 us, along with it 131),
+// and with three or more chunks after the row sum, where their registers are free and their odd
+// addresses in ragged rows hold nothing up (300 x 10001 7.1 -> 6.6 us, 1800 x 3001 fp16+fp32 13.5 ->
+// 13.0, 900 x 28672 39.1 -> 38.6; with one chunk 1-3 % slower).
 // Default of the knob grid -> here, us: 16 x 4096 bf16 3.0 -> 2.2, 64 x 8192 3.9 -> 2.9, 512 x 8192
 // 8.2 -> 5.8, 4096 x 4096 21.2 -> 19.8, 20000 x 5120 152 -> 126 (6.5 TB/s), 32768 x 7168 340 -> 304,
 // 2048 x 8192 fp32 56.4 -> 45.3, 900 x 28672 fp16 44.3 -> 39.8.
-// Ragged: 2047 x 4095 fp16 18.6 -> 12.8 (buffers from HBM 27.0 -> 13.4), 9000 x 6150 bf16 95.5 ->
-// 77, 300 x 10001 9.3 -> 7.5, 8192 x 1000 fp16+fp32 18.2 -> 17.1 (from HBM 23.5 -> 20.1); the single
+// Ragged: 2047 x 4095 fp16 18.6 -> 12.6 (buffers from HBM 27.0 -> 13.3), 9000 x 6150 bf16 95.5 ->
+// 77, 300 x 10001 9.3 -> 6.6, 8192 x 1000 fp16+fp32 18.2 -> 17.1 (from HBM 23.5 -> 20.1); the single
 // elements cost the first 0.7 us and weights at odd addresses 0.4 of what an aligned row would not.
 template <int DT, int VEC, int CPT, int POL, bool RAG, bool DEFER, bool MULTI>
 __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* __restrict__ rp,
@@ -160,7 +163,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
     constexpr int UNR = VEC * CPT <= 32 ? CPT : (CPT + 1) / 2;
-    constexpr bool BF = T::BF, EARLY_WEIGHTS = POL == POL_WT && CPT <= 2;
+    constexpr bool BF = T::BF, EARLY_WEIGHTS = POL == POL_WT && CPT <= 2, LAST_WEIGHTS = POL == POL_NT && CPT >= 3;
     extern __shared__ double lds[];
 
     const uint32_t lane = threadIdx.x, ry = MULTI ? threadIdx.y : 0u;
@@ -229,9 +232,10 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
         if (g + UNR < CPT) __builtin_amdgcn_sched_barrier(0);
     }
     acc = one.add(acc);
-    if constexpr (!EARLY_WEIGHTS) load_weights();
+    if constexpr (!EARLY_WEIGHTS && !LAST_WEIGHTS) load_weights();
 
     const double ss = row_sum(acc, RED_WAVE, tpr, lane, ry, lds);
+    if constexpr (LAST_WEIGHTS) load_weights();
     const float rstd = rsqrt_to_f32(__builtin_fma(ss, inv_n, static_cast<double>(eps)));
 
     if constexpr (DEFER) {
