@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cstdint>
 
 #include "addrms_direct.h"
 #include "direct_kernel.h"
@@ -148,6 +149,10 @@ void set_flat(addrms_host::DirectPlan* out, int64_t pieces, int64_t units, int64
 }
 constexpr int64_t kFlatMax = 1ll << 31;                       // positions the flat kernels divide exactly
 
+// A launch has at most 2^32 - 1 threads.  With one thread per piece that is 137 GB of 16-bit rows, or half where a row
+// fills half of its threads; what has more rows is left to the default configuration, whose threads take several pieces.
+bool launchable(int64_t workgroups, int64_t threads) { return workgroups <= UINT32_MAX / threads; }
+
 }  // namespace
 
 namespace addrms_host {
@@ -164,7 +169,7 @@ static bool direct_addrms_long_plan(int64_t M, int64_t N, int dtype, bool split,
     const int64_t fit = (hw().lds_bytes_per_cu - 128) / slot;                                   // behind one fp64 sum per wave
     out->units = static_cast<unsigned>(std::min(fit, std::max<int64_t>(0, need - kLongRegValues / vec)));
     out->fn = addrms_long_fn(dtype, nt ? POL_NT : POL_CACHED, rag);
-    if (!out->fn) return false;
+    if (!out->fn || !launchable(M, kLongThreads)) return false;
     out->long_index = static_cast<unsigned>(dtype) * 4u + (nt ? 2u : 0u) + (rag ? 1u : 0u);
     out->block_x = kLongThreads;
     out->grid = static_cast<unsigned>(M);
@@ -213,7 +218,9 @@ bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintpt
     out->block_y = tpr == 32 || (thick && tpr <= 256 && M >= 512) ? 2u : 1u;
     out->fn = addrms_fn(dtype, static_cast<int>(cpt), pol, rag, out->block_y > 1);
     if (!out->fn) return false;
-    out->grid = static_cast<unsigned>((M + out->block_y - 1) / out->block_y);
+    const int64_t workgroups = (M + out->block_y - 1) / out->block_y;
+    if (!launchable(workgroups, tpr * out->block_y)) return false;
+    out->grid = static_cast<unsigned>(workgroups);
     out->lds = tpr > 64 ? out->block_y * 16u * 8u : 0u;        // one fp64 sum per wave
     return true;
 }

@@ -262,3 +262,28 @@ def test_calls_without_a_configuration_in_a_graph():
         torch.cuda.synchronize()
         got = [(bits(s[6]), bits(s[7])) for s in state] + [(bits(out), bits(out))]
         assert all(torch.equal(a, c) and torch.equal(b, d) for (a, b), (c, d) in zip(got, want))
+
+
+@pytest.mark.parametrize("less", [2, 0])
+def test_as_many_rows_as_one_launch_takes_and_more(less):
+    """32 threads a row: 2^27 - 2 rows are the most that the 2^32 - 1 threads of a launch cover; from 2^27 on the
+    default configuration with its 16 threads a row runs instead.  1024 different rows, repeated."""
+    M, N, block = 2 ** 27, 128, 1024
+    if torch.cuda.mem_get_info()[0] < 90 << 30:
+        pytest.skip("needs 70 GB of device memory")
+    want = [normal((block, N), torch.bfloat16, s) for s in (1, 2)]
+    weight = normal((N,), torch.bfloat16, 3)
+    x, r = (t.view(1, -1).expand(M // block, -1).contiguous() for t in want)
+    before = [t.view(-1)[-less * N:].clone() if less else None for t in (x, r)]
+    B.addrms_run(want[0], want[1], weight, 1e-5, block, N, "bf16", B.addrms_default_cfg(N, "bf16"))
+    rows = M - less
+    B.addrms_run(x.view(-1)[:rows * N], r.view(-1)[:rows * N], weight, 1e-5, rows, N, "bf16")
+    torch.cuda.synchronize()
+    for got, ref, old in ((x, want[0], before[0]), (r, want[1], before[1])):
+        if less:
+            assert torch.equal(bits(got.view(-1)[-less * N:]), bits(old))
+            got.view(-1)[-less * N:] = ref.view(-1)[-less * N:]
+        for c in range(0, M // block, 8192):
+            assert bool((bits(got[c:c + 8192]) == bits(ref).view(1, -1)).all()), c
+    del x, r
+    torch.cuda.empty_cache()
