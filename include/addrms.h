@@ -116,7 +116,7 @@ typedef struct addrms_cfg {
  *   cfg      host; NULL = look (M, N, dtype) up in the specialised table
  *            (nearest tuned M for the same N and dtype), else a kernel and launch shape
  *            chosen for the problem outside the knob grid, and where that does not
- *            apply (rows beyond the registers) the default cfg; arguments are accepted
+ *            apply (rows of a few elements, for one) the default cfg; arguments are accepted
  *            or refused as the default cfg accepts or refuses them
  *   stream   a hipStream_t passed as void*; NULL = the default stream
  * Never synchronises, never allocates device memory.  Arguments are checked
