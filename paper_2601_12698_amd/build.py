@@ -117,10 +117,10 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
 
     objs = [u[:-4] + ".o" for u in units]
     hdrs = [os.path.join(ROOT, "include", "addrms.h"), os.path.join(ROOT, "include", "silumul.h"), os.path.join(ROOT, "include", "mergestates.h"),
-            os.path.join(CSRC, "addrms_internal.h")]
+            os.path.join(CSRC, "addrms_internal.h"), os.path.join(CSRC, "direct_route.h")]
     gen = [os.path.join(BUILD, f) for f in ("gen_instances.inc", "gen_resources.inc",
                                              "gen_dispatch_decl.inc", "gen_dispatch_rows.inc")]
-    for name in ("addrms_cfg.cpp", "addrms_table.cpp", "addrms_search.cpp", "addrms_general.cpp", "addrms_audit.cpp"):
+    for name in ("addrms_cfg.cpp", "addrms_table.cpp", "addrms_search.cpp", "addrms_general.cpp", "addrms_audit.cpp", "direct_route.cpp"):
         src = os.path.join(CSRC, name)
         obj = os.path.join(BUILD, name + ".o")
         if force or not _newer(obj, src, *hdrs, *gen):

@@ -1,13 +1,13 @@
 // Kernels behind a call that names no configuration and has none in the specialised table.
 // They are not points of the knob grid: their launch shape follows from the problem by the
-// rules in addrms_direct.hip.
+// rules in direct_route.cpp.
 //
 // Store policy.  A workgroup's ordinary stores leave dirty lines in its XCD's L2, which are
 // written back when the kernel ends: a serial tail of up to 32 MB.  Non-temporal stores have
 // no such tail, but nothing of them stays in the memory-side cache either, where the next
 // kernel of the program looks for its input.  Write-through stores (sc1) go to the memory
 // side as they are issued and stay there.  Which one a problem takes is decided by what it
-// writes (write_through_max in addrms_direct.hip has both sides measured).
+// writes (write_through_max in direct_route.cpp has both sides measured).
 //
 // Ragged rows (RAG).  A row length that VEC does not divide used to mean accesses as narrow
 // as one element, and one that 128 bytes do not divide waves whose lines are shared with the
@@ -19,12 +19,10 @@
 #include <type_traits>
 
 #include "addrms_kernel.h"
+#include "direct_route.h"
 #include "silumul_kernel.h"
 
 namespace addrms {
-
-// POL_CACHED: ordinary loads and stores.  POL_NT: both non-temporal.  POL_WT: non-temporal loads, write-through stores.
-enum : int { POL_CACHED = 0, POL_NT = 1, POL_WT = 2 };
 
 template <typename T, int AL> struct at_align { typedef T type __attribute__((aligned(AL))); };
 
@@ -467,8 +465,6 @@ __device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __
 // the quotient is below n / 2^31 of 1 / d.
 struct FlatDiv { uint32_t mul, shift; };
 __device__ __forceinline__ uint32_t flat_div(uint32_t n, FlatDiv f) { return __umulhi(n, f.mul) >> f.shift; }
-
-constexpr int kFlatThreads = 256;
 
 // units: pieces of a row, or for ragged rows (RAG: d is no multiple of VEC) its elements; total:
 // the same for the whole output.  A piece of a ragged output begins anywhere in a row: its inputs

@@ -87,9 +87,11 @@ def test_gated_activation_with_bases_that_are_not_16_byte_aligned(off):
     assert e.value.status == B.ERR_MISALIGNED
 
 
-@pytest.mark.parametrize("dtype,rows,d", [("bf16", 30000, 64), ("fp16", 20011, 128), ("bf16", 9001, 192), ("bf16", 24576, 256),
-                                          ("fp16", 7003, 1000), ("bf16", 250_000, 256), ("fp16", 3, 128), ("bf16", 60000, 72),
-                                          ("bf16", 40000, 100)])
+MERGE = [("bf16", 30000, 64), ("fp16", 20011, 128), ("bf16", 9001, 192), ("bf16", 24576, 256), ("fp16", 7003, 1000),
+         ("bf16", 250_000, 256), ("fp16", 3, 128), ("bf16", 60000, 72), ("bf16", 40000, 100)]
+
+
+@pytest.mark.parametrize("dtype,rows,d", MERGE)
 def test_merge_of_attention_states(dtype, rows, d):
     t = W.x_torch_dtype(dtype)
     va, vb = normal((rows, d), t, 1), normal((rows, d), t, 2)
@@ -136,13 +138,13 @@ def check_norm(M, N, dtype, off=0, special=None):
 
 # N in pieces of 16 bytes (8 or 4 elements): half a wave and one more, whole waves and one more, one piece per thread
 # at its limit and beyond, the most a thread holds; M around the rows of a workgroup; sizes on both sides of the store
-# policy's two limits (16 and 96 MB)
+# policy's two limits (512 KB and 96 MB)
 NORM = [("bf16", 1, 136), ("bf16", 7, 256), ("bf16", 8, 264), ("fp16", 5, 512), ("fp16", 3, 520), ("bf16", 2, 8192),
         ("bf16", 3, 8200), ("fp16", 2, 16384), ("fp16", 2, 24584), ("bf16", 2, 32768), ("fp32", 3, 68), ("fp32", 5, 132),
         ("fp32", 2, 4096), ("fp32", 2, 4100), ("fp32", 2, 16388), ("fp32", 2, 24580), ("fp32", 1, 32768),
         ("fp16_res32", 3, 72), ("fp16_res32", 9, 1000), ("fp16_res32", 3, 1004), ("fp16_res32", 2, 20484),
         ("fp16_res32", 2, 32764), ("bf16", 4096, 1024), ("bf16", 4095, 1024), ("bf16", 6144, 4096), ("bf16", 6145, 4096),
-        ("fp32", 700, 3584), ("fp16_res32", 5000, 2880)]
+        ("fp32", 700, 3584), ("fp16_res32", 5000, 2880), ("bf16", 127, 1024), ("bf16", 128, 1024)]
 
 
 @pytest.mark.parametrize("dtype,M,N", NORM)
