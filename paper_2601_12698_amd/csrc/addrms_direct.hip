@@ -45,12 +45,19 @@ template <int DT, int CPT, int POL, bool RAG, bool MULTI> const void* addrms_fn3
     if constexpr (direct_instance(VEC, CPT, POL, RAG, MULTI)) return reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL, RAG, MULTI>);
     else return nullptr;
 }
+template <int DT, int CPT, int POL> const void* addrms_fn2(bool rag, bool multi)
+{
+    return rag ? (multi ? addrms_fn3<DT, CPT, POL, true, true>() : addrms_fn3<DT, CPT, POL, true, false>())
+               : (multi ? addrms_fn3<DT, CPT, POL, false, true>() : addrms_fn3<DT, CPT, POL, false, false>());
+}
 template <int DT, int CPT> const void* addrms_fn2(int pol, bool rag, bool multi)
 {
-    if (pol == POL_NT) return rag ? (multi ? addrms_fn3<DT, CPT, POL_NT, true, true>() : addrms_fn3<DT, CPT, POL_NT, true, false>())
-                                  : (multi ? addrms_fn3<DT, CPT, POL_NT, false, true>() : addrms_fn3<DT, CPT, POL_NT, false, false>());
-    return rag ? (multi ? addrms_fn3<DT, CPT, POL_WT, true, true>() : addrms_fn3<DT, CPT, POL_WT, true, false>())
-               : (multi ? addrms_fn3<DT, CPT, POL_WT, false, true>() : addrms_fn3<DT, CPT, POL_WT, false, false>());
+    switch (pol) {
+    case POL_NT: return addrms_fn2<DT, CPT, POL_NT>(rag, multi);
+    case POL_WT: return addrms_fn2<DT, CPT, POL_WT>(rag, multi);
+    case POL_SHARED: return addrms_fn2<DT, CPT, POL_SHARED>(rag, multi);
+    default: return nullptr;
+    }
 }
 template <int DT> const void* addrms_fn1(int cpt, int pol, bool rag, bool multi)
 {

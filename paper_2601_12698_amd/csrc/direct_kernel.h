@@ -7,7 +7,8 @@
 // no such tail, but nothing of them stays in the memory-side cache either, where the next
 // kernel of the program looks for its input.  Write-through stores (sc1) go to the memory
 // side as they are issued and stay there.  Which one a problem takes is decided by what it
-// writes (write_through_max in direct_route.cpp has both sides measured).
+// writes (write_through_max in direct_route.cpp has both sides measured).  Loads are
+// non-temporal too, except where a wave shares lines with the waves beside it (POL_SHARED).
 //
 // Ragged rows (RAG).  A row length that VEC does not divide used to mean accesses as narrow
 // as one element, and one that 128 bytes do not divide waves whose lines are shared with the
@@ -32,7 +33,7 @@ template <typename T, int AL> struct at_align { typedef T type __attribute__((al
 template <int POL, int BYTES, int AL>
 __device__ __forceinline__ void ld_stream(const char* base, uint64_t off, raw_t<BYTES>& v)
 {
-    constexpr bool NT = POL != POL_CACHED;
+    constexpr bool NT = POL == POL_NT || POL == POL_WT;
     if constexpr (AL >= 16 || AL >= BYTES) {
         ld_raw<BYTES, NT>(base + off, v);
     } else {
@@ -49,7 +50,7 @@ __device__ __forceinline__ void ld_stream(const char* base, uint64_t off, raw_t<
 template <int POL, int BYTES>
 __device__ __forceinline__ void st_stream(char* base, uint32_t off, const raw_t<BYTES>& v)
 {
-    if constexpr (POL == POL_WT) {
+    if constexpr (POL == POL_WT || POL == POL_SHARED) {
         constexpr int kSc1 = 16;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000);
         if constexpr (BYTES == 8) {
@@ -161,7 +162,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
     constexpr int UNR = VEC * CPT <= 32 ? CPT : (CPT + 1) / 2;
-    constexpr bool BF = T::BF, EARLY_WEIGHTS = POL == POL_WT && CPT <= 2, LAST_WEIGHTS = POL == POL_NT && CPT >= 3;
+    constexpr bool BF = T::BF, EARLY_WEIGHTS = (POL == POL_WT || POL == POL_SHARED) && CPT <= 2, LAST_WEIGHTS = POL == POL_NT && CPT >= 3;
     extern __shared__ double lds[];
 
     const uint32_t lane = threadIdx.x, ry = MULTI ? threadIdx.y : 0u;

@@ -73,24 +73,40 @@ static bool direct_addrms_long_route(int64_t M, int64_t N, int dtype, bool split
 // write-through store only waits longer (16 x 4096 bf16 2.2 us against 2.4; from 1 MB on write-through wins, 64 x 8192
 // 2.9 against 3.4), and for rows with single elements, whose partly written lines a write-through store sends out at
 // once (2047 x 4095 fp16 12.9 us and from HBM 13.5 against 13.3 and 15.9).
+// Rows of whole vectors that are not whole lines: where waves share lines with the waves beside them, a non-temporal load
+// gives up a line that the next wave still wants, and a non-temporal store sends out half of one.  They take ordinary loads
+// and write-through stores at every size from 512 KB on: rows that are not walked by lines, whose every wave shares two,
+// and walked ones of up to 3 KB of x, where the lines at a row's ends are one in twelve or more.  On three buffer sets /
+// from HBM, us, the knob grid's default, non-temporal loads (with the stores of the size), this:
+//   124 x 30008 fp16 (15 MB)              7.5 / 11.1       8.5 / 12.3      6.7 / 9.1    (7.5, 8.5, 6.7: one set)
+//   22500 x 1000 bf16 (90 MB)            32.2 / 35.6      31.9 / 40.6     28.0 / 31.7
+//   108333 x 200 fp16+fp32 (130 MB)      48.8 / 49.8      51.2 / 51.8     43.9 / 43.8
+//   228658 x 328 bf16 (300 MB)          113.3 / 112.0    125.8 / 125.4    99.7 / 99.7
+//   500000 x 100 fp32 (400 MB)          136.2 / 136.0    151.2 / 151.0   133.5 / 133.3
+// Longer walked rows (2056 bf16, 400 MB: 127.4 against 130.3 with this; 10008 fp16, 250 MB: 82.5 against 88.4) keep the
+// policy of their size.
 // Ragged walk: where a vector access does not divide the row, unless all of it is under 1 MB and the default
 // configuration's accesses are at least two elements wide (40 x 1030 bf16 3.3 us against 3.2); and where rows are whole
-// vectors but not whole lines, from 16 MB on (below, 1000 x 1000 bf16 3.6 us against 3.5).
+// vectors but not whole lines, from 16 MB on (below, 1000 x 1000 bf16 3.6 us against 3.5) and from 64 pieces a row on
+// (22500 x 1000 bf16 28.0 us and from HBM 31.7 against 30.6 and 34.9; 28846 x 520 19.6 / 24.3 against 19.8 / 21.7; 31492 x
+// 516 fp32 45.3 / 44.9 against 47.0 / 46.5; shorter rows lose: 108333 x 200 fp16+fp32 56.1 / 56.3 against 43.9 / 43.8).
 // A default configuration with narrower accesses than these admits bases that they do not (86912 fp32: two elements per
 // access): such rows take the ragged walk, whole vectors or not.
 bool direct_addrms_route(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, uintptr_t w, DirectRoute* out)
 {
-    constexpr int64_t kWriteThroughMin = 512 << 10, kRaggedMin = 1 << 20, kLineWalkMin = 16 << 20;
+    constexpr int64_t kWriteThroughMin = 512 << 10, kRaggedMin = 1 << 20, kLineWalkMin = 16 << 20, kSharedLinesRow = 3072;
     const int vec = direct_vec(dtype), xb = x_bytes(dtype), rb = r_bytes(dtype);
     const int64_t bytes = M * N * (xb + rb);
     const bool split = N % vec != 0 || x % (vec * xb) != 0 || r % (vec * rb) != 0 || w % (vec * xb) != 0;   // single elements
-    const bool rag = split || ((N * xb) % kLineBytes != 0 && bytes >= kLineWalkMin && N >= 128 * vec);
+    const bool partial_lines = (N * xb) % kLineBytes != 0;
+    const bool rag = split || (partial_lines && bytes >= kLineWalkMin && N >= 64 * vec);
     if (split && ((x / xb) % vec != (r / rb) % vec || (bytes < kRaggedMin && default_vec > 1))) return false;
     const int line = kLineBytes / xb;                                                 // elements
     const int64_t pieces = (N + (rag ? line - 1 : 0) + vec - 1) / vec;                // a ragged row begins anywhere in a line
     if (N < 16 * vec) return false;
     if (pieces * vec > 32 * 1024) return direct_addrms_long_route(M, N, dtype, split, out);
-    const int pol = bytes >= kWriteThroughMin && bytes <= write_through_max() && !split ? POL_WT : POL_NT;
+    const bool shared_lines = partial_lines && !split && (!rag || N * xb <= kSharedLinesRow);
+    const int pol = split || bytes < kWriteThroughMin ? POL_NT : shared_lines ? POL_SHARED : bytes <= write_through_max() ? POL_WT : POL_NT;
     const bool thick = rag && bytes <= write_through_max();
     int64_t cpt = std::max<int64_t>((pieces + 1023) / 1024, thick && split ? 3 : thick || (pol == POL_WT && pieces > 256) ? 2 : 1);
     int64_t tpr = (pieces + cpt - 1) / cpt;

@@ -8,7 +8,8 @@
 namespace addrms {
 
 // Loads and stores.  POL_CACHED: ordinary.  POL_NT: both non-temporal.  POL_WT: non-temporal loads, write-through stores.
-enum : int { POL_CACHED = 0, POL_NT = 1, POL_WT = 2 };
+// POL_SHARED: ordinary loads, write-through stores, for waves that share cache lines with the waves beside them.
+enum : int { POL_CACHED = 0, POL_NT = 1, POL_WT = 2, POL_SHARED = 3 };
 
 constexpr int kFlatThreads = 256;
 // Workgroups of 1024 threads leave each 128 registers: 48 values of the row stay there.  (512 threads with 144 values
@@ -20,11 +21,12 @@ constexpr int direct_vec(int dtype) { return dtype == ADDRMS_BF16 || dtype == AD
 
 // The add+RMSNorm kernels with the row in registers that the rules can ask for: at most 32 values per thread, because a
 // workgroup of 1024 threads leaves each 128 registers.  Rows of whole vectors share a workgroup only where 32 threads
-// take one piece each; ragged walks with write-through stores have at least two pieces per thread, and exactly two where
-// rows share a workgroup.
+// take one piece each; walks by lines with write-through stores have at least two pieces per thread, and exactly two
+// where rows share a workgroup; with ordinary loads two in a shared workgroup and one otherwise.
 constexpr bool direct_instance(int vec, int cpt, int pol, bool rag, bool multi)
 {
-    if ((pol != POL_NT && pol != POL_WT) || cpt < 1 || (vec == 8 ? cpt > 4 : cpt > 4 && cpt != 6 && cpt != 8)) return false;
+    if (pol == POL_CACHED || cpt < 1 || (vec == 8 ? cpt > 4 : cpt > 4 && cpt != 6 && cpt != 8)) return false;
+    if (rag && pol == POL_SHARED) return cpt == (multi ? 2 : 1);
     if (rag) return pol == POL_WT ? (multi ? cpt == 2 : cpt >= 2) : (!multi || cpt <= 3);
     return !multi || cpt == 1;
 }

@@ -144,7 +144,11 @@ NORM = [("bf16", 1, 136), ("bf16", 7, 256), ("bf16", 8, 264), ("fp16", 5, 512), 
         ("fp32", 2, 4096), ("fp32", 2, 4100), ("fp32", 2, 16388), ("fp32", 2, 24580), ("fp32", 1, 32768),
         ("fp16_res32", 3, 72), ("fp16_res32", 9, 1000), ("fp16_res32", 3, 1004), ("fp16_res32", 2, 20484),
         ("fp16_res32", 2, 32764), ("bf16", 4096, 1024), ("bf16", 4095, 1024), ("bf16", 6144, 4096), ("bf16", 6145, 4096),
-        ("fp32", 700, 3584), ("fp16_res32", 5000, 2880), ("bf16", 127, 1024), ("bf16", 128, 1024)]
+        ("fp32", 700, 3584), ("fp16_res32", 5000, 2880), ("bf16", 127, 1024), ("bf16", 128, 1024),
+        # whole vectors but not whole lines, from 512 KB on: every number of pieces per thread, two rows in a workgroup
+        ("bf16", 2001, 136), ("fp16", 300, 1000), ("bf16", 40, 10008), ("bf16", 20, 22376), ("fp16", 11, 30008), ("fp32", 1001, 100),
+        ("fp32", 200, 1004), ("fp32", 40, 5004), ("fp32", 20, 10004), ("fp32", 20, 15004), ("fp32", 12, 20004), ("fp32", 10, 28004),
+        ("fp16_res32", 2003, 100), ("fp16_res32", 700, 200), ("fp16_res32", 20, 12004), ("bf16", 150_001, 200)]
 
 
 @pytest.mark.parametrize("dtype,M,N", NORM)
@@ -159,7 +163,9 @@ RAGGED = [("bf16", 67, 129), ("bf16", 66, 131), ("fp16", 130, 255), ("fp16", 9, 
           ("fp32", 35, 67), ("fp32", 9, 1001), ("fp32", 300, 1002), ("fp32", 3, 4067), ("fp32", 3, 4069), ("fp16_res32", 65, 67),
           ("fp16_res32", 9, 1001), ("fp16_res32", 9, 4033), ("fp16_res32", 9, 4035), ("bf16", 40, 1030), ("bf16", 3, 8129),
           ("bf16", 3, 8131), ("fp16", 2, 16385), ("fp16", 2, 32705), ("fp16", 2, 32707), ("fp32", 2, 32737), ("fp32", 2, 32739),
-          ("fp16_res32", 2, 32705), ("bf16", 4500, 1000), ("fp16_res32", 3000, 1000), ("fp32", 2200, 1004), ("bf16", 9000, 6150)]
+          ("fp16_res32", 2, 32705), ("bf16", 4500, 1000), ("fp16_res32", 3000, 1000), ("fp32", 2200, 1004), ("bf16", 9000, 6150),
+          ("bf16", 3001, 1528), ("bf16", 3001, 1544), ("bf16", 26001, 1000), ("fp32", 17001, 764), ("fp16_res32", 11003, 260),
+          ("fp16_res32", 17001, 1000)]
 
 
 @pytest.mark.parametrize("dtype,M,N", RAGGED)

@@ -45,9 +45,9 @@ def test_the_kernels_asked_for_are_the_kernels_built(driver):
 def test_the_gpu_cases_run_what_they_are_meant_for(driver):
     for (dtype, M, N), got in zip(NORM, routes(driver, [("addrms", *c) for c in NORM])):
         assert got.startswith("row") and "ragged" not in got, (dtype, M, N, got)
-    # on the other side of a limit: too small; one element longer than the registers; too short for a walk by lines
+    # on the other side of a limit: too small; one element longer than the registers
     beside = {("bf16", 5, 450): "default", ("bf16", 40, 1030): "default", ("fp16", 2, 32707): "long cached ragged parked=0",
-              ("fp32", 2, 32739): "long cached ragged parked=0", ("bf16", 4500, 1000): "row writethrough pieces=1 threads=128 rows=1"}
+              ("fp32", 2, 32739): "long cached ragged parked=0"}
     for (dtype, M, N), got in zip(RAGGED, routes(driver, [("addrms", *c) for c in RAGGED])):
         want = beside.get((dtype, M, N))
         assert got == want if want else got.startswith("row") and "ragged" in got, (dtype, M, N, got)
@@ -74,6 +74,20 @@ LIMITS = [
     (("addrms", "bf16", 6145, 4096), "row nontemporal pieces=1 threads=512 rows=1"),
     (("addrms", "bf16", 614, 40960), "long cached parked=0"),
     (("addrms", "bf16", 615, 40960), "long nontemporal parked=0"),
+    # whole vectors but not whole lines: ordinary loads from 512 KB on; walked by lines from 16 MB and 64 pieces on, and then
+    # only rows of up to 3 KB of x; never non-temporal loads where waves share lines
+    (("addrms", "bf16", 131, 1000), "row nontemporal pieces=1 threads=128 rows=1"),
+    (("addrms", "bf16", 132, 1000), "row shared pieces=1 threads=128 rows=1"),
+    (("addrms", "fp16", 139, 30008), "row shared pieces=4 threads=960 rows=1"),
+    (("addrms", "fp16", 140, 30008), "row writethrough ragged pieces=4 threads=960 rows=1"),
+    (("addrms", "bf16", 30000, 504), "row shared pieces=1 threads=64 rows=1"),
+    (("addrms", "bf16", 30000, 520), "row shared ragged pieces=2 threads=64 rows=2"),
+    (("addrms", "bf16", 9000, 1528), "row shared ragged pieces=2 threads=128 rows=2"),
+    (("addrms", "bf16", 9000, 1544), "row writethrough ragged pieces=2 threads=128 rows=2"),
+    (("addrms", "bf16", 228658, 328), "row shared pieces=1 threads=64 rows=1"),
+    (("addrms", "fp32", 500000, 100), "row shared pieces=1 threads=32 rows=2"),
+    (("addrms", "bf16", 62500, 1000), "row shared ragged pieces=1 threads=192 rows=1"),
+    (("addrms", "bf16", 62500, 2056), "row nontemporal ragged pieces=1 threads=320 rows=1"),
     (("silumul", "bf16", 4096, 12288), "flat writethrough"),
     (("silumul", "bf16", 4097, 12288), "flat nontemporal"),
     (("merge", "bf16", 196608, 256), "flat writethrough"),
