@@ -60,15 +60,29 @@ static bool direct_addrms_long_route(int64_t M, int64_t N, int dtype, bool split
     return true;
 }
 
+// Bytes of x and residual up to which rows with single elements are left to the default configuration.  Where its accesses
+// are at least two elements wide, 1 MB (40 x 1030 bf16 3.2 us against 3.3), and half as much again or, for accesses of four,
+// twice as much for 16-bit rows under 1024 elements, which its 256 threads hold in one access or two each (us, this against
+// the walk: 268 x 932 bf16 3.1 / 3.5, 536 x 932 3.4 / 3.6, 804 x 932 the same; 500 x 514 3.0 / 3.1, 1000 x 514 the same).
+// Where they are one element, 1 MB for 16-bit rows so short that its many threads are ahead of the few pieces (380 x 131
+// bf16 2.6 / 2.8; 579 x 259 the same).
+static int64_t ragged_min(int vec, int default_vec, int64_t N)
+{
+    constexpr int64_t kMB = 1 << 20;
+    if (default_vec > 1) return vec == 8 && N < 128 * vec ? (default_vec > 2 ? 2 * kMB : kMB + kMB / 2) : kMB;
+    return vec == 8 && N < 32 * vec ? kMB : 0;
+}
+
 // Threads per row: one per piece up to 1024, then as few pieces per thread as that allows, in equal shares: on 40 shapes
 // tried with 1 to 8 the fewest were the fastest, by 2-8 % against twice as many.  Written-through rows of more than 256
 // pieces take at least two, which then are stored in one go after the row sum (256 x 8192 bf16 4.0 us against 4.2 and from
 // HBM 4.4 against 5.6; 512 x 8192 5.8 against 6.5; 4096 x 4096 the same; shorter rows 1-2 % slower).
-// Ragged rows up to 96 MB take three pieces per thread (two where there are no single elements: 8192 x 1000 fp16+fp32
-// 17.1 us against 17.5) and two rows per workgroup, so that fewer waves repeat what a
+// Ragged rows from 4 MB (single elements) or 16 MB to 96 MB take three pieces per thread (two where there are no single
+// elements: 8192 x 1000 fp16+fp32 17.1 us against 17.5) and two rows per workgroup, so that fewer waves repeat what a
 // row costs before and after its pieces (2047 x 4095 fp16 12.9 us against 14.0 with one piece per thread, 5000 x 1001
-// fp32 15.5 against 16.0, 300 x 10001 bf16 7.4 against 8.2 with two); beyond, one is as good or better (9000 x 6150
-// bf16 76.4-79.7 us against 78.1-78.9).
+// fp32 15.5 against 16.0, 4285 x 700 bf16 6.5 against 7.3); beyond, one is as good or better (9000 x 6150 bf16 76.4-79.7 us
+// against 78.1-78.9), and so it is below, where the chip is not full and a row should arrive early (41 x 6001 bf16 3.2-3.3
+// us against 3.8-4.0, 1072 x 932 3.9-4.0 against 3.8-4.2).
 // Store policy: as above, but non-temporal below 512 KB of x and residual, where the launch is all there is and a
 // write-through store only waits longer (16 x 4096 bf16 2.2 us against 2.4; from 1 MB on write-through wins, 64 x 8192
 // 2.9 against 3.4), and for rows with single elements, whose partly written lines a write-through store sends out at
@@ -85,8 +99,8 @@ static bool direct_addrms_long_route(int64_t M, int64_t N, int dtype, bool split
 //   500000 x 100 fp32 (400 MB)          136.2 / 136.0    151.2 / 151.0   133.5 / 133.3
 // Longer walked rows (2056 bf16, 400 MB: 127.4 against 130.3 with this; 10008 fp16, 250 MB: 82.5 against 88.4) keep the
 // policy of their size.
-// Ragged walk: where a vector access does not divide the row, unless all of it is under 1 MB and the default
-// configuration's accesses are at least two elements wide (40 x 1030 bf16 3.3 us against 3.2); and where rows are whole
+// Ragged walk: where a vector access does not divide the row, unless it is small and the default configuration's accesses
+// reach (ragged_min); and where rows are whole
 // vectors but not whole lines, from 16 MB on (below, 1000 x 1000 bf16 3.6 us against 3.5) and from 64 pieces a row on
 // (22500 x 1000 bf16 28.0 us and from HBM 31.7 against 30.6 and 34.9; 28846 x 520 19.6 / 24.3 against 19.8 / 21.7; 31492 x
 // 516 fp32 45.3 / 44.9 against 47.0 / 46.5; shorter rows lose: 108333 x 200 fp16+fp32 56.1 / 56.3 against 43.9 / 43.8).
@@ -94,13 +108,13 @@ static bool direct_addrms_long_route(int64_t M, int64_t N, int dtype, bool split
 // access): such rows take the ragged walk, whole vectors or not.
 bool direct_addrms_route(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, uintptr_t w, DirectRoute* out)
 {
-    constexpr int64_t kWriteThroughMin = 512 << 10, kRaggedMin = 1 << 20, kLineWalkMin = 16 << 20, kSharedLinesRow = 3072;
+    constexpr int64_t kWriteThroughMin = 512 << 10, kThreePiecesMin = 4 << 20, kLineWalkMin = 16 << 20, kSharedLinesRow = 3072;
     const int vec = direct_vec(dtype), xb = x_bytes(dtype), rb = r_bytes(dtype);
     const int64_t bytes = M * N * (xb + rb);
     const bool split = N % vec != 0 || x % (vec * xb) != 0 || r % (vec * rb) != 0 || w % (vec * xb) != 0;   // single elements
     const bool partial_lines = (N * xb) % kLineBytes != 0;
     const bool rag = split || (partial_lines && bytes >= kLineWalkMin && N >= 64 * vec);
-    if (split && ((x / xb) % vec != (r / rb) % vec || (bytes < kRaggedMin && default_vec > 1))) return false;
+    if (split && ((x / xb) % vec != (r / rb) % vec || bytes < ragged_min(vec, default_vec, N))) return false;
     const int line = kLineBytes / xb;                                                 // elements
     const int64_t pieces = (N + (rag ? line - 1 : 0) + vec - 1) / vec;                // a ragged row begins anywhere in a line
     if (N < 16 * vec) return false;
@@ -108,7 +122,8 @@ bool direct_addrms_route(int64_t M, int64_t N, int dtype, int default_vec, uintp
     const bool shared_lines = partial_lines && !split && (!rag || N * xb <= kSharedLinesRow);
     const int pol = split || bytes < kWriteThroughMin ? POL_NT : shared_lines ? POL_SHARED : bytes <= write_through_max() ? POL_WT : POL_NT;
     const bool thick = rag && bytes <= write_through_max();
-    int64_t cpt = std::max<int64_t>((pieces + 1023) / 1024, thick && split ? 3 : thick || (pol == POL_WT && pieces > 256) ? 2 : 1);
+    const int64_t thickness = split ? (thick && bytes >= kThreePiecesMin ? 3 : 1) : thick || (pol == POL_WT && pieces > 256) ? 2 : 1;
+    int64_t cpt = std::max<int64_t>((pieces + 1023) / 1024, thickness);
     int64_t tpr = (pieces + cpt - 1) / cpt;
     tpr = tpr <= 32 ? 32 : (tpr + 63) / 64 * 64;
     cpt = (pieces + tpr - 1) / tpr;

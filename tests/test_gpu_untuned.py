@@ -157,7 +157,7 @@ def test_norm(dtype, M, N):
 
 
 # rows that 16 bytes do not divide (every remainder), that lines do not divide, that begin at every element of a line,
-# with as many pieces as threads and one more, and the longest ones; under 1 MB with a default access of two elements
+# with as many pieces as threads and one more, and the longest ones; small ones that the default configuration keeps
 RAGGED = [("bf16", 67, 129), ("bf16", 66, 131), ("fp16", 130, 255), ("fp16", 9, 1001), ("fp16", 9, 1003), ("bf16", 9, 1005),
           ("bf16", 9, 1007), ("bf16", 700, 1030), ("bf16", 600, 1020), ("bf16", 5, 449), ("bf16", 5, 450), ("fp32", 70, 65),
           ("fp32", 35, 67), ("fp32", 9, 1001), ("fp32", 300, 1002), ("fp32", 3, 4067), ("fp32", 3, 4069), ("fp16_res32", 65, 67),
@@ -165,7 +165,10 @@ RAGGED = [("bf16", 67, 129), ("bf16", 66, 131), ("fp16", 130, 255), ("fp16", 9, 
           ("bf16", 3, 8131), ("fp16", 2, 16385), ("fp16", 2, 32705), ("fp16", 2, 32707), ("fp32", 2, 32737), ("fp32", 2, 32739),
           ("fp16_res32", 2, 32705), ("bf16", 4500, 1000), ("fp16_res32", 3000, 1000), ("fp32", 2200, 1004), ("bf16", 9000, 6150),
           ("bf16", 3001, 1528), ("bf16", 3001, 1544), ("bf16", 26001, 1000), ("fp32", 17001, 764), ("fp16_res32", 11003, 260),
-          ("fp16_res32", 17001, 1000)]
+          ("fp16_res32", 17001, 1000),
+          # from 4 MB on with up to three pieces per thread, and one or two rows in a workgroup
+          ("bf16", 12001, 129), ("bf16", 9001, 131), ("fp16", 5001, 255), ("bf16", 5003, 451), ("bf16", 1603, 1020), ("fp16", 2101, 1001),
+          ("bf16", 501, 4001), ("fp32", 601, 1001), ("fp32", 300, 2001), ("fp16_res32", 901, 1001), ("fp16_res32", 300, 4001)]
 
 
 @pytest.mark.parametrize("dtype,M,N", RAGGED)

@@ -46,7 +46,7 @@ def test_the_gpu_cases_run_what_they_are_meant_for(driver):
     for (dtype, M, N), got in zip(NORM, routes(driver, [("addrms", *c) for c in NORM])):
         assert got.startswith("row") and "ragged" not in got, (dtype, M, N, got)
     # on the other side of a limit: too small; one element longer than the registers
-    beside = {("bf16", 5, 450): "default", ("bf16", 40, 1030): "default", ("fp16", 2, 32707): "long cached ragged parked=0",
+    beside = {("bf16", 67, 129): "default", ("bf16", 66, 131): "default", ("fp16", 130, 255): "default", ("bf16", 5, 450): "default", ("bf16", 40, 1030): "default", ("fp16", 2, 32707): "long cached ragged parked=0",
               ("fp32", 2, 32739): "long cached ragged parked=0"}
     for (dtype, M, N), got in zip(RAGGED, routes(driver, [("addrms", *c) for c in RAGGED])):
         want = beside.get((dtype, M, N))
@@ -94,11 +94,27 @@ LIMITS = [
     (("merge", "bf16", 196609, 256), "flat nontemporal"),
     (("merge", "bf16", 2709, 256), "default"),
     (("merge", "bf16", 2710, 256), "flat writethrough"),
-    # single elements: three pieces per thread, two rows per workgroup, up to 96 MB; never write-through
+    # single elements: small ones are the default configuration's, up to 1 to 2 MB where its accesses are wide or rows short
+    (("addrms", "bf16", 254, 1030), "default"),
+    (("addrms", "bf16", 255, 1030), "row nontemporal ragged pieces=1 threads=192 rows=1"),
+    (("addrms", "bf16", 562, 932), "default"),
+    (("addrms", "bf16", 563, 932), "row nontemporal ragged pieces=1 threads=128 rows=2"),
+    (("addrms", "bf16", 765, 514), "default"),
+    (("addrms", "bf16", 766, 514), "row nontemporal ragged pieces=1 threads=128 rows=2"),
+    (("addrms", "bf16", 2031, 129), "default"),
+    (("addrms", "bf16", 2033, 129), "row nontemporal ragged pieces=1 threads=32 rows=2"),
+    (("addrms", "bf16", 5, 259), "row nontemporal ragged pieces=1 threads=64 rows=1"),
+    (("addrms", "fp32", 130, 1002), "default"),
+    (("addrms", "fp32", 131, 1002), "row nontemporal ragged pieces=1 threads=320 rows=1"),
+    (("addrms", "fp32", 5, 65), "row nontemporal ragged pieces=1 threads=32 rows=2"),
+    # three pieces per thread from 4 MB, two rows per workgroup; one piece beyond 96 MB; never write-through
+    (("addrms", "bf16", 1047, 1001), "row nontemporal ragged pieces=1 threads=192 rows=2"),
+    (("addrms", "bf16", 1048, 1001), "row nontemporal ragged pieces=3 threads=64 rows=2"),
+    (("addrms", "bf16", 511, 2055), "row nontemporal ragged pieces=3 threads=128 rows=1"),
     (("addrms", "fp16", 2047, 4095), "row nontemporal ragged pieces=3 threads=192 rows=2"),
     (("addrms", "bf16", 9000, 6150), "row nontemporal ragged pieces=1 threads=832 rows=1"),
     # bases: the streams at different elements, the weights alone off a 16-byte address, a base no access fits
-    (("addrms", "bf16", 17, 1001, 2, 2, 2), "row nontemporal ragged pieces=3 threads=64 rows=1"),
+    (("addrms", "bf16", 17, 1001, 2, 2, 2), "row nontemporal ragged pieces=1 threads=192 rows=1"),
     (("addrms", "bf16", 17, 1001, 2, 0, 2), "default"),
     (("addrms", "bf16", 17, 1000, 2, 2, 2), "misaligned"),
     (("silumul", "bf16", 9, 1001, 2, 0), "flat writethrough ragged"),
