@@ -6,11 +6,13 @@ The comparison is of bits.  A row's sum of squares is taken in fp64 in another o
 so rstd may in principle round to the neighbouring fp32 value: two orders differ by about sqrt(N) * 2^-53, which crosses
 one of the rounding boundaries 2^-24 apart in some 1e-7 of rows, a hundredth of one row over all the rows here.  The
 seeds are fixed, so what passes keeps passing."""
+import numpy as np
 import pytest
 import torch
 
 from paper_2601_12698_amd import binding as B
 from paper_2601_12698_amd import workloads as W
+from ulp import ulp_distance
 
 pytestmark = pytest.mark.gpu
 PAD = 64            # canary elements on either side of an output
@@ -104,6 +106,39 @@ def test_merge_of_attention_states(dtype, rows, d):
     B.mergestates_run(va, sa, vb, sb, vo, so, rows, d, dtype)
     torch.cuda.synchronize()
     assert torch.equal(bits(vo), bits(vw).view(-1)) and torch.equal(bits(so), bits(sw)) and vok() and sok()
+
+
+def test_merge_of_states_with_scores_far_apart(oracle):
+    """Scores from equal to 2000 apart, at a size that the flat kernel takes (above 4 MB), against the oracle: the part with
+    the larger score by far comes out as it went in.  Bounds as in test_gpu_mergestates.py; repeated rows, so that every pair
+    of scores meets every place in a workgroup."""
+    pairs = torch.tensor([[0.0, 0.0], [5.0, -5.0], [-5.0, 5.0], [90.0, -90.0], [-90.0, 90.0], [1e3, -1e3], [-1e3, 1e3], [3.25, 3.25],
+                          [3.25, 3.2500002], [-1e3, -1e3], [1e3, 1e3]])
+    d, rows = 128, 11 * 700
+    va, vb = (finite((rows, d), torch.bfloat16, s).abs() + 0.125 for s in (5, 6))       # one sign: nothing cancels
+    sa, sb = pairs[:, 0].repeat(700).cuda(), pairs[:, 1].repeat(700).cuda()
+    vo, so = torch.empty_like(va), torch.empty_like(sa)
+    B.mergestates_run(va, sa, vb, sb, vo, so, rows, d, "bf16")
+    torch.cuda.synchronize()
+    vref, sref = oracle.mergestates(W.to_bits(va), sa.cpu().numpy(), W.to_bits(vb), sb.cpu().numpy(), 0)
+    assert ulp_distance(W.to_bits(vo), vref).max() <= 1
+    assert np.allclose(so.cpu().numpy(), sref, rtol=0, atol=4e-7 * np.maximum(1.0, np.abs(sref)))
+    k = torch.arange(rows, device="cuda") % 11
+    assert torch.equal(vo[(k == 3) | (k == 5)], va[(k == 3) | (k == 5)]) and torch.equal(vo[(k == 4) | (k == 6)], vb[(k == 4) | (k == 6)])
+
+
+def test_merge_of_states_with_scores_that_are_not_finite():
+    """Outside what the operator promises; the flat kernel gives the bits of the default configuration even so."""
+    inf, nan = float("inf"), float("nan")
+    pairs = torch.tensor([[-inf, 0.0], [0.0, -inf], [-inf, -inf], [inf, 0.0], [inf, inf], [nan, 0.0], [0.0, nan]])
+    d, rows = 256, 7 * 500
+    va, vb = finite((rows, d), torch.float16, 7), finite((rows, d), torch.float16, 8)
+    sa, sb = pairs[:, 0].repeat(500).cuda(), pairs[:, 1].repeat(500).cuda()
+    vw, sw, vo, so = torch.empty_like(va), torch.empty_like(sa), torch.empty_like(va), torch.empty_like(sa)
+    B.mergestates_run(va, sa, vb, sb, vw, sw, rows, d, "fp16", B.mergestates_default_cfg(d, "fp16"))
+    B.mergestates_run(va, sa, vb, sb, vo, so, rows, d, "fp16")
+    torch.cuda.synchronize()
+    assert torch.equal(bits(vo), bits(vw)) and torch.equal(bits(so), bits(sw))
 
 
 def norm_inputs(M, N, dtype, seed, off=0, special=None):

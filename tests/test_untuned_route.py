@@ -59,6 +59,7 @@ def test_the_gpu_cases_run_what_they_are_meant_for(driver):
         assert want, (dtype, M, d, got)
     for (dtype, rows, d), got in zip(MERGE, routes(driver, [("merge", *c) for c in MERGE])):
         assert (got == "default") == (d % 8 != 0 or rows * d * 6 < 4 << 20), (dtype, rows, d, got)
+    assert routes(driver, [("merge", "bf16", 11 * 700, 128), ("merge", "fp16", 7 * 500, 256)]) == ["flat writethrough"] * 2
 
 
 LIMITS = [
