@@ -123,9 +123,10 @@ typedef struct addrms_cfg {
  * before anything is launched (Section 3.3: invalid launches are pruned, not
  * attempted).  x, residual and weight must not overlap.  Re-entrant: host threads
  * may call it concurrently on their own streams.  It can be recorded into a HIP
- * graph (stream capture); the first launch of a cfg whose occupancy cap pads the
- * LDS allocation beyond 64 KiB raises that kernel's dynamic-LDS limit once per
- * process, so issue one such launch eagerly before capturing.
+ * graph (stream capture); the first launch of a kernel whose LDS allocation is
+ * beyond 64 KiB (an occupancy cap that pads it, rows that continue in LDS, with or
+ * without a cfg) raises that kernel's dynamic-LDS limit once per process, so issue
+ * one such launch eagerly before capturing.
  */
 int addrms_run(void* x, void* residual, const void* weight, float eps,
                int64_t M, int64_t N, int dtype, const addrms_cfg* cfg, void* stream);
@@ -218,7 +219,8 @@ typedef struct addrms_tune_report {
     int64_t n_failed;        /* cfgs that failed the correctness gate or a launch          */
     int64_t best_found_at;   /* 1-based count of measured cfgs when the winner first ran   */
     double  best_us;         /* confirmed mean time of the returned cfg                    */
-    double  default_us;      /* confirmed mean time of the default cfg                     */
+    double  default_us;      /* confirmed mean time of the default cfg (what a call without
+                                a cfg launches is not a cfg and not among the candidates)  */
     double  wall_ms;         /* whole call                                                 */
     double  time_to_best_ms; /* wall time until the winner was first measured              */
     addrms_cfg best;
@@ -234,6 +236,9 @@ typedef struct addrms_tune_report {
  * agreement with the default configuration's output (bit-exact residual,
  * y within 1 unit in the last place), re-test the Top-K with the confirmation
  * protocol, store the winner in the specialised table and return it.
+ * From then on calls without a cfg run the winner at this N and dtype, also where the
+ * kernel that they ran before, which the search does not time, is faster: compare
+ * addrms_measure(NULL) before and after.
  * Blocking.  Allocates and frees its own device buffers (rotated so that the
  * timed launches stream from HBM rather than from cache).
  *   budget  host, may be NULL (all defaults)
@@ -380,8 +385,9 @@ int addrms_audit_rules(int64_t M, int64_t N, int dtype, const addrms_budget* bud
 int addrms_audit_rules_with_backend(int64_t M, int64_t N, int dtype, const addrms_budget* budget,
                                     const addrms_backend* backend, addrms_audit_report* report);
 
-/* addrms_measure: mean time in microseconds of `cfg` (NULL = table/default, as
- * in addrms_run) on (M, N, dtype) over `reps` launches after `warmup`, on
+/* addrms_measure: mean time in microseconds of `cfg` (NULL = what addrms_run launches
+ * without one: the table's entry, else the kernel chosen for the problem, else the
+ * default cfg; for the default cfg itself pass addrms_default_cfg's) on (M, N, dtype) over `reps` launches after `warmup`, on
  * library-allocated synthetic buffers.  rotate != 0 cycles through enough
  * buffer sets to exceed the last-level caches; rotate == 0 reuses one set
  * (a cache-warm figure).  A batch shorter than 30 ms is preceded by that much

@@ -56,6 +56,7 @@ int mergestates_select_general(const addrms_shape* shapes, int32_t n, int dtype,
 int mergestates_tune_rounds(const addrms_shape* shapes, int32_t n, int dtype, const addrms_budget* budget,
                             addrms_cfg* out_general, addrms_rounds_report* report);
 
+/* As addrms_measure.  cfg NULL: what mergestates_run launches without one. */
 int mergestates_measure(const addrms_cfg* cfg, int64_t rows, int64_t d, int dtype, int warmup, int reps,
                         int rotate, double* mean_us);
 int mergestates_table_lookup(int64_t rows, int64_t d, int dtype, addrms_cfg* out);

@@ -59,7 +59,8 @@ int silumul_tune_rounds(const addrms_shape* shapes, int32_t n, int dtype, const 
                         addrms_cfg* out_general, addrms_rounds_report* report);
 
 /* Mean time in microseconds over `reps` launches after `warmup`, on library-allocated
- * synthetic buffers rotated past the last-level cache (rotate != 0). */
+ * synthetic buffers rotated past the last-level cache (rotate != 0).  cfg NULL: what
+ * silumul_run launches without one. */
 int silumul_measure(const addrms_cfg* cfg, int64_t M, int64_t d, int dtype, int warmup, int reps, int rotate,
                     double* mean_us);
 

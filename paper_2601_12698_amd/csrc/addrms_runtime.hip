@@ -133,8 +133,9 @@ int resolve_cfg(const addrms_cfg* cfg, int64_t M, int64_t N, int dtype, addrms_c
 // ---- resolved calls -----------------------------------------------------------------
 // What a *_run call decides before it launches depends on its sizes, its configuration (if any), the table and the
 // alignment of its tensors, not on their contents or addresses.  Deciding it takes from 0.8 us to 13 us (a default
-// configuration behind several infeasible ones) beside a launch of 2 us, so each thread keeps its last decisions:
-// 64 of them, looked up by everything they depend on.
+// configuration behind several infeasible ones) beside a launch of 2 us, so each thread keeps decisions in 64 slots,
+// looked up by everything they depend on.  A problem has one slot, which the three operators share: of two problems that
+// fall into the same one, each call decides anew.
 struct Resolved {
     Feas f;                  // of c, which has passed every check
     addrms_cfg c{};

@@ -139,21 +139,27 @@ struct SingleElement {
 // ---- add + RMSNorm ---------------------------------------------------------------------------
 // A workgroup per row (MULTI: several, for rows shorter than a wave and ragged ones), a thread
 // holds CPT chunks of VEC elements from the loads to the stores.  Same arithmetic as addrms_body,
-// bit for bit.  HBM-bound: all loads of a thread are issued before the first value is used (in two
+// element by element; the sum over a row is taken in fp64 as there, but in another order, so that
+// rstd may round to the neighbouring fp32 value in some 1e-7 of rows.
+// HBM-bound: all loads of a thread are issued before the first value is used (in two
 // batches beyond 32 values), and a row is spread over many threads with few chunks each, so that it
 // arrives early.  DEFER (more than one chunk): both streams written after the row sum, 1-3 % there.
+// Times: us per launch, back to back in a graph, on three sets of buffers in rotation unless said
+// otherwise, each pair from one run on one card (a kernel's own duration in a trace is the same within
+// 0.3).
 // With written-through stores and up to two chunks the weights are fetched along with the row, so
-// that nothing is loaded behind a store (400 x 6144 bf16 4.7 -> 4.0 us, 1000 x 4096 fp32 10.3 ->
-// 10.1); with non-temporal ones they are fetched after it (20000 x 5120 126 us, along with it 131),
-// and with three or more chunks after the row sum, where their registers are free and their odd
-// addresses in ragged rows hold nothing up (300 x 10001 7.1 -> 6.6 us, 1800 x 3001 fp16+fp32 13.5 ->
-// 13.0, 900 x 28672 39.1 -> 38.6; with one chunk 1-3 % slower).
-// Default of the knob grid -> here, us: 16 x 4096 bf16 3.0 -> 2.2, 64 x 8192 3.9 -> 2.9, 512 x 8192
-// 8.2 -> 5.8, 4096 x 4096 21.2 -> 19.8, 20000 x 5120 152 -> 126 (6.5 TB/s), 32768 x 7168 340 -> 304,
-// 2048 x 8192 fp32 56.4 -> 45.3, 900 x 28672 fp16 44.3 -> 39.8.
-// Ragged: 2047 x 4095 fp16 18.6 -> 12.6 (buffers from HBM 27.0 -> 13.3), 9000 x 6150 bf16 95.5 ->
-// 77, 300 x 10001 9.3 -> 6.6, 8192 x 1000 fp16+fp32 18.2 -> 17.1 (from HBM 23.5 -> 20.1); the single
-// elements cost the first 0.7 us and weights at odd addresses 0.4 of what an aligned row would not.
+// that nothing is loaded behind a store (64 x 8192 bf16 3.4 -> 3.0, 400 x 6144 4.7 -> 4.0, 2048 x
+// 1024 4.0 -> 3.8, 1000 x 4096 fp32 10.3 -> 10.1); with non-temporal ones they are fetched after it
+// (20000 x 5120 bf16 126, along with it 133), and with three or more chunks after the row sum, where
+// their registers are free and their odd addresses in ragged rows hold nothing up (300 x 10001 7.8 ->
+// 6.7, 900 x 28672 39.3 -> 38.8, 1800 x 3001 fp16+fp32 the same and from HBM 14.0 -> 13.6; with one
+// chunk 9000 x 6150 72.4 -> 75.1, 20000 x 5120 126 -> 127).
+// Default of the knob grid -> here: 16 x 4096 bf16 2.9 -> 2.3, 64 x 8192 3.8 -> 3.0, 512 x 8192 8.0 ->
+// 5.7, 4096 x 4096 20.9 -> 19.8, 20000 x 5120 146 -> 127 (6.5 TB/s), 32768 x 7168 329 -> 298, 2048 x
+// 8192 fp32 56.1 -> 45.3, 900 x 28672 fp16 43.2 -> 38.7.
+// Ragged: 2047 x 4095 fp16 18.0 -> 12.9 (from HBM 27.2 -> 13.3), 9000 x 6150 bf16 91 -> 73, 300 x
+// 10001 8.9 -> 6.7, 8192 x 1000 fp16+fp32 17.9 -> 15.5 (from HBM 23.1 -> 18.7); the single elements
+// cost the first 0.7 and weights at odd addresses 0.4 of what an aligned row would not.
 template <int DT, int VEC, int CPT, int POL, bool RAG, bool DEFER, bool MULTI>
 __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* __restrict__ rp,
                                                    const void* __restrict__ wp, float eps, double inv_n, int32_t N,
@@ -273,10 +279,12 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
 // (1-3 % against fetching each behind the stores before it).  Bound by one workgroup filling a CU:
 // it reads its row, then writes it, and nothing else runs there meanwhile.  Write-through stores
 // lose here (1024 x 131072 bf16 234 us against 211): the next loads wait for their acknowledgement.
-// Default of the knob grid -> here, us: 1024 x 131072 bf16 248 -> 210, 2048 x 65536 221 -> 198,
-// 4096 x 40960 264 -> 232, 300 x 110592 77 -> 58, 230 x 86912 fp32 87 -> 59, 500 x 200000 fp32
-// 408 -> 356, 230 x 86912 bf16 35 -> 26; ragged rows, which were read one to four elements at a
-// time: 300 x 33333 bf16 41 -> 22, 700 x 99991 240 -> 113, 100 x 180001 113 -> 39.
+// Default of the knob grid -> here, us on three sets of buffers: 1024 x 131072 bf16 246 -> 208, 2048 x
+// 65536 219 -> 193, 4096 x 40960 261 -> 227, 300 x 110592 74 -> 56, 230 x 86912 fp32 85 -> 58, 500 x
+// 200000 fp32 404 -> 352, 230 x 86912 bf16 33 -> 25; ragged rows, which were read one to four elements
+// at a time: 300 x 33333 bf16 39 -> 21, 700 x 99991 236 -> 108, 100 x 180001 111 -> 37.  Called again
+// and again on one set of 100 to 250 MB, which the memory-side cache just holds, the default's ordinary
+// accesses are ahead (166 x 120004 fp32 51 against 69; 86 against 69 on three sets).
 template <int DT, int VEC, int CPT, int UNR, int POL, bool RAG>
 __device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __restrict__ rp,
                                                  const void* __restrict__ wp, float eps, double inv_n, int32_t N,
@@ -456,10 +464,14 @@ __device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __
 // length, no lane is idle for rows that a launch shape does not divide, and a small problem
 // spreads over as many workgroups as it has pieces.  One piece per lane: two in flight per lane
 // (half as many workgroups) lost 1-18 %; workgroups of 64 to 256 threads are the same.
-// silu_and_mul, default of the knob grid -> here, buffers cycled by the program: 4096 x 11008
-// bf16 57.2 -> 39.5 us (6.85 TB/s; the memory-side cache serves part of it), 16000 x 11008 208 ->
-// 168 (6.3 TB/s), 64 x 14336 fp16 4.5 -> 2.3, 2000 x 4099 bf16 12.4 -> 10.3.
-// merge_attn_states: 24576 x 256 bf16 7.7 -> 7.4, 20480 x 128 fp16 4.6 -> 3.9.
+// Default of the knob grid -> here, us per launch, on one set of buffers / three in rotation / from HBM:
+//   silu_and_mul  4096 x 11008 bf16  43.4 / 56.3 / 56.8 -> 38.8 / 39.7 / 42.5 (6.8 TB/s on three sets: the
+//                 memory-side cache serves part of it)    16000 x 11008  204 / 204 / 204 -> 163 / 164 / 164
+//                 (6.45 TB/s)    64 x 14336 fp16  4.3 / 4.3 / 7.4 -> 2.2 / 2.1 / 2.5
+//                 2000 x 4099 bf16  12.0 / 12.0 / 16.7 -> 8.5 / 9.8 / 10.7
+//   merge_attn_states  24576 x 256 bf16  6.4 / 7.5 / 10.0 -> 4.5 / 7.5 / 8.7    20480 x 128 fp16  3.6 / 4.5 /
+//                 5.7 -> 2.9 / 3.8 / 4.5    38759 x 256 bf16  10.8 / 10.7 / 14.0 -> 9.1 / 11.4 / 12.2 (the one
+//                 kind of buffers where the default is ahead; write_through_max in direct_route.cpp has why)
 
 // n / d for n < 2^31 and d >= 2 as (n * mul) >> 32 >> shift, where shift = ceil(log2 d) - 1 and
 // mul = ceil(2^(32 + shift) / d) < 2^32: the error of mul * d is below d <= 2^(shift + 1), so that of

@@ -1,4 +1,7 @@
 // Calls without a configuration: the rules.  Which kernel of direct_kernel.h a problem takes, and in what shape.
+//
+// Times in this file are microseconds per launch, back to back in a graph, all taken on one card in one run: on one set of
+// buffers / on three in rotation / on buffers from HBM; or the last two, or the last one, where the others say nothing.
 #include "direct_route.h"
 
 #include <algorithm>
@@ -7,15 +10,24 @@ using namespace addrms;
 
 namespace {
 
-// Write-through stores up to this many bytes of output, non-temporal ones beyond: three eighths of the
-// memory-side cache, so that the output is still there when the next kernel reads it.  Measured on buffers
-// that a program cycles through (three sets) / on buffers from HBM, write-through against non-temporal, in us:
-//   silu_and_mul  5.5 MB of traffic  2.3 / 3.0 against 2.9 / 2.8      49 MB   8.6 / 9.9 against 9.3 / 9.8
-//               270 MB, 90 MB out   39.5 / 43.2 against 42.0 / 42.5  344 MB, 115 MB out  57.2 / 56.9 against 55.9 / 56.0
-//              1057 MB, 352 MB out   171 / 170 against 168 / 166
-//   add+RMSNorm (in place) 17 MB 6.3 / 7.0 against 6.3 / 6.6         67 MB  20.1 / 24.2 against 22.9 / 23.5
-//               104 MB          34.9 / 37.6 against 34.8 / 34.9     235 MB  78.7 / 76.3 against 77.2 / 76.1
-//   merge_attn_states  38 MB  7.4 / 8.6 against 7.6 / 8.3   24 MB  5.3 / 6.3 against 5.1 / 5.8
+// Write-through stores up to this many bytes of output, non-temporal ones beyond: three eighths of the memory-side cache,
+// so that the output is still there when the next kernel reads it.  Write-through against non-temporal:
+//   add+RMSNorm N = 4096 bf16, in place  17 MB  6.5 /  6.4 /  8.0 against  6.0 /  6.9 /  7.6
+//                                        67 MB 20.0 / 19.8 / 23.5 against 21.4 / 22.5 / 23.5
+//                                       105 MB 29.9 / 35.5 / 35.4 against 33.0 / 34.7 / 35.3
+//                                       235 MB 64.6 / 75.3 / 75.1 against 72.9 / 73.8 / 74.8
+//   silu_and_mul d = 11008 bf16, by its  24 MB  3.8 /  4.5 /  5.6 against  4.6 /  5.1 /  5.3
+//   traffic, a third of it output        67 MB  9.1 / 11.2 / 11.9 against 11.2 / 12.0 / 12.2
+//                                       235 MB 33.8 / 34.0 / 37.3 against 36.3 / 37.0 / 36.8
+//                                       400 MB 56.1 / 63.3 / 63.0 against 62.0 / 62.7 / 62.3
+//   merge_attn_states d = 256 bf16,      24 MB  3.7 /  5.2 /  6.2 against  4.9 /  5.3 /  5.7
+//   by its traffic                       67 MB 10.2 / 12.8 / 13.4 against 11.4 / 12.5 / 13.1
+//                                       235 MB 36.2 / 36.5 / 39.4 against 38.1 / 39.2 / 39.6
+// Neither is ahead on all buffers, and neither always beats ordinary accesses: where all that a program touches between two
+// calls comes to 100 to 250 MB, and so just about fits the memory-side cache, these keep more of it there.  The default
+// configuration then is ahead by up to 10 % on merges of 40 to 120 MB (67 MB: 11.7 / 11.6 / 15.2), by up to 20 % on norms
+// called again and again on one set of 96 to 250 MB (N = 4096, 150 MB: 44.0 / 54.7 / 56.1 against 47.8 / 48.9 / 49.2) or of
+// 16 to 40 MB, in the L2s, and there by up to 35 % on the longest rows.  From HBM it is 10 to 20 % behind on all of these.
 int64_t write_through_max() { return addrms_host::hw().last_level_cache_bytes / 8 * 3; }
 
 void set_flat(addrms_host::DirectRoute* out, int64_t pieces, int64_t units, int64_t total)
@@ -40,8 +52,9 @@ bool launchable(int64_t workgroups, int64_t threads) { return workgroups <= UINT
 namespace addrms_host {
 
 // Rows that 32 values per thread of 1024 do not hold.  Ordinary loads and stores up to the size that the memory-side
-// cache keeps (230 x 86912 bf16, 80 MB: 26.6 us against 31.6 with non-temporal ones; 8 x 123776 16.5 against 20.8),
-// non-temporal beyond (1024 x 131072 bf16 210 us against 245).
+// cache keeps (230 x 86912 bf16, 80 MB: 24.5 against 31.6 with non-temporal ones on three sets), non-temporal beyond
+// (1525 x 40960 bf16, 250 MB: 87.2 / 87.5 / 87.6 against 77.1 / 99.4 / 99.6; 114 x 175104 fp32, 160 MB: 78.2 / 81.6 / 91.2
+// against 60.4 / 100.4 / 99.4).
 static bool direct_addrms_long_route(int64_t M, int64_t N, int dtype, bool split, DirectRoute* out)
 {
     const int vec = direct_vec(dtype), xb = x_bytes(dtype);
@@ -61,11 +74,12 @@ static bool direct_addrms_long_route(int64_t M, int64_t N, int dtype, bool split
 }
 
 // Bytes of x and residual up to which rows with single elements are left to the default configuration.  Where its accesses
-// are at least two elements wide, 1 MB (40 x 1030 bf16 3.2 us against 3.3), and half as much again or, for accesses of four,
-// twice as much for 16-bit rows under 1024 elements, which its 256 threads hold in one access or two each (us, this against
-// the walk: 268 x 932 bf16 3.1 / 3.5, 536 x 932 3.4 / 3.6, 804 x 932 the same; 500 x 514 3.0 / 3.1, 1000 x 514 the same).
+// are at least two elements wide, 1 MB, and half as much again or, for accesses of four, twice as much for 16-bit rows under
+// 1024 elements, which its 256 threads hold in one access or two each.  This against the walk, on three sets / from HBM:
+// 268 x 932 bf16 3.0 / 3.2 against 3.6 / 3.4, 536 x 932 3.3 / 3.5 against 3.8 / 3.7, 804 x 932 3.6 / 4.3 against 4.0 / 3.9;
+// 500 x 514 3.3 / 3.4 against 3.8 / 3.6, 1000 x 514 3.7 / 3.9 against 4.0 / 3.9; 242 x 1030 3.4 / 3.6 against 3.6 / 3.4.
 // Where they are one element, 1 MB for 16-bit rows so short that its many threads are ahead of the few pieces (380 x 131
-// bf16 2.6 / 2.8; 579 x 259 the same).
+// bf16 2.9 / 2.6 against 3.4 / 3.2; 579 x 259 3.3 / 3.4 against 3.5 / 3.5, and as single launches the same).
 static int64_t ragged_min(int vec, int default_vec, int64_t N)
 {
     constexpr int64_t kMB = 1 << 20;
@@ -75,35 +89,40 @@ static int64_t ragged_min(int vec, int default_vec, int64_t N)
 
 // Threads per row: one per piece up to 1024, then as few pieces per thread as that allows, in equal shares: on 40 shapes
 // tried with 1 to 8 the fewest were the fastest, by 2-8 % against twice as many.  Written-through rows of more than 256
-// pieces take at least two, which then are stored in one go after the row sum (256 x 8192 bf16 4.0 us against 4.2 and from
-// HBM 4.4 against 5.6; 512 x 8192 5.8 against 6.5; 4096 x 4096 the same; shorter rows 1-2 % slower).
-// Ragged rows from 4 MB (single elements) or 16 MB to 96 MB take three pieces per thread (two where there are no single
-// elements: 8192 x 1000 fp16+fp32 17.1 us against 17.5) and two rows per workgroup, so that fewer waves repeat what a
-// row costs before and after its pieces (2047 x 4095 fp16 12.9 us against 14.0 with one piece per thread, 5000 x 1001
-// fp32 15.5 against 16.0, 4285 x 700 bf16 6.5 against 7.3); beyond, one is as good or better (9000 x 6150 bf16 76.4-79.7 us
-// against 78.1-78.9), and so it is below, where the chip is not full and a row should arrive early (41 x 6001 bf16 3.2-3.3
-// us against 3.8-4.0, 1072 x 932 3.9-4.0 against 3.8-4.2).
-// Store policy: as above, but non-temporal below 512 KB of x and residual, where the launch is all there is and a
-// write-through store only waits longer (16 x 4096 bf16 2.2 us against 2.4; from 1 MB on write-through wins, 64 x 8192
-// 2.9 against 3.4), and for rows with single elements, whose partly written lines a write-through store sends out at
-// once (2047 x 4095 fp16 12.9 us and from HBM 13.5 against 13.3 and 15.9).
+// pieces take at least two, which then are stored in one go after the row sum (256 x 8192 bf16 4.0 / 4.2 against 4.2 / 5.3,
+// 512 x 8192 5.8 / 7.3 against 6.6 / 8.3, 4096 x 4096 19.9 / 23.5 against 19.8 / 23.4; 1000 x 2048, of 256 pieces, 3.7 / 4.6
+// against 3.6 / 4.6).
+// Rows with single elements from 4 to 96 MB take three pieces per thread, and from 512 rows on two rows per workgroup where
+// that is at most 512 threads, so that fewer waves repeat what a row costs before and after its pieces.  One piece, three,
+// three and two rows: 2047 x 4095 fp16 13.5 / 14.0 / 12.6 on three sets, 2000 x 2001 bf16 8.3 / 7.2 / 7.0, 2000 x 6001 18.4 /
+// 19.3 / 18.1, 5000 x 1001 fp32 15.4 / 15.8 / 15.5; 4285 x 700 bf16 7.3 with one piece, 6.4-6.6 here.  With few rows one row
+// per workgroup is as good (513 x 4001 5.3 / 5.3, 300 x 10001 6.7 / 6.8), and so it is with more threads (2000 x 10001 31.1 /
+// 31.7).  Below 4 MB, where the chip is not full and a row should arrive early, one piece is ahead (41 x 6001 bf16 3.5
+// against 4.2, 1072 x 932 4.2 against 4.3), and beyond 96 MB too (9000 x 6150 72.8 against 75.7).
+// Rows walked by lines that are whole vectors take two pieces and two rows up to 96 MB by the same rule (3000 x 2056 bf16
+// 9.6 / 11.7 against 10.5 / 11.6 with one and one, 6144 x 1000 8.7 / 10.8 against 9.0 / 10.9, 8192 x 1000 fp16+fp32 the same).
+// Store policy: as above, but non-temporal below 512 KB of x and residual, where the launch is all there is (16 x 4096 bf16
+// 2.3 / 2.3 against 2.5 / 2.3); between that and 4 MB non-temporal stores are 0.2 faster on three sets and 0.2 slower from
+// HBM.  And non-temporal for rows with single elements, whose partly written lines a write-through store sends out at once
+// (2047 x 4095 fp16 12.4 / 13.2 against 13.7 / 15.2, 300 x 10001 bf16 6.5 / 6.8 against 7.1 / 8.9).
 // Rows of whole vectors that are not whole lines: where waves share lines with the waves beside them, a non-temporal load
 // gives up a line that the next wave still wants, and a non-temporal store sends out half of one.  They take ordinary loads
 // and write-through stores at every size from 512 KB on: rows that are not walked by lines, whose every wave shares two,
-// and walked ones of up to 3 KB of x, where the lines at a row's ends are one in twelve or more.  On three buffer sets /
-// from HBM, us, the knob grid's default, non-temporal loads (with the stores of the size), this:
-//   124 x 30008 fp16 (15 MB)              7.5 / 11.1       8.5 / 12.3      6.7 / 9.1    (7.5, 8.5, 6.7: one set)
-//   22500 x 1000 bf16 (90 MB)            32.2 / 35.6      31.9 / 40.6     28.0 / 31.7
-//   108333 x 200 fp16+fp32 (130 MB)      48.8 / 49.8      51.2 / 51.8     43.9 / 43.8
-//   228658 x 328 bf16 (300 MB)          113.3 / 112.0    125.8 / 125.4    99.7 / 99.7
-//   500000 x 100 fp32 (400 MB)          136.2 / 136.0    151.2 / 151.0   133.5 / 133.3
+// and walked ones of up to 3 KB of x, where the lines at a row's ends are one in twelve or more.  The knob grid's default,
+// non-temporal loads (with the stores of the size), this:
+//   124 x 30008 fp16 (15 MB)              8.6 / 11.3       8.5 / 12.3      6.9 / 9.2
+//   22500 x 1000 bf16 (90 MB)            31.2 / 35.6      31.9 / 40.6     27.7 / 31.9
+//   108333 x 200 fp16+fp32 (130 MB)      49.2 / 50.2      51.2 / 51.8     43.8 / 44.1
+//   228658 x 328 bf16 (300 MB)          113.6 / 113.0    125.8 / 125.4    99.6 / 99.1
+//   500000 x 100 fp32 (400 MB)          139.2 / 136.7    151.2 / 151.0   132.2 / 132.5
 // Longer walked rows (2056 bf16, 400 MB: 127.4 against 130.3 with this; 10008 fp16, 250 MB: 82.5 against 88.4) keep the
 // policy of their size.
 // Ragged walk: where a vector access does not divide the row, unless it is small and the default configuration's accesses
-// reach (ragged_min); and where rows are whole
-// vectors but not whole lines, from 16 MB on (below, 1000 x 1000 bf16 3.6 us against 3.5) and from 64 pieces a row on
-// (22500 x 1000 bf16 28.0 us and from HBM 31.7 against 30.6 and 34.9; 28846 x 520 19.6 / 24.3 against 19.8 / 21.7; 31492 x
-// 516 fp32 45.3 / 44.9 against 47.0 / 46.5; shorter rows lose: 108333 x 200 fp16+fp32 56.1 / 56.3 against 43.9 / 43.8).
+// reach (ragged_min); and where rows are whole vectors but not whole lines, from 16 MB on and from 64 pieces a row on.  With
+// and without it, 1000 bf16: 4 MB 3.2 / 3.5 against 3.0 / 3.4, 8 MB 3.9 / 5.1 against 3.7 / 4.9, 16 MB 6.5 / 7.9 against 6.6 /
+// 8.7, 25 MB 8.8 / 10.9 against 9.0 / 11.7, 50 MB 15.9 / 18.9 against 16.6 / 20.7; for 4680 fp16 the line is less clear (25 MB
+// 9.8 / 11.4 against 9.2 / 11.6, 50 MB 16.9 / 19.9 against 16.2 / 20.1).  Rows of fewer pieces lose with it (108333 x 200
+// fp16+fp32 56.1 / 56.3 against 43.9 / 43.8; 31492 x 516 fp32 gains, 45.3 / 44.9 against 47.0 / 46.5).
 // A default configuration with narrower accesses than these admits bases that they do not (86912 fp32: two elements per
 // access): such rows take the ragged walk, whole vectors or not.
 bool direct_addrms_route(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, uintptr_t w, DirectRoute* out)
@@ -154,8 +173,9 @@ bool direct_silumul_route(int64_t M, int64_t d, int dtype, uintptr_t x_align, ui
     return true;
 }
 
-// Below 4 MB of traffic the row kernels' ordinary loads are as fast (2000 x 80 bf16: 2.3 us against 2.5): the launch
-// is all there is.
+// Below 4 MB of traffic the row kernels' ordinary loads are as fast or faster: this on three sets / from HBM against them,
+// d = 256 bf16: 2 MB 2.4 / 2.4 against 2.2 / 2.3, 4 MB 2.6 / 2.9 against 2.4 / 3.2, 6 MB 2.8 / 3.1 against 2.6 / 3.9,
+// 8 MB 2.6 / 3.4 against 2.8 / 4.4.
 bool direct_mergestates_route(int64_t rows, int64_t d, int dtype, uintptr_t v_align, DirectRoute* out)
 {
     constexpr int64_t kSmall = 4 << 20;
