@@ -163,11 +163,11 @@ def check_norm(M, N, dtype, off=0, special=None):
     B.addrms_run(x, r, w, 1e-6, M, N, dtype)
     torch.cuda.synchronize()
     # what is compared must be able to differ: y finite, and zero only where a sum of the inputs or a weight happens to be
-    # (16-bit normals: one in a few hundred at most)
+    # (16-bit normals: one in a few hundred, so half of even the shortest rows, of 8 elements, is one row in 10^8)
     plain = xw.view(M, N)
     if special:
         plain = plain[[row for row in range(M) if row not in {s[0] for s in special}]]
-    assert bool(torch.isfinite(plain).all()) and bool(((plain != 0).float().mean(dim=1) > 0.95).all())
+    assert bool(torch.isfinite(plain).all()) and bool(((plain != 0).float().mean(dim=1) > 0.5).all())
     assert torch.equal(bits(r), bits(rw)) and torch.equal(bits(x), bits(xw)) and xok() and rok()
 
 
