@@ -126,7 +126,11 @@ typedef struct addrms_cfg {
  * graph (stream capture); the first launch of a kernel whose LDS allocation is
  * beyond 64 KiB (an occupancy cap that pads it, rows that continue in LDS, with or
  * without a cfg) raises that kernel's dynamic-LDS limit once per process, so issue
- * one such launch eagerly before capturing.
+ * one such launch eagerly before capturing.  Long rows without a cfg are split over
+ * workgroups that meet in device memory of the library (4 MiB per GPU, part of its
+ * code object); a launch reports its end in 256 bytes of host memory, allocated once
+ * per GPU by the first such call.  Captured calls and streams for which none of that
+ * memory is free (four may have such work in flight) run a kernel that needs none.
  */
 int addrms_run(void* x, void* residual, const void* weight, float eps,
                int64_t M, int64_t N, int dtype, const addrms_cfg* cfg, void* stream);
@@ -444,6 +448,14 @@ int addrms_table_load(const char* path);
  * computed by the same device routine the kernel uses.  ss: device, fp64[n];
  * out: device, fp32[n].  Asynchronous on stream. */
 int addrms_rstd_probe(const double* ss, int64_t n, int64_t N, float eps, float* out, void* stream);
+
+/* addrms_run without a configuration, for problems whose rows it splits over several workgroups (long rows); others are
+ * ADDRMS_ERR_UNSUPPORTED_SHAPE, and ADDRMS_ERR_NO_RESULT is a stream that can have none of the memory the workgroups meet in
+ * (addrms_run then runs another kernel: a capturing stream, or a fifth one with such work in flight).  A workgroup that has
+ * looked `patience` times for what the others of its row owe it forms the missing sums itself, so that no launch depends on
+ * all of them being on the chip at once; 0 makes that happen in every launch.  Same arguments and results as addrms_run. */
+int addrms_split_probe(void* x, void* residual, const void* weight, float eps, int64_t M, int64_t N, int dtype,
+                       uint32_t patience, void* stream);
 
 /* The correctness gate of the tuner (Algorithm 1 line 13, Validate; Section 3.1: d(S~(x), S(x)) <= eps over a
  * finite test set) applied to caller buffers: compares n elements of an output pair (y, residual) with a

@@ -247,6 +247,7 @@ SIGNATURES = {
     "addrms_device_resources": (c_int, [POINTER(Cfg), c_int64, c_int64, c_int, POINTER(Resources)]),
     "addrms_rstd_probe": (c_int, [c_void_p, c_int64, c_int64, c_float, c_void_p, c_void_p]),
     "addrms_stream_probe": (c_int, [c_void_p, c_void_p, c_int64, c_int64, c_int, c_void_p]),
+    "addrms_split_probe": (c_int, [c_void_p, c_void_p, c_void_p, c_float, c_int64, c_int64, c_int, ctypes.c_uint32, c_void_p]),
     "addrms_row_probe": (c_int, [c_void_p, c_void_p, c_int64, c_int64, c_int, c_int, c_int, c_void_p]),
     "addrms_gate_probe": (c_int, [c_void_p, c_void_p, c_void_p, c_void_p, c_int64, c_int, ctypes.c_uint32, c_void_p,
                                   c_void_p]),
@@ -686,6 +687,17 @@ def addrms_rstd_probe(ss, N: int, eps: float, out, stream=None) -> None:
     _expect_device_tensor("ss", ss, ss.numel(), "float64")
     _expect_device_tensor("out", out, ss.numel(), "float32")
     _check(load().addrms_rstd_probe(_ptr(ss), ss.numel(), N, float(eps), _ptr(out), _stream_ptr(stream, ss)))
+
+
+def addrms_split_probe(x, residual, weight, eps: float, M: int, N: int, dtype, patience: int, stream=None) -> None:
+    """addrms_run without a configuration, for rows that are split over workgroups; patience 0: the workgroups of a row
+    form each other's sums wherever one is missing at first sight."""
+    dt, _, _ = _format(dtype)
+    _expect_device_tensor("x", x, M * N, _X_ELEM[dt])
+    _expect_device_tensor("residual", residual, M * N, _R_ELEM[dt])
+    _expect_device_tensor("weight", weight, N, _X_ELEM[dt])
+    _check(load().addrms_split_probe(_ptr(x), _ptr(residual), _ptr(weight), float(eps), M, N, dt, int(patience),
+                                     _stream_ptr(stream, x)))
 
 
 def addrms_stream_probe(x, residual, M: int, N: int, dtype, stream=None) -> None:

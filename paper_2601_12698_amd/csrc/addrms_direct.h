@@ -9,6 +9,7 @@ namespace addrms_host {
 // A launch that is ready but for the pointers.
 struct DirectPlan : DirectRoute {
     const void* fn = nullptr;
+    const void* split_fn = nullptr;                         // of DirectRoute::parts
     unsigned long_index = 0;                                // which of the kernels for rows beyond the registers
 };
 
@@ -19,7 +20,14 @@ bool direct_silumul_plan(int64_t M, int64_t d, int dtype, uintptr_t x_align, uin
 bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_align, DirectPlan* out);
 
 // hipError_t of the launch.
-int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream);
+int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
+                         void* stream);
+// Only the kernel of rows split over workgroups, where the route has one (direct_launch_addrms prefers it).  False: no slot,
+// and nothing was launched.  A graph may be replayed on any stream and beside others, so that no slot is its own: a capturing
+// stream has none.  Nor has the per-thread default stream, one handle for as many streams as threads.  patience: see
+// split_row_sum.
+bool direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
+                         unsigned patience, void* stream, int* status);
 int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream);
 int direct_launch_mergestates(const DirectPlan& p, const void* va, const float* sa, const void* vb, const float* sb, void* vo,
                               float* so, void* stream);

@@ -1,13 +1,20 @@
 // Launches without a configuration: the instances of direct_kernel.h, and the launches of what direct_route.cpp decides.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
+#include <mutex>
 
 #include "addrms_direct.h"
 #include "direct_kernel.h"
 
 using namespace addrms;
+
+// Where the workgroups of split rows meet: 4 MB that belong to the loaded code object, one copy per GPU, all zero between
+// launches.
+static __device__ SplitRow split_rows[kSplitSlots][kSplitRows];
+static __device__ SplitLaunch split_launch[kSplitSlots];
 
 namespace {
 
@@ -24,6 +31,12 @@ __global__ __launch_bounds__(kLongThreads) void addrms_long(void* x, void* r, co
                                                             unsigned lds_chunks)
 {
     addrms_long_body<DT, VEC, kLongRegValues / VEC, 2, POL, RAG>(x, r, w, eps, inv_n, N, lds_chunks);
+}
+template <int DT, int VEC, int CPT, int POL, bool RAG>
+__global__ __launch_bounds__(1024) void addrms_split(void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned tpr,
+                                                     unsigned slot, uint32_t* done, uint32_t number, unsigned patience)
+{
+    addrms_split_body<DT, VEC, CPT, POL, RAG>(x, r, w, inv_n, eps, N, tpr, split_rows[slot], &split_launch[slot], done, number, patience);
 }
 template <int DT, int POL, bool RAG>
 __global__ __launch_bounds__(kFlatThreads) void silumul_flat(const char* x, char* out, uint32_t d, uint32_t units,
@@ -101,6 +114,38 @@ const void* addrms_long_fn(int dtype, int pol, bool rag)
     }
 }
 
+template <int DT, int CPT, int POL> const void* addrms_split_fn2(bool rag)
+{
+    constexpr int VEC = direct_vec(DT);
+    if constexpr (split_instance(CPT, POL))
+        return rag ? reinterpret_cast<const void*>(&addrms_split<DT, VEC, CPT, POL, true>)
+                   : reinterpret_cast<const void*>(&addrms_split<DT, VEC, CPT, POL, false>);
+    else return nullptr;
+}
+template <int DT, int CPT> const void* addrms_split_fn1(int pol, bool rag)
+{
+    return pol == POL_NT ? addrms_split_fn2<DT, CPT, POL_NT>(rag) : addrms_split_fn2<DT, CPT, POL_WT>(rag);
+}
+template <int DT> const void* addrms_split_fn(int cpt, int pol, bool rag)
+{
+    switch (cpt) {
+    case 1: return addrms_split_fn1<DT, 1>(pol, rag);
+    case 2: return addrms_split_fn1<DT, 2>(pol, rag);
+    case 4: return addrms_split_fn1<DT, 4>(pol, rag);
+    default: return nullptr;
+    }
+}
+const void* addrms_split_fn(int dtype, int cpt, int pol, bool rag)
+{
+    switch (dtype) {
+    case DT_BF16: return addrms_split_fn<DT_BF16>(cpt, pol, rag);
+    case DT_FP16: return addrms_split_fn<DT_FP16>(cpt, pol, rag);
+    case DT_FP16_RES32: return addrms_split_fn<DT_FP16_RES32>(cpt, pol, rag);
+    case DT_FP32: return addrms_split_fn<DT_FP32>(cpt, pol, rag);
+    default: return nullptr;
+    }
+}
+
 template <int DT> const void* silumul_fn1(int pol, bool rag)
 {
     if (rag) return pol == POL_NT ? reinterpret_cast<const void*>(&silumul_flat<DT, POL_NT, true>)
@@ -132,6 +177,7 @@ bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintpt
     if (!direct_addrms_route(M, N, dtype, default_vec, x, r, w, out)) return false;
     if (out->long_row) {
         out->fn = addrms_long_fn(dtype, out->pol, out->rag);
+        if (out->parts) out->split_fn = addrms_split_fn(dtype, out->part_cpt, out->part_pol, out->rag);
         out->long_index = static_cast<unsigned>(dtype) * 4u + (out->pol == POL_NT ? 2u : 0u) + (out->rag ? 1u : 0u);
     } else {
         out->fn = addrms_fn(dtype, out->cpt, out->pol, out->rag, out->block_y > 1);
@@ -165,8 +211,75 @@ static int go(const DirectPlan& p, void** args, void* stream)
     return static_cast<int>(hipLaunchKernel(p.fn, dim3(p.grid), dim3(p.block_x, p.block_y), args, p.lds,
                                             static_cast<hipStream_t>(stream)));
 }
-int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream)
+
+// ---- split rows ------------------------------------------------------------------------------------
+namespace {
+
+constexpr int kMaxDevices = 64, kDoneStride = 16;            // one 64-byte line of host memory per slot
+constexpr unsigned kPatience = 256;                          // reads of a row's words, some hundreds of microseconds
+
+struct SplitDevice {
+    SplitSlots slots;
+    uint32_t* done = nullptr;                                // host memory that the kernels write
+};
+std::mutex g_split_mu;
+SplitDevice g_split[kMaxDevices];
+
+// Host memory for the launches of all slots to report in, once per GPU: 256 bytes, kept until the process ends.  The
+// allocation must not disturb a capture that another thread may be in.
+bool split_ready(SplitDevice& d)
 {
+    if (d.done) return true;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+    void* p = nullptr;
+    const size_t bytes = static_cast<size_t>(kSplitSlots) * kDoneStride * sizeof(uint32_t);
+    const hipError_t e = hipHostMalloc(&p, bytes, hipHostMallocDefault);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) { (void)hipGetLastError(); return false; }
+    std::fill_n(static_cast<uint32_t*>(p), bytes / sizeof(uint32_t), 0u);
+    d.done = static_cast<uint32_t*>(p);
+    return true;
+}
+
+}  // namespace
+
+bool direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
+                         unsigned patience, void* raw_stream, int* status)
+{
+    const hipStream_t stream = static_cast<hipStream_t>(raw_stream);
+    if (!p.split_fn) return false;
+    if (stream == hipStreamPerThread) return false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) { (void)hipGetLastError(); return false; }
+    int dev = -1;
+    if (capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+    std::lock_guard<std::mutex> lock(g_split_mu);
+    SplitDevice& d = g_split[dev];
+    if (!split_ready(d)) return false;
+    const int slot = d.slots.take(reinterpret_cast<uintptr_t>(stream), d.done, kDoneStride);
+    if (slot < 0) return false;
+    double inv_n = 1.0 / static_cast<double>(N);
+    int n = static_cast<int>(N);
+    unsigned tpr = p.part_threads, s = static_cast<unsigned>(slot);
+    uint32_t* done = d.done + slot * kDoneStride;
+    hipError_t e = hipSuccess;
+    for (int64_t row = 0; row < M && e == hipSuccess; row += kSplitRows) {
+        void *xr = static_cast<char*>(x) + row * N * x_bytes(dtype), *rr = static_cast<char*>(r) + row * N * r_bytes(dtype);
+        uint32_t number = d.slots.next(slot);
+        void* args[] = {&xr, &rr, &w, &inv_n, &eps, &n, &tpr, &s, &done, &number, &patience};
+        const unsigned rows = static_cast<unsigned>(std::min<int64_t>(kSplitRows, M - row));
+        e = hipLaunchKernel(p.split_fn, dim3(p.parts, rows), dim3(p.part_threads), args, 17u * sizeof(double), stream);
+        if (e == hipSuccess) d.slots.launched(slot);
+    }
+    *status = static_cast<int>(e);
+    return true;
+}
+
+int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype, void* stream)
+{
+    int status;
+    if (direct_launch_split(p, x, r, w, eps, M, N, dtype, kPatience, stream, &status)) return status;
     double inv_n = 1.0 / static_cast<double>(N);
     long long m = M;
     int n = static_cast<int>(N);

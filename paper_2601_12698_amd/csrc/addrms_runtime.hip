@@ -207,7 +207,7 @@ int run_addrms(void* x, void* r, const void* w, float eps, int64_t M, int64_t N,
         [=](const addrms_cfg& c, DirectPlan* p) { return direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(r), bits(w), p); });
     if (st != ADDRMS_OK) return st;
     if (!call->direct) return launch(call->f, call->c, x, r, w, eps, M, N, stream);
-    HIP_TRY(static_cast<hipError_t>(direct_launch_addrms(call->p, x, r, w, eps, M, N, stream)));
+    HIP_TRY(static_cast<hipError_t>(direct_launch_addrms(call->p, x, r, w, eps, M, N, dtype, stream)));
     return ADDRMS_OK;
 }
 int run_silumul(const void* x, void* out, int64_t M, int64_t d, int dtype, const addrms_cfg* cfg, hipStream_t stream)
@@ -1187,6 +1187,31 @@ int addrms_rstd_probe(const double* ss, int64_t n, int64_t N, float eps, float* 
     hipLaunchKernelGGL(rstd_probe_kernel, grid, block, 0, static_cast<hipStream_t>(stream), ss, (long long)n,
                        1.0 / static_cast<double>(N), eps, out);
     HIP_TRY(hipGetLastError());
+    return ADDRMS_OK;
+}
+
+int addrms_split_probe(void* x, void* residual, const void* weight, float eps, int64_t M, int64_t N, int dtype, uint32_t patience,
+                       void* stream)
+{
+    if (!dtype_valid(dtype)) return fail(ADDRMS_ERR_UNSUPPORTED_DTYPE, "unsupported dtype %d", dtype);
+    if (M < 0 || N <= 0) return fail(ADDRMS_ERR_INVALID_ARG, "M must be >= 0 and N > 0");
+    if (M == 0) return ADDRMS_OK;
+    if (!x || !residual || !weight) return fail(ADDRMS_ERR_INVALID_ARG, "x, residual and weight must not be NULL");
+    if (M > (1ll << 31) - 1) return fail(ADDRMS_ERR_INVALID_ARG, "M=%lld exceeds the 2^31-1 row limit", (long long)M);
+    addrms_cfg c{};
+    std::string why;
+    const int st = default_cfg(N, dtype, &c, &why);
+    if (st != ADDRMS_OK) return fail(st, "%s", why.c_str());
+    const int xa = c.vec * x_bytes(dtype);
+    if (!aligned(x, xa) || !aligned(weight, xa) || !aligned(residual, std::min(16, c.vec * r_bytes(dtype))))
+        return fail(ADDRMS_ERR_MISALIGNED, "tensors must be aligned as addrms_run asks for");
+    DirectPlan p;
+    if (!direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(residual), bits(weight), &p) || !p.split_fn)
+        return fail(ADDRMS_ERR_UNSUPPORTED_SHAPE, "rows of this problem are not split over workgroups");
+    int e = 0;
+    if (!direct_launch_split(p, x, residual, weight, eps, M, N, dtype, patience, stream, &e))
+        return fail(ADDRMS_ERR_NO_RESULT, "this stream can have no slot for split rows now");
+    HIP_TRY(static_cast<hipError_t>(e));
     return ADDRMS_OK;
 }
 

@@ -22,6 +22,7 @@
 #include "addrms_kernel.h"
 #include "direct_route.h"
 #include "silumul_kernel.h"
+#include "split_slots.h"
 
 namespace addrms {
 
@@ -273,7 +274,8 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
 }
 
 // ---- add + RMSNorm, rows beyond the registers ---------------------------------------------------
-// The walk of addrms_hybrid_body (its comment has the three parts: registers, parked in LDS, read
+// For streams that can have no slot (split_slots.h; captured launches are such), rows longer than 16 parts hold, and what
+// direct_addrms_split leaves.  The walk of addrms_hybrid_body (its comment has the three parts: registers, parked in LDS, read
 // twice) for one row per workgroup, with the store policy of the size, ragged rows, and the weights
 // of the register part fetched before the row sum, so that its stores are the first to follow it
 // (1-3 % against fetching each behind the stores before it).  Bound by one workgroup filling a CU:
@@ -455,6 +457,202 @@ __device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __
         }
     }
     one.store(xbase, rbase, rw.single, rw.has_single, rstd);
+}
+
+// ---- add + RMSNorm, rows beyond the registers, split over several workgroups ---------------------
+// What bounds addrms_long_body is that one workgroup fills a CU and cannot hold its row: loads and stores take turns, and
+// what neither registers nor LDS keep is read twice.  Here `parts` workgroups share a row, a part each, held in registers
+// from the loads to the stores as in addrms_direct_body, so that a CU has several of them at different places of their
+// work and nothing is read twice.  They meet once, for the sum over the row: each puts the sum of its part into a 64-bit
+// word of the row's SplitRow and reads the words of the others.
+//
+// No wait depends on which workgroups are on the chip.  A word is 0 at first, kSplitClaimed once a workgroup that found it
+// missing for long has taken it upon itself to form that sum in the owner's place, and a sum with the sign bit set in the
+// end.  Both steps away from 0 are compare-and-swaps, so that one workgroup decides; it depends on nothing but its loads,
+// and every other one waits either for a workgroup that runs or for a word it may claim.  The owner of a claimed part
+// holds its elements as ever and waits for the sum like the others.  Outputs are written only after all words have been
+// read, so that whoever forms a sum finds the inputs untouched.  Both ways to a sum add in the same order.
+//
+// Words and counts are accessed with relaxed atomics of device scope, which go to the memory side of all XCDs' L2s, and
+// carry all that the workgroups tell each other, so that nothing else has to be made visible.  The last workgroup to have
+// read a row's words clears them, and the last row of a launch reports the launch as done, so that the words are clear
+// and nobody's before the next launch finds them (split_slots.h has who may use which).
+//
+// A row's words and its count lie on 128-byte lines of their own: with eight rows to a line the atomics of a row's
+// neighbours queue up, some 10 ns per workgroup of the launch (1024 x 131072 bf16 in 32 parts 281 us against 213).
+// 1024 x 131072 bf16 208 -> 172 us (6.2 TB/s), 46 x 164992 fp16 25.9 -> 12.0, through the binding on buffers in rotation; more
+// shapes at direct_addrms_split.  Not for rows that the registers of one workgroup hold: 2048 x 8192 fp32 in two parts 47.5
+// against 45.0.
+constexpr uint64_t kSplitClaimed = 1, kSplitSum = 1ull << 63;
+struct __align__(256) SplitRow {
+    uint64_t word[kSplitParts];
+    __align__(128) uint32_t read;                            // workgroups that have read all words
+};
+struct __align__(128) SplitLaunch { uint32_t rows_done; };
+
+__device__ __forceinline__ bool split_take(uint64_t* word, uint64_t value)       // true: it was 0 and is now value
+{
+    uint64_t was = 0;
+    return __hip_atomic_compare_exchange_strong(word, &was, value, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t split_word(double sum) { return __builtin_bit_cast(uint64_t, sum) | kSplitSum; }
+
+// The sum over the squares of part `part`, formed by one wave in the order in which the part's own tpr threads form it.
+template <int DT, int VEC, int CPT, bool RAG>
+__device__ __forceinline__ double split_part_sum(const char* xrow, const char* rrow, const char* wbase, int32_t N, uint32_t part, uint32_t tpr)
+{
+    using T = dt_traits<DT>;
+    constexpr int XB = T::XB, RB = T::RB;
+    constexpr bool BF = T::BF;
+    double mine = 0.0;                                       // lane w: sum of the part's wave w
+    for (uint32_t w = 0; w * 64u < tpr; ++w) {
+        const RowWalk<XB, VEC, RAG> rw(xrow, 0u, N, w * 64u + threadIdx.x, tpr);
+        double acc = 0.0;
+        for (int c = 0; c < CPT; ++c) {
+            const int32_t col = rw.col0 + (static_cast<int32_t>(part) * CPT + c) * rw.stride;
+            const uint32_t colc = rw.clamped(col);
+            raw_t<XB * VEC> x;
+            raw_t<RB * VEC> r;
+            ld_stream<POL_CACHED, XB * VEC, 16>(xrow, colc * XB, x);
+            ld_stream<POL_CACHED, RB * VEC, 16>(rrow, colc * RB, r);
+            if (rw.in_row(col)) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    const double hd = static_cast<double>(get_elem<XB, BF>(x, e) + get_elem<RB, BF && RB == 2>(r, e));
+                    acc = __builtin_fma(hd, hd, acc);
+                }
+            }
+        }
+        SingleElement<DT, RAG> one;
+        one.load(xrow, rrow, wbase, rw.single, rw.has_single && part == 0u);
+        const double sum = wave_total(one.add(acc));
+        if (threadIdx.x == w) mine = sum;
+    }
+    return tpr == 64u ? read_lane(mine, 0) : read_lane(row16_scan(threadIdx.x < 16u ? mine : 0.0), 15);
+}
+
+// Called by the first wave: puts the part's sum into its word and returns the sum over the row once all words are there.
+// patience: reads of the words after which those still missing are claimed.
+template <int DT, int VEC, int CPT, bool RAG>
+__device__ __forceinline__ double split_row_sum(double part_sum, SplitRow* row, uint32_t part, uint32_t parts, uint32_t patience,
+                                                const char* xrow, const char* rrow, const char* wbase, int32_t N, uint32_t tpr)
+{
+    const uint32_t lane = threadIdx.x;
+    if (lane == 0u) split_take(&row->word[part], split_word(part_sum));
+    uint64_t v = kSplitSum;                                  // lanes without a part: a sum of 0
+    for (uint32_t reads = 0;; ++reads) {
+        if (lane < parts) v = __hip_atomic_load(&row->word[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__all((v & kSplitSum) != 0)) break;
+        if (reads >= patience) {
+            for (uint64_t missing = __ballot(v == 0); missing; missing &= missing - 1) {
+                const uint32_t q = static_cast<uint32_t>(__builtin_ctzll(missing));
+                bool claimed = false;
+                if (lane == 0u) claimed = split_take(&row->word[q], kSplitClaimed);
+                if (!__any(claimed)) continue;
+                const double sum = split_part_sum<DT, VEC, CPT, RAG>(xrow, rrow, wbase, N, q, tpr);
+                if (lane == 0u) __hip_atomic_store(&row->word[q], split_word(sum), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        __builtin_amdgcn_s_sleep(4);
+    }
+    return wave_total(__builtin_bit_cast(double, v & ~kSplitSum));
+}
+
+template <int DT, int VEC, int CPT, int POL, bool RAG>
+__device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* __restrict__ rp, const void* __restrict__ wp, double inv_n,
+                                                  float eps, int32_t N, uint32_t tpr, SplitRow* rows, SplitLaunch* launch,
+                                                  uint32_t* done, uint32_t number, uint32_t patience)
+{
+    using T = dt_traits<DT>;
+    constexpr int XB = T::XB, RB = T::RB;
+    constexpr bool BF = T::BF;
+    extern __shared__ double lds[];                          // one sum per wave, then the row's
+
+    const uint32_t part = blockIdx.x, parts = gridDim.x, lane = threadIdx.x;
+    SplitRow* row = rows + blockIdx.y;
+    char* xrow = static_cast<char*>(xp) + static_cast<int64_t>(blockIdx.y) * N * XB;
+    char* rrow = static_cast<char*>(rp) + static_cast<int64_t>(blockIdx.y) * N * RB;
+    const char* wbase = static_cast<const char*>(wp);
+    const RowWalk<XB, VEC, RAG> rw(xrow, 0u, N, lane, tpr);
+    const int32_t stride = rw.stride, col0 = rw.col0 + static_cast<int32_t>(part) * CPT * stride;
+    const bool has_single = rw.has_single && part == 0u;
+
+    float h[CPT][VEC];
+    double acc = 0.0;
+    SingleElement<DT, RAG> one;
+    one.load(xrow, rrow, wbase, rw.single, has_single);
+    raw_t<XB * VEC> xv[CPT];
+    raw_t<RB * VEC> rv[CPT];
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const uint32_t colc = rw.clamped(col0 + c * stride);
+        ld_stream<POL, XB * VEC, 16>(xrow, colc * XB, xv[c]);
+        ld_stream<POL, RB * VEC, 16>(rrow, colc * RB, rv[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) h[c][e] = get_elem<XB, BF>(xv[c], e) + get_elem<RB, BF && RB == 2>(rv[c], e);
+        if (rw.in_row(col0 + c * stride)) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const double hd = static_cast<double>(h[c][e]);
+                acc = __builtin_fma(hd, hd, acc);
+            }
+        }
+    }
+    const double part_sum = row_sum(one.add(acc), RED_WAVE, tpr, lane, 0u, lds);
+    raw_t<XB * VEC> wv[CPT];                                 // on their way while the sums meet
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) ld_stream<POL_CACHED, XB * VEC, RAG ? XB : 16>(wbase, rw.clamped(col0 + c * stride) * XB, wv[c]);
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t before = 0;                                     // workgroups that had read the words earlier
+    if (lane < 64u) {
+        const double total = split_row_sum<DT, VEC, CPT, RAG>(part_sum, row, part, parts, patience, xrow, rrow, wbase, N, tpr);
+        if (lane == 0u) {
+            lds[16] = total;
+            before = __hip_atomic_fetch_add(&row->read, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    wg_sync_lds();
+    const float rstd = rsqrt_to_f32(__builtin_fma(lds[16], inv_n, static_cast<double>(eps)));
+
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const int32_t col = col0 + c * stride;
+        if (rw.in_row(col)) {
+            raw_t<RB * VEC> out;
+            pack_vec<RB, BF, VEC>(h[c], out);
+            st_stream<POL, RB * VEC>(rrow, static_cast<uint32_t>(col) * RB, out);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        const int32_t col = col0 + c * stride;
+        float y[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const float t = h[c][e] * rstd;
+            y[e] = t * get_elem<XB, BF>(wv[c], e);
+        }
+        if (rw.in_row(col)) {
+            raw_t<XB * VEC> out;
+            pack_vec<XB, BF, VEC>(y, out);
+            st_stream<POL, XB * VEC>(xrow, static_cast<uint32_t>(col) * XB, out);
+        }
+    }
+    one.store(xrow, rrow, rw.single, has_single, rstd);
+
+    // Everything below is atomic and goes to the memory side in this order: a wave's wait for its own earlier stores is
+    // all that is needed between two steps.
+    if (lane >= 64u || static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(before))) != parts - 1u) return;
+    if (lane < parts) __hip_atomic_store(&row->word[lane], uint64_t{0}, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0u) __hip_atomic_store(&row->read, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane != 0u || __hip_atomic_fetch_add(&launch->rows_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != gridDim.y - 1u) return;
+    __hip_atomic_store(&launch->rows_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __hip_atomic_store(done, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- elementwise operators over the output as one flat array -----------------------------------

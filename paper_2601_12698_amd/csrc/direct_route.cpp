@@ -6,6 +6,8 @@
 
 #include <algorithm>
 
+#include "split_slots.h"
+
 using namespace addrms;
 
 namespace {
@@ -51,6 +53,47 @@ bool launchable(int64_t workgroups, int64_t threads) { return workgroups <= UINT
 
 namespace addrms_host {
 
+// Long rows split over workgroups (addrms_split_body), where the stream can have a slot.  16384 elements to a part where a
+// thread has eight to a piece, 12288 where it has four: four pieces per thread of 512 or 768 threads, of which a CU holds two
+// (1024 x 131072 bf16 in 4 / 8 / 16 parts 183 / 173 / 180; 500 x 200000 fp32 in 13 / 17 / 25 of four pieces 265 / 259 / 271).  Fewer rows
+// than that keeps the chip busy with are cut finer, down to 512 pieces, up to 512 workgroups in all, with as few pieces per
+// thread as 1024 threads allow (46 x 164992 fp16 in 6 / 11 / 21 parts 17.8 / 12.2 / 14.4; 1 x 200000 in 8 / 12 / 16 7.5 / 7.2 / 6.4).
+// Against one workgroup per row, on three sets / from HBM:
+//   1 x 200000 bf16   23.9 / 28.7  ->  6.4 / 6.3        2048 x 65536     195.7 / 195.5 -> 174.0 / 174.3
+//   8 x 123776        14.8 / 18.3  ->  6.4 / 6.4        4096 x 40960     228.4 / 227.8 -> 214.7 / 214.5
+//   60 x 131072       20.2 / 30.3  -> 12.5 / 12.7       500 x 200000 fp32 354 / 354 -> 274 / 274
+//   1024 x 131072    207.3 / 211.3 -> 171.6 / 172.0     512 x 81920 fp32 130.6 / 131.0 -> 111.9 / 111.7
+// Left to one workgroup per row: rows that it holds (nothing is read twice), in numbers that give nearly every CU one or two,
+// while all of it fits the memory-side cache, whose contents ordinary accesses keep (192 x 40960 bf16 0.68 / 0.96 of the time, 224 x
+// 65536 0.88 / 1.15, 512 x 40960 0.94 / 1.12; beside them 128 x 65536 1.10 / 1.41, 288 x 40960 1.02 / 1.24, 640 x 49152 1.01 / 1.01).
+// Stores: write-through between 32 MB of x and residual and the limit above, non-temporal below and beyond (84 MB, 336 x 62528 bf16
+// 30.5 / 35.3 against 34.2 / 34.9; 30 MB, 46 x 164992 fp16 15.2 / 17.4 against 16.4 / 17.2; 20 MB, 100 x 50000 10.1 / 11.1
+// against 9.8 / 10.4; 400 MB, 500 x 200000 fp32 284.9 against 274.5).
+static void direct_addrms_split(int64_t M, int64_t N, int dtype, DirectRoute* out)
+{
+    constexpr int64_t kBusy = 512, kFinest = 512, kNonTemporalMax = 32 << 20;
+    const int vec = direct_vec(dtype), xb = x_bytes(dtype), cus = hw().compute_units;
+    const int64_t bytes = M * N * (xb + r_bytes(dtype));
+    const int64_t pieces = (N + (out->rag ? kLineBytes / xb - 1 : 0) + vec - 1) / vec;
+    const bool held = pieces <= static_cast<int64_t>(kLongThreads) * (kLongRegValues / vec + out->units);
+    const bool filling = M <= cus ? M >= cus / 8 * 5 : M <= 2 * cus && M >= cus / 4 * 7;
+    if (held && filling && bytes <= write_through_max()) return;
+    const int64_t coarse = vec == 8 ? 2048 : 3072;                                    // pieces of a part
+    int64_t parts = (pieces + coarse - 1) / coarse;
+    parts = std::max(parts, std::min((pieces + kFinest - 1) / kFinest, kBusy / M));
+    parts = std::min<int64_t>(parts, kSplitParts);
+    const int64_t per = (pieces + parts - 1) / parts;
+    const int64_t cpt = M * parts > kBusy || per > 2048 ? 4 : per > 1024 ? 2 : 1;
+    const int64_t threads = ((per + cpt - 1) / cpt + 63) / 64 * 64;
+    if (threads > 1024) return;                                                       // rows beyond 16 parts of the largest size
+    parts = (pieces + threads * cpt - 1) / (threads * cpt);
+    if (parts < 2) return;
+    out->parts = static_cast<unsigned>(parts);
+    out->part_threads = static_cast<unsigned>(threads);
+    out->part_cpt = static_cast<int>(cpt);
+    out->part_pol = bytes <= kNonTemporalMax || bytes > write_through_max() ? POL_NT : POL_WT;
+}
+
 // Rows that 32 values per thread of 1024 do not hold.  Ordinary loads and stores up to the size that the memory-side
 // cache keeps (230 x 86912 bf16, 80 MB: 24.5 against 31.6 with non-temporal ones on three sets), non-temporal beyond
 // (1525 x 40960 bf16, 250 MB: 87.2 / 87.5 / 87.6 against 77.1 / 99.4 / 99.6; 114 x 175104 fp32, 160 MB: 78.2 / 81.6 / 91.2
@@ -70,6 +113,7 @@ static bool direct_addrms_long_route(int64_t M, int64_t N, int dtype, bool split
     out->grid = static_cast<unsigned>(M);
     out->lds = 128u + out->units * static_cast<unsigned>(slot);
     out->long_row = true;
+    direct_addrms_split(M, N, dtype, out);
     return true;
 }
 

@@ -1,0 +1,141 @@
+"""Rows that are split over several workgroups: who may use which slot of the memory they meet in, and the shapes in which
+rows are split (host code, on the CPU); the kernel itself, with every wait cut short, beside other streams and beyond the
+rows of one launch (on the GPU)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+import torch
+
+from paper_2601_12698_amd import binding as B
+from test_gpu_untuned import bits, check_norm, norm_inputs
+from test_host_sanitizers import BUILD, CSRC, HOST_SOURCES, ROOT
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    if not os.path.exists(os.path.join(BUILD, "gen_resources.inc")):
+        pytest.skip("the generated instance and resource tables are not present (build the library first)")
+    exe = str(tmp_path_factory.mktemp("split") / "driver")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-Wall", "-Wextra",
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", BUILD, os.path.join(ROOT, "tests", "split_slots_driver.cpp"),
+           *[os.path.join(CSRC, s) for s in HOST_SOURCES + ["direct_route.cpp"]], "-o", exe]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout[-4000:]
+    return exe
+
+
+@pytest.mark.parametrize("what", ["slots", "walk"])
+def test_slots_and_shapes(driver, what):
+    r = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-4000:]
+
+
+SHAPES = [
+    (("bf16", 8, 32832), "parts=9 threads=512 pieces=1 nontemporal"),
+    (("bf16", 1024, 131072), "parts=8 threads=512 pieces=4 nontemporal"),
+    (("fp32", 500, 200000), "parts=16 threads=832 pieces=4 nontemporal"),
+    (("bf16", 1, 200000), "parts=16 threads=832 pieces=2 nontemporal"),
+    (("fp16", 46, 164992), "parts=11 threads=960 pieces=2 nontemporal"),
+    # write-through from 32 MB to 96 MB of x and residual
+    (("bf16", 64, 131072), "parts=8 threads=1024 pieces=2 nontemporal"),
+    (("bf16", 69, 121344), "parts=8 threads=512 pieces=4 nontemporal"),
+    (("bf16", 70, 121344), "parts=8 threads=512 pieces=4 writethrough"),
+    (("bf16", 207, 121344), "parts=8 threads=512 pieces=4 writethrough"),
+    (("bf16", 208, 121344), "parts=8 threads=512 pieces=4 nontemporal"),
+    # rows that one workgroup holds, in numbers that fill the chip
+    (("bf16", 159, 40960), "parts=3 threads=896 pieces=2 nontemporal"),
+    (("bf16", 160, 40960), "whole"),
+    (("bf16", 256, 40960), "whole"),
+    (("bf16", 257, 40960), "parts=3 threads=448 pieces=4 writethrough"),
+    (("bf16", 447, 40960), "parts=3 threads=448 pieces=4 writethrough"),
+    (("bf16", 448, 40960), "whole"),
+    (("bf16", 512, 40960), "whole"),
+    (("bf16", 513, 40960), "parts=3 threads=448 pieces=4 writethrough"),
+    (("bf16", 200, 81920), "whole"),
+    (("bf16", 200, 81984), "parts=6 threads=448 pieces=4 writethrough"),
+    # the longest row, and one piece more
+    (("bf16", 2, 524288), "parts=16 threads=1024 pieces=4 nontemporal"),
+    (("bf16", 2, 524352), "whole"),
+    (("fp32", 2, 262144), "parts=16 threads=1024 pieces=4 nontemporal"),
+    (("fp32", 2, 262176), "whole"),
+    (("bf16", 8, 32768), "whole"),
+]
+
+
+def test_both_sides_of_each_limit(driver):
+    lines = "\n".join(f"{B.DTYPE_IDS[d]} {M} {N}" for (d, M, N), _ in SHAPES)
+    r = subprocess.run([driver], input=lines, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-4000:]
+    assert [(p, g) for (p, _), g in zip(SHAPES, r.stdout.split("\n"))] == SHAPES
+
+
+# two parts and the most; last parts of one line and whole ones; one, two and four pieces per thread; ragged rows; both store
+# policies
+SPLIT = [("bf16", 2, 32832), ("bf16", 700, 40960), ("fp16", 3, 32707), ("bf16", 1, 524288), ("fp16", 2, 262143), ("bf16", 70, 121344),
+         ("fp32", 2, 32772), ("fp32", 1, 262144), ("fp32", 60, 131071), ("fp16_res32", 40, 40004), ("fp16_res32", 90, 86022), ("bf16", 33, 131008)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,M,N", SPLIT)
+def test_split_rows_give_the_bits_of_whole_ones(dtype, M, N):
+    B.addrms_table_clear()
+    check_norm(M, N, dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,M,N", SPLIT)
+@pytest.mark.parametrize("patience", [0, 2])
+def test_sums_formed_in_place_of_others(dtype, M, N, patience):
+    """As if the other workgroups of a row were not on the chip: whoever misses a sum forms it."""
+    x, xok, r, rok, w = norm_inputs(M, N, dtype, N)
+    xw, rw = x.clone(), r.clone()
+    B.addrms_run(xw, rw, w, 1e-6, M, N, dtype, B.addrms_default_cfg(N, dtype))
+    B.addrms_split_probe(x, r, w, 1e-6, M, N, dtype, patience)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(r), bits(rw)) and torch.equal(bits(x), bits(xw)) and xok() and rok()
+
+
+@pytest.mark.gpu
+def test_problems_that_are_not_split_are_refused():
+    x, _, r, _, w = norm_inputs(2, 4096, "bf16", 1)
+    with pytest.raises(B.AddrmsError) as e:
+        B.addrms_split_probe(x, r, w, 1e-6, 2, 4096, "bf16", 8)
+    assert e.value.status == B.ERR_UNSUPPORTED_SHAPE
+
+
+@pytest.mark.gpu
+def test_more_rows_than_one_launch_takes():
+    B.addrms_table_clear()
+    check_norm(4099, 33000, "bf16")
+
+
+@pytest.mark.gpu
+def test_more_streams_than_slots():
+    """Six streams with several launches in flight each: four may split their rows, the others take the kernel that does
+    not; all give the same."""
+    B.addrms_table_clear()
+    M, N, dtype = 300, 50000, "bf16"
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    inputs = [norm_inputs(M, N, dtype, 11 * k) for k in range(6)]
+    want = []
+    for x, _, r, _, w in inputs:
+        xw, rw = x.clone(), r.clone()
+        for _ in range(5):
+            B.addrms_run(xw, rw, w, 1e-6, M, N, dtype, B.addrms_default_cfg(N, dtype))
+        want.append((xw, rw))
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for s, (x, _, r, _, w) in zip(streams, inputs):
+            B.addrms_run(x, r, w, 1e-6, M, N, dtype, None, s)
+    torch.cuda.synchronize()
+    for (x, xok, r, rok, _), (xw, rw) in zip(inputs, want):
+        assert torch.equal(bits(x), bits(xw)) and torch.equal(bits(r), bits(rw)) and xok() and rok()
+    for _ in range(8):                                            # slots are given back: a new stream can have one
+        s = torch.cuda.Stream()
+        x, _, r, _, w = inputs[0]
+        B.addrms_split_probe(x, r, w, 1e-6, M, N, dtype, 256, s)
+        s.synchronize()
