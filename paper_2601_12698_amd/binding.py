@@ -335,12 +335,22 @@ class _Torch:
 
 
 _torch_facts = None
+_native = None          # module _native, which takes the usual calls as one native call (csrc/native_calls.cpp)
 
 
 def _torch() -> _Torch:
-    global _torch_facts
+    global _torch_facts, _native
     if _torch_facts is None:
         _torch_facts = _Torch()
+        try:
+            from . import _native as native
+        except ImportError:     # built for another torch: the calls below do the same, slower
+            native = None
+        if native is not None and os.path.exists(LIB_PATH):
+            lib = load()
+            native.bind(DTYPE_IDS, Cfg, *(ctypes.cast(getattr(lib, f), c_void_p).value for f in
+                                          ("addrms_run", "silumul_run", "mergestates_run", "addrms_gate_probe_noalloc")))
+            _native = native
     return _torch_facts
 
 
@@ -401,6 +411,12 @@ def addrms_algorithmic_bytes(M: int, N: int, dtype) -> int:
 def addrms_run(x, residual, weight, eps: float, M: int, N: int, dtype, cfg: Optional[Cfg] = None,
                stream=None) -> None:
     """In place: residual <- round(x + residual), x <- rmsnorm(x + residual) * weight."""
+    if stream is None and _native is not None:
+        st = _native.addrms_run(x, residual, weight, eps, M, N, dtype, cfg)
+        if st is not None:
+            if st:
+                _check(st)
+            return
     dt, xe, re = _format(dtype)
     n = M * N
     if not (_fits(x, xe, n) and _fits(residual, re, n) and _fits(weight, xe, N)):
@@ -746,6 +762,12 @@ def addrms_gate_probe(y, y_ref, residual, residual_ref, dtype, tol: int, counts_
 
 def addrms_gate_probe_noalloc(y, y_ref, residual, residual_ref, dtype, tol: int, counts_out, stream=None) -> None:
     """Same verdict as addrms_gate_probe; allocates nothing and does not wait for the stream."""
+    if stream is None and _native is not None:
+        st = _native.addrms_gate_probe_noalloc(y, y_ref, residual, residual_ref, dtype, tol, counts_out)
+        if st is not None:
+            if st:
+                _check(st)
+            return
     n, dt = _gate_args(y, y_ref, residual, residual_ref, dtype, counts_out)
     _check(load().addrms_gate_probe_noalloc(_ptr(y), _ptr(y_ref), _ptr(residual), _ptr(residual_ref), n, dt, int(tol),
                                             _ptr(counts_out), _stream_ptr(stream, y)))
@@ -759,6 +781,12 @@ def silumul_algorithmic_bytes(M: int, d: int, dtype) -> int:
 
 def silumul_run(x, out, M: int, d: int, dtype, cfg: Optional[Cfg] = None, stream=None) -> None:
     """out[i, j] = silu(x[i, j]) * x[i, d + j]; x is [M, 2d], out is [M, d], both on the device."""
+    if stream is None and _native is not None:
+        st = _native.silumul_run(x, out, M, d, dtype, cfg)
+        if st is not None:
+            if st:
+                _check(st)
+            return
     dt, xe, _ = _format(dtype)
     n = M * d
     if not (_fits(x, xe, 2 * n) and _fits(out, xe, n)):
@@ -871,6 +899,12 @@ def mergestates_algorithmic_bytes(rows: int, d: int, dtype) -> int:
 def mergestates_run(v_a, s_a, v_b, s_b, v_out, s_out, rows: int, d: int, dtype, cfg: Optional[Cfg] = None,
                     stream=None) -> None:
     """Merge two partial attention states; v tensors [rows, d], scores fp32 [rows], all on the device."""
+    if stream is None and _native is not None:
+        st = _native.mergestates_run(v_a, s_a, v_b, s_b, v_out, s_out, rows, d, dtype, cfg)
+        if st is not None:
+            if st:
+                _check(st)
+            return
     dt, xe, _ = _format(dtype)
     n, f32 = rows * d, _torch().float32
     if not (_fits(v_a, xe, n) and _fits(v_b, xe, n) and _fits(v_out, xe, n) and _fits(s_a, f32, rows) and

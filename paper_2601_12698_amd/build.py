@@ -1,9 +1,9 @@
-"""Builds ``libaddrms.so`` for gfx950 with hipcc, in-tree.
+"""Builds ``libaddrms.so`` for gfx950 with hipcc, and ``_native.so`` (calls from Python) with g++, in-tree.
 
 Steps: generate the kernel instantiation units; compile them (in parallel)
 while capturing the compiler's per-kernel resource report; turn that report
 into the table the feasible-region deriver reads; compile the host units;
-link.  Objects live under ``_build/`` next to this file; the shared library
+link; compile the module that calls the library from Python against torch's headers.  Objects live under ``_build/`` next to this file; the shared library
 is written into the package directory.
 
     python -m paper_2601_12698_amd.build [--force] [-j N]
@@ -22,6 +22,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libaddrms.so")
+NATIVE = os.path.join(HERE, "_native.so")
 ARCH = "gfx950"
 
 # -packed-fp32-ops off: packed fp32 instruction selection stays disabled for all device code.
@@ -89,6 +90,25 @@ def _compile_kernel_unit(src: str, force: bool) -> str:
     return r.stderr
 
 
+def _build_native(force: bool) -> None:
+    """The extension module _native, for the torch that is importable here."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    src, obj = os.path.join(CSRC, "native_calls.cpp"), os.path.join(BUILD, "native_calls.cpp.o")
+    if not force and _newer(NATIVE, src, os.path.join(tdir, "version.py")):
+        return
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    inc = [os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    _run(["g++", *HOST_FLAGS, "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+          *(a for i in inc for a in ("-isystem", i)), "-c", src, "-o", obj])
+    tmp = NATIVE + f".{os.getpid()}.tmp"
+    _run(["g++", "-shared", "-o", tmp, obj, "-L", os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
+    os.replace(tmp, NATIVE)
+
+
 def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
     sys.path.insert(0, CSRC)
     try:
@@ -138,6 +158,7 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
     tmp = LIB + f".{os.getpid()}.tmp"
     _run(["hipcc", "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *objs])
     os.replace(tmp, LIB)
+    _build_native(force)
     if verbose:
         print(f"built {LIB}: {len(rows)} kernel instances")
     return LIB
