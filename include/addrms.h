@@ -480,13 +480,15 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
 
 /* addrms_gate_probe for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments and the same verdict in counts_out, but the
- * per-workgroup partial counts live in an 8 KiB array that is part of the library's device code (one copy per GPU,
- * held until the process ends), so this call allocates nothing, frees nothing and does not wait: both kernels
- * are only enqueued on `stream`, and counts_out is valid once the stream has reached them.  Nothing in it is a
- * memset, so a capturing caller records two kernel nodes.  n beyond 2^32-1 is INVALID_ARG as above (the array
- * itself never limits n: a launch uses at most 512 slots whatever n is).  Every call on a GPU shares that GPU's
- * array: calls that may overlap in time on one GPU (different streams, concurrent graphs) race on it and must be
- * serialised by the caller; calls on one stream are ordered and safe. */
+ * per-workgroup partial counts live in arrays that are part of the library's device code (one copy per GPU, held until
+ * the process ends), so this call allocates no device memory, frees nothing and does not wait: its kernels are only
+ * enqueued on `stream`, and counts_out is valid once the stream has reached them.  Up to 96 workgroups (4096 elements of
+ * 16 bits or 2048 of 32 each) are one kernel, where the stream is not capturing and fewer than four others have such a
+ * call in flight (these calls report their end in 256 bytes of host memory, allocated once per GPU by the first of them);
+ * else two.  Nothing in it is a memset: a capturing caller records two kernel nodes, or one for a single workgroup.
+ * n beyond 2^32-1 is INVALID_ARG as above (the arrays never limit n: a launch uses at most 512 workgroups whatever n is).
+ * Every call on a GPU may use that GPU's array: calls that may overlap in time on one GPU (different streams, concurrent
+ * graphs) race on it and must be serialised by the caller; calls on one stream are ordered and safe. */
 int addrms_gate_probe_noalloc(const void* y, const void* y_ref, const void* residual, const void* residual_ref,
                               int64_t n, int dtype, uint32_t tol, addrms_gate_counts* counts_out, void* stream);
 

@@ -138,7 +138,7 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
     objs = [u[:-4] + ".o" for u in units]
     hdrs = [os.path.join(ROOT, "include", "addrms.h"), os.path.join(ROOT, "include", "silumul.h"), os.path.join(ROOT, "include", "mergestates.h"),
             os.path.join(CSRC, "addrms_internal.h"), os.path.join(CSRC, "direct_route.h"),
-            os.path.join(CSRC, "split_slots.h")]
+            os.path.join(CSRC, "stream_slots.h"), os.path.join(CSRC, "slot_pool.h")]
     gen = [os.path.join(BUILD, f) for f in ("gen_instances.inc", "gen_resources.inc",
                                              "gen_dispatch_decl.inc", "gen_dispatch_rows.inc")]
     for name in ("addrms_cfg.cpp", "addrms_table.cpp", "addrms_search.cpp", "addrms_general.cpp", "addrms_audit.cpp", "direct_route.cpp"):

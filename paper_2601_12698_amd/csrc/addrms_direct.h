@@ -22,10 +22,8 @@ bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_ali
 // hipError_t of the launch.
 int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
                          void* stream);
-// Only the kernel of rows split over workgroups, where the route has one (direct_launch_addrms prefers it).  False: no slot,
-// and nothing was launched.  A graph may be replayed on any stream and beside others, so that no slot is its own: a capturing
-// stream has none.  Nor has the per-thread default stream, one handle for as many streams as threads.  patience: see
-// split_row_sum.
+// Only the kernel of rows split over workgroups, where the route has one (direct_launch_addrms prefers it).  False: the
+// stream can have no slot (slot_pool.h), and nothing was launched.  patience: see split_row_sum.
 bool direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
                          unsigned patience, void* stream, int* status);
 int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream);

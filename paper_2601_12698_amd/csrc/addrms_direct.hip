@@ -4,17 +4,17 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdint>
-#include <mutex>
 
 #include "addrms_direct.h"
 #include "direct_kernel.h"
+#include "slot_pool.h"
 
 using namespace addrms;
 
 // Where the workgroups of split rows meet: 4 MB that belong to the loaded code object, one copy per GPU, all zero between
 // launches.
-static __device__ SplitRow split_rows[kSplitSlots][kSplitRows];
-static __device__ SplitLaunch split_launch[kSplitSlots];
+static __device__ SplitRow split_rows[kStreamSlots][kSplitRows];
+static __device__ SplitLaunch split_launch[kStreamSlots];
 
 namespace {
 
@@ -213,64 +213,26 @@ static int go(const DirectPlan& p, void** args, void* stream)
 }
 
 // ---- split rows ------------------------------------------------------------------------------------
-namespace {
-
-constexpr int kMaxDevices = 64, kDoneStride = 16;            // one 64-byte line of host memory per slot
+static SlotPool g_split_slots;
 constexpr unsigned kPatience = 256;                          // reads of a row's words, some hundreds of microseconds
 
-struct SplitDevice {
-    SplitSlots slots;
-    uint32_t* done = nullptr;                                // host memory that the kernels write
-};
-std::mutex g_split_mu;
-SplitDevice g_split[kMaxDevices];
-
-// Host memory for the launches of all slots to report in, once per GPU: 256 bytes, kept until the process ends.  The
-// allocation must not disturb a capture that another thread may be in.
-bool split_ready(SplitDevice& d)
-{
-    if (d.done) return true;
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
-    void* p = nullptr;
-    const size_t bytes = static_cast<size_t>(kSplitSlots) * kDoneStride * sizeof(uint32_t);
-    const hipError_t e = hipHostMalloc(&p, bytes, hipHostMallocDefault);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (e != hipSuccess) { (void)hipGetLastError(); return false; }
-    std::fill_n(static_cast<uint32_t*>(p), bytes / sizeof(uint32_t), 0u);
-    d.done = static_cast<uint32_t*>(p);
-    return true;
-}
-
-}  // namespace
-
 bool direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
-                         unsigned patience, void* raw_stream, int* status)
+                         unsigned patience, void* stream, int* status)
 {
-    const hipStream_t stream = static_cast<hipStream_t>(raw_stream);
-    if (!p.split_fn) return false;
-    if (stream == hipStreamPerThread) return false;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) { (void)hipGetLastError(); return false; }
-    int dev = -1;
-    if (capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
-    std::lock_guard<std::mutex> lock(g_split_mu);
-    SplitDevice& d = g_split[dev];
-    if (!split_ready(d)) return false;
-    const int slot = d.slots.take(reinterpret_cast<uintptr_t>(stream), d.done, kDoneStride);
-    if (slot < 0) return false;
+    SlotPool::Lease lease;
+    if (!p.split_fn || !g_split_slots.take(static_cast<hipStream_t>(stream), &lease)) return false;
     double inv_n = 1.0 / static_cast<double>(N);
     int n = static_cast<int>(N);
-    unsigned tpr = p.part_threads, s = static_cast<unsigned>(slot);
-    uint32_t* done = d.done + slot * kDoneStride;
+    unsigned tpr = p.part_threads, slot = lease.slot();
+    uint32_t* done = lease.done();
     hipError_t e = hipSuccess;
     for (int64_t row = 0; row < M && e == hipSuccess; row += kSplitRows) {
         void *xr = static_cast<char*>(x) + row * N * x_bytes(dtype), *rr = static_cast<char*>(r) + row * N * r_bytes(dtype);
-        uint32_t number = d.slots.next(slot);
-        void* args[] = {&xr, &rr, &w, &inv_n, &eps, &n, &tpr, &s, &done, &number, &patience};
+        uint32_t number = lease.number();
+        void* args[] = {&xr, &rr, &w, &inv_n, &eps, &n, &tpr, &slot, &done, &number, &patience};
         const unsigned rows = static_cast<unsigned>(std::min<int64_t>(kSplitRows, M - row));
-        e = hipLaunchKernel(p.split_fn, dim3(p.parts, rows), dim3(p.part_threads), args, 17u * sizeof(double), stream);
-        if (e == hipSuccess) d.slots.launched(slot);
+        e = hipLaunchKernel(p.split_fn, dim3(p.parts, rows), dim3(p.part_threads), args, 17u * sizeof(double), static_cast<hipStream_t>(stream));
+        if (e == hipSuccess) lease.launched();
     }
     *status = static_cast<int>(e);
     return true;

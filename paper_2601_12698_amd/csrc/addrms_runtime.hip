@@ -14,6 +14,7 @@
 #include "addrms_internal.h"
 #include "mergestates.h"
 #include "mergestates_kernel.h"
+#include "slot_pool.h"
 #include "silumul.h"
 #include "silumul_kernel.h"
 
@@ -424,15 +425,68 @@ __device__ __forceinline__ void gate_block(unsigned& rbad, unsigned& ybad, unsig
         }
 }
 
+// A small comparison is two launches of latency and little else, so up to 96 workgroups meet within one launch.  Elements of
+// bf16, one launch against two, through the binding: 4 k (one workgroup) 4.1 us against 7.0, 64 k 4.5 / 6.9, 256 k (64) 5.1 /
+// 6.9, 384 k (96) 5.6 / 7.1, 640 k (160) 6.4 / 7.3, 768 k (192) 7.0 / 6.6, 16 M (512) 25.8 / 23.2: workgroups that arrive together are
+// counted one after the other, 10 ns each (in groups and then the groups: another trip to memory, 24.6 / 23.2).
+constexpr int kGateMeetMax = 96;
+// Where they meet: all zero between launches.
+constexpr uint64_t kGateHere = 1ull << 63;
+struct __align__(128) GateWords { uint64_t bad, most; };
+struct GateMeeting {
+    GateWords words[kGateMeetMax];
+    __align__(128) uint32_t arrived;
+};
+static __device__ GateMeeting gate_meeting[addrms::kStreamSlots];
+
+__device__ __forceinline__ uint64_t gate_word(const uint64_t* w)
+{
+    uint64_t v;
+    do v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); while (!(v & kGateHere));
+    return v & ~kGateHere;
+}
+// The last workgroup to arrive folds the counts of all.  They are stored and the arrival counted without a wait in between,
+// so it may find a word still on its way, which it looks at again; no workgroup waits for one that has not arrived.
+// Everything here is accessed with relaxed atomics of device scope, which go to the memory side of the XCDs' L2s.
+__device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned ymax, GateMeeting* m, unsigned* out, uint32_t* done, uint32_t number)
+{
+    __shared__ unsigned before;
+    const unsigned n = gridDim.x;
+    if (threadIdx.x == 0) {
+        GateWords* w = &m->words[blockIdx.x];
+        __hip_atomic_store(&w->bad, kGateHere | static_cast<uint64_t>(ybad) << 31 | rbad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&w->most, kGateHere | ymax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = __hip_atomic_fetch_add(&m->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (before != n - 1u) return;
+    rbad = ybad = ymax = 0u;
+    if (threadIdx.x < n) {
+        GateWords* w = &m->words[threadIdx.x];
+        const uint64_t bad = gate_word(&w->bad);
+        ymax = static_cast<unsigned>(gate_word(&w->most));
+        rbad = static_cast<unsigned>(bad & 0x7fffffffu);
+        ybad = static_cast<unsigned>(bad >> 31);
+        __hip_atomic_store(&w->bad, uint64_t{0}, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&w->most, uint64_t{0}, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) __hip_atomic_store(&m->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    gate_block(rbad, ybad, ymax);                            // its barrier: every wave's words are clear
+    if (threadIdx.x != 0) return;
+    *reinterpret_cast<addrms::u32x4*>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
+    __hip_atomic_store(done, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The three counts of a workgroup's grid-stride slice, valid in thread 0.
 template <int XB, int RB>
-__global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(const char* y, const char* y_ref, const char* r,
-                                                                   const char* r_ref, long long n, unsigned tol,
-                                                                   unsigned* partial)
+__device__ __forceinline__ void gate_slice(const char* y, const char* y_ref, const char* r, const char* r_ref, long long n, unsigned tol,
+                                           unsigned& rbad, unsigned& ybad, unsigned& ymax)
 {
     using YP = typename gate_piece<XB>::type;
     using RP = typename gate_piece<RB>::type;
     constexpr int E = 16 / XB, RPP = E * RB / 16;        // elements per piece; residual pieces beside it
-    unsigned rbad = 0, ybad = 0, ymax = 0;
+    rbad = ybad = ymax = 0;
     const unsigned pieces = static_cast<unsigned>(n / E), step = gridDim.x * kGateBlock;
     for (unsigned long long p = blockIdx.x * kGateBlock + threadIdx.x; p < pieces; p += step) {
         const addrms::u32x4 a = gate_load<YP>(y + p * 16), b = gate_load<YP>(y_ref + p * 16);
@@ -469,8 +523,26 @@ __global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(const char* y,
         else rbad += reinterpret_cast<const uint16_t*>(r)[i] != reinterpret_cast<const uint16_t*>(r_ref)[i];
     }
     gate_block(rbad, ybad, ymax);
+}
+template <int XB, int RB>
+__global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(const char* y, const char* y_ref, const char* r,
+                                                                   const char* r_ref, long long n, unsigned tol,
+                                                                   unsigned* partial)
+{
+    unsigned rbad, ybad, ymax;
+    gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, rbad, ybad, ymax);
     if (threadIdx.x == 0)
         reinterpret_cast<addrms::u32x4*>(partial)[blockIdx.x] = addrms::u32x4{rbad, ybad, ymax, 0u};
+}
+template <int XB, int RB>
+__global__ __launch_bounds__(kGateBlock) void gate_one_kernel(const char* y, const char* y_ref, const char* r, const char* r_ref,
+                                                               long long n, unsigned tol, unsigned* out, unsigned slot,
+                                                               uint32_t* done, uint32_t number)
+{
+    unsigned rbad, ybad, ymax;
+    gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, rbad, ybad, ymax);
+    if (gridDim.x > 1u) gate_meet(rbad, ybad, ymax, &gate_meeting[slot], out, done, number);
+    else if (threadIdx.x == 0) *reinterpret_cast<addrms::u32x4*>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
 }
 // One workgroup.  accumulate != 0 folds the new counts into what `out` already holds
 // (a second comparison graded into the same verdict).
@@ -519,6 +591,31 @@ int launch_gate(const void* y, const void* y_ref, const void* r, const void* r_r
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(gate_finish_kernel, dim3(1), block, 0, stream, partial, static_cast<int>(grid.x), out, accumulate ? 1 : 0);
     HIP_TRY(hipGetLastError());
+    return ADDRMS_OK;
+}
+
+SlotPool g_gate_slots;
+
+// The gate in one launch, where one workgroup does it or a few and the stream can have a slot.  *launched: whether it was.
+int launch_gate_in_one(const void* y, const void* y_ref, const void* r, const void* r_ref, long long n, int xb, int rb, unsigned tol,
+                       unsigned* out, hipStream_t stream, bool* launched)
+{
+    const int workgroups = gate_grid(n, xb);
+    SlotPool::Lease lease;
+    *launched = workgroups <= kGateMeetMax && (workgroups == 1 || g_gate_slots.take(stream, &lease));
+    if (!*launched) return ADDRMS_OK;
+    const bool meet = workgroups > 1;
+    const unsigned slot = meet ? lease.slot() : 0u;
+    uint32_t* done = meet ? lease.done() : nullptr;
+    const uint32_t number = meet ? lease.number() : 0u;
+    const dim3 block(kGateBlock), grid(static_cast<unsigned>(workgroups));
+    const char *py = static_cast<const char*>(y), *pyr = static_cast<const char*>(y_ref);
+    const char *pr = static_cast<const char*>(r), *prr = static_cast<const char*>(r_ref);
+    if (xb == 2 && rb == 2) hipLaunchKernelGGL((gate_one_kernel<2, 2>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, slot, done, number);
+    else if (xb == 2) hipLaunchKernelGGL((gate_one_kernel<2, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, slot, done, number);
+    else hipLaunchKernelGGL((gate_one_kernel<4, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, slot, done, number);
+    HIP_TRY(hipGetLastError());
+    if (meet) lease.launched();
     return ADDRMS_OK;
 }
 
@@ -1342,6 +1439,10 @@ int addrms_gate_probe_noalloc(const void* y, const void* y_ref, const void* resi
 {
     int st = check_gate_args(y, y_ref, residual, residual_ref, n, dtype, counts_out);
     if (st != ADDRMS_OK) return st;
+    bool launched = false;
+    st = launch_gate_in_one(y, y_ref, residual, residual_ref, n, x_bytes(dtype), r_bytes(dtype), tol, reinterpret_cast<unsigned*>(counts_out),
+                            static_cast<hipStream_t>(stream), &launched);
+    if (st != ADDRMS_OK || launched) return st;
     unsigned* partial = nullptr;
     st = gate_scratch_on_current_device(&partial);
     if (st != ADDRMS_OK) return st;

@@ -6,8 +6,6 @@
 
 #include <algorithm>
 
-#include "split_slots.h"
-
 using namespace addrms;
 
 namespace {

@@ -31,6 +31,8 @@ constexpr bool direct_instance(int vec, int cpt, int pol, bool rag, bool multi)
     return !multi || cpt == 1;
 }
 
+constexpr int kSplitRows = 4096;                             // rows of one launch of split rows; more are several launches
+constexpr int kSplitParts = 16;                              // workgroups a row may be split over
 // The kernels of split rows: pieces per thread and store policy.  With fewer than four pieces 512 workgroups are within 32 MB.
 constexpr bool split_instance(int cpt, int pol) { return cpt == 4 ? pol == POL_NT || pol == POL_WT : (cpt == 1 || cpt == 2) && pol == POL_NT; }
 
@@ -46,7 +48,7 @@ struct DirectRoute {
     bool long_row = false;                                  // rows beyond the registers: units = chunks parked in LDS
     unsigned grid = 0, block_x = 0, block_y = 1, lds = 0;   // block_y: rows of a workgroup
     unsigned units = 0, total = 0, mul = 0, shift = 0;      // flat operators: see direct_kernel.h
-    // Long rows that are split over workgroups where the stream can have a slot (split_slots.h); the rest of the route is
+    // Long rows that are split over workgroups where the stream can have a slot (stream_slots.h); the rest of the route is
     // what runs where it cannot.
     unsigned parts = 0, part_threads = 0;                   // 0: not split
     int part_cpt = 0, part_pol = 0;

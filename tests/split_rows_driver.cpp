@@ -1,4 +1,4 @@
-// Slots of split rows (split_slots.h) and the shapes in which rows are split, for tests/test_split_rows.py.  Host code only.
+// Slots of split rows (stream_slots.h) and the shapes in which rows are split, for tests/test_split_rows.py.  Host code only.
 //   slots   who gets which slot; prints "ok"
 //   walk    the split of rows of many lengths and numbers; prints the number of decisions and the kernels asked for
 //   (no argument)  one problem per line: dtype M N; one split per line of output
@@ -10,7 +10,7 @@
 #include <tuple>
 
 #include "direct_route.h"
-#include "split_slots.h"
+#include "stream_slots.h"
 
 using namespace addrms_host;
 using namespace addrms;
@@ -19,10 +19,10 @@ using namespace addrms;
 
 static int slots()
 {
-    SplitSlots s;
-    uint32_t done[kSplitSlots * 2] = {};
-    int got[kSplitSlots];
-    for (int i = 0; i < kSplitSlots; ++i) {                       // streams 100, 101, ...: a slot each
+    StreamSlots s;
+    uint32_t done[kStreamSlots * 2] = {};
+    int got[kStreamSlots];
+    for (int i = 0; i < kStreamSlots; ++i) {                       // streams 100, 101, ...: a slot each
         got[i] = s.take(100u + i, done, 2);
         EXPECT(got[i] >= 0);
         for (int j = 0; j < i; ++j) EXPECT(got[j] != got[i]);

@@ -21,7 +21,7 @@ def driver(tmp_path_factory):
         pytest.skip("the generated instance and resource tables are not present (build the library first)")
     exe = str(tmp_path_factory.mktemp("split") / "driver")
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-Wall", "-Wextra",
-           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", BUILD, os.path.join(ROOT, "tests", "split_slots_driver.cpp"),
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", BUILD, os.path.join(ROOT, "tests", "split_rows_driver.cpp"),
            *[os.path.join(CSRC, s) for s in HOST_SOURCES + ["direct_route.cpp"]], "-o", exe]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=600)
     assert r.returncode == 0, r.stdout[-4000:]
