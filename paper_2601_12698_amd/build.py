@@ -32,8 +32,7 @@ ARCH = "gfx950"
 DEVICE_FLAGS = [f"--offload-arch={ARCH}", "-O3", "-fPIC", "-std=c++17", "-ffp-contract=off",
                 "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                 "-Wno-unused-command-line-argument"]
-# Kernel arguments in scalar registers when a wave starts, for the kernels whose smallest launches are a few chained
-# loads long (the grid's instances keep their resource figures, which saved configurations depend on).
+# Kernel arguments in scalar registers when a wave starts: a workgroup of these kernels is a few chained loads long.
 PRELOAD_FLAGS = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 HOST_FLAGS = ["-O2", "-fPIC", "-std=c++17", "-Wall", "-Wextra"]
 INCLUDES = ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", BUILD]
@@ -84,7 +83,7 @@ def _compile_kernel_unit(src: str, force: bool) -> str:
             _newer(obj, src, os.path.join(CSRC, "addrms_kernel.h"), os.path.join(CSRC, "silumul_kernel.h"),
                    os.path.join(CSRC, "mergestates_kernel.h"))):
         return open(rem).read()
-    r = _run(["hipcc", *DEVICE_FLAGS, *INCLUDES, "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj])
+    r = _run(["hipcc", *DEVICE_FLAGS, *PRELOAD_FLAGS, *INCLUDES, "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj])
     with open(rem, "w") as f:
         f.write(r.stderr)
     return r.stderr

@@ -83,39 +83,41 @@ int launch_instance(const Feas& f, const addrms_cfg& c, int64_t M, int op, void*
     return ADDRMS_OK;
 }
 
+unsigned shape_argument(const addrms_cfg& c)
+{
+    return static_cast<unsigned>(c.threads_per_row) | static_cast<unsigned>(c.rows_per_wg) << 16;
+}
+
 int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, float eps, int64_t M, int64_t N,
            hipStream_t stream)
 {
     double inv_n = 1.0 / static_cast<double>(N);
-    long long m = M;
     int n = static_cast<int>(N);
-    unsigned flags = static_cast<unsigned>(c.flags);
-    int reduce = c.reduce;
+    unsigned m = static_cast<unsigned>(M), shape = shape_argument(c);                    // the callers checked M < 2^31
+    unsigned mode = static_cast<unsigned>(c.flags) | static_cast<unsigned>(c.reduce) << 16;
     // the last argument is the number of row blocks (persistent grids walk them), or, for the forms that
     // continue the row cache in LDS, the chunks per thread the LDS allocation holds
     unsigned nblocks = f.lds_chunks >= 0 ? static_cast<unsigned>(f.lds_chunks) : static_cast<unsigned>(n_row_blocks(c, M));
-    void* args[] = {&x, &r, &w, &eps, &inv_n, &m, &n, &flags, &reduce, &nblocks};
+    void* args[] = {&x, &r, &w, &inv_n, &eps, &n, &m, &shape, &mode, &nblocks};
     return launch_instance(f, c, M, OP_ADDRMS, args, stream);
 }
 
 int launch_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out, int64_t M, int64_t d, hipStream_t stream)
 {
-    long long m = M;
     int dd = static_cast<int>(d);
-    unsigned flags = static_cast<unsigned>(c.flags);
+    unsigned m = static_cast<unsigned>(M), shape = shape_argument(c), flags = static_cast<unsigned>(c.flags);
     unsigned nblocks = static_cast<unsigned>(n_row_blocks(c, M));
-    void* args[] = {&x, &out, &m, &dd, &flags, &nblocks};
+    void* args[] = {&x, &out, &dd, &m, &shape, &flags, &nblocks};
     return launch_instance(f, c, M, OP_SILUMUL, args, stream);
 }
 
 int launch_mergestates(const Feas& f, const addrms_cfg& c, const void* va, const float* sa, const void* vb,
                        const float* sb, void* vo, float* so, int64_t rows, int64_t d, hipStream_t stream)
 {
-    long long m = rows;
     int dd = static_cast<int>(d);
-    unsigned flags = static_cast<unsigned>(c.flags);
+    unsigned m = static_cast<unsigned>(rows), shape = shape_argument(c), flags = static_cast<unsigned>(c.flags);
     unsigned nblocks = static_cast<unsigned>(n_row_blocks(c, rows));
-    void* args[] = {&va, &sa, &vb, &sb, &vo, &so, &m, &dd, &flags, &nblocks};
+    void* args[] = {&va, &vb, &dd, &m, &shape, &flags, &sa, &sb, &vo, &so, &nblocks};
     return launch_instance(f, c, rows, OP_MERGE, args, stream);
 }
 

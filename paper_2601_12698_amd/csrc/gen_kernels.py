@@ -96,24 +96,28 @@ def name(op, dt, vec, cpt, unr, nt, df=0):
     return f"{OP_PREFIX[op]}_k_d{dt}_v{vec}_c{cpt}_u{unr}_n{nt}" + ("_s1" if df else "")
 
 
+# shape: threads per row and, from bit 16 on, rows per workgroup; mode: flags and, from bit 16 on, the reduction style.  What
+# the first address depends on comes first: the first 16 dwords or so are in scalar registers when a wave starts.
 ARGS = {
-    OP_ADDRMS: ("void* x, void* r, const void* w, float eps, double inv_n, "
-                "long long M, int N, unsigned flags, int reduce, unsigned nblocks"),
-    OP_SILUMUL: "const void* x, void* out, long long M, int d, unsigned flags, unsigned nblocks",
-    OP_MERGE: ("const void* va, const float* sa, const void* vb, const float* sb, void* vo, float* so, "
-               "long long rows, int d, unsigned flags, unsigned nblocks"),
+    OP_ADDRMS: ("void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned M, unsigned shape, "
+                "unsigned mode, unsigned nblocks"),
+    OP_SILUMUL: "const void* x, void* out, int d, unsigned M, unsigned shape, unsigned flags, unsigned nblocks",
+    OP_MERGE: ("const void* va, const void* vb, int d, unsigned rows, unsigned shape, unsigned flags, "
+               "const float* sa, const float* sb, void* vo, float* so, unsigned nblocks"),
 }
+ADDRMS_ARGS = "(x, r, w, eps, inv_n, M, N, mode & 0xffffu, mode >> 16, nblocks, shape & 0xffffu, shape >> 16);"
 CALL = {
-    OP_ADDRMS: "addrms::addrms_body<{dt}, {vec}, {cpt}, {unr}, {nt}, {df}>(x, r, w, eps, inv_n, M, N, flags, reduce, nblocks);",
-    OP_SILUMUL: "addrms::silumul_body<{dt}, {vec}, {cpt}, {unr}, {nt}>(x, out, M, d, flags, nblocks);",
+    OP_ADDRMS: "addrms::addrms_body<{dt}, {vec}, {cpt}, {unr}, {nt}, {df}>" + ADDRMS_ARGS,
+    OP_SILUMUL: "addrms::silumul_body<{dt}, {vec}, {cpt}, {unr}, {nt}>(x, out, M, d, flags, nblocks, shape & 0xffffu, shape >> 16);",
     OP_MERGE: ("addrms::mergestates_body<{dt}, {vec}, {cpt}, {unr}, {nt}>"
-               "(va, sa, vb, sb, vo, so, rows, d, flags, nblocks);"),
+               "(va, sa, vb, sb, vo, so, rows, d, flags, nblocks, shape & 0xffffu, shape >> 16);"),
 }
-TWO_PASS_CALL = "addrms::addrms_twopass_body<{dt}, {vec}, {unr}, {nt}>(x, r, w, eps, inv_n, M, N, flags, reduce, nblocks);"
-HYBRID_CALL = ("addrms::addrms_hybrid_body<{dt}, {vec}, {cpt}, {unr}, {nt}>"
-               "(x, r, w, eps, inv_n, M, N, flags, reduce, nblocks);")
-SPAN_CALL = ("addrms::addrms_span_body<{dt}, {vec}, {cpt}, {unr}, {nt}, {df}>"
-             "(x, r, w, eps, inv_n, M, N, flags, reduce, nblocks);")
+TWO_PASS_CALL = "addrms::addrms_twopass_body<{dt}, {vec}, {unr}, {nt}>" + ADDRMS_ARGS
+HYBRID_CALL = "addrms::addrms_hybrid_body<{dt}, {vec}, {cpt}, {unr}, {nt}>" + ADDRMS_ARGS
+SPAN_CALL = "addrms::addrms_span_body<{dt}, {vec}, {cpt}, {unr}, {nt}, {df}>" + ADDRMS_ARGS
+# (op, dt, vec, cpt, unr): waves per SIMD that the compiler is held to, where it would otherwise end two registers above them
+# (98 for 96) and refuse configurations that are feasible with them.
+WAVES = {(OP_ADDRMS, 1, 2, 16, 4): 5}
 HEADER = {OP_ADDRMS: "addrms_kernel.h", OP_SILUMUL: "silumul_kernel.h", OP_MERGE: "mergestates_kernel.h"}
 
 
@@ -134,7 +138,9 @@ def main(outdir: str) -> None:
                 fmt = SPAN_CALL
             call = fmt.format(dt=dt, vec=vec, cpt=cpt % 100, unr=unr, nt="true" if nt else "false",
                               df="true" if df else "false")
-            lines.append(f'extern "C" __global__ __launch_bounds__({maxt}) void {name(op, dt, vec, cpt, unr, nt, df)}'
+            waves = WAVES.get((op, dt, vec, cpt, unr)) if not df else None
+            attr = f" __attribute__((amdgpu_waves_per_eu({waves})))" if waves else ""
+            lines.append(f'extern "C" __global__ __launch_bounds__({maxt}){attr} void {name(op, dt, vec, cpt, unr, nt, df)}'
                          f"({ARGS[op]})\n{{ {call} }}")
         _write(os.path.join(outdir, f"kern_{OP_PREFIX[op]}_d{dt}_v{vec}.hip"), "\n".join(lines) + "\n")
     decl, table, inst = [], [], []

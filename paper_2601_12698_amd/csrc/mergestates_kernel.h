@@ -20,13 +20,12 @@ template <int DT, int VEC, int CPT, int UNR, bool NT>
 __device__ __forceinline__ void mergestates_body(const void* __restrict__ vap, const float* __restrict__ sap,
                                                  const void* __restrict__ vbp, const float* __restrict__ sbp,
                                                  void* __restrict__ vop, float* __restrict__ sop, int64_t rows,
-                                                 int32_t d, uint32_t flags, uint32_t nblocks)
+                                                 int32_t d, uint32_t flags, uint32_t nblocks, uint32_t tpr, uint32_t rpw)
 {
     using T = dt_traits<DT>;
     constexpr int ES = T::XB;
     constexpr bool BF = T::BF;
     constexpr float kLog2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;
-    const uint32_t tpr = blockDim.x, rpw = blockDim.y;
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     uint32_t blk = blockIdx.x;
     if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, gridDim.x);

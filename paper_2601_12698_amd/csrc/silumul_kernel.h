@@ -26,12 +26,11 @@ __device__ __forceinline__ float silu_times(float g, float u)
 
 template <int DT, int VEC, int CPT, int UNR, bool NT>
 __device__ __forceinline__ void silumul_body(const void* __restrict__ xp, void* __restrict__ op, int64_t M,
-                                             int32_t d, uint32_t flags, uint32_t nblocks)
+                                             int32_t d, uint32_t flags, uint32_t nblocks, uint32_t tpr, uint32_t rpw)
 {
     using T = dt_traits<DT>;
     constexpr int ES = T::XB;
     constexpr bool BF = T::BF;
-    const uint32_t tpr = blockDim.x, rpw = blockDim.y;
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     uint32_t blk = blockIdx.x;
     if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, gridDim.x);
