@@ -33,10 +33,10 @@ __global__ __launch_bounds__(kLongThreads) void addrms_long(void* x, void* r, co
     addrms_long_body<DT, VEC, kLongRegValues / VEC, 2, POL, RAG>(x, r, w, eps, inv_n, N, lds_chunks);
 }
 template <int DT, int VEC, int CPT, int POL, bool RAG>
-__global__ __launch_bounds__(1024) void addrms_split(void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned tpr,
-                                                     unsigned slot, uint32_t* done, uint32_t number, unsigned patience)
+__global__ __launch_bounds__(1024) void addrms_split(void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned shape,
+                                                     unsigned rows, unsigned slot, uint32_t* done, uint32_t number, unsigned patience)
 {
-    addrms_split_body<DT, VEC, CPT, POL, RAG>(x, r, w, inv_n, eps, N, tpr, split_rows[slot], &split_launch[slot], done, number, patience);
+    addrms_split_body<DT, VEC, CPT, POL, RAG>(x, r, w, inv_n, eps, N, shape & 0xffffu, shape >> 16, rows, split_rows[slot], &split_launch[slot], done, number, patience);
 }
 template <int DT, int POL, bool RAG>
 __global__ __launch_bounds__(kFlatThreads) void silumul_flat(const char* x, char* out, uint32_t d, uint32_t units,
@@ -223,14 +223,14 @@ bool direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, f
     if (!p.split_fn || !g_split_slots.take(static_cast<hipStream_t>(stream), &lease)) return false;
     double inv_n = 1.0 / static_cast<double>(N);
     int n = static_cast<int>(N);
-    unsigned tpr = p.part_threads, slot = lease.slot();
+    unsigned shape = p.part_threads | p.parts << 16, slot = lease.slot();
     uint32_t* done = lease.done();
     hipError_t e = hipSuccess;
     for (int64_t row = 0; row < M && e == hipSuccess; row += kSplitRows) {
         void *xr = static_cast<char*>(x) + row * N * x_bytes(dtype), *rr = static_cast<char*>(r) + row * N * r_bytes(dtype);
         uint32_t number = lease.number();
-        void* args[] = {&xr, &rr, &w, &inv_n, &eps, &n, &tpr, &slot, &done, &number, &patience};
-        const unsigned rows = static_cast<unsigned>(std::min<int64_t>(kSplitRows, M - row));
+        unsigned rows = static_cast<unsigned>(std::min<int64_t>(kSplitRows, M - row));
+        void* args[] = {&xr, &rr, &w, &inv_n, &eps, &n, &shape, &rows, &slot, &done, &number, &patience};
         e = hipLaunchKernel(p.split_fn, dim3(p.parts, rows), dim3(p.part_threads), args, 17u * sizeof(double), static_cast<hipStream_t>(stream));
         if (e == hipSuccess) lease.launched();
     }

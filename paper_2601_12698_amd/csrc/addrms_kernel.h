@@ -26,10 +26,11 @@
 // VEC, CPT, UNR, NT and DEFER are compile-time; the rest are launch-time and
 // uniform over the workgroup.  All of them are arguments, the launch shape too, and
 // lie in scalar registers when a wave starts: a workgroup lives some 7 us, and blockDim
-// would be one more load before its first address is known.  Configured calls, us per launch
-// with blockDim and with arguments: 936 x 2880 fp16+fp32 7.2 -> 6.4, 213 x 7168 bf16 3.52 -> 3.32,
-// 1658 x 7168 18.3 -> 17.3, silu_and_mul 626 x 11008 bf16 9.4 -> 8.4, 5580 x 5120 fp16+fp32
-// 56.1 -> 55.5, 32768 x 7168 bf16 295.7 -> 295.4.
+// would be one more load before its first address is known.  Nor is gridDim read: a kernel
+// that asks for neither has a quarter of the arguments to be written at each launch.
+// Configured calls, us per launch with blockDim and with arguments: 936 x 2880 fp16+fp32 7.2 ->
+// 6.6, 213 x 7168 bf16 4.1 -> 3.9, 1658 x 7168 18.1 -> 17.3, 5580 x 5120 fp16+fp32 56.6 -> 55.9,
+// silu_and_mul 626 x 11008 bf16 9.5 -> 8.5, merge_attn_states 2048 x 192 bf16 4.2 -> 3.4 (the call).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -360,7 +361,7 @@ __device__ __forceinline__ void load_group(const char* xbase, const char* rbase,
 
 // The grid has either one workgroup per block of rows_per_wg rows, or fewer
 // (a persistent grid sized to what is resident on the chip): a workgroup then
-// walks blocks blk, blk + gridDim.x, ... and issues the first loads of its
+// walks blocks blk, blk + grid, ... and issues the first loads of its
 // next block before reducing the current one, so that it always has requests
 // in flight.  Every workgroup leaves the loop after its last block; there is
 // no waiting between workgroups.
@@ -368,7 +369,7 @@ template <int DT, int VEC, int CPT, int UNR, bool NT, bool DEFER>
 __device__ __forceinline__ void addrms_body(void* __restrict__ xp, void* __restrict__ rp,
                                             const void* __restrict__ wp, float eps, double inv_n,
                                             int64_t M, int32_t N, uint32_t flags, int32_t reduce,
-                                            uint32_t nblocks, uint32_t tpr, uint32_t rpw)
+                                            uint32_t nblocks, uint32_t tpr, uint32_t rpw, uint32_t grid)
 {
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
@@ -377,7 +378,7 @@ __device__ __forceinline__ void addrms_body(void* __restrict__ xp, void* __restr
 
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     uint32_t blk = blockIdx.x;
-    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, gridDim.x);
+    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, grid);
 
     const char* wbase = static_cast<const char*>(wp);
     const uint32_t col0 = lane * VEC;
@@ -429,7 +430,7 @@ __device__ __forceinline__ void addrms_body(void* __restrict__ xp, void* __restr
             if (g + UNR < CPT) __builtin_amdgcn_sched_barrier(0);
         }
 
-        const uint32_t next = blk + gridDim.x;
+        const uint32_t next = blk + grid;
         const bool more = next < nblocks;         // uniform over the workgroup
         RowAddr rn = ra;
         if (more) {
@@ -497,7 +498,7 @@ template <int DT, int VEC, int UNR, bool NT>
 __device__ __forceinline__ void addrms_twopass_body(void* __restrict__ xp, void* __restrict__ rp,
                                                     const void* __restrict__ wp, float eps, double inv_n,
                                                     int64_t M, int32_t N, uint32_t flags, int32_t reduce,
-                                                    uint32_t nblocks, uint32_t tpr, uint32_t rpw)
+                                                    uint32_t nblocks, uint32_t tpr, uint32_t rpw, uint32_t grid)
 {
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
@@ -507,7 +508,7 @@ __device__ __forceinline__ void addrms_twopass_body(void* __restrict__ xp, void*
 
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     uint32_t blk = blockIdx.x;
-    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, gridDim.x);
+    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, grid);
 
     const RowAddr ra = row_addr<XB, RB>(xp, rp, blk, rpw, ry, M, N);
     const char* wbase = static_cast<const char*>(wp);
@@ -602,7 +603,7 @@ template <int DT, int VEC, int CPT, int UNR, bool NT>
 __device__ __forceinline__ void addrms_hybrid_body(void* __restrict__ xp, void* __restrict__ rp,
                                                    const void* __restrict__ wp, float eps, double inv_n,
                                                    int64_t M, int32_t N, uint32_t flags, int32_t reduce,
-                                                   uint32_t lds_chunks, uint32_t tpr, uint32_t rpw)
+                                                   uint32_t lds_chunks, uint32_t tpr, uint32_t rpw, uint32_t grid)
 {
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
@@ -611,7 +612,7 @@ __device__ __forceinline__ void addrms_hybrid_body(void* __restrict__ xp, void* 
 
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     uint32_t blk = blockIdx.x;
-    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, gridDim.x);
+    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, grid);
 
     const RowAddr ra = row_addr<XB, RB>(xp, rp, blk, rpw, ry, M, N);
     const char* wbase = static_cast<const char*>(wp);
@@ -824,7 +825,7 @@ template <int DT, int VEC, int CPT, int UNR, bool NT, bool DEFER>
 __device__ __forceinline__ void addrms_span_body(void* __restrict__ xp, void* __restrict__ rp,
                                                  const void* __restrict__ wp, float eps, double inv_n,
                                                  int64_t M, int32_t N, uint32_t flags, int32_t reduce,
-                                                 uint32_t nblocks, uint32_t tpr, uint32_t rpw)
+                                                 uint32_t nblocks, uint32_t tpr, uint32_t rpw, uint32_t grid)
 {
     using T_ = dt_traits<DT>;
     constexpr int XB = T_::XB, RB = T_::RB;
@@ -836,7 +837,7 @@ __device__ __forceinline__ void addrms_span_body(void* __restrict__ xp, void* __
     const uint32_t T = tpr * rpw, R = rpw;
     const uint32_t t = threadIdx.y * tpr + threadIdx.x;
     uint32_t blk = blockIdx.x;
-    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, gridDim.x);
+    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, grid);
     const int64_t row0 = static_cast<int64_t>(blk) * R;
     const int64_t left = M - row0;
     const uint32_t rows_here = left < static_cast<int64_t>(R) ? static_cast<uint32_t>(left) : R;

@@ -64,12 +64,10 @@ std::atomic<bool> g_big_lds_enabled[sizeof(kDispatch) / sizeof(kDispatch[0])];
 bool aligned(const void* p, int bytes) { return (reinterpret_cast<uintptr_t>(p) % static_cast<uintptr_t>(bytes)) == 0; }
 
 // Launch of a kernel instance with every check already done.
-int launch_instance(const Feas& f, const addrms_cfg& c, int64_t M, int op, void** args, hipStream_t stream)
+int launch_instance(const Feas& f, const addrms_cfg& c, unsigned grid, void** args, hipStream_t stream)
 {
-    const dim3 grid(static_cast<unsigned>(n_workgroups(c, M, f.res.wgs_per_cu)));
     const dim3 block(static_cast<unsigned>(c.threads_per_row), static_cast<unsigned>(c.rows_per_wg));
     const int lds = f.dyn_lds;
-    (void)op;
     if (lds > kDefaultDynamicLdsLimit) {
         // Occupancy padding beyond the default per-launch limit has to be enabled once per kernel.
         std::atomic<bool>& done = g_big_lds_enabled[f.inst];
@@ -79,7 +77,7 @@ int launch_instance(const Feas& f, const addrms_cfg& c, int64_t M, int op, void*
             done.store(true, std::memory_order_release);
         }
     }
-    HIP_TRY(hipLaunchKernel(kDispatch[f.inst].fn, grid, block, args, static_cast<size_t>(lds), stream));
+    HIP_TRY(hipLaunchKernel(kDispatch[f.inst].fn, dim3(grid), block, args, static_cast<size_t>(lds), stream));
     return ADDRMS_OK;
 }
 
@@ -98,8 +96,9 @@ int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, 
     // the last argument is the number of row blocks (persistent grids walk them), or, for the forms that
     // continue the row cache in LDS, the chunks per thread the LDS allocation holds
     unsigned nblocks = f.lds_chunks >= 0 ? static_cast<unsigned>(f.lds_chunks) : static_cast<unsigned>(n_row_blocks(c, M));
-    void* args[] = {&x, &r, &w, &inv_n, &eps, &n, &m, &shape, &mode, &nblocks};
-    return launch_instance(f, c, M, OP_ADDRMS, args, stream);
+    unsigned grid = static_cast<unsigned>(n_workgroups(c, M, f.res.wgs_per_cu));
+    void* args[] = {&x, &r, &w, &inv_n, &eps, &n, &m, &shape, &mode, &nblocks, &grid};
+    return launch_instance(f, c, grid, args, stream);
 }
 
 int launch_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out, int64_t M, int64_t d, hipStream_t stream)
@@ -107,8 +106,9 @@ int launch_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out,
     int dd = static_cast<int>(d);
     unsigned m = static_cast<unsigned>(M), shape = shape_argument(c), flags = static_cast<unsigned>(c.flags);
     unsigned nblocks = static_cast<unsigned>(n_row_blocks(c, M));
-    void* args[] = {&x, &out, &dd, &m, &shape, &flags, &nblocks};
-    return launch_instance(f, c, M, OP_SILUMUL, args, stream);
+    unsigned grid = static_cast<unsigned>(n_workgroups(c, M, f.res.wgs_per_cu));
+    void* args[] = {&x, &out, &dd, &m, &shape, &flags, &nblocks, &grid};
+    return launch_instance(f, c, grid, args, stream);
 }
 
 int launch_mergestates(const Feas& f, const addrms_cfg& c, const void* va, const float* sa, const void* vb,
@@ -117,8 +117,9 @@ int launch_mergestates(const Feas& f, const addrms_cfg& c, const void* va, const
     int dd = static_cast<int>(d);
     unsigned m = static_cast<unsigned>(rows), shape = shape_argument(c), flags = static_cast<unsigned>(c.flags);
     unsigned nblocks = static_cast<unsigned>(n_row_blocks(c, rows));
-    void* args[] = {&va, &vb, &dd, &m, &shape, &flags, &sa, &sb, &vo, &so, &nblocks};
-    return launch_instance(f, c, rows, OP_MERGE, args, stream);
+    unsigned grid = static_cast<unsigned>(n_workgroups(c, rows, f.res.wgs_per_cu));
+    void* args[] = {&va, &vb, &dd, &m, &shape, &flags, &sa, &sb, &vo, &so, &nblocks, &grid};
+    return launch_instance(f, c, grid, args, stream);
 }
 
 // *untuned (may be NULL): true if neither the caller nor the table names a configuration.

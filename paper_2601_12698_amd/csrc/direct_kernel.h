@@ -296,7 +296,8 @@ __device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __
     constexpr bool BF = T::BF;
     extern __shared__ double lds[];
 
-    const uint32_t tpr = blockDim.x, lane = threadIdx.x;
+    constexpr uint32_t tpr = kLongThreads;
+    const uint32_t lane = threadIdx.x;
     char* xbase = static_cast<char*>(xp) + static_cast<int64_t>(blockIdx.x) * N * XB;
     char* rbase = static_cast<char*>(rp) + static_cast<int64_t>(blockIdx.x) * N * RB;
     const char* wbase = static_cast<const char*>(wp);
@@ -559,15 +560,15 @@ __device__ __forceinline__ double split_row_sum(double part_sum, SplitRow* row, 
 
 template <int DT, int VEC, int CPT, int POL, bool RAG>
 __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* __restrict__ rp, const void* __restrict__ wp, double inv_n,
-                                                  float eps, int32_t N, uint32_t tpr, SplitRow* rows, SplitLaunch* launch,
-                                                  uint32_t* done, uint32_t number, uint32_t patience)
+                                                  float eps, int32_t N, uint32_t tpr, uint32_t parts, uint32_t M, SplitRow* rows,
+                                                  SplitLaunch* launch, uint32_t* done, uint32_t number, uint32_t patience)
 {
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
     constexpr bool BF = T::BF;
     extern __shared__ double lds[];                          // one sum per wave, then the row's
 
-    const uint32_t part = blockIdx.x, parts = gridDim.x, lane = threadIdx.x;
+    const uint32_t part = blockIdx.x, lane = threadIdx.x;
     SplitRow* row = rows + blockIdx.y;
     char* xrow = static_cast<char*>(xp) + static_cast<int64_t>(blockIdx.y) * N * XB;
     char* rrow = static_cast<char*>(rp) + static_cast<int64_t>(blockIdx.y) * N * RB;
@@ -648,7 +649,7 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     if (lane < parts) __hip_atomic_store(&row->word[lane], uint64_t{0}, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (lane == 0u) __hip_atomic_store(&row->read, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lane != 0u || __hip_atomic_fetch_add(&launch->rows_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != gridDim.y - 1u) return;
+    if (lane != 0u || __hip_atomic_fetch_add(&launch->rows_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != M - 1u) return;
     __hip_atomic_store(&launch->rows_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __hip_atomic_store(done, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

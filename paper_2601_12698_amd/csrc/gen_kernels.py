@@ -97,27 +97,27 @@ def name(op, dt, vec, cpt, unr, nt, df=0):
 
 
 # shape: threads per row and, from bit 16 on, rows per workgroup; mode: flags and, from bit 16 on, the reduction style.  What
-# the first address depends on comes first: the first 16 dwords or so are in scalar registers when a wave starts.
+# the first address depends on comes first: the first 14 dwords or so are in scalar registers when a wave starts (build.py).
 ARGS = {
     OP_ADDRMS: ("void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned M, unsigned shape, "
-                "unsigned mode, unsigned nblocks"),
-    OP_SILUMUL: "const void* x, void* out, int d, unsigned M, unsigned shape, unsigned flags, unsigned nblocks",
+                "unsigned mode, unsigned nblocks, unsigned grid"),
+    OP_SILUMUL: "const void* x, void* out, int d, unsigned M, unsigned shape, unsigned flags, unsigned nblocks, unsigned grid",
     OP_MERGE: ("const void* va, const void* vb, int d, unsigned rows, unsigned shape, unsigned flags, "
-               "const float* sa, const float* sb, void* vo, float* so, unsigned nblocks"),
+               "const float* sa, const float* sb, void* vo, float* so, unsigned nblocks, unsigned grid"),
 }
-ADDRMS_ARGS = "(x, r, w, eps, inv_n, M, N, mode & 0xffffu, mode >> 16, nblocks, shape & 0xffffu, shape >> 16);"
+ADDRMS_ARGS = "(x, r, w, eps, inv_n, M, N, mode & 0xffffu, mode >> 16, nblocks, shape & 0xffffu, shape >> 16, grid);"
 CALL = {
     OP_ADDRMS: "addrms::addrms_body<{dt}, {vec}, {cpt}, {unr}, {nt}, {df}>" + ADDRMS_ARGS,
-    OP_SILUMUL: "addrms::silumul_body<{dt}, {vec}, {cpt}, {unr}, {nt}>(x, out, M, d, flags, nblocks, shape & 0xffffu, shape >> 16);",
+    OP_SILUMUL: "addrms::silumul_body<{dt}, {vec}, {cpt}, {unr}, {nt}>(x, out, M, d, flags, nblocks, shape & 0xffffu, shape >> 16, grid);",
     OP_MERGE: ("addrms::mergestates_body<{dt}, {vec}, {cpt}, {unr}, {nt}>"
-               "(va, sa, vb, sb, vo, so, rows, d, flags, nblocks, shape & 0xffffu, shape >> 16);"),
+               "(va, sa, vb, sb, vo, so, rows, d, flags, nblocks, shape & 0xffffu, shape >> 16, grid);"),
 }
 TWO_PASS_CALL = "addrms::addrms_twopass_body<{dt}, {vec}, {unr}, {nt}>" + ADDRMS_ARGS
 HYBRID_CALL = "addrms::addrms_hybrid_body<{dt}, {vec}, {cpt}, {unr}, {nt}>" + ADDRMS_ARGS
 SPAN_CALL = "addrms::addrms_span_body<{dt}, {vec}, {cpt}, {unr}, {nt}, {df}>" + ADDRMS_ARGS
-# (op, dt, vec, cpt, unr): waves per SIMD that the compiler is held to, where it would otherwise end two registers above them
-# (98 for 96) and refuse configurations that are feasible with them.
-WAVES = {(OP_ADDRMS, 1, 2, 16, 4): 5}
+# (op, dt, vec, cpt, unr, df): waves per SIMD that the compiler is held to, where it would otherwise end two registers above
+# what they leave (98 for 96, 74 for 72) and make configurations infeasible that were feasible.
+WAVES = {(OP_ADDRMS, 1, 2, 16, 4, 0): 5, (OP_ADDRMS, 0, 1, 12, 2, 1): 7}
 HEADER = {OP_ADDRMS: "addrms_kernel.h", OP_SILUMUL: "silumul_kernel.h", OP_MERGE: "mergestates_kernel.h"}
 
 
@@ -138,7 +138,7 @@ def main(outdir: str) -> None:
                 fmt = SPAN_CALL
             call = fmt.format(dt=dt, vec=vec, cpt=cpt % 100, unr=unr, nt="true" if nt else "false",
                               df="true" if df else "false")
-            waves = WAVES.get((op, dt, vec, cpt, unr)) if not df else None
+            waves = WAVES.get((op, dt, vec, cpt, unr, df))
             attr = f" __attribute__((amdgpu_waves_per_eu({waves})))" if waves else ""
             lines.append(f'extern "C" __global__ __launch_bounds__({maxt}){attr} void {name(op, dt, vec, cpt, unr, nt, df)}'
                          f"({ARGS[op]})\n{{ {call} }}")

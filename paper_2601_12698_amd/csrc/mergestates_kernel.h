@@ -20,7 +20,7 @@ template <int DT, int VEC, int CPT, int UNR, bool NT>
 __device__ __forceinline__ void mergestates_body(const void* __restrict__ vap, const float* __restrict__ sap,
                                                  const void* __restrict__ vbp, const float* __restrict__ sbp,
                                                  void* __restrict__ vop, float* __restrict__ sop, int64_t rows,
-                                                 int32_t d, uint32_t flags, uint32_t nblocks, uint32_t tpr, uint32_t rpw)
+                                                 int32_t d, uint32_t flags, uint32_t nblocks, uint32_t tpr, uint32_t rpw, uint32_t grid)
 {
     using T = dt_traits<DT>;
     constexpr int ES = T::XB;
@@ -28,7 +28,7 @@ __device__ __forceinline__ void mergestates_body(const void* __restrict__ vap, c
     constexpr float kLog2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     uint32_t blk = blockIdx.x;
-    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, gridDim.x);
+    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, grid);
     const uint32_t col_first = lane * VEC;
     const uint32_t stride = tpr * VEC;
     const uint32_t nlast = static_cast<uint32_t>(d) - VEC;
@@ -90,7 +90,7 @@ __device__ __forceinline__ void mergestates_body(const void* __restrict__ vap, c
             }
             if (g0 + UNR < CPT) __builtin_amdgcn_sched_barrier(0);
         }
-        const uint32_t next = blk + gridDim.x;      // a persistent grid walks several row blocks
+        const uint32_t next = blk + grid;      // a persistent grid walks several row blocks
         if (next >= nblocks) break;
         blk = next;
     }

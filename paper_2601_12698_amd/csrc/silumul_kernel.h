@@ -26,14 +26,14 @@ __device__ __forceinline__ float silu_times(float g, float u)
 
 template <int DT, int VEC, int CPT, int UNR, bool NT>
 __device__ __forceinline__ void silumul_body(const void* __restrict__ xp, void* __restrict__ op, int64_t M,
-                                             int32_t d, uint32_t flags, uint32_t nblocks, uint32_t tpr, uint32_t rpw)
+                                             int32_t d, uint32_t flags, uint32_t nblocks, uint32_t tpr, uint32_t rpw, uint32_t grid)
 {
     using T = dt_traits<DT>;
     constexpr int ES = T::XB;
     constexpr bool BF = T::BF;
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     uint32_t blk = blockIdx.x;
-    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, gridDim.x);
+    if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, grid);
     const uint32_t col_first = lane * VEC;
     const uint32_t stride = tpr * VEC;
     const uint32_t nlast = static_cast<uint32_t>(d) - VEC;
@@ -79,7 +79,7 @@ __device__ __forceinline__ void silumul_body(const void* __restrict__ xp, void* 
             }
             if (g0 + UNR < CPT) __builtin_amdgcn_sched_barrier(0);
         }
-        const uint32_t next = blk + gridDim.x;      // a persistent grid walks several row blocks
+        const uint32_t next = blk + grid;      // a persistent grid walks several row blocks
         if (next >= nblocks) break;
         blk = next;
     }
