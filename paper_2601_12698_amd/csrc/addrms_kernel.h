@@ -40,7 +40,8 @@ namespace addrms {
 enum : int { DT_BF16 = 0, DT_FP16 = 1, DT_FP16_RES32 = 2, DT_FP32 = 3 };
 enum : int { RED_WAVE = 0, RED_LDS = 1 };
 enum : uint32_t { FLAG_XCD_CONTIG = 1u, FLAG_NONTEMPORAL = 2u, FLAG_PERSISTENT = 4u, FLAG_TWO_PASS = 8u,
-                  FLAG_LDS_CACHE = 16u, FLAG_DEFER_STORE = 32u, FLAG_ALIGNED_SPAN = 64u };
+                  FLAG_LDS_CACHE = 16u, FLAG_DEFER_STORE = 32u, FLAG_ALIGNED_SPAN = 64u,
+                  LAUNCH_PACED = 0x8000u };      // not a knob: set by the host for large launches (wait_one_load)
 
 template <int DT> struct dt_traits;
 template <> struct dt_traits<DT_BF16>       { static constexpr int XB = 2, RB = 2; static constexpr bool BF = true;  };
@@ -342,6 +343,16 @@ __device__ __forceinline__ RowAddr row_addr(void* xp, void* rp, uint32_t blk, ui
     return a;
 }
 
+// Lets a wave wait for one small load (an element at p, which all waves read) before it asks for anything else.  Where
+// more workgroups are resident than the memory system serves best, their requests queue up ahead of it, and a wave that
+// has to queue itself once before it adds its own keeps them fewer: an admission control.
+__device__ __forceinline__ void wait_one_load(const void* p)
+{
+    const uint32_t v = __hip_atomic_load(static_cast<const uint16_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    asm volatile("" ::"v"(v));
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Issues the loads of chunk group g (UNR chunks starting at chunk g) of one row.
 template <int XB, int RB, int VEC, int CPT, int UNR, bool NT>
 __device__ __forceinline__ void load_group(const char* xbase, const char* rbase, uint32_t rowoff, uint32_t col0,
@@ -387,6 +398,7 @@ __device__ __forceinline__ void addrms_body(void* __restrict__ xp, void* __restr
     // LDS region of one reduction; consecutive iterations alternate between two regions
     const uint32_t lds_region = (reduce == RED_WAVE) ? rpw * 16u : rpw * tpr;
 
+    if (flags & LAUNCH_PACED) wait_one_load(wp);
     raw_t<XB * VEC> xv[UNR];
     raw_t<RB * VEC> rv[UNR];
     RowAddr ra = row_addr<XB, RB>(xp, rp, blk, rpw, ry, M, N);

@@ -86,13 +86,24 @@ unsigned shape_argument(const addrms_cfg& c)
     return static_cast<unsigned>(c.threads_per_row) | static_cast<unsigned>(c.rows_per_wg) << 16;
 }
 
-int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, float eps, int64_t M, int64_t N,
+// Launches whose waves wait for one load before they ask for more (wait_one_load).  Configured calls, us without and with:
+// add+RMSNorm 32768 x 7168 bf16 (1.9 GB) 302.4 / 299.8, 20000 x 5120 (0.8 GB) 147.7 / 145.3, 12000 x 8192 (0.8 GB) 125.5 / 126.2, 6000 x
+// 8192 (0.4 GB) 63.6 / 64.1, 1658 x 7168 (95 MB) 17.3 / 17.6; silu_and_mul, which holds nothing back by itself, 16000 x 11008 bf16 (1.1 GB)
+// 168.3 / 160.2, 4096 x 11008 43.8 / 42.6, 626 x 11008 (41 MB) 8.5 / 8.2.
+unsigned paced(int op, int64_t M, int64_t N, int dtype)
+{
+    constexpr int64_t kAddrms = 800'000'000, kSilumul = 32'000'000;
+    const int64_t per = op == OP_ADDRMS ? 2 * (x_bytes(dtype) + r_bytes(dtype)) : 3 * x_bytes(dtype);
+    return M * N * per >= (op == OP_ADDRMS ? kAddrms : kSilumul) ? static_cast<unsigned>(addrms::LAUNCH_PACED) : 0u;
+}
+
+int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
            hipStream_t stream)
 {
     double inv_n = 1.0 / static_cast<double>(N);
     int n = static_cast<int>(N);
     unsigned m = static_cast<unsigned>(M), shape = shape_argument(c);                    // the callers checked M < 2^31
-    unsigned mode = static_cast<unsigned>(c.flags) | static_cast<unsigned>(c.reduce) << 16;
+    unsigned mode = static_cast<unsigned>(c.flags) | paced(OP_ADDRMS, M, N, dtype) | static_cast<unsigned>(c.reduce) << 16;
     // the last argument is the number of row blocks (persistent grids walk them), or, for the forms that
     // continue the row cache in LDS, the chunks per thread the LDS allocation holds
     unsigned nblocks = f.lds_chunks >= 0 ? static_cast<unsigned>(f.lds_chunks) : static_cast<unsigned>(n_row_blocks(c, M));
@@ -101,10 +112,10 @@ int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, 
     return launch_instance(f, c, grid, args, stream);
 }
 
-int launch_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out, int64_t M, int64_t d, hipStream_t stream)
+int launch_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out, int64_t M, int64_t d, int dtype, hipStream_t stream)
 {
     int dd = static_cast<int>(d);
-    unsigned m = static_cast<unsigned>(M), shape = shape_argument(c), flags = static_cast<unsigned>(c.flags);
+    unsigned m = static_cast<unsigned>(M), shape = shape_argument(c), flags = static_cast<unsigned>(c.flags) | paced(OP_SILUMUL, M, d, dtype);
     unsigned nblocks = static_cast<unsigned>(n_row_blocks(c, M));
     unsigned grid = static_cast<unsigned>(n_workgroups(c, M, f.res.wgs_per_cu));
     void* args[] = {&x, &out, &dd, &m, &shape, &flags, &nblocks, &grid};
@@ -210,7 +221,7 @@ int run_addrms(void* x, void* r, const void* w, float eps, int64_t M, int64_t N,
         },
         [=](const addrms_cfg& c, DirectPlan* p) { return direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(r), bits(w), p); });
     if (st != ADDRMS_OK) return st;
-    if (!call->direct) return launch(call->f, call->c, x, r, w, eps, M, N, stream);
+    if (!call->direct) return launch(call->f, call->c, x, r, w, eps, M, N, dtype, stream);
     HIP_TRY(static_cast<hipError_t>(direct_launch_addrms(call->p, x, r, w, eps, M, N, dtype, stream)));
     return ADDRMS_OK;
 }
@@ -226,7 +237,7 @@ int run_silumul(const void* x, void* out, int64_t M, int64_t d, int dtype, const
         },
         [=](const addrms_cfg&, DirectPlan* p) { return direct_silumul_plan(M, d, dtype, bits(x), bits(out), p); });
     if (st != ADDRMS_OK) return st;
-    if (!call->direct) return launch_silumul(call->f, call->c, x, out, M, d, stream);
+    if (!call->direct) return launch_silumul(call->f, call->c, x, out, M, d, dtype, stream);
     HIP_TRY(static_cast<hipError_t>(direct_launch_silumul(call->p, x, out, d, stream)));
     return ADDRMS_OK;
 }
@@ -708,7 +719,7 @@ struct Harness {
     int run_on(const addrms_cfg& c, const Feas& f, int set)
     {
         if (untuned) return run_addrms(xs[set], rs[set], w, eps, M, N, dtype, nullptr, stream);
-        return launch(f, c, xs[set], rs[set], w, eps, M, N, stream);
+        return launch(f, c, xs[set], rs[set], w, eps, M, N, dtype, stream);
     }
 
     int make_reference(const addrms_cfg& c)
@@ -717,7 +728,7 @@ struct Harness {
         if (f.status != ADDRMS_OK) return fail(f.status, "reference cfg infeasible: %s", f.reason.c_str());
         HIP_TRY(hipMemcpyAsync(yref, x0, xbytes, hipMemcpyDeviceToDevice, stream));
         HIP_TRY(hipMemcpyAsync(rref, r0, rbytes, hipMemcpyDeviceToDevice, stream));
-        const int st = launch(f, c, yref, rref, w, eps, M, N, stream);
+        const int st = launch(f, c, yref, rref, w, eps, M, N, dtype, stream);
         if (st != ADDRMS_OK) return st;
         HIP_TRY(hipStreamSynchronize(stream));
         have_ref = true;
@@ -868,7 +879,7 @@ struct SiluHarness {
     {
         const Feas f = check_cfg(c, M, d, dtype, OP_SILUMUL);
         if (f.status != ADDRMS_OK) return fail(f.status, "reference cfg infeasible: %s", f.reason.c_str());
-        const int st = launch_silumul(f, c, ins[0], ref, M, d, stream);
+        const int st = launch_silumul(f, c, ins[0], ref, M, d, dtype, stream);
         if (st != ADDRMS_OK) return st;
         HIP_TRY(hipStreamSynchronize(stream));
         return ADDRMS_OK;
@@ -878,7 +889,7 @@ struct SiluHarness {
         const Feas f = check_cfg(c, M, d, dtype, OP_SILUMUL);
         if (f.status != ADDRMS_OK) return f.status;
         HIP_TRY(hipMemsetAsync(outs[0], 0xff, outbytes, stream));     // stale output must not pass for a result
-        int st = launch_silumul(f, c, ins[0], outs[0], M, d, stream);
+        int st = launch_silumul(f, c, ins[0], outs[0], M, d, dtype, stream);
         if (st != ADDRMS_OK) return st;
         // the residual slots of the comparison are fed the same buffer twice: only the output is graded
         st = launch_gate(outs[0], ref, ref, ref, static_cast<long long>(M) * d, x_bytes(dtype), x_bytes(dtype), 1u,
@@ -900,7 +911,7 @@ struct SiluHarness {
         for (int i = 0; i < warmup + reps; ++i) {
             if (i == warmup) HIP_TRY(hipEventRecord(ev0, stream));
             const int st = untuned ? run_silumul(ins[set], outs[set], M, d, dtype, nullptr, stream)
-                                   : launch_silumul(f, c, ins[set], outs[set], M, d, stream);
+                                   : launch_silumul(f, c, ins[set], outs[set], M, d, dtype, stream);
             if (st != ADDRMS_OK) return st;
             set = (set + 1) % nsets;
         }

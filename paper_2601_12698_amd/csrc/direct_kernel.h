@@ -664,8 +664,8 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
 // (half as many workgroups) lost 1-18 %; workgroups of 64 to 256 threads are the same.
 // Default of the knob grid -> here, us per launch, on one set of buffers / three in rotation / from HBM:
 //   silu_and_mul  4096 x 11008 bf16  43.4 / 56.3 / 56.8 -> 38.8 / 39.7 / 42.5 (6.8 TB/s on three sets: the
-//                 memory-side cache serves part of it)    16000 x 11008  204 / 204 / 204 -> 163 / 164 / 164
-//                 (6.45 TB/s)    64 x 14336 fp16  4.3 / 4.3 / 7.4 -> 2.2 / 2.1 / 2.5
+//                 memory-side cache serves part of it)    16000 x 11008  204 / 204 / 204 -> 158 on all
+//                 (6.7 TB/s)    64 x 14336 fp16  4.3 / 4.3 / 7.4 -> 2.2 / 2.1 / 2.5
 //                 2000 x 4099 bf16  12.0 / 12.0 / 16.7 -> 8.5 / 9.8 / 10.7
 //   merge_attn_states  24576 x 256 bf16  6.4 / 7.5 / 10.0 -> 4.5 / 7.5 / 8.7    20480 x 128 fp16  3.6 / 4.5 /
 //                 5.7 -> 2.9 / 3.8 / 4.5    38759 x 256 bf16  10.8 / 10.7 / 14.0 -> 9.1 / 11.4 / 12.2 (the one
@@ -691,6 +691,10 @@ __device__ __forceinline__ void silumul_flat_body(const char* __restrict__ x, ch
     const uint32_t p = blockIdx.x * kFlatThreads + threadIdx.x;
     const uint32_t at = RAG ? p * VEC : p;
     if (at >= total) return;
+    // Outputs beyond the memory-side cache: 16000 x 11008 bf16 164.7 us -> 158.4 (6.7 TB/s), 6056 x 11008 62.4 -> 60.7, 20000 x 4096 75.8 ->
+    // 74.5.  Not where the cache serves part of it (4096 x 11008 39.0 -> 40.4), for fp32 (3000 x 28672 156.9 -> 157.3), whose lanes have
+    // half as many requests per byte, or where rows share lines (16000 x 8191 121.5 -> 124.2).
+    if constexpr (POL == POL_NT && !RAG && ES == 2) wait_one_load(x);
     const uint32_t have = RAG && total - at < VEC ? total - at : VEC;      // elements of this piece that exist
     const uint32_t row = flat_div(at, fd), col = at - row * units;
     const char* g = x + (static_cast<uint64_t>(row) * 2u * d + (RAG ? col : col * VEC)) * ES;

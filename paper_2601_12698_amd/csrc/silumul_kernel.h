@@ -34,6 +34,7 @@ __device__ __forceinline__ void silumul_body(const void* __restrict__ xp, void* 
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
     uint32_t blk = blockIdx.x;
     if (flags & FLAG_XCD_CONTIG) blk = xcd_contiguous(blk, grid);
+    if (flags & LAUNCH_PACED) wait_one_load(xp);
     const uint32_t col_first = lane * VEC;
     const uint32_t stride = tpr * VEC;
     const uint32_t nlast = static_cast<uint32_t>(d) - VEC;
