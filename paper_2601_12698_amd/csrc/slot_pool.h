@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <thread>
 
 #include "stream_slots.h"
 
@@ -39,7 +40,14 @@ public:
         if (hipStreamIsCapturing(stream, &capture) != hipSuccess) { (void)hipGetLastError(); return false; }
         int dev = -1;
         if (capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
-        lease->lock_ = std::unique_lock<std::mutex>(mu_);
+        // A launch may wait for room in its stream's queue, and that stream for something the threads waiting here have yet
+        // to do: they wait some tens of microseconds, ten launches' time, and then do without.
+        lease->lock_ = std::unique_lock<std::mutex>(mu_, std::try_to_lock);
+        for (int i = 0; i < 200 && !lease->lock_; ++i) {
+            std::this_thread::yield();
+            (void)lease->lock_.try_lock();
+        }
+        if (!lease->lock_) return false;
         Device& d = device_[dev];
         if (!d.done && !allocate(d)) return false;
         lease->slot_ = d.slots.take(reinterpret_cast<uintptr_t>(stream), d.done, kStride);

@@ -139,3 +139,31 @@ def test_more_streams_than_slots():
         x, _, r, _, w = inputs[0]
         B.addrms_split_probe(x, r, w, 1e-6, M, N, dtype, 256, s)
         s.synchronize()
+
+
+@pytest.mark.gpu
+def test_threads_that_launch_at_the_same_time():
+    """Each on a stream of its own; whoever does not get a slot in time takes the kernel that needs none."""
+    import threading
+    B.addrms_table_clear()
+    M, N, dtype, failures = 7, 40000, "bf16", []
+
+    def work(k):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                x, xok, r, rok, w = norm_inputs(M, N, dtype, 3 * k)
+                xw, rw = x.clone(), r.clone()
+                for _ in range(30):
+                    B.addrms_run(x, r, w, 1e-6, M, N, dtype)
+                    B.addrms_run(xw, rw, w, 1e-6, M, N, dtype, B.addrms_default_cfg(N, dtype))
+                torch.cuda.current_stream().synchronize()
+                assert torch.equal(bits(x), bits(xw)) and torch.equal(bits(r), bits(rw)) and xok() and rok()
+        except Exception as e:                                    # noqa: BLE001
+            failures.append(repr(e))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failures, failures
