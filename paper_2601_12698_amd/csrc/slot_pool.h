@@ -38,8 +38,9 @@ public:
         if (stream == hipStreamPerThread) return false;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &capture) != hipSuccess) { (void)hipGetLastError(); return false; }
+        // A launch goes to its stream's GPU and meets in that GPU's memory, whichever GPU is the current one.
         int dev = -1;
-        if (capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+        if (capture != hipStreamCaptureStatusNone || device_of(stream, &dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
         // A launch may wait for room in its stream's queue, and that stream for something the threads waiting here have yet
         // to do: they wait some tens of microseconds, ten launches' time, and then do without.
         lease->lock_ = std::unique_lock<std::mutex>(mu_, std::try_to_lock);
@@ -63,6 +64,11 @@ private:
         StreamSlots slots;
         uint32_t* done = nullptr;
     };
+    // The null stream's handle is the same on every GPU: it is the current one's.
+    static hipError_t device_of(hipStream_t stream, int* dev)
+    {
+        return stream == nullptr || stream == hipStreamLegacy ? hipGetDevice(dev) : hipStreamGetDevice(stream, dev);
+    }
     // 256 bytes, once per GPU, kept until the process ends.  Must not disturb a capture that another thread may be in.
     static bool allocate(Device& d)
     {
