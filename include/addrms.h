@@ -127,10 +127,12 @@ typedef struct addrms_cfg {
  * beyond 64 KiB (an occupancy cap that pads it, rows that continue in LDS, with or
  * without a cfg) raises that kernel's dynamic-LDS limit once per process, so issue
  * one such launch eagerly before capturing.  Long rows without a cfg are split over
- * workgroups that meet in device memory of the library (4 MiB per GPU, part of its
- * code object); a launch reports its end in 256 bytes of host memory, allocated once
- * per GPU by the first such call.  Captured calls and streams for which none of that
- * memory is free (four may have such work in flight) run a kernel that needs none.
+ * workgroups that meet in device memory of the library (16 MiB per GPU, part of its
+ * code object), a launch in a piece of its own until it has reported its end in 4 KiB of
+ * pinned host memory, allocated once by the first such call.  A call that finds no piece
+ * free, 2.7 ms or more of such work being in flight, waits for one as it would for room in a
+ * full queue, at most 4 ms, and not again after a wait in vain until one has been free; then,
+ * and where the stream is capturing, it runs a kernel that needs none.
  */
 int addrms_run(void* x, void* residual, const void* weight, float eps,
                int64_t M, int64_t N, int dtype, const addrms_cfg* cfg, void* stream);
@@ -450,8 +452,8 @@ int addrms_table_load(const char* path);
 int addrms_rstd_probe(const double* ss, int64_t n, int64_t N, float eps, float* out, void* stream);
 
 /* addrms_run without a configuration, for problems whose rows it splits over several workgroups (long rows); others are
- * ADDRMS_ERR_UNSUPPORTED_SHAPE, and ADDRMS_ERR_NO_RESULT is a stream that can have none of the memory the workgroups meet in
- * (addrms_run then runs another kernel: a capturing stream, or a fifth one with such work in flight).  A workgroup that has
+ * ADDRMS_ERR_UNSUPPORTED_SHAPE, and ADDRMS_ERR_NO_RESULT is a call for which none of the memory the workgroups meet in is to be
+ * had (addrms_run then runs another kernel: the stream is capturing, or other such work has it all).  A workgroup that has
  * looked `patience` times for what the others of its row owe it forms the missing sums itself, so that no launch depends on
  * all of them being on the chip at once; 0 makes that happen in every launch.  Same arguments and results as addrms_run. */
 int addrms_split_probe(void* x, void* residual, const void* weight, float eps, int64_t M, int64_t N, int dtype,
@@ -483,9 +485,10 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
  * per-workgroup partial counts live in arrays that are part of the library's device code (one copy per GPU, held until
  * the process ends), so this call allocates no device memory, frees nothing and does not wait: its kernels are only
  * enqueued on `stream`, and counts_out is valid once the stream has reached them.  Up to 96 workgroups (4096 elements of
- * 16 bits or 2048 of 32 each) are one kernel, where the stream is not capturing and fewer than four others have such a
- * call in flight (these calls report their end in 256 bytes of host memory, allocated once per GPU by the first of them);
- * else two.  Nothing in it is a memset: a capturing caller records two kernel nodes, or one for a single workgroup.
+ * 16 bits or 2048 of 32 each) are one kernel, unless the stream is capturing; else two.  (One-kernel calls report their end
+ * in 1 KiB of pinned host memory, allocated once by the first of them.  With 256 of them in flight a call waits for one to
+ * end as it would for room in a full queue, at most 4 ms, and not again after a wait in vain until one has ended; then it
+ * is two kernels.)  Nothing in it is a memset: a capturing caller records two kernel nodes, or one for a single workgroup.
  * n beyond 2^32-1 is INVALID_ARG as above (the arrays never limit n: a launch uses at most 512 workgroups whatever n is).
  * Every call on a GPU may use that GPU's array: calls that may overlap in time on one GPU (different streams, concurrent
  * graphs) race on it and must be serialised by the caller; calls on one stream are ordered and safe. */

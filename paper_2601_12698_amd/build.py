@@ -139,7 +139,7 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
     objs = [u[:-4] + ".o" for u in units]
     hdrs = [os.path.join(ROOT, "include", "addrms.h"), os.path.join(ROOT, "include", "silumul.h"), os.path.join(ROOT, "include", "mergestates.h"),
             os.path.join(CSRC, "addrms_internal.h"), os.path.join(CSRC, "direct_route.h"),
-            os.path.join(CSRC, "stream_slots.h"), os.path.join(CSRC, "slot_pool.h")]
+            os.path.join(CSRC, "slot_map.h"), os.path.join(CSRC, "slot_pool.h")]
     gen = [os.path.join(BUILD, f) for f in ("gen_instances.inc", "gen_resources.inc",
                                              "gen_dispatch_decl.inc", "gen_dispatch_rows.inc")]
     for name in ("addrms_cfg.cpp", "addrms_table.cpp", "addrms_search.cpp", "addrms_general.cpp", "addrms_audit.cpp", "direct_route.cpp"):
@@ -150,11 +150,11 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
         objs.append(obj)
     dev_hdrs = [os.path.join(CSRC, f) for f in ("addrms_kernel.h", "silumul_kernel.h", "mergestates_kernel.h",
                                                  "direct_kernel.h", "addrms_direct.h")]
-    for name in ("addrms_runtime.hip", "addrms_direct.hip"):
+    for name in ("addrms_runtime.hip", "addrms_direct.hip", "addrms_split.hip"):
         src = os.path.join(CSRC, name)
         obj = os.path.join(BUILD, name[:-4] + ".o")
         if force or not _newer(obj, src, *dev_hdrs, *hdrs, *gen):
-            _run(["hipcc", *DEVICE_FLAGS, *(PRELOAD_FLAGS if name == "addrms_direct.hip" else []), *INCLUDES, "-c", src, "-o", obj])
+            _run(["hipcc", *DEVICE_FLAGS, *(PRELOAD_FLAGS if name != "addrms_runtime.hip" else []), *INCLUDES, "-c", src, "-o", obj])
         objs.append(obj)
     tmp = LIB + f".{os.getpid()}.tmp"
     _run(["hipcc", "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *objs])

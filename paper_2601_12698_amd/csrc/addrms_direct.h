@@ -22,10 +22,14 @@ bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_ali
 // hipError_t of the launch.
 int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
                          void* stream);
-// Only the kernel of rows split over workgroups, where the route has one (direct_launch_addrms prefers it).  False: the
-// stream can have no slot (slot_pool.h), and nothing was launched.  patience: see split_row_sum.
-bool direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
-                         unsigned patience, void* stream, int* status);
+// The kernel of rows split over workgroups; NULL where the route splits none.
+const void* direct_split_fn(const DirectRoute& p, int dtype);
+constexpr unsigned kSplitPatience = 256;                    // reads of a row's words, some hundreds of microseconds
+// Only the kernel of rows split over workgroups, where the route has one (direct_launch_addrms prefers it).  Returns how many
+// of the M rows have been launched: fewer where a launch failed (*status, a hipError_t) or could have no units (slot_pool.h).
+// patience: see split_row_sum.
+int64_t direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
+                            unsigned patience, void* stream, int* status);
 int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream);
 int direct_launch_mergestates(const DirectPlan& p, const void* va, const float* sa, const void* vb, const float* sb, void* vo,
                               float* so, void* stream);

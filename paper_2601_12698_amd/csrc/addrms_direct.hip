@@ -1,20 +1,13 @@
 // Launches without a configuration: the instances of direct_kernel.h, and the launches of what direct_route.cpp decides.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <atomic>
 #include <cstdint>
 
 #include "addrms_direct.h"
 #include "direct_kernel.h"
-#include "slot_pool.h"
 
 using namespace addrms;
-
-// Where the workgroups of split rows meet: 4 MB that belong to the loaded code object, one copy per GPU, all zero between
-// launches.
-static __device__ SplitRow split_rows[kStreamSlots][kSplitRows];
-static __device__ SplitLaunch split_launch[kStreamSlots];
 
 namespace {
 
@@ -31,12 +24,6 @@ __global__ __launch_bounds__(kLongThreads) void addrms_long(void* x, void* r, co
                                                             unsigned lds_chunks)
 {
     addrms_long_body<DT, VEC, kLongRegValues / VEC, 2, POL, RAG>(x, r, w, eps, inv_n, N, lds_chunks);
-}
-template <int DT, int VEC, int CPT, int POL, bool RAG>
-__global__ __launch_bounds__(1024) void addrms_split(void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned shape,
-                                                     unsigned rows, unsigned slot, uint32_t* done, uint32_t number, unsigned patience)
-{
-    addrms_split_body<DT, VEC, CPT, POL, RAG>(x, r, w, inv_n, eps, N, shape & 0xffffu, shape >> 16, rows, split_rows[slot], &split_launch[slot], done, number, patience);
 }
 template <int DT, int POL, bool RAG>
 __global__ __launch_bounds__(kFlatThreads) void silumul_flat(const char* x, char* out, uint32_t d, uint32_t units,
@@ -114,38 +101,6 @@ const void* addrms_long_fn(int dtype, int pol, bool rag)
     }
 }
 
-template <int DT, int CPT, int POL> const void* addrms_split_fn2(bool rag)
-{
-    constexpr int VEC = direct_vec(DT);
-    if constexpr (split_instance(CPT, POL))
-        return rag ? reinterpret_cast<const void*>(&addrms_split<DT, VEC, CPT, POL, true>)
-                   : reinterpret_cast<const void*>(&addrms_split<DT, VEC, CPT, POL, false>);
-    else return nullptr;
-}
-template <int DT, int CPT> const void* addrms_split_fn1(int pol, bool rag)
-{
-    return pol == POL_NT ? addrms_split_fn2<DT, CPT, POL_NT>(rag) : addrms_split_fn2<DT, CPT, POL_WT>(rag);
-}
-template <int DT> const void* addrms_split_fn(int cpt, int pol, bool rag)
-{
-    switch (cpt) {
-    case 1: return addrms_split_fn1<DT, 1>(pol, rag);
-    case 2: return addrms_split_fn1<DT, 2>(pol, rag);
-    case 4: return addrms_split_fn1<DT, 4>(pol, rag);
-    default: return nullptr;
-    }
-}
-const void* addrms_split_fn(int dtype, int cpt, int pol, bool rag)
-{
-    switch (dtype) {
-    case DT_BF16: return addrms_split_fn<DT_BF16>(cpt, pol, rag);
-    case DT_FP16: return addrms_split_fn<DT_FP16>(cpt, pol, rag);
-    case DT_FP16_RES32: return addrms_split_fn<DT_FP16_RES32>(cpt, pol, rag);
-    case DT_FP32: return addrms_split_fn<DT_FP32>(cpt, pol, rag);
-    default: return nullptr;
-    }
-}
-
 template <int DT> const void* silumul_fn1(int pol, bool rag)
 {
     if (rag) return pol == POL_NT ? reinterpret_cast<const void*>(&silumul_flat<DT, POL_NT, true>)
@@ -177,7 +132,7 @@ bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintpt
     if (!direct_addrms_route(M, N, dtype, default_vec, x, r, w, out)) return false;
     if (out->long_row) {
         out->fn = addrms_long_fn(dtype, out->pol, out->rag);
-        if (out->parts) out->split_fn = addrms_split_fn(dtype, out->part_cpt, out->part_pol, out->rag);
+        out->split_fn = direct_split_fn(*out, dtype);
         out->long_index = static_cast<unsigned>(dtype) * 4u + (out->pol == POL_NT ? 2u : 0u) + (out->rag ? 1u : 0u);
     } else {
         out->fn = addrms_fn(dtype, out->cpt, out->pol, out->rag, out->block_y > 1);
@@ -197,7 +152,7 @@ bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_ali
     return true;
 }
 
-static int go(const DirectPlan& p, void** args, void* stream)
+static int go(const DirectPlan& p, unsigned grid, void** args, void* stream)
 {
     if (p.lds > 64u * 1024u) {                                 // beyond the default limit: once per kernel, as launch_instance
         static std::atomic<uint64_t> allowed{0};               // one bit per long-row kernel
@@ -208,58 +163,34 @@ static int go(const DirectPlan& p, void** args, void* stream)
             allowed.fetch_or(bit, std::memory_order_acq_rel);
         }
     }
-    return static_cast<int>(hipLaunchKernel(p.fn, dim3(p.grid), dim3(p.block_x, p.block_y), args, p.lds,
+    return static_cast<int>(hipLaunchKernel(p.fn, dim3(grid), dim3(p.block_x, p.block_y), args, p.lds,
                                             static_cast<hipStream_t>(stream)));
-}
-
-// ---- split rows ------------------------------------------------------------------------------------
-static SlotPool g_split_slots;
-constexpr unsigned kPatience = 256;                          // reads of a row's words, some hundreds of microseconds
-
-bool direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
-                         unsigned patience, void* stream, int* status)
-{
-    SlotPool::Lease lease;
-    if (!p.split_fn || !g_split_slots.take(static_cast<hipStream_t>(stream), &lease)) return false;
-    double inv_n = 1.0 / static_cast<double>(N);
-    int n = static_cast<int>(N);
-    unsigned shape = p.part_threads | p.parts << 16, slot = lease.slot();
-    uint32_t* done = lease.done();
-    hipError_t e = hipSuccess;
-    for (int64_t row = 0; row < M && e == hipSuccess; row += kSplitRows) {
-        void *xr = static_cast<char*>(x) + row * N * x_bytes(dtype), *rr = static_cast<char*>(r) + row * N * r_bytes(dtype);
-        uint32_t number = lease.number();
-        unsigned rows = static_cast<unsigned>(std::min<int64_t>(kSplitRows, M - row));
-        void* args[] = {&xr, &rr, &w, &inv_n, &eps, &n, &shape, &rows, &slot, &done, &number, &patience};
-        e = hipLaunchKernel(p.split_fn, dim3(p.parts, rows), dim3(p.part_threads), args, 17u * sizeof(double), static_cast<hipStream_t>(stream));
-        if (e == hipSuccess) lease.launched();
-    }
-    *status = static_cast<int>(e);
-    return true;
 }
 
 int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype, void* stream)
 {
     int status;
-    if (direct_launch_split(p, x, r, w, eps, M, N, dtype, kPatience, stream, &status)) return status;
+    const int64_t split = direct_launch_split(p, x, r, w, eps, M, N, dtype, kSplitPatience, stream, &status);
+    if (status != static_cast<int>(hipSuccess) || split == M) return status;
     double inv_n = 1.0 / static_cast<double>(N);
     long long m = M;
     int n = static_cast<int>(N);
     if (p.long_row) {
         unsigned lds_chunks = p.units;
-        void* args[] = {&x, &r, &w, &eps, &inv_n, &n, &lds_chunks};
-        return go(p, args, stream);
+        void *xr = static_cast<char*>(x) + split * N * x_bytes(dtype), *rr = static_cast<char*>(r) + split * N * r_bytes(dtype);
+        void* args[] = {&xr, &rr, &w, &eps, &inv_n, &n, &lds_chunks};
+        return go(p, static_cast<unsigned>(M - split), args, stream);
     }
     unsigned tpr = p.block_x, rpw = p.block_y;
     void* args[] = {&x, &r, &w, &inv_n, &eps, &n, &tpr, &rpw, &m};
-    return go(p, args, stream);
+    return go(p, p.grid, args, stream);
 }
 int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream)
 {
     uint32_t ud = static_cast<uint32_t>(d), units = p.units, total = p.total;
     FlatDiv fd{p.mul, p.shift};
     void* args[] = {&x, &out, &ud, &units, &total, &fd};
-    return go(p, args, stream);
+    return go(p, p.grid, args, stream);
 }
 int direct_launch_mergestates(const DirectPlan& p, const void* va, const float* sa, const void* vb, const float* sb, void* vo,
                               float* so, void* stream)
@@ -267,7 +198,7 @@ int direct_launch_mergestates(const DirectPlan& p, const void* va, const float* 
     uint32_t units = p.units, total = p.total;
     FlatDiv fd{p.mul, p.shift};
     void* args[] = {&va, &sa, &vb, &sb, &vo, &so, &units, &total, &fd};
-    return go(p, args, stream);
+    return go(p, p.grid, args, stream);
 }
 
 }  // namespace addrms_host

@@ -444,14 +444,15 @@ __device__ __forceinline__ void gate_block(unsigned& rbad, unsigned& ybad, unsig
 // 6.9, 384 k (96) 5.6 / 7.1, 640 k (160) 6.4 / 7.3, 768 k (192) 7.0 / 6.6, 16 M (512) 25.8 / 23.2: workgroups that arrive together are
 // counted one after the other, 10 ns each (in groups and then the groups: another trip to memory, 24.6 / 23.2).
 constexpr int kGateMeetMax = 96;
-// Where they meet: all zero between launches.
+// Where they meet.  A unit that no launch has is all zero.
 constexpr uint64_t kGateHere = 1ull << 63;
 struct __align__(128) GateWords { uint64_t bad, most; };
 struct GateMeeting {
     GateWords words[kGateMeetMax];
     __align__(128) uint32_t arrived;
 };
-static __device__ GateMeeting gate_meeting[addrms::kStreamSlots];
+constexpr int kGateUnits = 256;                          // launches in flight: 1 ms of them
+static __device__ GateMeeting gate_meeting[kGateUnits];
 
 __device__ __forceinline__ uint64_t gate_word(const uint64_t* w)
 {
@@ -550,12 +551,12 @@ __global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(const char* y,
 }
 template <int XB, int RB>
 __global__ __launch_bounds__(kGateBlock) void gate_one_kernel(const char* y, const char* y_ref, const char* r, const char* r_ref,
-                                                               long long n, unsigned tol, unsigned* out, unsigned slot,
+                                                               long long n, unsigned tol, unsigned* out, unsigned unit,
                                                                uint32_t* done, uint32_t number)
 {
     unsigned rbad, ybad, ymax;
     gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, rbad, ybad, ymax);
-    if (gridDim.x > 1u) gate_meet(rbad, ybad, ymax, &gate_meeting[slot], out, done, number);
+    if (gridDim.x > 1u) gate_meet(rbad, ybad, ymax, &gate_meeting[unit], out, done, number);
     else if (threadIdx.x == 0) *reinterpret_cast<addrms::u32x4*>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
 }
 // One workgroup.  accumulate != 0 folds the new counts into what `out` already holds
@@ -608,26 +609,26 @@ int launch_gate(const void* y, const void* y_ref, const void* r, const void* r_r
     return ADDRMS_OK;
 }
 
-SlotPool g_gate_slots;
+SlotPool<kGateUnits> g_gate_slots;
 
-// The gate in one launch, where one workgroup does it or a few and the stream can have a slot.  *launched: whether it was.
+// The gate in one launch, where one workgroup does it or a few and the launch can have a unit.  *launched: whether it was.
 int launch_gate_in_one(const void* y, const void* y_ref, const void* r, const void* r_ref, long long n, int xb, int rb, unsigned tol,
                        unsigned* out, hipStream_t stream, bool* launched)
 {
     const int workgroups = gate_grid(n, xb);
-    SlotPool::Lease lease;
-    *launched = workgroups <= kGateMeetMax && (workgroups == 1 || g_gate_slots.take(stream, &lease));
+    SlotPool<kGateUnits>::Lease lease;
+    *launched = workgroups <= kGateMeetMax && (workgroups == 1 || g_gate_slots.take(stream, 1, &lease));
     if (!*launched) return ADDRMS_OK;
     const bool meet = workgroups > 1;
-    const unsigned slot = meet ? lease.slot() : 0u;
+    const unsigned unit = meet ? lease.unit() : 0u;
     uint32_t* done = meet ? lease.done() : nullptr;
     const uint32_t number = meet ? lease.number() : 0u;
     const dim3 block(kGateBlock), grid(static_cast<unsigned>(workgroups));
     const char *py = static_cast<const char*>(y), *pyr = static_cast<const char*>(y_ref);
     const char *pr = static_cast<const char*>(r), *prr = static_cast<const char*>(r_ref);
-    if (xb == 2 && rb == 2) hipLaunchKernelGGL((gate_one_kernel<2, 2>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, slot, done, number);
-    else if (xb == 2) hipLaunchKernelGGL((gate_one_kernel<2, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, slot, done, number);
-    else hipLaunchKernelGGL((gate_one_kernel<4, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, slot, done, number);
+    if (xb == 2 && rb == 2) hipLaunchKernelGGL((gate_one_kernel<2, 2>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, unit, done, number);
+    else if (xb == 2) hipLaunchKernelGGL((gate_one_kernel<2, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, unit, done, number);
+    else hipLaunchKernelGGL((gate_one_kernel<4, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, unit, done, number);
     HIP_TRY(hipGetLastError());
     if (meet) lease.launched();
     return ADDRMS_OK;
@@ -1320,9 +1321,9 @@ int addrms_split_probe(void* x, void* residual, const void* weight, float eps, i
     if (!direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(residual), bits(weight), &p) || !p.split_fn)
         return fail(ADDRMS_ERR_UNSUPPORTED_SHAPE, "rows of this problem are not split over workgroups");
     int e = 0;
-    if (!direct_launch_split(p, x, residual, weight, eps, M, N, dtype, patience, stream, &e))
-        return fail(ADDRMS_ERR_NO_RESULT, "this stream can have no slot for split rows now");
+    const int64_t rows = direct_launch_split(p, x, residual, weight, eps, M, N, dtype, patience, stream, &e);
     HIP_TRY(static_cast<hipError_t>(e));
+    if (rows < M) return fail(ADDRMS_ERR_NO_RESULT, "the call can have no units for split rows now (%lld rows are launched)", (long long)rows);
     return ADDRMS_OK;
 }
 

@@ -1,0 +1,100 @@
+// Long rows without a configuration, split over workgroups: the instances of addrms_split_body and their launch.  A code
+// object of their own, because the memory in it is cleared when it is loaded, with the first of these launches (some
+// milliseconds), and other calls should not pay for that.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+
+#include "addrms_direct.h"
+#include "direct_kernel.h"
+#include "slot_pool.h"
+
+using namespace addrms;
+
+// Where the workgroups of split rows meet: memory that belongs to the loaded code object, one copy per GPU.  A unit that no
+// launch has is all zero.
+static __device__ SplitRow split_rows[kSplitUnits][kSplitUnitRows];
+static __device__ SplitLaunch split_launch[kSplitUnits];
+
+namespace {
+
+template <int DT, int VEC, int CPT, int POL, bool RAG>
+__global__ __launch_bounds__(1024) void addrms_split(void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned shape,
+                                                     unsigned rows, unsigned unit, uint32_t* done, uint32_t number, unsigned patience)
+{
+    addrms_split_body<DT, VEC, CPT, POL, RAG>(x, r, w, inv_n, eps, N, shape & 0xffffu, shape >> 16, rows, split_rows[unit],
+                                              &split_launch[unit], done, number, patience);
+}
+
+template <int DT, int CPT, int POL> const void* addrms_split_fn2(bool rag)
+{
+    constexpr int VEC = direct_vec(DT);
+    if constexpr (split_instance(CPT, POL))
+        return rag ? reinterpret_cast<const void*>(&addrms_split<DT, VEC, CPT, POL, true>)
+                   : reinterpret_cast<const void*>(&addrms_split<DT, VEC, CPT, POL, false>);
+    else return nullptr;
+}
+template <int DT, int CPT> const void* addrms_split_fn1(int pol, bool rag)
+{
+    return pol == POL_NT ? addrms_split_fn2<DT, CPT, POL_NT>(rag) : addrms_split_fn2<DT, CPT, POL_WT>(rag);
+}
+template <int DT> const void* addrms_split_fn(int cpt, int pol, bool rag)
+{
+    switch (cpt) {
+    case 1: return addrms_split_fn1<DT, 1>(pol, rag);
+    case 2: return addrms_split_fn1<DT, 2>(pol, rag);
+    case 4: return addrms_split_fn1<DT, 4>(pol, rag);
+    default: return nullptr;
+    }
+}
+const void* addrms_split_fn(int dtype, int cpt, int pol, bool rag)
+{
+    switch (dtype) {
+    case DT_BF16: return addrms_split_fn<DT_BF16>(cpt, pol, rag);
+    case DT_FP16: return addrms_split_fn<DT_FP16>(cpt, pol, rag);
+    case DT_FP16_RES32: return addrms_split_fn<DT_FP16_RES32>(cpt, pol, rag);
+    case DT_FP32: return addrms_split_fn<DT_FP32>(cpt, pol, rag);
+    default: return nullptr;
+    }
+}
+
+}  // namespace
+
+namespace addrms_host {
+
+const void* direct_split_fn(const DirectRoute& p, int dtype)
+{
+    return p.parts ? addrms_split_fn(dtype, p.part_cpt, p.part_pol, p.rag) : nullptr;
+}
+
+static SlotPool<kSplitUnits> g_split_slots;
+
+int64_t direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
+                            unsigned patience, void* stream, int* status)
+{
+    *status = static_cast<int>(hipSuccess);
+    if (!p.split_fn) return 0;
+    double inv_n = 1.0 / static_cast<double>(N);
+    int n = static_cast<int>(N);
+    unsigned shape = p.part_threads | p.parts << 16;
+    int64_t row = 0;
+    while (row < M) {
+        unsigned rows = static_cast<unsigned>(std::min<int64_t>(kSplitRows, M - row));
+        SlotPool<kSplitUnits>::Lease lease;
+        if (!g_split_slots.take(static_cast<hipStream_t>(stream), (static_cast<int>(rows) + kSplitUnitRows - 1) / kSplitUnitRows, &lease)) break;
+        void *xr = static_cast<char*>(x) + row * N * x_bytes(dtype), *rr = static_cast<char*>(r) + row * N * r_bytes(dtype);
+        unsigned unit = lease.unit();
+        uint32_t *done = lease.done(), number = lease.number();
+        void* args[] = {&xr, &rr, &w, &inv_n, &eps, &n, &shape, &rows, &unit, &done, &number, &patience};
+        const hipError_t e = hipLaunchKernel(p.split_fn, dim3(p.parts, rows), dim3(p.part_threads), args, 17u * sizeof(double),
+                                             static_cast<hipStream_t>(stream));
+        *status = static_cast<int>(e);
+        if (e != hipSuccess) break;
+        lease.launched();
+        row += rows;
+    }
+    return row;
+}
+
+}  // namespace addrms_host

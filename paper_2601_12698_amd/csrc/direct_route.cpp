@@ -51,7 +51,7 @@ bool launchable(int64_t workgroups, int64_t threads) { return workgroups <= UINT
 
 namespace addrms_host {
 
-// Long rows split over workgroups (addrms_split_body), where the stream can have a slot.  16384 elements to a part where a
+// Long rows split over workgroups (addrms_split_body), where the launch can have units.  16384 elements to a part where a
 // thread has eight to a piece, 12288 where it has four: four pieces per thread of 512 or 768 threads, of which a CU holds two
 // (1024 x 131072 bf16 in 4 / 8 / 16 parts 183 / 173 / 180; 500 x 200000 fp32 in 13 / 17 / 25 of four pieces 265 / 259 / 271).  Fewer rows
 // than that keeps the chip busy with are cut finer, down to 512 pieces, up to 512 workgroups in all, with as few pieces per

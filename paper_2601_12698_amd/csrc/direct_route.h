@@ -32,6 +32,9 @@ constexpr bool direct_instance(int vec, int cpt, int pol, bool rag, bool multi)
 }
 
 constexpr int kSplitRows = 4096;                             // rows of one launch of split rows; more are several launches
+// The memory that they meet in: units of 64 rows (16 KB), 16 MB in all.  A row is at least 32769 elements long, 42 ns of
+// bf16 at 6.2 TB/s, so that all units are taken no sooner than 2.7 ms of such launches are in flight.
+constexpr int kSplitUnits = 1024, kSplitUnitRows = 64;
 constexpr int kSplitParts = 16;                              // workgroups a row may be split over
 // The kernels of split rows: pieces per thread and store policy.  With fewer than four pieces 512 workgroups are within 32 MB.
 constexpr bool split_instance(int cpt, int pol) { return cpt == 4 ? pol == POL_NT || pol == POL_WT : (cpt == 1 || cpt == 2) && pol == POL_NT; }
@@ -48,7 +51,7 @@ struct DirectRoute {
     bool long_row = false;                                  // rows beyond the registers: units = chunks parked in LDS
     unsigned grid = 0, block_x = 0, block_y = 1, lds = 0;   // block_y: rows of a workgroup
     unsigned units = 0, total = 0, mul = 0, shift = 0;      // flat operators: see direct_kernel.h
-    // Long rows that are split over workgroups where the stream can have a slot (stream_slots.h); the rest of the route is
+    // Long rows that are split over workgroups where the launch can have units (slot_map.h); the rest of the route is
     // what runs where it cannot.
     unsigned parts = 0, part_threads = 0;                   // 0: not split
     int part_cpt = 0, part_pol = 0;

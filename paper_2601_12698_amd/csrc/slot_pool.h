@@ -1,90 +1,108 @@
-// Slots of device memory for launches whose workgroups meet in it (stream_slots.h has the rule), and the host memory in which
-// these launches report that they are done with their slot.
+// Units of device memory for launches whose workgroups meet in it (slot_map.h has the rule), and the host memory in which
+// these launches report that they are done with theirs.
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <mutex>
 #include <thread>
 
-#include "stream_slots.h"
+#include "slot_map.h"
 
 namespace addrms_host {
 
 // One pool per kind of launch, for all GPUs.
+template <int UNITS>
 class SlotPool {
 public:
-    // A slot, held from its choice to the launches that use it.
+    // A launch's units.  They go back where launched() is not called.
     class Lease {
     public:
-        unsigned slot() const { return static_cast<unsigned>(slot_); }
-        // What the next launch is to write, and where, when it is done with the slot (system scope, the launch's last access).
-        uint32_t number() const { return slots_->next(slot_); }
+        Lease() = default;
+        Lease(const Lease&) = delete;
+        Lease& operator=(const Lease&) = delete;
+        ~Lease() { if (pool_) pool_->give_back(unit_); }
+        unsigned unit() const { return static_cast<unsigned>(unit_); }
+        // What the launch is to write, and where, when it is done with its units (system scope, its last access).
+        uint32_t number() const { return number_; }
         uint32_t* done() const { return done_; }
-        void launched() { slots_->launched(slot_); }
+        void launched() { pool_ = nullptr; }
 
     private:
         friend class SlotPool;
-        std::unique_lock<std::mutex> lock_;
-        StreamSlots* slots_ = nullptr;
+        SlotPool* pool_ = nullptr;
         uint32_t* done_ = nullptr;
-        int slot_ = -1;
+        uint32_t number_ = 0;
+        int unit_ = -1;
     };
 
-    // False: none.  A graph may be replayed on any stream and beside others, so that no slot is its own: a capturing stream
-    // has none.  Nor has the per-thread default stream, one handle for as many streams as threads.
-    bool take(hipStream_t stream, Lease* lease)
+    // False: none.  A graph may be replayed beside itself and others, so that no units are its own: a capturing stream has none.
+    // Where launches in flight have them all, this one waits for one of them to end, as it would for room in a full queue: a
+    // program that queues 400 launches of 172 us at once gets 172.5 us each, and 194.7 where those that find no units take the
+    // other kernel.  But what is in flight may depend on something that the caller has yet to do.  So the wait is bounded, and
+    // after one in vain nobody waits until units have been found again.
+    bool take(hipStream_t stream, int units, Lease* lease)
     {
-        if (stream == hipStreamPerThread) return false;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &capture) != hipSuccess) { (void)hipGetLastError(); return false; }
-        // A launch goes to its stream's GPU and meets in that GPU's memory, whichever GPU is the current one.
-        int dev = -1;
-        if (capture != hipStreamCaptureStatusNone || device_of(stream, &dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
-        // A launch may wait for room in its stream's queue, and that stream for something the threads waiting here have yet
-        // to do: they wait some tens of microseconds, ten launches' time, and then do without.
-        lease->lock_ = std::unique_lock<std::mutex>(mu_, std::try_to_lock);
-        for (int i = 0; i < 200 && !lease->lock_; ++i) {
-            std::this_thread::yield();
-            (void)lease->lock_.try_lock();
+        uint32_t* done = capture == hipStreamCaptureStatusNone ? reports() : nullptr;
+        if (!done) return false;
+        using clock = std::chrono::steady_clock;
+        for (clock::time_point began{};; std::this_thread::sleep_for(std::chrono::microseconds(20))) {
+            std::lock_guard<std::mutex> lock(mu_);
+            const int u = map_.take(units, done);
+            in_vain_ = in_vain_ && u < 0;
+            if (u >= 0) {
+                lease->pool_ = this;
+                lease->done_ = done + u;
+                lease->number_ = map_.number(u);
+                lease->unit_ = u;
+                return true;
+            }
+            if (in_vain_) return false;
+            if (began == clock::time_point{}) began = clock::now();
+            else if (clock::now() - began > std::chrono::milliseconds(4)) {
+                in_vain_ = true;
+                return false;
+            }
         }
-        if (!lease->lock_) return false;
-        Device& d = device_[dev];
-        if (!d.done && !allocate(d)) return false;
-        lease->slot_ = d.slots.take(reinterpret_cast<uintptr_t>(stream), d.done, kStride);
-        if (lease->slot_ < 0) return false;
-        lease->slots_ = &d.slots;
-        lease->done_ = d.done + lease->slot_ * kStride;
-        return true;
     }
 
 private:
-    static constexpr int kMaxDevices = 64, kStride = 16;     // one 64-byte line of host memory per slot
-    struct Device {
-        StreamSlots slots;
-        uint32_t* done = nullptr;
-    };
-    // The null stream's handle is the same on every GPU: it is the current one's.
-    static hipError_t device_of(hipStream_t stream, int* dev)
+    void give_back(int unit)
     {
-        return stream == nullptr || stream == hipStreamLegacy ? hipGetDevice(dev) : hipStreamGetDevice(stream, dev);
+        std::lock_guard<std::mutex> lock(mu_);
+        map_.give_back(unit);
     }
-    // 256 bytes, once per GPU, kept until the process ends.  Must not disturb a capture that another thread may be in.
-    static bool allocate(Device& d)
+    // One word per unit, which every GPU can write, allocated once and kept until the process ends.  NULL: not there (yet: no
+    // thread waits for the one that allocates it).  Must not disturb a capture that another thread may be in.
+    uint32_t* reports()
     {
+        uint32_t* done = done_.load(std::memory_order_acquire);
+        if (done || allocating_.exchange(true)) return done;
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
-        void* p = nullptr;
-        const size_t n = static_cast<size_t>(addrms::kStreamSlots) * kStride;
-        const hipError_t e = hipHostMalloc(&p, n * sizeof(uint32_t), hipHostMallocDefault);
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (e != hipSuccess) { (void)hipGetLastError(); return false; }
-        std::fill_n(static_cast<uint32_t*>(p), n, 0u);
-        d.done = static_cast<uint32_t*>(p);
-        return true;
+        if (hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
+            void* p = nullptr;
+            const hipError_t e = hipHostMalloc(&p, UNITS * sizeof(uint32_t), hipHostMallocPortable);
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+            if (e == hipSuccess) done = static_cast<uint32_t*>(p);
+            else (void)hipGetLastError();
+        }
+        if (done) {
+            std::fill_n(done, UNITS, 0u);
+            done_.store(done, std::memory_order_release);
+        } else {
+            allocating_.store(false);
+        }
+        return done;
     }
     std::mutex mu_;
-    Device device_[kMaxDevices];
+    SlotMap<UNITS> map_;
+    bool in_vain_ = false;
+    std::atomic<uint32_t*> done_{nullptr};
+    std::atomic<bool> allocating_{false};
 };
 
 }  // namespace addrms_host

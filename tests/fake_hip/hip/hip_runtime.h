@@ -14,7 +14,7 @@ typedef struct ihipStream_t* hipStream_t;
 typedef int hipDevice_t;
 #define hipStreamLegacy ((hipStream_t)1)
 #define hipStreamPerThread ((hipStream_t)2)
-constexpr unsigned hipHostMallocDefault = 0;
+constexpr unsigned hipHostMallocDefault = 0, hipHostMallocPortable = 1;
 
 namespace fake_hip {
 inline int current = 0;

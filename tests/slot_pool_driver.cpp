@@ -9,6 +9,8 @@ using namespace addrms_host;
 
 #define EXPECT(c) do { if (!(c)) { printf("line %d: %s\n", __LINE__, #c); return 1; } } while (0)
 
+using Pool = SlotPool<8>;
+
 static hipStream_t stream(size_t handle, int device)
 {
     const hipStream_t s = reinterpret_cast<hipStream_t>(handle);
@@ -16,19 +18,19 @@ static hipStream_t stream(size_t handle, int device)
     return s;
 }
 
-// A launch that is queued and does not end: the slot it has.
-static int launch(SlotPool& pool, hipStream_t s)
+// A launch that is queued and does not end: the unit it has.
+static int launch(Pool& pool, hipStream_t s)
 {
-    SlotPool::Lease lease;
-    if (!pool.take(s, &lease)) return -1;
+    Pool::Lease lease;
+    if (!pool.take(s, 1, &lease)) return -1;
     lease.launched();
-    return static_cast<int>(lease.slot());
+    return static_cast<int>(lease.unit());
 }
 
 // Launches on streams of one GPU, in flight together, with another GPU current at some of the calls.
 static int devices()
 {
-    static SlotPool pool;
+    static Pool pool;
     const hipStream_t a = stream(0x1000, 1), b = stream(0x2000, 1);
     fake_hip::current = 0;
     const int first = launch(pool, a);
@@ -43,9 +45,67 @@ static int devices()
     return 0;
 }
 
+// A stream that is destroyed with its launch in flight, and another one that is created and gets the same handle.
+static int handles()
+{
+    static Pool pool;
+    const int first = launch(pool, stream(0x1000, 0));
+    fake_hip::device.clear();
+    const int second = launch(pool, stream(0x1000, 0));
+    EXPECT(first >= 0 && second >= 0 && first != second);
+    return 0;
+}
+
+// All units in flight: a call waits for one, for a bounded time, and after that nobody does until one has been free again.
+static int waiting()
+{
+    static Pool pool;
+    using clock = std::chrono::steady_clock;
+    const auto ms = [](clock::time_point since) { return std::chrono::duration<double, std::milli>(clock::now() - since).count(); };
+    const hipStream_t s = stream(0x1000, 0);
+    Pool::Lease all, one;
+    EXPECT(pool.take(s, 8, &all));
+    all.launched();
+    clock::time_point t = clock::now();
+    EXPECT(launch(pool, s) == -1 && ms(t) > 4.0);
+    t = clock::now();
+    for (int i = 0; i < 20; ++i) EXPECT(launch(pool, s) == -1);
+    EXPECT(ms(t) < 40.0);                                    // 20 waits would be 80
+    *all.done() = all.number();
+    EXPECT(pool.take(s, 8, &one));
+    one.launched();
+    std::thread ends([&] { std::this_thread::sleep_for(std::chrono::milliseconds(1)); __atomic_store_n(one.done(), one.number(), __ATOMIC_SEQ_CST); });
+    const int got = launch(pool, s);
+    ends.join();
+    EXPECT(got >= 0);
+    return 0;
+}
+
+// Units go back where nothing was launched, and once a launch has reported itself; a capturing stream has none.
+static int leases()
+{
+    static Pool pool;
+    const hipStream_t s = stream(0x1000, 0), capturing = stream(0x2000, 0);
+    for (int i = 0; i < 100; ++i) {
+        Pool::Lease lease;
+        EXPECT(pool.take(s, 3, &lease));
+    }
+    for (int i = 0; i < 100; ++i) {
+        Pool::Lease lease;
+        EXPECT(pool.take(hipStreamPerThread, 3, &lease));
+        lease.launched();
+        *lease.done() = lease.number();
+    }
+    fake_hip::capturing.insert(capturing);
+    Pool::Lease lease;
+    EXPECT(!pool.take(capturing, 1, &lease) && pool.take(s, 8, &lease));
+    fake_hip::capturing.clear();
+    return 0;
+}
+
 int main(int, char** argv)
 {
-    const int bad = !strcmp(argv[1], "devices") ? devices() : 1;
+    const int bad = !strcmp(argv[1], "devices") ? devices() : !strcmp(argv[1], "handles") ? handles() : !strcmp(argv[1], "waiting") ? waiting() : leases();
     if (!bad) printf("ok\n");
     return bad;
 }

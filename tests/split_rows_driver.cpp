@@ -1,5 +1,6 @@
-// Slots of split rows (stream_slots.h) and the shapes in which rows are split, for tests/test_split_rows.py.  Host code only.
-//   slots   who gets which slot; prints "ok"
+// Units of the memory that split rows meet in (slot_map.h) and the shapes in which rows are split, for
+// tests/test_split_rows.py.  Host code only.
+//   slots   who gets which units; prints "ok"
 //   walk    the split of rows of many lengths and numbers; prints the number of decisions and the kernels asked for
 //   (no argument)  one problem per line: dtype M N; one split per line of output
 #include <stdio.h>
@@ -8,44 +9,63 @@
 #include <initializer_list>
 #include <set>
 #include <tuple>
+#include <vector>
 
 #include "direct_route.h"
-#include "stream_slots.h"
+#include "slot_map.h"
 
 using namespace addrms_host;
 using namespace addrms;
 
 #define EXPECT(c) do { if (!(c)) { printf("line %d: %s\n", __LINE__, #c); return 1; } } while (0)
 
+// A launch in flight is one that has taken units and not reported: no two of them have a unit in common, whatever ends when.
+static int in_any_order()
+{
+    static SlotMap<64> map;
+    uint32_t done[64] = {};
+    struct Launch { int first, units; uint32_t number; };
+    std::vector<Launch> flying;
+    uint32_t seed = 1;
+    const auto random = [&](uint32_t n) { seed = seed * 1664525u + 1013904223u; return (seed >> 16) % n; };
+    int refused = 0;
+    for (int k = 0; k < 200000; ++k) {
+        const int units = 1 + static_cast<int>(random(k % 3 == 0 ? 24 : 4));
+        const int u = map.take(units, done);
+        if (u < 0) ++refused;
+        else {
+            EXPECT(u + units <= 64);
+            for (const Launch& l : flying) EXPECT(u + units <= l.first || l.first + l.units <= u);
+            if (random(8) == 0) map.give_back(u);
+            else flying.push_back({u, units, map.number(u)});
+        }
+        for (uint32_t ends = random(3); ends && !flying.empty(); --ends) {
+            const size_t i = random(2) ? 0 : random(static_cast<uint32_t>(flying.size()));
+            done[flying[i].first] = flying[i].number;
+            flying.erase(flying.begin() + static_cast<long>(i));
+        }
+    }
+    EXPECT(refused > 100 && refused < 150000);
+    for (const Launch& l : flying) done[l.first] = l.number;
+    EXPECT(map.take(64, done) == 0);                              // nothing is lost: when all have ended, all is free
+    return 0;
+}
+
 static int slots()
 {
-    StreamSlots s;
-    uint32_t done[kStreamSlots * 2] = {};
-    int got[kStreamSlots];
-    for (int i = 0; i < kStreamSlots; ++i) {                       // streams 100, 101, ...: a slot each
-        got[i] = s.take(100u + i, done, 2);
-        EXPECT(got[i] >= 0);
-        for (int j = 0; j < i; ++j) EXPECT(got[j] != got[i]);
-        EXPECT(s.next(got[i]) == 1u);
-        s.launched(got[i]);
-    }
-    EXPECT(s.take(7, done, 2) == -1);                             // all in flight
-    for (int k = 0; k < 1000; ++k) {                              // a stream's launches share its slot, however many there are
-        EXPECT(s.take(101, done, 2) == got[1] && s.next(got[1]) == 2u + k);
-        s.launched(got[1]);
-    }
-    done[got[1] * 2] = 1000;                                      // all but the last of them
-    EXPECT(s.take(7, done, 2) == -1);
-    done[got[1] * 2] = 1001;
-    EXPECT(s.take(7, done, 2) == got[1]);                         // idle: given to another stream, the numbers go on
-    EXPECT(s.next(got[1]) == 1002u);
-    EXPECT(s.take(7, done, 2) == got[1]);                         // a launch that failed was not announced
-    s.launched(got[1]);
-    EXPECT(s.take(101, done, 2) == -1);                           // the stream that had it before has none now
-    EXPECT(s.take(100, done, 2) == got[0]);
-    done[got[3] * 2] = 1;
-    EXPECT(s.take(0, done, 2) == got[3]);                         // the null stream is a stream like others
-    EXPECT(s.take(0, done, 2) == got[3]);
+    static SlotMap<8> map;
+    uint32_t done[8] = {};
+    for (int i = 0; i < 4; ++i) EXPECT(map.take(2, done) == 2 * i && map.number(2 * i) == 1u);
+    EXPECT(map.take(1, done) == -1);                              // all in flight
+    done[4] = 1;
+    EXPECT(map.take(3, done) == -1);                              // two are free, three are not
+    EXPECT(map.take(1, done) == 4 && map.number(4) == 2u);
+    EXPECT(map.take(1, done) == 5 && map.take(1, done) == -1);
+    map.give_back(5);
+    EXPECT(map.take(1, done) == 5 && map.number(5) == 2u);        // a launch that was not made
+    done[0] = done[2] = 1;
+    EXPECT(map.take(4, done) == 0 && map.number(0) == 2u && map.take(1, done) == -1);
+    if (in_any_order()) return 1;
     printf("ok\n");
     return 0;
 }

@@ -21,8 +21,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["devices"])
-def test_slots_of_launches_in_flight(driver, what):
+@pytest.mark.parametrize("what", ["devices", "handles", "leases", "waiting"])
+def test_units_of_launches_in_flight(driver, what):
     r = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300,
                        env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
     assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout[-4000:]

@@ -1,4 +1,4 @@
-"""Rows that are split over several workgroups: who may use which slot of the memory they meet in, and the shapes in which
+"""Rows that are split over several workgroups: who may use which units of the memory they meet in, and the shapes in which
 rows are split (host code, on the CPU); the kernel itself, with every wait cut short, beside other streams and beyond the
 rows of one launch (on the GPU)."""
 import os
@@ -115,8 +115,7 @@ def test_more_rows_than_one_launch_takes():
 
 @pytest.mark.gpu
 def test_more_streams_than_slots():
-    """Six streams with several launches in flight each: four may split their rows, the others take the kernel that does
-    not; all give the same."""
+    """Six streams with several launches in flight each."""
     B.addrms_table_clear()
     M, N, dtype = 300, 50000, "bf16"
     streams = [torch.cuda.Stream() for _ in range(6)]
@@ -134,7 +133,7 @@ def test_more_streams_than_slots():
     torch.cuda.synchronize()
     for (x, xok, r, rok, _), (xw, rw) in zip(inputs, want):
         assert torch.equal(bits(x), bits(xw)) and torch.equal(bits(r), bits(rw)) and xok() and rok()
-    for _ in range(8):                                            # slots are given back: a new stream can have one
+    for _ in range(8):                                            # units are given back: a new stream can have some
         s = torch.cuda.Stream()
         x, _, r, _, w = inputs[0]
         B.addrms_split_probe(x, r, w, 1e-6, M, N, dtype, 256, s)
@@ -143,7 +142,7 @@ def test_more_streams_than_slots():
 
 @pytest.mark.gpu
 def test_threads_that_launch_at_the_same_time():
-    """Each on a stream of its own; whoever does not get a slot in time takes the kernel that needs none."""
+    """Each on a stream of its own."""
     import threading
     B.addrms_table_clear()
     M, N, dtype, failures = 7, 40000, "bf16", []
