@@ -273,7 +273,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
 }
 
 // ---- add + RMSNorm, rows beyond the registers ---------------------------------------------------
-// For streams that can have no slot (stream_slots.h; captured launches are such), rows longer than 16 parts hold, and what
+// For launches that can have no units (slot_map.h; captured ones are such), rows longer than 16 parts hold, and what
 // direct_addrms_split leaves.  The walk of addrms_hybrid_body (its comment has the three parts: registers, parked in LDS, read
 // twice) for one row per workgroup, with the store policy of the size, ragged rows, and the weights
 // of the register part fetched before the row sum, so that its stores are the first to follow it
@@ -476,7 +476,7 @@ __device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __
 // Words and counts are accessed with relaxed atomics of device scope, which go to the memory side of all XCDs' L2s, and
 // carry all that the workgroups tell each other, so that nothing else has to be made visible.  The last workgroup to have
 // read a row's words clears them, and the last row of a launch reports the launch as done, so that the words are clear
-// and nobody's before the next launch finds them (stream_slots.h has who may use which).
+// before they are another launch's (slot_map.h has who may use which).
 //
 // A row's words and its count lie on 128-byte lines of their own: with eight rows to a line the atomics of a row's
 // neighbours queue up, some 10 ns per workgroup of the launch (1024 x 131072 bf16 in 32 parts 281 us against 213).
