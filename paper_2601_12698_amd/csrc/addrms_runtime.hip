@@ -620,16 +620,14 @@ int launch_gate_in_one(const void* y, const void* y_ref, const void* r, const vo
     *launched = workgroups <= kGateMeetMax && (workgroups == 1 || g_gate_slots.take(stream, 1, &lease));
     if (!*launched) return ADDRMS_OK;
     const bool meet = workgroups > 1;
-    const unsigned unit = meet ? lease.unit() : 0u;
-    uint32_t* done = meet ? lease.done() : nullptr;
-    const uint32_t number = meet ? lease.number() : 0u;
-    const dim3 block(kGateBlock), grid(static_cast<unsigned>(workgroups));
-    const char *py = static_cast<const char*>(y), *pyr = static_cast<const char*>(y_ref);
-    const char *pr = static_cast<const char*>(r), *prr = static_cast<const char*>(r_ref);
-    if (xb == 2 && rb == 2) hipLaunchKernelGGL((gate_one_kernel<2, 2>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, unit, done, number);
-    else if (xb == 2) hipLaunchKernelGGL((gate_one_kernel<2, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, unit, done, number);
-    else hipLaunchKernelGGL((gate_one_kernel<4, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, out, unit, done, number);
-    HIP_TRY(hipGetLastError());
+    unsigned unit = meet ? lease.unit() : 0u;
+    uint32_t *done = meet ? lease.done() : nullptr, number = meet ? lease.number() : 0u;
+    const void* fn = xb == 4   ? reinterpret_cast<const void*>(&gate_one_kernel<4, 4>)
+                     : rb == 4 ? reinterpret_cast<const void*>(&gate_one_kernel<2, 4>)
+                               : reinterpret_cast<const void*>(&gate_one_kernel<2, 2>);
+    void* args[] = {&y, &y_ref, &r, &r_ref, &n, &tol, &out, &unit, &done, &number};
+    // The launch's own status: hipGetLastError may have an older error, of the caller's, for a launch that is queued.
+    HIP_TRY(hipLaunchKernel(fn, dim3(static_cast<unsigned>(workgroups)), dim3(kGateBlock), args, 0, stream));
     if (meet) lease.launched();
     return ADDRMS_OK;
 }

@@ -1,5 +1,8 @@
 """Small comparisons are one launch whose last workgroup folds the counts of all: on either side of one workgroup and of the
 most that meet, call after call, and recorded in a graph (where they are two launches)."""
+import ctypes
+import os
+
 import pytest
 import torch
 
@@ -60,3 +63,22 @@ def test_streams_of_their_own_and_a_graph():
         torch.cuda.synchronize()
         assert [tuple(o.cpu().tolist()) for o in outs] == want
         assert counts(B.addrms_gate_probe_noalloc, cases[3], "bf16", 1) == want[3]
+
+
+def test_an_older_error_of_the_callers_is_not_the_launchs():
+    """A call that failed before, an invalid device asked for, leaves its error pending in the thread: the comparison is
+    queued all the same, and says so, and the error stays for whoever asks for it."""
+    case = planted("bf16", 5000, 3, 3, 4, 5)
+    want = counts(B.addrms_gate_probe, case, "bf16", 1)
+    out = torch.zeros(4, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL(os.path.join(os.path.dirname(torch.__file__), "lib", "libamdhip64.so"))
+    error = hip.hipSetDevice(9999)
+    assert error != 0
+    try:
+        B.addrms_gate_probe_noalloc(*case, "bf16", 1, out)
+        pending = hip.hipPeekAtLastError()
+    finally:
+        hip.hipGetLastError()
+    torch.cuda.synchronize()
+    assert pending == error and tuple(out.cpu().tolist()) == want
