@@ -45,9 +45,10 @@ public:
     // after one in vain nobody waits until units have been found again.
     bool take(hipStream_t stream, int units, Lease* lease)
     {
+        const bool pending = hipPeekAtLastError() != hipSuccess;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &capture) != hipSuccess) { (void)hipGetLastError(); return false; }
-        uint32_t* done = capture == hipStreamCaptureStatusNone ? reports() : nullptr;
+        if (hipStreamIsCapturing(stream, &capture) != hipSuccess) return forget_error(pending);
+        uint32_t* done = capture == hipStreamCaptureStatusNone ? reports(pending) : nullptr;
         if (!done) return false;
         using clock = std::chrono::steady_clock;
         for (clock::time_point began{};; std::this_thread::sleep_for(std::chrono::microseconds(20))) {
@@ -71,6 +72,13 @@ public:
     }
 
 private:
+    // A call above has failed, which is nothing to the caller: the thread's error goes, unless one was pending before, for
+    // whoever caused that one to find.
+    static bool forget_error(bool pending)
+    {
+        if (!pending) (void)hipGetLastError();
+        return false;
+    }
     void give_back(int unit)
     {
         std::lock_guard<std::mutex> lock(mu_);
@@ -78,7 +86,7 @@ private:
     }
     // One word per unit, which every GPU can write, allocated once and kept until the process ends.  NULL: not there (yet: no
     // thread waits for the one that allocates it).  Must not disturb a capture that another thread may be in.
-    uint32_t* reports()
+    uint32_t* reports(bool pending)
     {
         uint32_t* done = done_.load(std::memory_order_acquire);
         if (done || allocating_.exchange(true)) return done;
@@ -88,7 +96,7 @@ private:
             const hipError_t e = hipHostMalloc(&p, UNITS * sizeof(uint32_t), hipHostMallocPortable);
             (void)hipThreadExchangeStreamCaptureMode(&mode);
             if (e == hipSuccess) done = static_cast<uint32_t*>(p);
-            else (void)hipGetLastError();
+            else forget_error(pending);
         }
         if (done) {
             std::fill_n(done, UNITS, 0u);

@@ -81,6 +81,21 @@ static int waiting()
     return 0;
 }
 
+// The null stream cannot be asked while another stream captures: no units, and no error is left, nor one of the caller's taken.
+static int errors()
+{
+    static Pool pool;
+    fake_hip::capturing.insert(stream(0x1000, 0));
+    Pool::Lease lease;
+    EXPECT(!pool.take(nullptr, 1, &lease) && hipPeekAtLastError() == hipSuccess);
+    fake_hip::is(hipErrorInvalidHandle);
+    EXPECT(!pool.take(nullptr, 1, &lease) && hipPeekAtLastError() != hipSuccess);
+    fake_hip::capturing.clear();
+    fake_hip::last = hipErrorInvalidHandle;
+    EXPECT(pool.take(nullptr, 1, &lease) && hipPeekAtLastError() == hipErrorInvalidHandle);
+    return 0;
+}
+
 // Units go back where nothing was launched, and once a launch has reported itself; a capturing stream has none.
 static int leases()
 {
@@ -105,7 +120,11 @@ static int leases()
 
 int main(int, char** argv)
 {
-    const int bad = !strcmp(argv[1], "devices") ? devices() : !strcmp(argv[1], "handles") ? handles() : !strcmp(argv[1], "waiting") ? waiting() : leases();
+    const struct { const char* name; int (*run)(); } tests[] = {{"devices", devices}, {"handles", handles}, {"leases", leases},
+                                                                {"waiting", waiting}, {"errors", errors}};
+    int bad = 1;
+    for (const auto& t : tests)
+        if (!strcmp(argv[1], t.name)) bad = t.run();
     if (!bad) printf("ok\n");
     return bad;
 }

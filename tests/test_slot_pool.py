@@ -21,7 +21,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["devices", "handles", "leases", "waiting"])
+@pytest.mark.parametrize("what", ["devices", "handles", "leases", "waiting", "errors"])
 def test_units_of_launches_in_flight(driver, what):
     r = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300,
                        env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
