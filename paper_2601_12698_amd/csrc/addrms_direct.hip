@@ -152,26 +152,33 @@ bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_ali
     return true;
 }
 
+// Once per kernel: LDS beyond the default limit of 64 KB has to be allowed, as in launch_instance, and this loads the kernel's
+// code object.
+static hipError_t prepare_long(const DirectPlan& p)
+{
+    static std::atomic<uint64_t> allowed{0};                   // one bit per kernel
+    const uint64_t bit = 1ull << p.long_index;
+    if (allowed.load(std::memory_order_acquire) & bit) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(p.fn, hipFuncAttributeMaxDynamicSharedMemorySize, hw().lds_bytes_per_cu);
+    if (e == hipSuccess) allowed.fetch_or(bit, std::memory_order_acq_rel);
+    return e;
+}
 static int go(const DirectPlan& p, unsigned grid, void** args, void* stream)
 {
-    if (p.lds > 64u * 1024u) {                                 // beyond the default limit: once per kernel, as launch_instance
-        static std::atomic<uint64_t> allowed{0};               // one bit per long-row kernel
-        const uint64_t bit = 1ull << p.long_index;
-        if (!(allowed.load(std::memory_order_acquire) & bit)) {
-            const hipError_t e = hipFuncSetAttribute(p.fn, hipFuncAttributeMaxDynamicSharedMemorySize, hw().lds_bytes_per_cu);
-            if (e != hipSuccess) return static_cast<int>(e);
-            allowed.fetch_or(bit, std::memory_order_acq_rel);
-        }
-    }
     return static_cast<int>(hipLaunchKernel(p.fn, dim3(grid), dim3(p.block_x, p.block_y), args, p.lds,
                                             static_cast<hipStream_t>(stream)));
 }
 
 int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype, void* stream)
 {
-    int status;
-    const int64_t split = direct_launch_split(p, x, r, w, eps, M, N, dtype, kSplitPatience, stream, &status);
-    if (status != static_cast<int>(hipSuccess) || split == M) return status;
+    int64_t split = 0;
+    if (p.long_row) {
+        // Also where the rows are split: what is captured later runs p.fn, and a capture is no place for this.
+        if (const hipError_t e = prepare_long(p); e != hipSuccess) return static_cast<int>(e);
+        int status;
+        split = direct_launch_split(p, x, r, w, eps, M, N, dtype, kSplitPatience, stream, &status);
+        if (status != static_cast<int>(hipSuccess) || split == M) return status;
+    }
     double inv_n = 1.0 / static_cast<double>(N);
     long long m = M;
     int n = static_cast<int>(N);
