@@ -131,8 +131,10 @@ typedef struct addrms_cfg {
  * code object), a launch in a piece of its own until it has reported its end in 4 KiB of
  * pinned host memory, allocated once by the first such call.  A call that finds no piece
  * free, 2.7 ms or more of such work being in flight, waits for one as it would for room in a
- * full queue, at most 4 ms, and not again after a wait in vain until one has been free; then,
- * and where the stream is capturing, it runs a kernel that needs none.
+ * full queue, at most 4 ms, and not again after a wait in vain until one has been free; then
+ * it runs a kernel that needs none and gives the same bits.  A captured call runs a third
+ * kernel, whose row sum is taken in another order: in some 1e-7 of rows rstd is rounded to
+ * the fp32 value beside the one that an eager call takes.
  */
 int addrms_run(void* x, void* residual, const void* weight, float eps,
                int64_t M, int64_t N, int dtype, const addrms_cfg* cfg, void* stream);
@@ -458,6 +460,11 @@ int addrms_rstd_probe(const double* ss, int64_t n, int64_t N, float eps, float* 
  * all of them being on the chip at once; 0 makes that happen in every launch.  Same arguments and results as addrms_run. */
 int addrms_split_probe(void* x, void* residual, const void* weight, float eps, int64_t M, int64_t N, int dtype,
                        uint32_t patience, void* stream);
+
+/* addrms_run without a configuration, for the same problems, by one of the two kernels for them that do not split rows: the one
+ * of captured calls (captured != 0) or the one of calls that find none of that memory free, which gives the bits of split rows. */
+int addrms_whole_rows_probe(void* x, void* residual, const void* weight, float eps, int64_t M, int64_t N, int dtype,
+                            int captured, void* stream);
 
 /* The correctness gate of the tuner (Algorithm 1 line 13, Validate; Section 3.1: d(S~(x), S(x)) <= eps over a
  * finite test set) applied to caller buffers: compares n elements of an output pair (y, residual) with a

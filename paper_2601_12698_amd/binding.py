@@ -248,6 +248,7 @@ SIGNATURES = {
     "addrms_rstd_probe": (c_int, [c_void_p, c_int64, c_int64, c_float, c_void_p, c_void_p]),
     "addrms_stream_probe": (c_int, [c_void_p, c_void_p, c_int64, c_int64, c_int, c_void_p]),
     "addrms_split_probe": (c_int, [c_void_p, c_void_p, c_void_p, c_float, c_int64, c_int64, c_int, ctypes.c_uint32, c_void_p]),
+    "addrms_whole_rows_probe": (c_int, [c_void_p, c_void_p, c_void_p, c_float, c_int64, c_int64, c_int, c_int, c_void_p]),
     "addrms_row_probe": (c_int, [c_void_p, c_void_p, c_int64, c_int64, c_int, c_int, c_int, c_void_p]),
     "addrms_gate_probe": (c_int, [c_void_p, c_void_p, c_void_p, c_void_p, c_int64, c_int, ctypes.c_uint32, c_void_p,
                                   c_void_p]),
@@ -714,6 +715,17 @@ def addrms_split_probe(x, residual, weight, eps: float, M: int, N: int, dtype, p
     _expect_device_tensor("weight", weight, N, _X_ELEM[dt])
     _check(load().addrms_split_probe(_ptr(x), _ptr(residual), _ptr(weight), float(eps), M, N, dt, int(patience),
                                      _stream_ptr(stream, x)))
+
+
+def addrms_whole_rows_probe(x, residual, weight, eps: float, M: int, N: int, dtype, captured: bool, stream=None) -> None:
+    """addrms_run without a configuration, for rows that are split over workgroups, by one of the kernels that do not split
+    them: the one of captured calls, or the one of calls that find no memory to meet in."""
+    dt, _, _ = _format(dtype)
+    _expect_device_tensor("x", x, M * N, _X_ELEM[dt])
+    _expect_device_tensor("residual", residual, M * N, _R_ELEM[dt])
+    _expect_device_tensor("weight", weight, N, _X_ELEM[dt])
+    _check(load().addrms_whole_rows_probe(_ptr(x), _ptr(residual), _ptr(weight), float(eps), M, N, dt, int(captured),
+                                          _stream_ptr(stream, x)))
 
 
 def addrms_stream_probe(x, residual, M: int, N: int, dtype, stream=None) -> None:

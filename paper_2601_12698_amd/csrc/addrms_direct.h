@@ -9,7 +9,7 @@ namespace addrms_host {
 // A launch that is ready but for the pointers.
 struct DirectPlan : DirectRoute {
     const void* fn = nullptr;
-    const void* split_fn = nullptr;                         // of DirectRoute::parts
+    const void *split_fn = nullptr, *alone_fn = nullptr;    // of DirectRoute::parts
     unsigned long_index = 0;                                // which of the kernels for rows beyond the registers
 };
 
@@ -22,14 +22,17 @@ bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_ali
 // hipError_t of the launch.
 int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
                          void* stream);
-// The kernel of rows split over workgroups; NULL where the route splits none.
-const void* direct_split_fn(const DirectRoute& p, int dtype);
+// The kernels of rows split over workgroups; NULL where the route splits none.
+void direct_split_kernels(int dtype, DirectPlan* p);
 constexpr unsigned kSplitPatience = 256;                    // reads of a row's words, some hundreds of microseconds
 // Only the kernel of rows split over workgroups, where the route has one (direct_launch_addrms prefers it).  Returns how many
-// of the M rows have been launched: fewer where a launch failed (*status, a hipError_t) or could have no units (slot_pool.h).
-// patience: see split_row_sum.
+// of the M rows have been launched: fewer where a launch failed (*status, a hipError_t) or could have no units (slot_pool.h;
+// *capturing: since the stream is).  patience: see split_row_sum.
 int64_t direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
-                            unsigned patience, void* stream, int* status);
+                            unsigned patience, void* stream, int* status, bool* capturing);
+// The kernels for the same rows that need no units: the one of calls that find none, and the one of captured calls.
+int direct_launch_alone(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream);
+int direct_launch_long(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream);
 int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream);
 int direct_launch_mergestates(const DirectPlan& p, const void* va, const float* sa, const void* vb, const float* sb, void* vo,
                               float* so, void* stream);

@@ -132,7 +132,7 @@ bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintpt
     if (!direct_addrms_route(M, N, dtype, default_vec, x, r, w, out)) return false;
     if (out->long_row) {
         out->fn = addrms_long_fn(dtype, out->pol, out->rag);
-        out->split_fn = direct_split_fn(*out, dtype);
+        direct_split_kernels(dtype, out);
         out->long_index = static_cast<unsigned>(dtype) * 4u + (out->pol == POL_NT ? 2u : 0u) + (out->rag ? 1u : 0u);
     } else {
         out->fn = addrms_fn(dtype, out->cpt, out->pol, out->rag, out->block_y > 1);
@@ -169,25 +169,33 @@ static int go(const DirectPlan& p, unsigned grid, void** args, void* stream)
                                             static_cast<hipStream_t>(stream)));
 }
 
+int direct_launch_long(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream)
+{
+    if (const hipError_t e = prepare_long(p); e != hipSuccess) return static_cast<int>(e);
+    double inv_n = 1.0 / static_cast<double>(N);
+    int n = static_cast<int>(N);
+    unsigned lds_chunks = p.units;
+    void* args[] = {&x, &r, &w, &eps, &inv_n, &n, &lds_chunks};
+    return go(p, static_cast<unsigned>(M), args, stream);
+}
 int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype, void* stream)
 {
-    int64_t split = 0;
-    if (p.long_row) {
-        // Also where the rows are split: what is captured later runs p.fn, and a capture is no place for this.
+    if (p.split_fn) {
+        // Of the kernel that a capture of this call runs: a capture is no place for this.
         if (const hipError_t e = prepare_long(p); e != hipSuccess) return static_cast<int>(e);
         int status;
-        split = direct_launch_split(p, x, r, w, eps, M, N, dtype, kSplitPatience, stream, &status);
+        bool capturing;
+        const int64_t split = direct_launch_split(p, x, r, w, eps, M, N, dtype, kSplitPatience, stream, &status, &capturing);
         if (status != static_cast<int>(hipSuccess) || split == M) return status;
+        // What is in flight decides whether there are units, but not the bits: the kernel behind it adds in the same order.
+        if (!capturing)
+            return direct_launch_alone(p, static_cast<char*>(x) + split * N * x_bytes(dtype), static_cast<char*>(r) + split * N * r_bytes(dtype), w,
+                                       eps, M - split, N, stream);
     }
+    if (p.long_row) return direct_launch_long(p, x, r, w, eps, M, N, stream);
     double inv_n = 1.0 / static_cast<double>(N);
     long long m = M;
     int n = static_cast<int>(N);
-    if (p.long_row) {
-        unsigned lds_chunks = p.units;
-        void *xr = static_cast<char*>(x) + split * N * x_bytes(dtype), *rr = static_cast<char*>(r) + split * N * r_bytes(dtype);
-        void* args[] = {&xr, &rr, &w, &eps, &inv_n, &n, &lds_chunks};
-        return go(p, static_cast<unsigned>(M - split), args, stream);
-    }
     unsigned tpr = p.block_x, rpw = p.block_y;
     void* args[] = {&x, &r, &w, &inv_n, &eps, &n, &tpr, &rpw, &m};
     return go(p, p.grid, args, stream);

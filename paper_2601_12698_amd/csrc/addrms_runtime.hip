@@ -617,7 +617,7 @@ int launch_gate_in_one(const void* y, const void* y_ref, const void* r, const vo
 {
     const int workgroups = gate_grid(n, xb);
     SlotPool<kGateUnits>::Lease lease;
-    *launched = workgroups <= kGateMeetMax && (workgroups == 1 || g_gate_slots.take(stream, 1, &lease));
+    *launched = workgroups <= kGateMeetMax && (workgroups == 1 || g_gate_slots.take(stream, 1, &lease) == Units::taken);
     if (!*launched) return ADDRMS_OK;
     const bool meet = workgroups > 1;
     unsigned unit = meet ? lease.unit() : 0u;
@@ -1300,8 +1300,8 @@ int addrms_rstd_probe(const double* ss, int64_t n, int64_t N, float eps, float* 
     return ADDRMS_OK;
 }
 
-int addrms_split_probe(void* x, void* residual, const void* weight, float eps, int64_t M, int64_t N, int dtype, uint32_t patience,
-                       void* stream)
+// The plan of addrms_run without a configuration, for problems whose rows it splits.
+static int split_plan(const void* x, const void* residual, const void* weight, int64_t M, int64_t N, int dtype, DirectPlan* p)
 {
     if (!dtype_valid(dtype)) return fail(ADDRMS_ERR_UNSUPPORTED_DTYPE, "unsupported dtype %d", dtype);
     if (M < 0 || N <= 0) return fail(ADDRMS_ERR_INVALID_ARG, "M must be >= 0 and N > 0");
@@ -1315,13 +1315,33 @@ int addrms_split_probe(void* x, void* residual, const void* weight, float eps, i
     const int xa = c.vec * x_bytes(dtype);
     if (!aligned(x, xa) || !aligned(weight, xa) || !aligned(residual, std::min(16, c.vec * r_bytes(dtype))))
         return fail(ADDRMS_ERR_MISALIGNED, "tensors must be aligned as addrms_run asks for");
-    DirectPlan p;
-    if (!direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(residual), bits(weight), &p) || !p.split_fn)
+    if (!direct_addrms_plan(M, N, dtype, c.vec, bits(x), bits(residual), bits(weight), p) || !p->split_fn)
         return fail(ADDRMS_ERR_UNSUPPORTED_SHAPE, "rows of this problem are not split over workgroups");
+    return ADDRMS_OK;
+}
+
+int addrms_split_probe(void* x, void* residual, const void* weight, float eps, int64_t M, int64_t N, int dtype, uint32_t patience,
+                       void* stream)
+{
+    DirectPlan p;
+    const int st = split_plan(x, residual, weight, M, N, dtype, &p);
+    if (st != ADDRMS_OK || M == 0) return st;
     int e = 0;
-    const int64_t rows = direct_launch_split(p, x, residual, weight, eps, M, N, dtype, patience, stream, &e);
+    bool capturing = false;
+    const int64_t rows = direct_launch_split(p, x, residual, weight, eps, M, N, dtype, patience, stream, &e, &capturing);
     HIP_TRY(static_cast<hipError_t>(e));
     if (rows < M) return fail(ADDRMS_ERR_NO_RESULT, "the call can have no units for split rows now (%lld rows are launched)", (long long)rows);
+    return ADDRMS_OK;
+}
+
+int addrms_whole_rows_probe(void* x, void* residual, const void* weight, float eps, int64_t M, int64_t N, int dtype, int captured,
+                            void* stream)
+{
+    DirectPlan p;
+    const int st = split_plan(x, residual, weight, M, N, dtype, &p);
+    if (st != ADDRMS_OK || M == 0) return st;
+    HIP_TRY(static_cast<hipError_t>(captured ? direct_launch_long(p, x, residual, weight, eps, M, N, stream)
+                                             : direct_launch_alone(p, x, residual, weight, eps, M, N, stream)));
     return ADDRMS_OK;
 }
 

@@ -1,4 +1,5 @@
-// Long rows without a configuration, split over workgroups: the instances of addrms_split_body and their launch.  A code
+// Long rows without a configuration, split over workgroups: the instances of addrms_split_body and addrms_alone_body, and
+// their launches.  A code
 // object of their own, because the memory in it is cleared when it is loaded, with the first of these launches (some
 // milliseconds), and other calls should not pay for that.
 #include <hip/hip_runtime.h>
@@ -27,6 +28,36 @@ __global__ __launch_bounds__(1024) void addrms_split(void* x, void* r, const voi
                                               &split_launch[unit], done, number, patience);
 }
 
+template <int DT, int VEC, int CPT, bool RAG>
+__global__ __launch_bounds__(1024) void addrms_alone(void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned shape)
+{
+    addrms_alone_body<DT, VEC, CPT, RAG>(x, r, w, inv_n, eps, N, shape & 0xffffu, shape >> 16);
+}
+
+template <int DT, int CPT> const void* addrms_alone_fn1(bool rag)
+{
+    constexpr int VEC = direct_vec(DT);
+    return rag ? reinterpret_cast<const void*>(&addrms_alone<DT, VEC, CPT, true>) : reinterpret_cast<const void*>(&addrms_alone<DT, VEC, CPT, false>);
+}
+template <int DT> const void* addrms_alone_fn(int cpt, bool rag)
+{
+    switch (cpt) {
+    case 1: return addrms_alone_fn1<DT, 1>(rag);
+    case 2: return addrms_alone_fn1<DT, 2>(rag);
+    case 4: return addrms_alone_fn1<DT, 4>(rag);
+    default: return nullptr;
+    }
+}
+const void* addrms_alone_fn(int dtype, int cpt, bool rag)
+{
+    switch (dtype) {
+    case DT_BF16: return addrms_alone_fn<DT_BF16>(cpt, rag);
+    case DT_FP16: return addrms_alone_fn<DT_FP16>(cpt, rag);
+    case DT_FP16_RES32: return addrms_alone_fn<DT_FP16_RES32>(cpt, rag);
+    case DT_FP32: return addrms_alone_fn<DT_FP32>(cpt, rag);
+    default: return nullptr;
+    }
+}
 template <int DT, int CPT, int POL> const void* addrms_split_fn2(bool rag)
 {
     constexpr int VEC = direct_vec(DT);
@@ -63,17 +94,20 @@ const void* addrms_split_fn(int dtype, int cpt, int pol, bool rag)
 
 namespace addrms_host {
 
-const void* direct_split_fn(const DirectRoute& p, int dtype)
+void direct_split_kernels(int dtype, DirectPlan* p)
 {
-    return p.parts ? addrms_split_fn(dtype, p.part_cpt, p.part_pol, p.rag) : nullptr;
+    if (!p->parts) return;
+    p->split_fn = addrms_split_fn(dtype, p->part_cpt, p->part_pol, p->rag);
+    p->alone_fn = addrms_alone_fn(dtype, p->part_cpt, p->rag);
 }
 
 static SlotPool<kSplitUnits> g_split_slots;
 
 int64_t direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
-                            unsigned patience, void* stream, int* status)
+                            unsigned patience, void* stream, int* status, bool* capturing)
 {
     *status = static_cast<int>(hipSuccess);
+    *capturing = false;
     if (!p.split_fn) return 0;
     double inv_n = 1.0 / static_cast<double>(N);
     int n = static_cast<int>(N);
@@ -82,7 +116,9 @@ int64_t direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w
     while (row < M) {
         unsigned rows = static_cast<unsigned>(std::min<int64_t>(kSplitRows, M - row));
         SlotPool<kSplitUnits>::Lease lease;
-        if (!g_split_slots.take(static_cast<hipStream_t>(stream), (static_cast<int>(rows) + kSplitUnitRows - 1) / kSplitUnitRows, &lease)) break;
+        const Units units = g_split_slots.take(static_cast<hipStream_t>(stream), (static_cast<int>(rows) + kSplitUnitRows - 1) / kSplitUnitRows, &lease);
+        *capturing = units == Units::capturing;
+        if (units != Units::taken) break;
         void *xr = static_cast<char*>(x) + row * N * x_bytes(dtype), *rr = static_cast<char*>(r) + row * N * r_bytes(dtype);
         unsigned unit = lease.unit();
         uint32_t *done = lease.done(), number = lease.number();
@@ -95,6 +131,16 @@ int64_t direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w
         row += rows;
     }
     return row;
+}
+
+int direct_launch_alone(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream)
+{
+    double inv_n = 1.0 / static_cast<double>(N);
+    int n = static_cast<int>(N);
+    unsigned shape = p.part_threads | p.parts << 16;
+    void* args[] = {&x, &r, &w, &inv_n, &eps, &n, &shape};
+    return static_cast<int>(hipLaunchKernel(p.alone_fn, dim3(static_cast<unsigned>(M)), dim3(p.part_threads), args, 32u * sizeof(double),
+                                            static_cast<hipStream_t>(stream)));
 }
 
 }  // namespace addrms_host

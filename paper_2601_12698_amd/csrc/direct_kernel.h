@@ -273,7 +273,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
 }
 
 // ---- add + RMSNorm, rows beyond the registers ---------------------------------------------------
-// For launches that can have no units (slot_map.h; captured ones are such), rows longer than 16 parts hold, and what
+// For captured launches, which can have no units (slot_map.h), rows longer than 16 parts hold, and what
 // direct_addrms_split leaves.  The walk of addrms_hybrid_body (its comment has the three parts: registers, parked in LDS, read
 // twice) for one row per workgroup, with the store policy of the size, ragged rows, and the weights
 // of the register part fetched before the row sum, so that its stores are the first to follow it
@@ -653,6 +653,90 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     __hip_atomic_store(&launch->rows_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __hip_atomic_store(done, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The same rows by one workgroup each, for a call that finds no units for the kernel above: whatever made it find none, its
+// results are that kernel's.  The workgroup forms the parts' sums one after the other, as each part's own would, adds them as
+// split_row_sum does, and then reads its row again.  Rarely run, and simple rather than fast: 1024 x 131072 bf16 311 us against
+// 173 split.
+template <int DT, int VEC, int CPT, bool RAG>
+__device__ __forceinline__ void addrms_alone_body(void* __restrict__ xp, void* __restrict__ rp, const void* __restrict__ wp, double inv_n,
+                                                  float eps, int32_t N, uint32_t tpr, uint32_t parts)
+{
+    using T = dt_traits<DT>;
+    constexpr int XB = T::XB, RB = T::RB;
+    constexpr bool BF = T::BF;
+    extern __shared__ double lds[];                          // one sum per wave, twice
+
+    const uint32_t lane = threadIdx.x;
+    char* xrow = static_cast<char*>(xp) + static_cast<int64_t>(blockIdx.x) * N * XB;
+    char* rrow = static_cast<char*>(rp) + static_cast<int64_t>(blockIdx.x) * N * RB;
+    const char* wbase = static_cast<const char*>(wp);
+    const RowWalk<XB, VEC, RAG> rw(xrow, 0u, N, lane, tpr);
+    const int32_t stride = rw.stride;
+    SingleElement<DT, RAG> one;
+    one.load(xrow, rrow, wbase, rw.single, rw.has_single);
+
+    double mine = 0.0;                                       // lane p of a wave: sum of part p
+    for (uint32_t part = 0; part < parts; ++part) {
+        const int32_t col0 = rw.col0 + static_cast<int32_t>(part) * CPT * stride;
+        raw_t<XB * VEC> xv[CPT];
+        raw_t<RB * VEC> rv[CPT];
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            const uint32_t colc = rw.clamped(col0 + c * stride);
+            ld_stream<POL_CACHED, XB * VEC, 16>(xrow, colc * XB, xv[c]);
+            ld_stream<POL_CACHED, RB * VEC, 16>(rrow, colc * RB, rv[c]);
+        }
+        double acc = 0.0;
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            if (rw.in_row(col0 + c * stride)) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    const double hd = static_cast<double>(get_elem<XB, BF>(xv[c], e) + get_elem<RB, BF && RB == 2>(rv[c], e));
+                    acc = __builtin_fma(hd, hd, acc);
+                }
+            }
+        }
+        if (part == 0u) acc = one.add(acc);
+        const double sum = row_sum(acc, RED_WAVE, tpr, lane, part & 1u, lds);
+        if ((lane & 63u) == part) mine = __builtin_bit_cast(double, split_word(sum) & ~kSplitSum);
+    }
+    const float rstd = rsqrt_to_f32(__builtin_fma(wave_total(mine), inv_n, static_cast<double>(eps)));
+
+    for (uint32_t part = 0; part < parts; ++part) {
+        const int32_t col0 = rw.col0 + static_cast<int32_t>(part) * CPT * stride;
+        raw_t<XB * VEC> xv[CPT], wv[CPT];
+        raw_t<RB * VEC> rv[CPT];
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            const uint32_t colc = rw.clamped(col0 + c * stride);
+            ld_stream<POL_CACHED, XB * VEC, 16>(xrow, colc * XB, xv[c]);
+            ld_stream<POL_CACHED, RB * VEC, 16>(rrow, colc * RB, rv[c]);
+            ld_stream<POL_CACHED, XB * VEC, RAG ? XB : 16>(wbase, colc * XB, wv[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            const int32_t col = col0 + c * stride;
+            float h[VEC], y[VEC];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                h[e] = get_elem<XB, BF>(xv[c], e) + get_elem<RB, BF && RB == 2>(rv[c], e);
+                const float t = h[e] * rstd;
+                y[e] = t * get_elem<XB, BF>(wv[c], e);
+            }
+            if (rw.in_row(col)) {
+                raw_t<RB * VEC> rout;
+                pack_vec<RB, BF, VEC>(h, rout);
+                st_stream<POL_CACHED, RB * VEC>(rrow, static_cast<uint32_t>(col) * RB, rout);
+                raw_t<XB * VEC> yout;
+                pack_vec<XB, BF, VEC>(y, yout);
+                st_stream<POL_CACHED, XB * VEC>(xrow, static_cast<uint32_t>(col) * XB, yout);
+            }
+        }
+    }
+    one.store(xrow, rrow, rw.single, rw.has_single, rstd);
 }
 
 // ---- elementwise operators over the output as one flat array -----------------------------------

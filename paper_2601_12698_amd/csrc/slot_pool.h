@@ -13,6 +13,8 @@
 
 namespace addrms_host {
 
+enum class Units { taken, none, capturing };
+
 // One pool per kind of launch, for all GPUs.
 template <int UNITS>
 class SlotPool {
@@ -38,18 +40,22 @@ public:
         int unit_ = -1;
     };
 
-    // False: none.  A graph may be replayed beside itself and others, so that no units are its own: a capturing stream has none.
+    // A graph may be replayed beside itself and others, so that no units are its own: a capturing stream has none.
     // Where launches in flight have them all, this one waits for one of them to end, as it would for room in a full queue: a
     // program that queues 400 launches of 172 us at once gets 172.5 us each, and 194.7 where those that find no units take the
     // other kernel.  But what is in flight may depend on something that the caller has yet to do.  So the wait is bounded, and
     // after one in vain nobody waits until units have been found again.
-    bool take(hipStream_t stream, int units, Lease* lease)
+    Units take(hipStream_t stream, int units, Lease* lease)
     {
         const bool pending = hipPeekAtLastError() != hipSuccess;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &capture) != hipSuccess) return forget_error(pending);
-        uint32_t* done = capture == hipStreamCaptureStatusNone ? reports(pending) : nullptr;
-        if (!done) return false;
+        if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+            forget_error(pending);
+            return Units::none;
+        }
+        if (capture != hipStreamCaptureStatusNone) return Units::capturing;
+        uint32_t* done = reports(pending);
+        if (!done) return Units::none;
         using clock = std::chrono::steady_clock;
         for (clock::time_point began{};; std::this_thread::sleep_for(std::chrono::microseconds(20))) {
             std::lock_guard<std::mutex> lock(mu_);
@@ -60,13 +66,13 @@ public:
                 lease->done_ = done + u;
                 lease->number_ = map_.number(u);
                 lease->unit_ = u;
-                return true;
+                return Units::taken;
             }
-            if (in_vain_) return false;
+            if (in_vain_) return Units::none;
             if (began == clock::time_point{}) began = clock::now();
             else if (clock::now() - began > std::chrono::milliseconds(4)) {
                 in_vain_ = true;
-                return false;
+                return Units::none;
             }
         }
     }
@@ -74,10 +80,9 @@ public:
 private:
     // A call above has failed, which is nothing to the caller: the thread's error goes, unless one was pending before, for
     // whoever caused that one to find.
-    static bool forget_error(bool pending)
+    static void forget_error(bool pending)
     {
         if (!pending) (void)hipGetLastError();
-        return false;
     }
     void give_back(int unit)
     {

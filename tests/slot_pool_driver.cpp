@@ -22,7 +22,7 @@ static hipStream_t stream(size_t handle, int device)
 static int launch(Pool& pool, hipStream_t s)
 {
     Pool::Lease lease;
-    if (!pool.take(s, 1, &lease)) return -1;
+    if (pool.take(s, 1, &lease) != Units::taken) return -1;
     lease.launched();
     return static_cast<int>(lease.unit());
 }
@@ -64,7 +64,7 @@ static int waiting()
     const auto ms = [](clock::time_point since) { return std::chrono::duration<double, std::milli>(clock::now() - since).count(); };
     const hipStream_t s = stream(0x1000, 0);
     Pool::Lease all, one;
-    EXPECT(pool.take(s, 8, &all));
+    EXPECT(pool.take(s, 8, &all) == Units::taken);
     all.launched();
     clock::time_point t = clock::now();
     EXPECT(launch(pool, s) == -1 && ms(t) > 4.0);
@@ -72,7 +72,7 @@ static int waiting()
     for (int i = 0; i < 20; ++i) EXPECT(launch(pool, s) == -1);
     EXPECT(ms(t) < 40.0);                                    // 20 waits would be 80
     *all.done() = all.number();
-    EXPECT(pool.take(s, 8, &one));
+    EXPECT(pool.take(s, 8, &one) == Units::taken);
     one.launched();
     std::thread ends([&] { std::this_thread::sleep_for(std::chrono::milliseconds(1)); __atomic_store_n(one.done(), one.number(), __ATOMIC_SEQ_CST); });
     const int got = launch(pool, s);
@@ -87,12 +87,12 @@ static int errors()
     static Pool pool;
     fake_hip::capturing.insert(stream(0x1000, 0));
     Pool::Lease lease;
-    EXPECT(!pool.take(nullptr, 1, &lease) && hipPeekAtLastError() == hipSuccess);
+    EXPECT(pool.take(nullptr, 1, &lease) == Units::none && hipPeekAtLastError() == hipSuccess);
     fake_hip::is(hipErrorInvalidHandle);
-    EXPECT(!pool.take(nullptr, 1, &lease) && hipPeekAtLastError() != hipSuccess);
+    EXPECT(pool.take(nullptr, 1, &lease) == Units::none && hipPeekAtLastError() != hipSuccess);
     fake_hip::capturing.clear();
     fake_hip::last = hipErrorInvalidHandle;
-    EXPECT(pool.take(nullptr, 1, &lease) && hipPeekAtLastError() == hipErrorInvalidHandle);
+    EXPECT(pool.take(nullptr, 1, &lease) == Units::taken && hipPeekAtLastError() == hipErrorInvalidHandle);
     return 0;
 }
 
@@ -103,17 +103,17 @@ static int leases()
     const hipStream_t s = stream(0x1000, 0), capturing = stream(0x2000, 0);
     for (int i = 0; i < 100; ++i) {
         Pool::Lease lease;
-        EXPECT(pool.take(s, 3, &lease));
+        EXPECT(pool.take(s, 3, &lease) == Units::taken);
     }
     for (int i = 0; i < 100; ++i) {
         Pool::Lease lease;
-        EXPECT(pool.take(hipStreamPerThread, 3, &lease));
+        EXPECT(pool.take(hipStreamPerThread, 3, &lease) == Units::taken);
         lease.launched();
         *lease.done() = lease.number();
     }
     fake_hip::capturing.insert(capturing);
     Pool::Lease lease;
-    EXPECT(!pool.take(capturing, 1, &lease) && pool.take(s, 8, &lease));
+    EXPECT(pool.take(capturing, 1, &lease) == Units::capturing && pool.take(s, 8, &lease) == Units::taken);
     fake_hip::capturing.clear();
     return 0;
 }

@@ -100,6 +100,43 @@ def test_sums_formed_in_place_of_others(dtype, M, N, patience):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype,M,N", SPLIT)
+def test_rows_of_calls_that_find_no_units(dtype, M, N):
+    x, xok, r, rok, w = norm_inputs(M, N, dtype, N, special=[(0, 5, float("inf")), (M - 1, N - 1, float("nan"))] if M > 2 else None)
+    xw, rw = x.clone(), r.clone()
+    B.addrms_split_probe(xw, rw, w, 1e-6, M, N, dtype, 256)
+    B.addrms_whole_rows_probe(x, r, w, 1e-6, M, N, dtype, False)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(r), bits(rw)) and torch.equal(bits(x), bits(xw)) and xok() and rok()
+
+
+# A row of 4096 elements b and then 2^-26 b, whose squares are lost one by one in a thread's sum that holds four b^2, but not
+# where a part of the row has none of the b: the sums are 15 * 2^-50 apart, and rstd's fp32 rounding changes between them.
+IN_BETWEEN = [float.fromhex(h) for h in ("0x1.457afap-6", "0x1.3e3ca4p-3", "0x1.738498p-3", "0x1.5bf846p-2", "0x1.0c41ep-1")]
+
+
+@pytest.mark.gpu
+def test_the_order_of_the_sum_does_not_depend_on_what_is_in_flight():
+    """Bits of rows for which the order of the row sum decides: the same from split rows, where every sum is formed by others,
+    and where no units are found.  (The kernel of captured calls adds in another order, which shows that the rows can tell.)"""
+    M, N = len(IN_BETWEEN), 262144
+    b = torch.tensor(IN_BETWEEN, dtype=torch.float64)[:, None].expand(M, N).clone()
+    b[:, 4096:] *= 2.0 ** -26
+    b[:, -1] = 2.0 ** -60                                         # its y is rstd, scaled
+    x0, w = b.float().cuda(), torch.ones(N, device="cuda")
+    assert torch.equal(x0.cpu().double(), b)
+    outs = []
+    for run in (lambda *a: B.addrms_run(*a), lambda *a: B.addrms_split_probe(*a, 0), lambda *a: B.addrms_whole_rows_probe(*a, False),
+                lambda *a: B.addrms_whole_rows_probe(*a, True)):
+        x, r = x0.clone(), torch.zeros_like(x0)
+        run(x, r, w, 1e-6, M, N, "fp32")
+        torch.cuda.synchronize()
+        outs.append(bits(x))
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    assert bool((outs[0][:, -1] != outs[3][:, -1]).all())
+
+
+@pytest.mark.gpu
 def test_problems_that_are_not_split_are_refused():
     x, _, r, _, w = norm_inputs(2, 4096, "bf16", 1)
     with pytest.raises(B.AddrmsError) as e:
