@@ -207,6 +207,30 @@ int64_t n_workgroups(const addrms_cfg& c, int64_t M, int wgs_per_cu)
     return std::min<int64_t>(blocks, static_cast<int64_t>(hw().compute_units) * std::max(1, wgs_per_cu) * std::max(1, c.walk));
 }
 
+// Paced against not paced, time of configured calls on three sets of buffers in rotation, by bytes of traffic; each row the
+// range over the configurations and row lengths named:
+//   add+RMSNorm, ordinary accesses (bf16, N = 1024 to 8192, default and four more; fp32 4096; fp16+fp32 4096 and 5120)
+//       100 MB 0.995-1.04   200 MB 0.94-1.001   300, 400 MB 0.96-0.999   0.6 to 1.6 GB 0.95-1.006 (one of 30 above 1.001)
+//     XCD_CONTIG 0.99-1.02, PERSISTENT 1.002-1.01, one element per access 1.008-1.09, from 100 MB to 1.6 GB
+//     non-temporal (four saved configurations of N = 2880 to 8192; bf16 4096, fp32 4096) 0.98-1.01, 400 MB to 1.9 GB
+//   silu_and_mul, 16-byte accesses, non-temporal, unroll 1 (d = 1024 to 28672, nine configurations)
+//       32 MB 0.99-1.04   48, 64 MB 0.95-1.02   96 to 600 MB 0.96-1.008 (28672 to 130 MB 1.03)   1 GB 0.95-1.002
+//     non-temporal, unroll 2: 40, 120 MB 0.98-1.04   400 MB 0.99-1.012   1 GB 0.98-1.001
+//     ordinary: 16, 40 MB 1.02-1.07   120 MB 0.99-1.02   400 MB 0.993-1.003   1 GB 0.987-0.999
+//     XCD_CONTIG 0.998-1.09, narrower accesses 1.005-1.10, from 16 MB to 1 GB
+// A cap on the resident waves already does what the wait is for, and is left alone.
+bool launch_paced(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op)
+{
+    constexpr int64_t kMB = 1000 * 1000, kAddrms = 200 * kMB, kStreamedSilu = 48 * kMB, kSilu = 800 * kMB;
+    const int widest = std::max(x_bytes(dtype), op == OP_ADDRMS ? r_bytes(dtype) : 0);
+    if (op == OP_MERGE || c.vec * widest < 16 || (c.flags & (ADDRMS_FLAG_XCD_CONTIG | ADDRMS_FLAG_PERSISTENT)) || c.max_waves_per_simd != 0)
+        return false;
+    const bool streamed = (c.flags & ADDRMS_FLAG_NONTEMPORAL) != 0;
+    const int64_t bytes = algorithmic_bytes(op, M, N, dtype);
+    if (op == OP_ADDRMS) return !streamed && bytes >= kAddrms;
+    return bytes >= (streamed && c.unroll == 1 ? kStreamedSilu : kSilu);
+}
+
 // ---- the rules ------------------------------------------------------------------
 static Feas infeasible(const char* rule, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 // Walking the whole grid rejects millions of points whose rationale nobody reads: the walk

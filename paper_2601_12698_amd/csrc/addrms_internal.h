@@ -106,6 +106,8 @@ int capped_wgs_per_cu(const addrms_cfg& c);
 // persistent cfg the number of workgroups resident on the chip (wgs_per_cu from check_cfg).
 int64_t n_row_blocks(const addrms_cfg& c, int64_t M);
 int64_t n_workgroups(const addrms_cfg& c, int64_t M, int wgs_per_cu);
+// Whether the waves of a launch with this cfg wait for one load before they ask for more (wait_one_load).
+bool launch_paced(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op);
 
 bool cfg_equal(const addrms_cfg& a, const addrms_cfg& b);
 uint64_t cfg_key(const addrms_cfg& c);

@@ -86,15 +86,9 @@ unsigned shape_argument(const addrms_cfg& c)
     return static_cast<unsigned>(c.threads_per_row) | static_cast<unsigned>(c.rows_per_wg) << 16;
 }
 
-// Launches whose waves wait for one load before they ask for more (wait_one_load).  Configured calls, us without and with:
-// add+RMSNorm 32768 x 7168 bf16 (1.9 GB) 302.4 / 299.8, 20000 x 5120 (0.8 GB) 147.7 / 145.3, 12000 x 8192 (0.8 GB) 125.5 / 126.2, 6000 x
-// 8192 (0.4 GB) 63.6 / 64.1, 1658 x 7168 (95 MB) 17.3 / 17.6; silu_and_mul, which holds nothing back by itself, 16000 x 11008 bf16 (1.1 GB)
-// 168.3 / 160.2, 4096 x 11008 43.8 / 42.6, 626 x 11008 (41 MB) 8.5 / 8.2.
-unsigned paced(int op, int64_t M, int64_t N, int dtype)
+unsigned paced(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op)
 {
-    constexpr int64_t kAddrms = 800'000'000, kSilumul = 32'000'000;
-    const int64_t per = op == OP_ADDRMS ? 2 * (x_bytes(dtype) + r_bytes(dtype)) : 3 * x_bytes(dtype);
-    return M * N * per >= (op == OP_ADDRMS ? kAddrms : kSilumul) ? static_cast<unsigned>(addrms::LAUNCH_PACED) : 0u;
+    return launch_paced(c, M, N, dtype, op) ? static_cast<unsigned>(addrms::LAUNCH_PACED) : 0u;
 }
 
 int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
@@ -103,7 +97,7 @@ int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, 
     double inv_n = 1.0 / static_cast<double>(N);
     int n = static_cast<int>(N);
     unsigned m = static_cast<unsigned>(M), shape = shape_argument(c);                    // the callers checked M < 2^31
-    unsigned mode = static_cast<unsigned>(c.flags) | paced(OP_ADDRMS, M, N, dtype) | static_cast<unsigned>(c.reduce) << 16;
+    unsigned mode = static_cast<unsigned>(c.flags) | paced(c, M, N, dtype, OP_ADDRMS) | static_cast<unsigned>(c.reduce) << 16;
     // the last argument is the number of row blocks (persistent grids walk them), or, for the forms that
     // continue the row cache in LDS, the chunks per thread the LDS allocation holds
     unsigned nblocks = f.lds_chunks >= 0 ? static_cast<unsigned>(f.lds_chunks) : static_cast<unsigned>(n_row_blocks(c, M));
@@ -115,7 +109,8 @@ int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, 
 int launch_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out, int64_t M, int64_t d, int dtype, hipStream_t stream)
 {
     int dd = static_cast<int>(d);
-    unsigned m = static_cast<unsigned>(M), shape = shape_argument(c), flags = static_cast<unsigned>(c.flags) | paced(OP_SILUMUL, M, d, dtype);
+    unsigned m = static_cast<unsigned>(M), shape = shape_argument(c);
+    unsigned flags = static_cast<unsigned>(c.flags) | paced(c, M, d, dtype, OP_SILUMUL);
     unsigned nblocks = static_cast<unsigned>(n_row_blocks(c, M));
     unsigned grid = static_cast<unsigned>(n_workgroups(c, M, f.res.wgs_per_cu));
     void* args[] = {&x, &out, &dd, &m, &shape, &flags, &nblocks, &grid};
