@@ -339,15 +339,21 @@ _torch_facts = None
 _native = None          # module _native, which takes the usual calls as one native call (csrc/native_calls.cpp)
 
 
+def torch_identity() -> str:
+    """What the module _native was built for and what is running are compared by."""
+    import torch
+    return f"{torch.__version__} {getattr(torch.version, 'git_version', '')}"
+
+
 def _torch() -> _Torch:
     global _torch_facts, _native
     if _torch_facts is None:
         _torch_facts = _Torch()
         try:
             from . import _native as native
-        except ImportError:     # built for another torch: the calls below do the same, slower
+        except ImportError:     # not built, or for another torch: the calls below do the same, slower
             native = None
-        if native is not None and os.path.exists(LIB_PATH):
+        if native is not None and getattr(native, "TORCH", None) == torch_identity() and os.path.exists(LIB_PATH):
             lib = load()
             native.bind(DTYPE_IDS, Cfg, *(ctypes.cast(getattr(lib, f), c_void_p).value for f in
                                           ("addrms_run", "silumul_run", "mergestates_run", "addrms_gate_probe_noalloc")))

@@ -96,15 +96,19 @@ def _build_native(force: bool) -> None:
     import sysconfig
 
     import torch
-    tdir = os.path.dirname(torch.__file__)
+
+    from .binding import torch_identity
+    tdir, identity = os.path.dirname(torch.__file__), torch_identity()
     src, obj = os.path.join(CSRC, "native_calls.cpp"), os.path.join(BUILD, "native_calls.cpp.o")
-    if not force and _newer(NATIVE, src, os.path.join(tdir, "version.py")):
-        return
+    if not force and _newer(NATIVE, src):
+        with open(NATIVE, "rb") as f:
+            if identity.encode() in f.read():
+                return
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     inc = [os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
            os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
     _run(["g++", *HOST_FLAGS, "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-          *(a for i in inc for a in ("-isystem", i)), "-c", src, "-o", obj])
+          f'-DTORCH_IDENTITY="{identity}"', *(a for i in inc for a in ("-isystem", i)), "-c", src, "-o", obj])
     tmp = NATIVE + f".{os.getpid()}.tmp"
     _run(["g++", "-shared", "-o", tmp, obj, "-L", os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
     os.replace(tmp, NATIVE)

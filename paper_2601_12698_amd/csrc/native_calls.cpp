@@ -7,6 +7,9 @@
 // Each function returns the status of the entry point, or None for what it does not take: a stream that was named, objects
 // that are not exactly what is usual (a tensor subclass, a numpy integer), and everything that is to be refused.  binding.py
 // then goes its general way, which knows all cases and has the words.
+//
+// torch's objects are read where the headers of the build say, so the module names the torch it was built for, and binding.py
+// does without it where that is another one.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -196,4 +199,9 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, g_methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native() { return PyModule_Create(&g_module); }
+PyMODINIT_FUNC PyInit__native()
+{
+    PyObject* m = PyModule_Create(&g_module);
+    if (m && PyModule_AddStringConstant(m, "TORCH", TORCH_IDENTITY) != 0) Py_CLEAR(m);
+    return m;
+}

@@ -38,6 +38,18 @@ def test_the_module_is_built_and_leaves_what_is_not_usual_to_the_general_way():
         B.addrms_run(x, x, x[0], 1e-6, 4, 64, "bf16")
 
 
+def test_a_module_built_for_another_torch_is_not_used(monkeypatch):
+    """It loads where the symbols it needs are there, but reads torch's objects where its own headers said."""
+    B._torch()
+    monkeypatch.setattr(B._native, "TORCH", "2.0.0 0000")
+    monkeypatch.setattr(B, "_torch_facts", None)
+    monkeypatch.setattr(B, "_native", None)
+    B._torch()
+    assert B._native is None
+    monkeypatch.undo()
+    assert B._native is not None and B._native.TORCH == B.torch_identity()
+
+
 def outcome(monkeypatch, native, make, call):
     """What a call does: its outputs' bits, or its error."""
     state = make()
