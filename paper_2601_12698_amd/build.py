@@ -1,10 +1,11 @@
-"""Builds ``libaddrms.so`` for gfx950 with hipcc, and ``_native.so`` (calls from Python) with g++, in-tree.
+"""Builds ``libaddrms.so`` for gfx950 with hipcc, and the module ``_native`` (calls from Python) with g++, in-tree.
 
 Steps: generate the kernel instantiation units; compile them (in parallel)
 while capturing the compiler's per-kernel resource report; turn that report
 into the table the feasible-region deriver reads; compile the host units;
-link; compile the module that calls the library from Python against torch's headers.  Objects live under ``_build/`` next to this file; the shared library
-is written into the package directory.
+link; compile the module that calls the library from Python against torch's headers
+(where that fails, a warning: the binding does without).  Objects live under ``_build/``
+next to this file; the libraries are written into the package directory.
 
     python -m paper_2601_12698_amd.build [--force] [-j N]
 """
@@ -16,13 +17,15 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libaddrms.so")
-NATIVE = os.path.join(HERE, "_native.so")
+NATIVE = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 ARCH = "gfx950"
 
 # -packed-fp32-ops off: packed fp32 instruction selection stays disabled for all device code.
@@ -91,10 +94,7 @@ def _compile_kernel_unit(src: str, force: bool) -> str:
     return r.stderr
 
 
-def _build_native(force: bool) -> None:
-    """The extension module _native, for the torch that is importable here."""
-    import sysconfig
-
+def _compile_native(force: bool) -> None:
     import torch
 
     from .binding import torch_identity
@@ -112,6 +112,14 @@ def _build_native(force: bool) -> None:
     tmp = NATIVE + f".{os.getpid()}.tmp"
     _run(["g++", "-shared", "-o", tmp, obj, "-L", os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
     os.replace(tmp, NATIVE)
+
+
+def build_native(force: bool) -> None:
+    """The extension module _native, for the torch and the Python that run this.  The binding does without it."""
+    try:
+        _compile_native(force)
+    except Exception as e:
+        warnings.warn(f"the module _native is not built, and calls from Python take some 2 us longer: {e}")
 
 
 def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
@@ -163,7 +171,7 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
     tmp = LIB + f".{os.getpid()}.tmp"
     _run(["hipcc", "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *objs])
     os.replace(tmp, LIB)
-    _build_native(force)
+    build_native(force)
     if verbose:
         print(f"built {LIB}: {len(rows)} kernel instances")
     return LIB

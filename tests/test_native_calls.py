@@ -1,6 +1,8 @@
 """The native form of the hot calls (module _native) against the general one: it takes the usual calls and nothing else, and
 what it takes gives the same outputs, statuses and errors."""
 import ctypes
+import importlib.machinery
+import os
 
 import numpy as np
 import pytest
@@ -48,6 +50,25 @@ def test_a_module_built_for_another_torch_is_not_used(monkeypatch):
     assert B._native is None
     monkeypatch.undo()
     assert B._native is not None and B._native.TORCH == B.torch_identity()
+
+
+def test_a_build_without_torchs_headers_warns_and_goes_on(monkeypatch, tmp_path):
+    """And a module for another torch or Python is built anew."""
+    from paper_2601_12698_amd import build
+    assert build.NATIVE.endswith(importlib.machinery.EXTENSION_SUFFIXES[0]) and os.path.exists(build.NATIVE)
+    ran = []
+
+    def run(cmd, **kw):
+        ran.append(cmd[0])
+        raise RuntimeError("no compiler")
+    monkeypatch.setattr(build, "_run", run)
+    build.build_native(force=False)                               # built already
+    assert not ran
+    monkeypatch.setattr(build, "NATIVE", str(tmp_path / "module.so"))
+    (tmp_path / "module.so").write_bytes(b"built for some other torch")
+    with pytest.warns(UserWarning, match="no compiler"):
+        build.build_native(force=False)
+    assert ran == ["g++"]
 
 
 def outcome(monkeypatch, native, make, call):
