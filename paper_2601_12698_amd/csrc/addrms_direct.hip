@@ -161,7 +161,7 @@ static hipError_t prepare_long(const DirectPlan& p)
     if (allowed.load(std::memory_order_acquire) & bit) return hipSuccess;
     const hipError_t e = hipFuncSetAttribute(p.fn, hipFuncAttributeMaxDynamicSharedMemorySize, hw().lds_bytes_per_cu);
     if (e == hipSuccess) allowed.fetch_or(bit, std::memory_order_acq_rel);
-    return e;
+    return p.lds > 64u * 1024u ? e : hipSuccess;
 }
 static int go(const DirectPlan& p, unsigned grid, void** args, void* stream)
 {
