@@ -508,6 +508,11 @@ __device__ __forceinline__ double split_part_sum(const char* xrow, const char* r
     for (uint32_t w = 0; w * 64u < tpr; ++w) {
         const RowWalk<XB, VEC, RAG> rw(xrow, 0u, N, w * 64u + threadIdx.x, tpr);
         double acc = 0.0;
+        // The wave holds its own part meanwhile, and what this needs on top decides how many workgroups a CU holds: not unrolled
+        // fp32 62 registers, unrolled 78 (500 x 200000 276 us against 307), bf16 87 and 102 (4096 x 32832 180 against 188); but
+        // 16-bit ragged rows 89 and 78 (1000 x 50001 79.5 against 77.1).
+        constexpr int kUnroll = RAG && VEC == 8 ? CPT : 1;
+#pragma unroll kUnroll
         for (int c = 0; c < CPT; ++c) {
             const int32_t col = rw.col0 + (static_cast<int32_t>(part) * CPT + c) * rw.stride;
             const uint32_t colc = rw.clamped(col);

@@ -2,6 +2,7 @@
 rows are split (host code, on the CPU); the kernel itself, with every wait cut short, beside other streams and beyond the
 rows of one launch (on the GPU)."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -9,6 +10,7 @@ import pytest
 import torch
 
 from paper_2601_12698_amd import binding as B
+from paper_2601_12698_amd import build
 from test_gpu_untuned import bits, check_norm, norm_inputs
 from test_host_sanitizers import BUILD, CSRC, HOST_SOURCES, ROOT
 
@@ -32,6 +34,25 @@ def driver(tmp_path_factory):
 def test_slots_and_shapes(driver, what):
     r = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-4000:]
+
+
+def test_registers_leave_room_for_workgroups():
+    """Waves per SIMD of the kernels with four pieces per thread: what the sizes of the parts were measured with.  A CU holds two
+    workgroups of 1024 threads, and three of 384 (16-bit rows), 512 where they are ragged."""
+    path = os.path.join(BUILD, "addrms_split.remarks")
+    if not os.path.exists(path):
+        pytest.skip("the library is not built here")
+    seen = 0
+    with open(path) as f:
+        kernels = build.parse_remarks(f.read())
+    for name, r in kernels.items():
+        m = re.search(r"addrms_splitILi(\d)ELi(\d)ELi(\d)ELi(\d)ELb(\d)E", name)
+        if m:
+            seen += 1
+            _, vec, pieces, _, ragged = map(int, m.groups())
+            least = 8 if pieces < 4 or vec == 4 else 6 if ragged else 5
+            assert r["occupancy"] >= least and r["scratch"] == 0, (name, r)
+    assert seen == 32
 
 
 SHAPES = [
