@@ -64,6 +64,15 @@ namespace addrms_host {
 // Left to one workgroup per row: rows that it holds (nothing is read twice), in numbers that give nearly every CU one or two,
 // while all of it fits the memory-side cache, whose contents ordinary accesses keep (192 x 40960 bf16 0.68 / 0.96 of the time, 224 x
 // 65536 0.88 / 1.15, 512 x 40960 0.94 / 1.12; beside them 128 x 65536 1.10 / 1.41, 288 x 40960 1.02 / 1.24, 640 x 49152 1.01 / 1.01).
+// And 16-bit rows of whole lines that its registers hold without LDS, where the CUs' last turn at them is not too empty, up to
+// as many turns as it is ahead; split / whole, us on three sets:
+//             350 rows     447          560          650          768          900          1000
+//   32832     18.8 / 18.0  22.5 / 21.1  27.1 / 27.2  32.6 / 32.1  40.7 / 38.4  46.2 / 44.3  50.4 / 48.9
+//   36864     20.4 / 19.1  24.1 / 22.3  30.5 / 30.2  39.9 / 36.1  44.3 / 42.2  50.1 / 49.0  55.0 / 53.8
+//   40960     21.9 / 20.4  26.2 / 24.1  36.5 / 34.1  40.9 / 39.8  46.8 / 45.8  53.6 / 54.0  58.7 / 59.1
+//   49152     24.3 / 23.7  33.1 / 32.0  41.8 / 42.9  47.5 / 47.5  54.2 / 55.5  62.8 / 65.1  69.0 / 71.8
+// (300 rows 16.5 / 16.9 to 20.9 / 21.7, 513 24.8 / 25.9 to 38.5 / 41.4; 1300 x 40960 73.9 / 77.4; ragged ones, which share lines with
+// their neighbours, 350 x 33333 20.6 / 21.8, 800 42.8 / 48.3; 32-bit ones 350 x 32832 33.7 / 35.2, 800 73.4 / 80.4).
 // Stores: write-through between 32 MB of x and residual and the limit above, non-temporal below and beyond (84 MB, 336 x 62528 bf16
 // 30.5 / 35.3 against 34.2 / 34.9; 30 MB, 46 x 164992 fp16 15.2 / 17.4 against 16.4 / 17.2; 20 MB, 100 x 50000 10.1 / 11.1
 // against 9.8 / 10.4; 400 MB, 500 x 200000 fp32 284.9 against 274.5).
@@ -76,6 +85,9 @@ static void direct_addrms_split(int64_t M, int64_t N, int dtype, DirectRoute* ou
     const bool held = pieces <= static_cast<int64_t>(kLongThreads) * (kLongRegValues / vec + out->units);
     const bool filling = M <= cus ? M >= cus / 8 * 5 : M <= 2 * cus && M >= cus / 4 * 7;
     if (held && filling && bytes <= write_through_max()) return;
+    const int64_t turns = (M + cus - 1) / cus, most = pieces <= 4608 ? 4 : pieces <= 5120 ? 3 : 2;
+    const int64_t tenths = turns == 2 ? 3 : turns == 3 ? 1 : 0;                       // of the CUs, in the last turn
+    if (vec == 8 && !out->rag && out->units == 0 && turns > 1 && turns <= most && 10 * (M - (turns - 1) * cus) >= tenths * cus) return;
     const int64_t coarse = vec == 8 ? 2048 : 3072;                                    // pieces of a part
     int64_t parts = (pieces + coarse - 1) / coarse;
     parts = std::max(parts, std::min((pieces + kFinest - 1) / kFinest, kBusy / M));

@@ -238,7 +238,7 @@ def test_norm_refuses_bases_the_default_configuration_refuses():
 
 # rows beyond the registers: the first length that is, and for the kernel of captured calls, which test_long_rows.py runs on
 # them, one chunk parked in LDS and one left over, as much as LDS holds and more (read twice), whole lines or not; both
-# store policies.  Eager calls split all of them but the longest.
+# store policies.  Eager calls split all of them but two.
 LONG = [("bf16", 2, 32776), ("bf16", 3, 32832), ("fp16", 2, 32707), ("bf16", 2, 49152), ("bf16", 2, 49160), ("fp16", 2, 57344),
         ("bf16", 2, 81920), ("bf16", 2, 81984), ("bf16", 2, 90113), ("fp16", 2, 131071), ("bf16", 1, 1 << 20), ("fp32", 2, 32772),
         ("fp32", 2, 32741), ("fp32", 2, 49156), ("fp32", 2, 86016), ("fp32", 2, 86048), ("fp32", 2, 86019), ("fp32", 2, 200001),

@@ -72,10 +72,27 @@ SHAPES = [
     (("bf16", 160, 40960), "whole"),
     (("bf16", 256, 40960), "whole"),
     (("bf16", 257, 40960), "parts=3 threads=448 pieces=4 writethrough"),
-    (("bf16", 447, 40960), "parts=3 threads=448 pieces=4 writethrough"),
-    (("bf16", 448, 40960), "whole"),
     (("bf16", 512, 40960), "whole"),
     (("bf16", 513, 40960), "parts=3 threads=448 pieces=4 writethrough"),
+    (("bf16", 447, 57344), "parts=4 threads=448 pieces=4 nontemporal"),
+    (("fp16_res32", 447, 32832), "parts=3 threads=704 pieces=4 writethrough"),
+    (("fp16_res32", 448, 32832), "whole"),
+    # 16-bit rows that its registers hold, where the last turn of the 256 CUs is not too empty: two, three or four
+    # turns by their length
+    (("bf16", 332, 40960), "parts=3 threads=448 pieces=4 writethrough"),
+    (("bf16", 333, 40960), "whole"),
+    (("bf16", 333, 49152), "whole"),
+    (("bf16", 333, 49160), "parts=4 threads=448 pieces=4 writethrough"),
+    (("bf16", 537, 40960), "parts=3 threads=448 pieces=4 writethrough"),
+    (("bf16", 538, 40960), "whole"),
+    (("bf16", 538, 41024), "parts=3 threads=448 pieces=4 writethrough"),
+    (("bf16", 768, 40960), "whole"),
+    (("bf16", 769, 40960), "parts=3 threads=448 pieces=4 nontemporal"),
+    (("fp16", 769, 36864), "whole"),
+    (("fp16", 769, 36928), "parts=3 threads=448 pieces=4 nontemporal"),
+    (("fp16", 1024, 36864), "whole"),
+    (("fp16", 1025, 36864), "parts=3 threads=384 pieces=4 nontemporal"),
+    (("bf16", 600, 33333), "parts=3 threads=384 pieces=4 writethrough"),
     (("bf16", 200, 81920), "whole"),
     (("bf16", 200, 81984), "parts=6 threads=448 pieces=4 writethrough"),
     # the longest row, and one piece more
@@ -96,7 +113,7 @@ def test_both_sides_of_each_limit(driver):
 
 # two parts and the most; last parts of one line and whole ones; one, two and four pieces per thread; ragged rows; both store
 # policies
-SPLIT = [("bf16", 2, 32832), ("bf16", 700, 40960), ("fp16", 3, 32707), ("bf16", 1, 524288), ("fp16", 2, 262143), ("bf16", 70, 121344),
+SPLIT = [("bf16", 2, 32832), ("bf16", 1300, 40960), ("fp16", 3, 32707), ("bf16", 1, 524288), ("fp16", 2, 262143), ("bf16", 70, 121344),
          ("fp32", 2, 32772), ("fp32", 1, 262144), ("fp32", 60, 131071), ("fp16_res32", 40, 40004), ("fp16_res32", 90, 86022), ("bf16", 33, 131008)]
 
 
