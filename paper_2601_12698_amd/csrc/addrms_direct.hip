@@ -189,8 +189,8 @@ int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, f
         if (status != static_cast<int>(hipSuccess) || split == M) return status;
         // What is in flight decides whether there are units, but not the bits: the kernel behind it adds in the same order.
         if (!capturing)
-            return direct_launch_alone(p, static_cast<char*>(x) + split * N * x_bytes(dtype), static_cast<char*>(r) + split * N * r_bytes(dtype), w,
-                                       eps, M - split, N, stream);
+            return direct_launch_alone(p, static_cast<char*>(x) + split * N * x_bytes(dtype),
+                                       static_cast<char*>(r) + split * N * r_bytes(dtype), w, eps, M - split, N, stream);
     }
     if (p.long_row) return direct_launch_long(p, x, r, w, eps, M, N, stream);
     double inv_n = 1.0 / static_cast<double>(N);

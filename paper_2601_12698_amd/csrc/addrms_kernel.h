@@ -31,6 +31,13 @@
 // Configured calls, us per launch with blockDim and with arguments: 936 x 2880 fp16+fp32 7.2 ->
 // 6.6, 213 x 7168 bf16 4.1 -> 3.9, 1658 x 7168 18.1 -> 17.3, 5580 x 5120 fp16+fp32 56.6 -> 55.9,
 // silu_and_mul 626 x 11008 bf16 9.5 -> 8.5, merge_attn_states 2048 x 192 bf16 4.2 -> 3.4 (the call).
+//
+// Arithmetic per row (what every instantiation must reproduce bit for bit):
+//   h = f32(x) + f32(r)                       one fp32 add
+//   residual <- RNE(h -> residual dtype)      in place
+//   ss = sum h^2  accumulated in fp64 (each h^2 is exact in fp64), any order
+//   rstd = fp32( rsqrt(ss * (1/N) + eps) )    fp64, refined to fp64 accuracy
+//   x <- RNE((h * rstd) * f32(w) -> x dtype)  two fp32 multiplies, in place
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

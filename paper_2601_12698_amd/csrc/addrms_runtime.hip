@@ -143,9 +143,9 @@ int resolve_cfg(const addrms_cfg* cfg, int64_t M, int64_t N, int dtype, addrms_c
 // ---- resolved calls -----------------------------------------------------------------
 // What a *_run call decides before it launches depends on its sizes, its configuration (if any), the table and the
 // alignment of its tensors, not on their contents or addresses.  Deciding it takes from 0.8 us to 13 us (a default
-// configuration behind several infeasible ones) beside a launch of 2 us, so each thread keeps decisions in 64 slots,
-// looked up by everything they depend on.  A problem has one slot, which the three operators share: of two problems that
-// fall into the same one, each call decides anew.
+// configuration behind several infeasible ones) beside a launch of 2 us, so each thread keeps decisions in 64 slots
+// per operator, looked up by everything they depend on.  A problem has one slot: of two problems of an operator that fall
+// into the same one, each call decides anew.
 struct Resolved {
     Feas f;                  // of c, which has passed every check
     addrms_cfg c{};
@@ -458,7 +458,8 @@ __device__ __forceinline__ uint64_t gate_word(const uint64_t* w)
 // The last workgroup to arrive folds the counts of all.  They are stored and the arrival counted without a wait in between,
 // so it may find a word still on its way, which it looks at again; no workgroup waits for one that has not arrived.
 // Everything here is accessed with relaxed atomics of device scope, which go to the memory side of the XCDs' L2s.
-__device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned ymax, GateMeeting* m, unsigned* out, uint32_t* done, uint32_t number)
+__device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned ymax, GateMeeting* m, unsigned* out, uint32_t* done,
+                                          uint32_t number)
 {
     __shared__ unsigned before;
     const unsigned n = gridDim.x;

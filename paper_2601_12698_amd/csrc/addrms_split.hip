@@ -37,7 +37,8 @@ __global__ __launch_bounds__(1024) void addrms_alone(void* x, void* r, const voi
 template <int DT, int CPT> const void* addrms_alone_fn1(bool rag)
 {
     constexpr int VEC = direct_vec(DT);
-    return rag ? reinterpret_cast<const void*>(&addrms_alone<DT, VEC, CPT, true>) : reinterpret_cast<const void*>(&addrms_alone<DT, VEC, CPT, false>);
+    return rag ? reinterpret_cast<const void*>(&addrms_alone<DT, VEC, CPT, true>)
+               : reinterpret_cast<const void*>(&addrms_alone<DT, VEC, CPT, false>);
 }
 template <int DT> const void* addrms_alone_fn(int cpt, bool rag)
 {
@@ -116,7 +117,8 @@ int64_t direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w
     while (row < M) {
         unsigned rows = static_cast<unsigned>(std::min<int64_t>(kSplitRows, M - row));
         SlotPool<kSplitUnits>::Lease lease;
-        const Units units = g_split_slots.take(static_cast<hipStream_t>(stream), (static_cast<int>(rows) + kSplitUnitRows - 1) / kSplitUnitRows, &lease);
+        const int needed = (static_cast<int>(rows) + kSplitUnitRows - 1) / kSplitUnitRows;
+        const Units units = g_split_slots.take(static_cast<hipStream_t>(stream), needed, &lease);
         *capturing = units == Units::capturing;
         if (units != Units::taken) break;
         void *xr = static_cast<char*>(x) + row * N * x_bytes(dtype), *rr = static_cast<char*>(r) + row * N * r_bytes(dtype);

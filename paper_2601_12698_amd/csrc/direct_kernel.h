@@ -499,7 +499,8 @@ __device__ __forceinline__ uint64_t split_word(double sum) { return __builtin_bi
 
 // The sum over the squares of part `part`, formed by one wave in the order in which the part's own tpr threads form it.
 template <int DT, int VEC, int CPT, bool RAG>
-__device__ __forceinline__ double split_part_sum(const char* xrow, const char* rrow, const char* wbase, int32_t N, uint32_t part, uint32_t tpr)
+__device__ __forceinline__ double split_part_sum(const char* xrow, const char* rrow, const char* wbase, int32_t N, uint32_t part,
+                                                 uint32_t tpr)
 {
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;

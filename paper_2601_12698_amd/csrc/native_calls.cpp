@@ -32,7 +32,8 @@ GateFn g_gate;
 PyObject* g_formats;                                         // dict: name of a storage format -> its number
 PyTypeObject* g_cfg;                                         // binding.Cfg
 
-constexpr at::ScalarType kX[] = {at::kBFloat16, at::kHalf, at::kHalf, at::kFloat}, kR[] = {at::kBFloat16, at::kHalf, at::kFloat, at::kFloat};
+constexpr at::ScalarType kX[] = {at::kBFloat16, at::kHalf, at::kHalf, at::kFloat};
+constexpr at::ScalarType kR[] = {at::kBFloat16, at::kHalf, at::kFloat, at::kFloat};
 
 bool whole(PyObject* o, int64_t* out)
 {
@@ -106,8 +107,9 @@ PyObject* addrms_run(PyObject*, PyObject* const* a, Py_ssize_t n)
         int64_t M, N, all;
         void *x, *r, *w;
         const void* cfg;
-        if (n != 8 || !g_run || !PyFloat_CheckExact(a[3]) || !whole(a[4], &M) || !whole(a[5], &N) || !format(a[6], &dt) || !configuration(a[7], &cfg) ||
-            __builtin_mul_overflow(M, N, &all) || !data(a[0], kX[dt], all, &x) || !data(a[1], kR[dt], all, &r) || !data(a[2], kX[dt], N, &w))
+        if (n != 8 || !g_run || !PyFloat_CheckExact(a[3]) || !whole(a[4], &M) || !whole(a[5], &N) || !format(a[6], &dt) ||
+            !configuration(a[7], &cfg) || __builtin_mul_overflow(M, N, &all) || !data(a[0], kX[dt], all, &x) ||
+            !data(a[1], kR[dt], all, &r) || !data(a[2], kX[dt], N, &w))
             return general();
         const float eps = static_cast<float>(PyFloat_AS_DOUBLE(a[3]));
         void* s = stream_of(a[0]);
@@ -145,7 +147,8 @@ PyObject* mergestates_run(PyObject*, PyObject* const* a, Py_ssize_t n)
             if (!(i % 2 ? data(a[i], at::kFloat, rows, &p[i]) : data(a[i], kX[dt], all, &p[i]))) return general();
         void* s = stream_of(a[0]);
         return status([=] {
-            return g_merge(p[0], static_cast<float*>(p[1]), p[2], static_cast<float*>(p[3]), p[4], static_cast<float*>(p[5]), rows, d, dt, cfg, s);
+            return g_merge(p[0], static_cast<float*>(p[1]), p[2], static_cast<float*>(p[3]), p[4], static_cast<float*>(p[5]), rows, d,
+                           dt, cfg, s);
         });
     });
 }

@@ -9,7 +9,8 @@ int main()
 {
     int op, dtype, v[8];
     long long M, N;
-    while (scanf("%d %d %lld %lld %d,%d,%d,%d,%d,%d,%d,%d", &op, &dtype, &M, &N, v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6, v + 7) == 12) {
+    while (scanf("%d %d %lld %lld", &op, &dtype, &M, &N) == 4 &&
+           scanf("%d,%d,%d,%d,%d,%d,%d,%d", v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6, v + 7) == 8) {
         const addrms_cfg c{v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
         printf("%d\n", addrms_host::launch_paced(c, M, N, dtype, op) ? 1 : 0);
     }

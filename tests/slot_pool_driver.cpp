@@ -74,7 +74,10 @@ static int waiting()
     *all.done() = all.number();
     EXPECT(pool.take(s, 8, &one) == Units::taken);
     one.launched();
-    std::thread ends([&] { std::this_thread::sleep_for(std::chrono::milliseconds(1)); __atomic_store_n(one.done(), one.number(), __ATOMIC_SEQ_CST); });
+    std::thread ends([&] {
+        std::this_thread::sleep_for(std::chrono::milliseconds(1));
+        __atomic_store_n(one.done(), one.number(), __ATOMIC_SEQ_CST);
+    });
     const int got = launch(pool, s);
     ends.join();
     EXPECT(got >= 0);
