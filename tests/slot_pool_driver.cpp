@@ -63,23 +63,27 @@ static int waiting()
     using clock = std::chrono::steady_clock;
     const auto ms = [](clock::time_point since) { return std::chrono::duration<double, std::milli>(clock::now() - since).count(); };
     const hipStream_t s = stream(0x1000, 0);
-    Pool::Lease all, one;
+    Pool::Lease all;
     EXPECT(pool.take(s, 8, &all) == Units::taken);
     all.launched();
     clock::time_point t = clock::now();
     EXPECT(launch(pool, s) == -1 && ms(t) > 4.0);
     t = clock::now();
     for (int i = 0; i < 20; ++i) EXPECT(launch(pool, s) == -1);
-    EXPECT(ms(t) < 40.0);                                    // 20 waits would be 80
+    EXPECT(ms(t) < 60.0);                                    // 20 waits would be 80
     *all.done() = all.number();
-    EXPECT(pool.take(s, 8, &one) == Units::taken);
-    one.launched();
-    std::thread ends([&] {
-        std::this_thread::sleep_for(std::chrono::milliseconds(1));
-        __atomic_store_n(one.done(), one.number(), __ATOMIC_SEQ_CST);
-    });
-    const int got = launch(pool, s);
-    ends.join();
+    int got = -1;
+    for (int trial = 0; trial < 50 && got < 0; ++trial) {    // a machine that is busy may end the launch too late
+        Pool::Lease one;
+        EXPECT(pool.take(s, 8, &one) == Units::taken);
+        one.launched();
+        std::thread ends([&] {
+            std::this_thread::sleep_for(std::chrono::milliseconds(1));
+            __atomic_store_n(one.done(), one.number(), __ATOMIC_SEQ_CST);
+        });
+        got = launch(pool, s);
+        ends.join();
+    }
     EXPECT(got >= 0);
     return 0;
 }
