@@ -13,7 +13,9 @@
 //   reduce  : wave64 cross-lane (DPP) sums + one LDS hop across waves, or an
 //             LDS-staged tree
 //   NT    non-temporal (streaming) cache policy on the x and residual loads
-//         and stores; the weight vector always uses the default policy
+//         and stores; the weight vector always uses the default policy.  Outputs
+//         of a size that stays in the memory-side cache are written through
+//         instead, which is the launch's business (launch_write_through)
 //   DEFER residual stored after the row reduction, all of its chunks first and
 //         then those of y, instead of chunk by chunk as the sums are formed: a
 //         workgroup then reads in one phase and writes in one phase, and no load
@@ -48,7 +50,8 @@ enum : int { DT_BF16 = 0, DT_FP16 = 1, DT_FP16_RES32 = 2, DT_FP32 = 3 };
 enum : int { RED_WAVE = 0, RED_LDS = 1 };
 enum : uint32_t { FLAG_XCD_CONTIG = 1u, FLAG_NONTEMPORAL = 2u, FLAG_PERSISTENT = 4u, FLAG_TWO_PASS = 8u,
                   FLAG_LDS_CACHE = 16u, FLAG_DEFER_STORE = 32u, FLAG_ALIGNED_SPAN = 64u,
-                  LAUNCH_PACED = 0x8000u };      // not a knob: set by the host (launch_paced)
+                  // not knobs: set by the host (launch_paced, launch_write_through)
+                  LAUNCH_PACED = 0x8000u, LAUNCH_WRITE_THROUGH = 0x4000u };
 
 template <int DT> struct dt_traits;
 template <> struct dt_traits<DT_BF16>       { static constexpr int XB = 2, RB = 2; static constexpr bool BF = true;  };
@@ -120,6 +123,37 @@ __device__ __forceinline__ void st_raw(char* p, const raw_t<BYTES>& v)
         st_as<NT, u32x4>(p, a);
         st_as<NT, u32x4>(p + 16, b);
     }
+}
+
+// Store to base + off, base being the same for the whole wave, past the L2 and into the memory-side cache (sc1, which only buffer
+// stores can ask for).
+template <int BYTES>
+__device__ __forceinline__ void st_write_through(char* base, uint32_t off, const raw_t<BYTES>& v)
+{
+    constexpr int kSc1 = 16;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000);
+    if constexpr (BYTES == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(v.d[0], rs, off, 0, kSc1);
+    } else if constexpr (BYTES == 8) {
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.d[0], v.d[1]}, rs, off, 0, kSc1);
+    } else {
+        static_assert(BYTES == 16, "one store");
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{v.d[0], v.d[1], v.d[2], v.d[3]}, rs, off, 0, kSc1);
+    }
+}
+
+// An output of a streaming instance: non-temporal, or (WT, what the instance is compiled for) written through where the launch
+// says so; of any other instance: an ordinary store.
+template <int BYTES, bool NT, bool WT>
+__device__ __forceinline__ void st_out(char* base, uint32_t off, const raw_t<BYTES>& v, uint32_t flags)
+{
+    if constexpr (NT && WT && BYTES <= 16) {
+        if (flags & LAUNCH_WRITE_THROUGH) {
+            st_write_through<BYTES>(base, off, v);
+            return;
+        }
+    }
+    st_raw<BYTES, NT>(base + static_cast<uint64_t>(off), v);
 }
 
 // Element e of a raw vector of ES-byte elements, widened to fp32 (exact).
@@ -391,7 +425,9 @@ __device__ __forceinline__ void addrms_body(void* __restrict__ xp, void* __restr
 {
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
-    constexpr bool BF = T::BF;
+    // Beyond six chunks, and with one element per chunk, the second kind of store takes registers that some instances do not have
+    // without giving up a wave per SIMD.
+    constexpr bool BF = T::BF, WT = VEC > 1 && CPT <= 6;
     extern __shared__ double lds[];
 
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
@@ -436,7 +472,7 @@ __device__ __forceinline__ void addrms_body(void* __restrict__ xp, void* __restr
                         if constexpr (!DEFER) {
                             raw_t<RB * VEC> out;
                             pack_vec<RB, BF, VEC>(h[c], out);
-                            st_raw<RB * VEC, NT>(ra.rbase + static_cast<uint64_t>((ra.rowoff + col) * RB), out);
+                            st_out<RB * VEC, NT, WT>(ra.rbase, (ra.rowoff + col) * RB, out, flags);
                         }
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) {
@@ -477,7 +513,7 @@ __device__ __forceinline__ void addrms_body(void* __restrict__ xp, void* __restr
                 if (ra.row_ok && col <= nlast) {
                     raw_t<RB * VEC> out;
                     pack_vec<RB, BF, VEC>(h[c], out);
-                    st_raw<RB * VEC, NT>(ra.rbase + static_cast<uint64_t>((ra.rowoff + col) * RB), out);
+                    st_out<RB * VEC, NT, WT>(ra.rbase, (ra.rowoff + col) * RB, out, flags);
                 }
             }
         }
@@ -493,7 +529,7 @@ __device__ __forceinline__ void addrms_body(void* __restrict__ xp, void* __restr
             if (ra.row_ok && col <= nlast) {
                 raw_t<XB * VEC> out;
                 pack_vec<XB, BF, VEC>(y, out);
-                st_raw<XB * VEC, NT>(ra.xbase + static_cast<uint64_t>((ra.rowoff + col) * XB), out);
+                st_out<XB * VEC, NT, WT>(ra.xbase, (ra.rowoff + col) * XB, out, flags);
             }
         }
         if (!more) break;
@@ -848,7 +884,7 @@ __device__ __forceinline__ void addrms_span_body(void* __restrict__ xp, void* __
 {
     using T_ = dt_traits<DT>;
     constexpr int XB = T_::XB, RB = T_::RB;
-    constexpr bool BF = T_::BF;
+    constexpr bool BF = T_::BF, WT = true;
     static_assert(VEC * XB <= 16 && VEC * RB <= 16, "one access per stream and piece");
     extern __shared__ double lds[];
     (void)reduce; (void)nblocks;
@@ -894,7 +930,7 @@ __device__ __forceinline__ void addrms_span_body(void* __restrict__ xp, void* __
                     if constexpr (!DEFER) {
                         raw_t<RB * VEC> out;
                         pack_vec<RB, BF, VEC>(h[c], out);
-                        st_raw<RB * VEC, NT>(rspan + static_cast<uint64_t>(p * (VEC * RB)), out);
+                        st_out<RB * VEC, NT, WT>(rspan, p * (VEC * RB), out, flags);
                     }
                     double acc = 0.0;
 #pragma unroll
@@ -936,7 +972,7 @@ __device__ __forceinline__ void addrms_span_body(void* __restrict__ xp, void* __
             if (p < S) {
                 raw_t<RB * VEC> out;
                 pack_vec<RB, BF, VEC>(h[c], out);
-                st_raw<RB * VEC, NT>(rspan + static_cast<uint64_t>(p * (VEC * RB)), out);
+                st_out<RB * VEC, NT, WT>(rspan, p * (VEC * RB), out, flags);
             }
         }
     }
@@ -953,7 +989,7 @@ __device__ __forceinline__ void addrms_span_body(void* __restrict__ xp, void* __
         if (p < S) {
             raw_t<XB * VEC> out;
             pack_vec<XB, BF, VEC>(y, out);
-            st_raw<XB * VEC, NT>(xspan + static_cast<uint64_t>(p * (VEC * XB)), out);
+            st_out<XB * VEC, NT, WT>(xspan, p * (VEC * XB), out, flags);
         }
     }
 }

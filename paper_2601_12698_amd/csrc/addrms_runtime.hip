@@ -86,9 +86,13 @@ unsigned shape_argument(const addrms_cfg& c)
     return static_cast<unsigned>(c.threads_per_row) | static_cast<unsigned>(c.rows_per_wg) << 16;
 }
 
-unsigned paced(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op)
+// The flags of the configuration and those that are the launch's own.
+unsigned launch_flags(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op)
 {
-    return launch_paced(c, M, N, dtype, op) ? static_cast<unsigned>(addrms::LAUNCH_PACED) : 0u;
+    unsigned flags = static_cast<unsigned>(c.flags);
+    if (launch_paced(c, M, N, dtype, op)) flags |= static_cast<unsigned>(addrms::LAUNCH_PACED);
+    if (launch_write_through(c, M, N, dtype, op)) flags |= static_cast<unsigned>(addrms::LAUNCH_WRITE_THROUGH);
+    return flags;
 }
 
 int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, int dtype,
@@ -97,7 +101,7 @@ int launch(const Feas& f, const addrms_cfg& c, void* x, void* r, const void* w, 
     double inv_n = 1.0 / static_cast<double>(N);
     int n = static_cast<int>(N);
     unsigned m = static_cast<unsigned>(M), shape = shape_argument(c);                    // the callers checked M < 2^31
-    unsigned mode = static_cast<unsigned>(c.flags) | paced(c, M, N, dtype, OP_ADDRMS) | static_cast<unsigned>(c.reduce) << 16;
+    unsigned mode = launch_flags(c, M, N, dtype, OP_ADDRMS) | static_cast<unsigned>(c.reduce) << 16;
     // the last argument is the number of row blocks (persistent grids walk them), or, for the forms that
     // continue the row cache in LDS, the chunks per thread the LDS allocation holds
     unsigned nblocks = f.lds_chunks >= 0 ? static_cast<unsigned>(f.lds_chunks) : static_cast<unsigned>(n_row_blocks(c, M));
@@ -110,7 +114,7 @@ int launch_silumul(const Feas& f, const addrms_cfg& c, const void* x, void* out,
 {
     int dd = static_cast<int>(d);
     unsigned m = static_cast<unsigned>(M), shape = shape_argument(c);
-    unsigned flags = static_cast<unsigned>(c.flags) | paced(c, M, d, dtype, OP_SILUMUL);
+    unsigned flags = launch_flags(c, M, d, dtype, OP_SILUMUL);
     unsigned nblocks = static_cast<unsigned>(n_row_blocks(c, M));
     unsigned grid = static_cast<unsigned>(n_workgroups(c, M, f.res.wgs_per_cu));
     void* args[] = {&x, &out, &dd, &m, &shape, &flags, &nblocks, &grid};

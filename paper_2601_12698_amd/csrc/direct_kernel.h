@@ -51,14 +51,7 @@ template <int POL, int BYTES>
 __device__ __forceinline__ void st_stream(char* base, uint32_t off, const raw_t<BYTES>& v)
 {
     if constexpr (POL == POL_WT || POL == POL_SHARED) {
-        constexpr int kSc1 = 16;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000);
-        if constexpr (BYTES == 8) {
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.d[0], v.d[1]}, rs, off, 0, kSc1);
-        } else {
-            static_assert(BYTES == 16, "one store");
-            __builtin_amdgcn_raw_buffer_store_b128(u32x4{v.d[0], v.d[1], v.d[2], v.d[3]}, rs, off, 0, kSc1);
-        }
+        st_write_through<BYTES>(base, off, v);
     } else {
         st_raw<BYTES, POL == POL_NT>(base + off, v);
     }

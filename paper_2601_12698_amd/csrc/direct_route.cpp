@@ -29,7 +29,7 @@ namespace {
 // called again and again on one set of 96 to 250 MB (N = 4096, 150 MB: 44.0 / 54.7 / 56.1 against 47.8 / 48.9 / 49.2) or of
 // 16 to 40 MB, in the L2s, and there by up to 35 % on the longest rows where they are not split (166 x 120004 fp32 51
 // against 69; split 55).  From HBM it is 10 to 20 % behind on all of these.
-int64_t write_through_max() { return addrms_host::hw().last_level_cache_bytes / 8 * 3; }
+using addrms_host::write_through_max;
 
 void set_flat(addrms_host::DirectRoute* out, int64_t pieces, int64_t units, int64_t total)
 {

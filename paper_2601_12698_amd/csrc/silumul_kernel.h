@@ -74,7 +74,7 @@ __device__ __forceinline__ void silumul_body(const void* __restrict__ xp, void* 
                     if (row_ok && col <= nlast) {
                         raw_t<ES * VEC> out;
                         pack_vec<ES, BF, VEC>(y, out);
-                        st_raw<ES * VEC, NT>(out_base + static_cast<uint64_t>((out_off + col) * ES), out);
+                        st_out<ES * VEC, NT, (VEC > 1)>(out_base, (out_off + col) * ES, out, flags);
                     }
                 }
             }
