@@ -493,8 +493,8 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
  * loops, harnesses that forbid hipMalloc.  Same arguments and the same verdict in counts_out, but the
  * per-workgroup partial counts live in arrays that are part of the library's device code (one copy per GPU, held until
  * the process ends), so this call allocates no device memory, frees nothing and does not wait: its kernels are only
- * enqueued on `stream`, and counts_out is valid once the stream has reached them.  Up to 96 workgroups (4096 elements of
- * 16 bits or 2048 of 32 each) are one kernel, unless the stream is capturing; else two.  (One-kernel calls report their end
+ * enqueued on `stream`, and counts_out is valid once the stream has reached them.  They are one kernel, or two if the
+ * stream is capturing.  (One-kernel calls of more than one workgroup, 4096 elements of 16 bits or 2048 of 32, report their end
  * in 1 KiB of pinned host memory, allocated once by the first of them.  With 256 of them in flight a call waits for one to
  * end as it would for room in a full queue, at most 4 ms, and not again after a wait in vain until one has ended; then it
  * is two kernels.)  Nothing in it is a memset: a capturing caller records two kernel nodes, or one for a single workgroup.

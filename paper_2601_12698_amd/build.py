@@ -166,7 +166,7 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
         src = os.path.join(CSRC, name)
         obj = os.path.join(BUILD, name[:-4] + ".o")
         if force or not _newer(obj, src, *dev_hdrs, *hdrs, *gen):
-            r = _run(["hipcc", *DEVICE_FLAGS, *(PRELOAD_FLAGS if name != "addrms_runtime.hip" else []), *INCLUDES,
+            r = _run(["hipcc", *DEVICE_FLAGS, *PRELOAD_FLAGS, *INCLUDES,
                       "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj])
             with open(obj[:-2] + ".remarks", "w") as f:
                 f.write(r.stderr)

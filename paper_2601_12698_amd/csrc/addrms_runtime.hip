@@ -365,9 +365,11 @@ __global__ void fill_kernel(void* p, long long n, uint32_t seed, float lo, float
 // Correctness gate d(S~(x), S(x)) <= eps (Section 3.1): residual must match bit
 // for bit; y may differ by at most `tol` units in the last place of its format
 // (+0 and -0 are the same value).  Counted in two stages so that the cost and the
-// result do not depend on how many elements disagree: every workgroup of
-// gate_partial_kernel walks a grid-stride slice and writes its three counts to its
-// own slot of `partial`; gate_finish_kernel folds the slots into `out`:
+// result do not depend on how many elements disagree: every workgroup walks a
+// grid-stride slice and writes its three counts to its own slot, and one workgroup
+// folds the slots into `out`, within one launch (gate_one_kernel) or, for captured
+// calls and those that can have no unit, in a second (gate_partial_kernel, whose
+// slots are `partial`, and gate_finish_kernel):
 //   out[0] = residual elements that differ, out[1] = y elements beyond tol,
 //   out[2] = largest y distance seen, out[3] = 0.
 // Every slot that is read was written by the same call, so the buffer needs no clearing.
@@ -422,7 +424,8 @@ __device__ __forceinline__ unsigned gate_wave(unsigned v)
     v = gate_fold<MAX, 1>(v); v = gate_fold<MAX, 2>(v); v = gate_fold<MAX, 4>(v);
     v = gate_fold<MAX, 8>(v); v = gate_fold<MAX, 16>(v); return gate_fold<MAX, 32>(v);
 }
-// The three counts of a workgroup, valid in thread 0.
+// The three counts of a workgroup, valid in thread 0.  USE: uses of one kernel have LDS of their own, and need no barrier between.
+template <int USE>
 __device__ __forceinline__ void gate_block(unsigned& rbad, unsigned& ybad, unsigned& ymax)
 {
     __shared__ unsigned red[3][kGateBlock / 64];
@@ -438,56 +441,50 @@ __device__ __forceinline__ void gate_block(unsigned& rbad, unsigned& ybad, unsig
         }
 }
 
-// A small comparison is two launches of latency and little else, so up to 96 workgroups meet within one launch.  Elements of
-// bf16, one launch against two, through the binding: 4 k (one workgroup) 4.1 us against 7.0, 64 k 4.5 / 6.9, 256 k (64) 5.1 /
-// 6.9, 384 k (96) 5.6 / 7.1, 640 k (160) 6.4 / 7.3, 768 k (192) 7.0 / 6.6, 16 M (512) 25.8 / 23.2: workgroups that arrive together are
-// counted one after the other, 10 ns each (in groups and then the groups: another trip to memory, 24.6 / 23.2).
-constexpr int kGateMeetMax = 96;
-// Where they meet.  A unit that no launch has is all zero.
-constexpr uint64_t kGateHere = 1ull << 63;
-struct __align__(128) GateWords { uint64_t bad, most; };
-struct GateMeeting {
-    GateWords words[kGateMeetMax];
-    __align__(128) uint32_t arrived;
-};
+// One launch: the workgroups put their counts into words of their own and end; the last one in the grid, which is the last to be
+// dispatched, waits for the words of all others and folds them.  It is the only one that waits, and they need nothing of it.
+// A word is a count and, in its upper half, the number of the launch, so that nothing has to be cleared and no arrival to be
+// counted: what a unit's earlier launches left has other numbers (a unit's numbers do not come round, slot_map.h).  Words are
+// accessed with relaxed atomics of device scope, which go to the memory side of the XCDs' L2s.
+// Through the binding, us; before, up to 96 workgroups met in one launch, whose last arrival, counted on one line, folded and
+// cleared the words, and more took two launches:
+//   8 k elements of bf16 (2 workgroups)  4.5 -> 3.7    28 k  4.7 -> 3.9    384 k (96)  5.5 -> 4.4    860 k (209)  5.9 -> 4.3
+//   2 M (512)  6.8 -> 5.8    4 M  8.8 -> 7.9    16 M  23.2 -> 22.5    64 M  77.4 -> 76.7
+// Two launches with arguments instead of gridDim: 860 k 7.0 -> 6.2.  Arguments in scalar registers when a wave starts: 28 k 4.3 ->
+// 3.9, 860 k 4.6 -> 4.3.
+struct GateWords { uint64_t rbad, ybad, ymax; };
 constexpr int kGateUnits = 256;                          // launches in flight: 1 ms of them
-static __device__ GateMeeting gate_meeting[kGateUnits];
+static __device__ GateWords gate_words[kGateUnits][kGateMaxGrid];
 
-__device__ __forceinline__ uint64_t gate_word(const uint64_t* w)
+__device__ __forceinline__ void gate_put(uint64_t* word, unsigned count, uint32_t number)
 {
-    uint64_t v;
-    do v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); while (!(v & kGateHere));
-    return v & ~kGateHere;
+    __hip_atomic_store(word, static_cast<uint64_t>(number) << 32 | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// The last workgroup to arrive folds the counts of all.  They are stored and the arrival counted without a wait in between,
-// so it may find a word still on its way, which it looks at again; no workgroup waits for one that has not arrived.
-// Everything here is accessed with relaxed atomics of device scope, which go to the memory side of the XCDs' L2s.
-__device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned ymax, GateMeeting* m, unsigned* out, uint32_t* done,
-                                          uint32_t number)
+__device__ __forceinline__ uint64_t gate_look(const uint64_t* word) { return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Thread 0's counts of workgroup `blockIdx.x` of n.
+__device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned ymax, unsigned n, GateWords* words, unsigned* out,
+                                          uint32_t* done, uint32_t number)
 {
-    __shared__ unsigned before;
-    const unsigned n = gridDim.x;
-    if (threadIdx.x == 0) {
-        GateWords* w = &m->words[blockIdx.x];
-        __hip_atomic_store(&w->bad, kGateHere | static_cast<uint64_t>(ybad) << 31 | rbad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&w->most, kGateHere | ymax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        before = __hip_atomic_fetch_add(&m->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (blockIdx.x != n - 1u) {
+        if (threadIdx.x == 0) {
+            GateWords* w = &words[blockIdx.x];
+            gate_put(&w->rbad, rbad, number); gate_put(&w->ybad, ybad, number); gate_put(&w->ymax, ymax, number);
+        }
+        return;
     }
-    __syncthreads();
-    if (before != n - 1u) return;
-    rbad = ybad = ymax = 0u;
-    if (threadIdx.x < n) {
-        GateWords* w = &m->words[threadIdx.x];
-        const uint64_t bad = gate_word(&w->bad);
-        ymax = static_cast<unsigned>(gate_word(&w->most));
-        rbad = static_cast<unsigned>(bad & 0x7fffffffu);
-        ybad = static_cast<unsigned>(bad >> 31);
-        __hip_atomic_store(&w->bad, uint64_t{0}, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&w->most, uint64_t{0}, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (threadIdx.x == 0) __hip_atomic_store(&m->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x != 0) rbad = ybad = ymax = 0u;
+    if (threadIdx.x < n - 1u) {
+        const GateWords* w = &words[threadIdx.x];
+        uint64_t a, b, c;
+        for (;; __builtin_amdgcn_s_sleep(1)) {               // three words in one trip to memory
+            a = gate_look(&w->rbad); b = gate_look(&w->ybad); c = gate_look(&w->ymax);
+            if ((a >> 32) == number && (b >> 32) == number && (c >> 32) == number) break;
+        }
+        rbad += static_cast<unsigned>(a);
+        ybad += static_cast<unsigned>(b);
+        ymax = static_cast<unsigned>(c) > ymax ? static_cast<unsigned>(c) : ymax;
     }
-    gate_block(rbad, ybad, ymax);                            // its barrier: every wave's words are clear
+    gate_block<1>(rbad, ybad, ymax);                         // its barrier: all words have been read
     if (threadIdx.x != 0) return;
     *reinterpret_cast<addrms::u32x4*>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
     __hip_atomic_store(done, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -496,13 +493,13 @@ __device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned
 // The three counts of a workgroup's grid-stride slice, valid in thread 0.
 template <int XB, int RB>
 __device__ __forceinline__ void gate_slice(const char* y, const char* y_ref, const char* r, const char* r_ref, long long n, unsigned tol,
-                                           unsigned& rbad, unsigned& ybad, unsigned& ymax)
+                                           unsigned grid, unsigned& rbad, unsigned& ybad, unsigned& ymax)
 {
     using YP = typename gate_piece<XB>::type;
     using RP = typename gate_piece<RB>::type;
     constexpr int E = 16 / XB, RPP = E * RB / 16;        // elements per piece; residual pieces beside it
     rbad = ybad = ymax = 0;
-    const unsigned pieces = static_cast<unsigned>(n / E), step = gridDim.x * kGateBlock;
+    const unsigned pieces = static_cast<unsigned>(n / E), step = grid * kGateBlock;
     for (unsigned long long p = blockIdx.x * kGateBlock + threadIdx.x; p < pieces; p += step) {
         const addrms::u32x4 a = gate_load<YP>(y + p * 16), b = gate_load<YP>(y_ref + p * 16);
         addrms::u32x4 ra[RPP], rb[RPP];
@@ -537,26 +534,26 @@ __device__ __forceinline__ void gate_slice(const char* y, const char* y_ref, con
         if constexpr (RB == 4) rbad += reinterpret_cast<const uint32_t*>(r)[i] != reinterpret_cast<const uint32_t*>(r_ref)[i];
         else rbad += reinterpret_cast<const uint16_t*>(r)[i] != reinterpret_cast<const uint16_t*>(r_ref)[i];
     }
-    gate_block(rbad, ybad, ymax);
+    gate_block<0>(rbad, ybad, ymax);
 }
 template <int XB, int RB>
 __global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(const char* y, const char* y_ref, const char* r,
                                                                    const char* r_ref, long long n, unsigned tol,
-                                                                   unsigned* partial)
+                                                                   unsigned grid, unsigned* partial)
 {
     unsigned rbad, ybad, ymax;
-    gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, rbad, ybad, ymax);
+    gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, grid, rbad, ybad, ymax);
     if (threadIdx.x == 0)
         reinterpret_cast<addrms::u32x4*>(partial)[blockIdx.x] = addrms::u32x4{rbad, ybad, ymax, 0u};
 }
 template <int XB, int RB>
 __global__ __launch_bounds__(kGateBlock) void gate_one_kernel(const char* y, const char* y_ref, const char* r, const char* r_ref,
-                                                               long long n, unsigned tol, unsigned* out, unsigned unit,
-                                                               uint32_t* done, uint32_t number)
+                                                               long long n, unsigned tol, unsigned grid, unsigned* out, unsigned unit,
+                                                               uint32_t number, uint32_t* done)
 {
     unsigned rbad, ybad, ymax;
-    gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, rbad, ybad, ymax);
-    if (gridDim.x > 1u) gate_meet(rbad, ybad, ymax, &gate_meeting[unit], out, done, number);
+    gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, grid, rbad, ybad, ymax);
+    if (grid > 1u) gate_meet(rbad, ybad, ymax, grid, gate_words[unit], out, done, number);
     else if (threadIdx.x == 0) *reinterpret_cast<addrms::u32x4*>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
 }
 // One workgroup.  accumulate != 0 folds the new counts into what `out` already holds
@@ -574,7 +571,7 @@ __global__ __launch_bounds__(kGateBlock) void gate_finish_kernel(const unsigned*
             c = v.z > c ? v.z : c;
         }
     }
-    gate_block(a, b, c);
+    gate_block<0>(a, b, c);
     if (threadIdx.x == 0) {
         if (accumulate) {
             out[0] += a; out[1] += b;
@@ -597,27 +594,27 @@ int gate_grid(long long n, int xb)
 int launch_gate(const void* y, const void* y_ref, const void* r, const void* r_ref, long long n, int xb, int rb,
                 unsigned tol, unsigned* partial, unsigned* out, bool accumulate, hipStream_t stream)
 {
-    const dim3 block(kGateBlock), grid(static_cast<unsigned>(gate_grid(n, xb)));
-    const char *py = static_cast<const char*>(y), *pyr = static_cast<const char*>(y_ref);
-    const char *pr = static_cast<const char*>(r), *prr = static_cast<const char*>(r_ref);
-    if (xb == 2 && rb == 2) hipLaunchKernelGGL((gate_partial_kernel<2, 2>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, partial);
-    else if (xb == 2) hipLaunchKernelGGL((gate_partial_kernel<2, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, partial);
-    else hipLaunchKernelGGL((gate_partial_kernel<4, 4>), grid, block, 0, stream, py, pyr, pr, prr, n, tol, partial);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(gate_finish_kernel, dim3(1), block, 0, stream, partial, static_cast<int>(grid.x), out, accumulate ? 1 : 0);
-    HIP_TRY(hipGetLastError());
+    unsigned grid = static_cast<unsigned>(gate_grid(n, xb));
+    const void* fn = xb == 4   ? reinterpret_cast<const void*>(&gate_partial_kernel<4, 4>)
+                     : rb == 4 ? reinterpret_cast<const void*>(&gate_partial_kernel<2, 4>)
+                               : reinterpret_cast<const void*>(&gate_partial_kernel<2, 2>);
+    void* args[] = {&y, &y_ref, &r, &r_ref, &n, &tol, &grid, &partial};
+    HIP_TRY(hipLaunchKernel(fn, dim3(grid), dim3(kGateBlock), args, 0, stream));
+    int slots = static_cast<int>(grid), more = accumulate ? 1 : 0;
+    void* last[] = {&partial, &slots, &out, &more};
+    HIP_TRY(hipLaunchKernel(reinterpret_cast<const void*>(&gate_finish_kernel), dim3(1), dim3(kGateBlock), last, 0, stream));
     return ADDRMS_OK;
 }
 
 SlotPool<kGateUnits> g_gate_slots;
 
-// The gate in one launch, where one workgroup does it or a few and the launch can have a unit.  *launched: whether it was.
+// The gate in one launch, where one workgroup does it or the launch can have a unit.  *launched: whether it was.
 int launch_gate_in_one(const void* y, const void* y_ref, const void* r, const void* r_ref, long long n, int xb, int rb, unsigned tol,
                        unsigned* out, hipStream_t stream, bool* launched)
 {
-    const int workgroups = gate_grid(n, xb);
+    unsigned workgroups = static_cast<unsigned>(gate_grid(n, xb));
     SlotPool<kGateUnits>::Lease lease;
-    *launched = workgroups <= kGateMeetMax && (workgroups == 1 || g_gate_slots.take(stream, 1, &lease) == Units::taken);
+    *launched = workgroups == 1 || g_gate_slots.take(stream, 1, &lease) == Units::taken;
     if (!*launched) return ADDRMS_OK;
     const bool meet = workgroups > 1;
     unsigned unit = meet ? lease.unit() : 0u;
@@ -625,9 +622,9 @@ int launch_gate_in_one(const void* y, const void* y_ref, const void* r, const vo
     const void* fn = xb == 4   ? reinterpret_cast<const void*>(&gate_one_kernel<4, 4>)
                      : rb == 4 ? reinterpret_cast<const void*>(&gate_one_kernel<2, 4>)
                                : reinterpret_cast<const void*>(&gate_one_kernel<2, 2>);
-    void* args[] = {&y, &y_ref, &r, &r_ref, &n, &tol, &out, &unit, &done, &number};
+    void* args[] = {&y, &y_ref, &r, &r_ref, &n, &tol, &workgroups, &out, &unit, &number, &done};
     // The launch's own status: hipGetLastError may have an older error, of the caller's, for a launch that is queued.
-    HIP_TRY(hipLaunchKernel(fn, dim3(static_cast<unsigned>(workgroups)), dim3(kGateBlock), args, 0, stream));
+    HIP_TRY(hipLaunchKernel(fn, dim3(workgroups), dim3(kGateBlock), args, 0, stream));
     if (meet) lease.launched();
     return ADDRMS_OK;
 }

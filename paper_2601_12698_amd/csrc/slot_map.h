@@ -10,7 +10,10 @@
 
 namespace addrms_host {
 
-template <int UNITS>
+// The launches with units from one place on are numbered from 1, and never with the same number again: what one of them leaves in
+// memory is told from what another has written there by the number (the gate).  After 2^32 - 1 of them, which take months, the
+// place is not used any more.
+template <int UNITS, typename Number = uint32_t>
 class SlotMap {
 public:
     // The first of `units` adjacent units that are free now; -1: none found.  Calls are serialised by the caller.
@@ -44,15 +47,15 @@ public:
 
 private:
     struct Unit {
-        uint32_t number;                                     // of the last launch with units from here on
+        Number number;                                       // of the last launch with units from here on
         int span;                                            // its units; 0: none, or free
     };
-    // 0: units [u, u + n) are free.  Else the end of the first launch's in flight.
+    // 0: units [u, u + n) are free.  Else where to look on: the end of the first launch's in flight.
     int busy_end(int u, int n, const volatile uint32_t* done) const
     {
         for (int i = u; i < u + n; i += unit_[i].span ? unit_[i].span : 1)
             if (unit_[i].span && done[i] != unit_[i].number) return i + unit_[i].span;
-        return 0;
+        return unit_[u].number == static_cast<Number>(-1) ? u + 1 : 0;       // no more launches from here on
     }
     Unit unit_[UNITS] = {};
     int next_ = 0;
