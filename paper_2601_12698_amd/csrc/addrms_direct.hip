@@ -14,29 +14,29 @@ namespace {
 // MULTI: several rows per workgroup (rpw).  The launch shape travels as arguments: together with the rest they are preloaded
 // into scalar registers, where blockDim would be another load before the first address is known.
 template <int DT, int VEC, int CPT, int POL, bool RAG, bool MULTI>
-__global__ __launch_bounds__(1024) void addrms_direct(void* x, void* r, const void* w, double inv_n, float eps, int N,
+__global__ __launch_bounds__(1024) void addrms_direct(addr_t x, addr_t r, addr_t w, double inv_n, float eps, int N,
                                                       unsigned tpr, unsigned rpw, long long M)
 {
-    addrms_direct_body<DT, VEC, CPT, POL, RAG, (CPT > 1), MULTI>(x, r, w, eps, inv_n, N, tpr, rpw, M);
+    addrms_direct_body<DT, VEC, CPT, POL, RAG, (CPT > 1), MULTI>(at_global(x), at_global(r), at_global(w), eps, inv_n, N, tpr, rpw, M);
 }
 template <int DT, int VEC, int POL, bool RAG>
-__global__ __launch_bounds__(kLongThreads) void addrms_long(void* x, void* r, const void* w, float eps, double inv_n, int N,
+__global__ __launch_bounds__(kLongThreads) void addrms_long(addr_t x, addr_t r, addr_t w, float eps, double inv_n, int N,
                                                             unsigned lds_chunks)
 {
-    addrms_long_body<DT, VEC, kLongRegValues / VEC, 2, POL, RAG>(x, r, w, eps, inv_n, N, lds_chunks);
+    addrms_long_body<DT, VEC, kLongRegValues / VEC, 2, POL, RAG>(at_global(x), at_global(r), at_global(w), eps, inv_n, N, lds_chunks);
 }
 template <int DT, int POL, bool RAG>
-__global__ __launch_bounds__(kFlatThreads) void silumul_flat(const char* x, char* out, uint32_t d, uint32_t units,
+__global__ __launch_bounds__(kFlatThreads) void silumul_flat(addr_t x, addr_t out, uint32_t d, uint32_t units,
                                                              uint32_t total, FlatDiv fd)
 {
-    silumul_flat_body<DT, POL, RAG>(x, out, d, units, total, fd);
+    silumul_flat_body<DT, POL, RAG>(at_global<char>(x), at_global<char>(out), d, units, total, fd);
 }
 template <int DT, int POL>
-__global__ __launch_bounds__(kFlatThreads) void mergestates_flat(const char* va, const float* sa, const char* vb,
-                                                                 const float* sb, char* vo, float* so, uint32_t units,
-                                                                 uint32_t total, FlatDiv fd)
+__global__ __launch_bounds__(kFlatThreads) void mergestates_flat(addr_t va, addr_t sa, addr_t vb, addr_t sb, addr_t vo, addr_t so,
+                                                                 uint32_t units, uint32_t total, FlatDiv fd)
 {
-    mergestates_flat_body<DT, POL>(va, sa, vb, sb, vo, so, units, total, fd);
+    mergestates_flat_body<DT, POL>(at_global<char>(va), at_global<float>(sa), at_global<char>(vb), at_global<float>(sb),
+                                   at_global<char>(vo), at_global<float>(so), units, total, fd);
 }
 
 template <int DT, int CPT, int POL, bool RAG, bool MULTI> const void* addrms_fn3()

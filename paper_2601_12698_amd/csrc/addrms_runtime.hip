@@ -27,6 +27,8 @@ static const DispatchEntry kDispatch[] = {
 };
 
 using namespace addrms_host;
+using addrms::addr_t;
+using addrms::at_global;
 
 // Partial-count slots of addrms_gate_probe_noalloc: device memory that belongs to the loaded
 // code object, one copy per GPU, so the entry point needs no allocation.  Host code never
@@ -537,36 +539,34 @@ __device__ __forceinline__ void gate_slice(const char* y, const char* y_ref, con
     gate_block<0>(rbad, ybad, ymax);
 }
 template <int XB, int RB>
-__global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(const char* y, const char* y_ref, const char* r,
-                                                                   const char* r_ref, long long n, unsigned tol,
-                                                                   unsigned grid, unsigned* partial)
+__global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(addr_t y, addr_t y_ref, addr_t r, addr_t r_ref, long long n,
+                                                                   unsigned tol, unsigned grid, addr_t partial)
 {
     unsigned rbad, ybad, ymax;
-    gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, grid, rbad, ybad, ymax);
+    gate_slice<XB, RB>(at_global<char>(y), at_global<char>(y_ref), at_global<char>(r), at_global<char>(r_ref), n, tol, grid, rbad, ybad, ymax);
     if (threadIdx.x == 0)
-        reinterpret_cast<addrms::u32x4*>(partial)[blockIdx.x] = addrms::u32x4{rbad, ybad, ymax, 0u};
+        at_global<addrms::u32x4>(partial)[blockIdx.x] = addrms::u32x4{rbad, ybad, ymax, 0u};
 }
 template <int XB, int RB>
-__global__ __launch_bounds__(kGateBlock) void gate_one_kernel(const char* y, const char* y_ref, const char* r, const char* r_ref,
-                                                               long long n, unsigned tol, unsigned grid, unsigned* out, unsigned unit,
-                                                               uint32_t number, uint32_t* done)
+__global__ __launch_bounds__(kGateBlock) void gate_one_kernel(addr_t y, addr_t y_ref, addr_t r, addr_t r_ref, long long n, unsigned tol,
+                                                               unsigned grid, addr_t out, unsigned unit, uint32_t number, addr_t done)
 {
     unsigned rbad, ybad, ymax;
-    gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, grid, rbad, ybad, ymax);
-    if (grid > 1u) gate_meet(rbad, ybad, ymax, grid, gate_words[unit], out, done, number);
-    else if (threadIdx.x == 0) *reinterpret_cast<addrms::u32x4*>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
+    gate_slice<XB, RB>(at_global<char>(y), at_global<char>(y_ref), at_global<char>(r), at_global<char>(r_ref), n, tol, grid, rbad, ybad, ymax);
+    if (grid > 1u) gate_meet(rbad, ybad, ymax, grid, gate_words[unit], at_global<unsigned>(out), at_global<uint32_t>(done), number);
+    else if (threadIdx.x == 0) *at_global<addrms::u32x4>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
 }
 // One workgroup.  accumulate != 0 folds the new counts into what `out` already holds
 // (a second comparison graded into the same verdict).
-__global__ __launch_bounds__(kGateBlock) void gate_finish_kernel(const unsigned* partial, int nslots, unsigned* out,
-                                                                  int accumulate)
+__global__ __launch_bounds__(kGateBlock) void gate_finish_kernel(addr_t partial, int nslots, addr_t out_at, int accumulate)
 {
+    unsigned* out = at_global<unsigned>(out_at);
     unsigned a = 0, b = 0, c = 0;
 #pragma unroll
     for (int k = 0; k < kGateMaxGrid / kGateBlock; ++k) {
         const int s = k * kGateBlock + static_cast<int>(threadIdx.x);
         if (s < nslots) {
-            const addrms::u32x4 v = reinterpret_cast<const addrms::u32x4*>(partial)[s];
+            const addrms::u32x4 v = at_global<const addrms::u32x4>(partial)[s];
             a += v.x; b += v.y;
             c = v.z > c ? v.z : c;
         }

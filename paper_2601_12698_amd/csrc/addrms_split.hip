@@ -21,17 +21,17 @@ static __device__ SplitLaunch split_launch[kSplitUnits];
 namespace {
 
 template <int DT, int VEC, int CPT, int POL, bool RAG>
-__global__ __launch_bounds__(1024) void addrms_split(void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned shape,
-                                                     unsigned rows, unsigned unit, uint32_t* done, uint32_t number, unsigned patience)
+__global__ __launch_bounds__(1024) void addrms_split(addr_t x, addr_t r, addr_t w, double inv_n, float eps, int N, unsigned shape,
+                                                     unsigned rows, unsigned unit, addr_t done, uint32_t number, unsigned patience)
 {
-    addrms_split_body<DT, VEC, CPT, POL, RAG>(x, r, w, inv_n, eps, N, shape & 0xffffu, shape >> 16, rows, split_rows[unit],
-                                              &split_launch[unit], done, number, patience);
+    addrms_split_body<DT, VEC, CPT, POL, RAG>(at_global(x), at_global(r), at_global(w), inv_n, eps, N, shape & 0xffffu, shape >> 16, rows,
+                                              split_rows[unit], &split_launch[unit], at_global<uint32_t>(done), number, patience);
 }
 
 template <int DT, int VEC, int CPT, bool RAG>
-__global__ __launch_bounds__(1024) void addrms_alone(void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned shape)
+__global__ __launch_bounds__(1024) void addrms_alone(addr_t x, addr_t r, addr_t w, double inv_n, float eps, int N, unsigned shape)
 {
-    addrms_alone_body<DT, VEC, CPT, RAG>(x, r, w, inv_n, eps, N, shape & 0xffffu, shape >> 16);
+    addrms_alone_body<DT, VEC, CPT, RAG>(at_global(x), at_global(r), at_global(w), inv_n, eps, N, shape & 0xffffu, shape >> 16);
 }
 
 template <int DT, int CPT> const void* addrms_alone_fn1(bool rag)

@@ -99,18 +99,19 @@ def name(op, dt, vec, cpt, unr, nt, df=0):
 # shape: threads per row and, from bit 16 on, rows per workgroup; mode: flags and, from bit 16 on, the reduction style.  What
 # the first address depends on comes first: the first 14 dwords or so are in scalar registers when a wave starts (build.py).
 ARGS = {
-    OP_ADDRMS: ("void* x, void* r, const void* w, double inv_n, float eps, int N, unsigned M, unsigned shape, "
+    OP_ADDRMS: ("addrms::addr_t x, addrms::addr_t r, addrms::addr_t w, double inv_n, float eps, int N, unsigned M, unsigned shape, "
                 "unsigned mode, unsigned nblocks, unsigned grid"),
-    OP_SILUMUL: "const void* x, void* out, int d, unsigned M, unsigned shape, unsigned flags, unsigned nblocks, unsigned grid",
-    OP_MERGE: ("const void* va, const void* vb, int d, unsigned rows, unsigned shape, unsigned flags, "
-               "const float* sa, const float* sb, void* vo, float* so, unsigned nblocks, unsigned grid"),
+    OP_SILUMUL: "addrms::addr_t x, addrms::addr_t out, int d, unsigned M, unsigned shape, unsigned flags, unsigned nblocks, unsigned grid",
+    OP_MERGE: ("addrms::addr_t va, addrms::addr_t vb, int d, unsigned rows, unsigned shape, unsigned flags, "
+               "addrms::addr_t sa, addrms::addr_t sb, addrms::addr_t vo, addrms::addr_t so, unsigned nblocks, unsigned grid"),
 }
-ADDRMS_ARGS = "(x, r, w, eps, inv_n, M, N, mode & 0xffffu, mode >> 16, nblocks, shape & 0xffffu, shape >> 16, grid);"
+ADDRMS_ARGS = "(addrms::at_global(x), addrms::at_global(r), addrms::at_global(w), eps, inv_n, M, N, mode & 0xffffu, mode >> 16, nblocks, shape & 0xffffu, shape >> 16, grid);"
 CALL = {
     OP_ADDRMS: "addrms::addrms_body<{dt}, {vec}, {cpt}, {unr}, {nt}, {df}>" + ADDRMS_ARGS,
-    OP_SILUMUL: "addrms::silumul_body<{dt}, {vec}, {cpt}, {unr}, {nt}>(x, out, M, d, flags, nblocks, shape & 0xffffu, shape >> 16, grid);",
+    OP_SILUMUL: ("addrms::silumul_body<{dt}, {vec}, {cpt}, {unr}, {nt}>"
+                "(addrms::at_global(x), addrms::at_global(out), M, d, flags, nblocks, shape & 0xffffu, shape >> 16, grid);"),
     OP_MERGE: ("addrms::mergestates_body<{dt}, {vec}, {cpt}, {unr}, {nt}>"
-               "(va, sa, vb, sb, vo, so, rows, d, flags, nblocks, shape & 0xffffu, shape >> 16, grid);"),
+               "(addrms::at_global(va), addrms::at_global<float>(sa), addrms::at_global(vb), addrms::at_global<float>(sb), addrms::at_global(vo), addrms::at_global<float>(so), rows, d, flags, nblocks, shape & 0xffffu, shape >> 16, grid);"),
 }
 TWO_PASS_CALL = "addrms::addrms_twopass_body<{dt}, {vec}, {unr}, {nt}>" + ADDRMS_ARGS
 HYBRID_CALL = "addrms::addrms_hybrid_body<{dt}, {vec}, {cpt}, {unr}, {nt}>" + ADDRMS_ARGS
