@@ -161,7 +161,7 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
             _run(["hipcc", "-x", "c++", *HOST_FLAGS, *INCLUDES, "-c", src, "-o", obj])
         objs.append(obj)
     dev_hdrs = [os.path.join(CSRC, f) for f in ("addrms_kernel.h", "silumul_kernel.h", "mergestates_kernel.h",
-                                                 "direct_kernel.h", "addrms_direct.h")]
+                                                 "direct_kernel.h", "addrms_direct.h", "unit_report.h")]
     for name in ("addrms_runtime.hip", "addrms_direct.hip", "addrms_split.hip"):
         src = os.path.join(CSRC, name)
         obj = os.path.join(BUILD, name[:-4] + ".o")

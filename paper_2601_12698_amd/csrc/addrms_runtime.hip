@@ -15,6 +15,7 @@
 #include "mergestates.h"
 #include "mergestates_kernel.h"
 #include "slot_pool.h"
+#include "unit_report.h"
 #include "silumul.h"
 #include "silumul_kernel.h"
 
@@ -452,24 +453,26 @@ __device__ __forceinline__ void gate_block(unsigned& rbad, unsigned& ybad, unsig
 // cleared the words, and more took two launches:
 //   8 k elements of bf16 (2 workgroups)  4.5 -> 3.7    28 k  4.7 -> 3.9    384 k (96)  5.5 -> 4.4    860 k (209)  5.9 -> 4.3
 //   2 M (512)  6.8 -> 5.8    4 M  8.8 -> 7.9    16 M  23.2 -> 22.5    64 M  77.4 -> 76.7
+// (with a report to host memory at the end, as before; unit_report.h has what is written now)
 // Two launches with arguments instead of gridDim: 860 k 7.0 -> 6.2.  Arguments in scalar registers when a wave starts: 28 k 4.3 ->
 // 3.9, 860 k 4.6 -> 4.3.
 struct GateWords { uint64_t rbad, ybad, ymax; };
 constexpr int kGateUnits = 256;                          // launches in flight: 1 ms of them
 static __device__ GateWords gate_words[kGateUnits][kGateMaxGrid];
+static __device__ addrms::UnitReports<kGateUnits> gate_reports;
 
 __device__ __forceinline__ void gate_put(uint64_t* word, unsigned count, uint32_t number)
 {
     __hip_atomic_store(word, static_cast<uint64_t>(number) << 32 | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint64_t gate_look(const uint64_t* word) { return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// Thread 0's counts of workgroup `blockIdx.x` of n.
-__device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned ymax, unsigned n, GateWords* words, unsigned* out,
-                                          uint32_t* done, uint32_t number)
+// Thread 0's counts of workgroup `block` of n.
+__device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned ymax, unsigned block, unsigned n, GateWords* words,
+                                          unsigned* out, uint64_t* state, uint32_t number)
 {
-    if (blockIdx.x != n - 1u) {
+    if (block != n - 1u) {
         if (threadIdx.x == 0) {
-            GateWords* w = &words[blockIdx.x];
+            GateWords* w = &words[block];
             gate_put(&w->rbad, rbad, number); gate_put(&w->ybad, ybad, number); gate_put(&w->ymax, ymax, number);
         }
         return;
@@ -489,20 +492,20 @@ __device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned
     gate_block<1>(rbad, ybad, ymax);                         // its barrier: all words have been read
     if (threadIdx.x != 0) return;
     *reinterpret_cast<addrms::u32x4*>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
-    __hip_atomic_store(done, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    addrms::unit_done(state, number);
 }
 
 // The three counts of a workgroup's grid-stride slice, valid in thread 0.
 template <int XB, int RB>
 __device__ __forceinline__ void gate_slice(const char* y, const char* y_ref, const char* r, const char* r_ref, long long n, unsigned tol,
-                                           unsigned grid, unsigned& rbad, unsigned& ybad, unsigned& ymax)
+                                           unsigned block, unsigned grid, unsigned& rbad, unsigned& ybad, unsigned& ymax)
 {
     using YP = typename gate_piece<XB>::type;
     using RP = typename gate_piece<RB>::type;
     constexpr int E = 16 / XB, RPP = E * RB / 16;        // elements per piece; residual pieces beside it
     rbad = ybad = ymax = 0;
     const unsigned pieces = static_cast<unsigned>(n / E), step = grid * kGateBlock;
-    for (unsigned long long p = blockIdx.x * kGateBlock + threadIdx.x; p < pieces; p += step) {
+    for (unsigned long long p = block * kGateBlock + threadIdx.x; p < pieces; p += step) {
         const addrms::u32x4 a = gate_load<YP>(y + p * 16), b = gate_load<YP>(y_ref + p * 16);
         addrms::u32x4 ra[RPP], rb[RPP];
 #pragma unroll
@@ -530,7 +533,7 @@ __device__ __forceinline__ void gate_slice(const char* y, const char* y_ref, con
     }
     // the last n % E elements, one per thread of the first workgroup
     const long long i = static_cast<long long>(pieces) * E + threadIdx.x;
-    if (blockIdx.x == 0 && i < n) {
+    if (block == 0 && i < n) {
         if constexpr (XB == 4) gate_count_y<4>(reinterpret_cast<const uint32_t*>(y)[i], reinterpret_cast<const uint32_t*>(y_ref)[i], tol, ybad, ymax);
         else gate_count_y<2>(reinterpret_cast<const uint16_t*>(y)[i], reinterpret_cast<const uint16_t*>(y_ref)[i], tol, ybad, ymax);
         if constexpr (RB == 4) rbad += reinterpret_cast<const uint32_t*>(r)[i] != reinterpret_cast<const uint32_t*>(r_ref)[i];
@@ -543,19 +546,28 @@ __global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(addr_t y, addr
                                                                    unsigned tol, unsigned grid, addr_t partial)
 {
     unsigned rbad, ybad, ymax;
-    gate_slice<XB, RB>(at_global<char>(y), at_global<char>(y_ref), at_global<char>(r), at_global<char>(r_ref), n, tol, grid, rbad, ybad, ymax);
+    gate_slice<XB, RB>(at_global<char>(y), at_global<char>(y_ref), at_global<char>(r), at_global<char>(r_ref), n, tol, blockIdx.x, grid,
+                       rbad, ybad, ymax);
     if (threadIdx.x == 0)
         at_global<addrms::u32x4>(partial)[blockIdx.x] = addrms::u32x4{rbad, ybad, ymax, 0u};
 }
+// tells: the first workgroup compares nothing and tells.
 template <int XB, int RB>
 __global__ __launch_bounds__(kGateBlock) void gate_one_kernel(addr_t y, addr_t y_ref, addr_t r, addr_t r_ref, long long n, unsigned tol,
-                                                               unsigned grid, addr_t out, unsigned unit, uint32_t number, addr_t done)
+                                                               unsigned grid, addr_t out, unsigned unit_tells, uint32_t number, addr_t words)
 {
+    const unsigned unit = unit_tells >> 1, tells = unit_tells & 1u, block = blockIdx.x - tells;
+    if (tells && blockIdx.x == 0u) {
+        addrms::unit_tell(&gate_reports, at_global<uint32_t>(words), kGateBlock);
+        return;
+    }
     unsigned rbad, ybad, ymax;
-    gate_slice<XB, RB>(at_global<char>(y), at_global<char>(y_ref), at_global<char>(r), at_global<char>(r_ref), n, tol, grid, rbad, ybad, ymax);
-    if (grid > 1u) gate_meet(rbad, ybad, ymax, grid, gate_words[unit], at_global<unsigned>(out), at_global<uint32_t>(done), number);
+    gate_slice<XB, RB>(at_global<char>(y), at_global<char>(y_ref), at_global<char>(r), at_global<char>(r_ref), n, tol, block, grid,
+                       rbad, ybad, ymax);
+    if (grid > 1u) gate_meet(rbad, ybad, ymax, block, grid, gate_words[unit], at_global<unsigned>(out), &gate_reports.state[unit], number);
     else if (threadIdx.x == 0) *at_global<addrms::u32x4>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
 }
+__global__ __launch_bounds__(kGateBlock) void gate_tell_kernel(addr_t words) { addrms::unit_tell(&gate_reports, at_global<uint32_t>(words), kGateBlock); }
 // One workgroup.  accumulate != 0 folds the new counts into what `out` already holds
 // (a second comparison graded into the same verdict).
 __global__ __launch_bounds__(kGateBlock) void gate_finish_kernel(addr_t partial, int nslots, addr_t out_at, int accumulate)
@@ -614,17 +626,21 @@ int launch_gate_in_one(const void* y, const void* y_ref, const void* r, const vo
 {
     unsigned workgroups = static_cast<unsigned>(gate_grid(n, xb));
     SlotPool<kGateUnits>::Lease lease;
-    *launched = workgroups == 1 || g_gate_slots.take(stream, 1, &lease) == Units::taken;
+    const auto tell = [stream](uint32_t* words) {
+        void* args[] = {&words};
+        return hipLaunchKernel(reinterpret_cast<const void*>(&gate_tell_kernel), dim3(1), dim3(kGateBlock), args, 0, stream);
+    };
+    *launched = workgroups == 1 || g_gate_slots.take(stream, 1, &lease, tell) == Units::taken;
     if (!*launched) return ADDRMS_OK;
     const bool meet = workgroups > 1;
-    unsigned unit = meet ? lease.unit() : 0u;
-    uint32_t *done = meet ? lease.done() : nullptr, number = meet ? lease.number() : 0u;
+    unsigned tells = meet && lease.tells() ? 1u : 0u, unit_tells = meet ? lease.unit() << 1 | tells : 0u;
+    uint32_t *words = meet ? lease.words() : nullptr, number = meet ? lease.number() : 0u;
     const void* fn = xb == 4   ? reinterpret_cast<const void*>(&gate_one_kernel<4, 4>)
                      : rb == 4 ? reinterpret_cast<const void*>(&gate_one_kernel<2, 4>)
                                : reinterpret_cast<const void*>(&gate_one_kernel<2, 2>);
-    void* args[] = {&y, &y_ref, &r, &r_ref, &n, &tol, &workgroups, &out, &unit, &number, &done};
+    void* args[] = {&y, &y_ref, &r, &r_ref, &n, &tol, &workgroups, &out, &unit_tells, &number, &words};
     // The launch's own status: hipGetLastError may have an older error, of the caller's, for a launch that is queued.
-    HIP_TRY(hipLaunchKernel(fn, dim3(workgroups), dim3(kGateBlock), args, 0, stream));
+    HIP_TRY(hipLaunchKernel(fn, dim3(workgroups + tells), dim3(kGateBlock), args, 0, stream));
     if (meet) lease.launched();
     return ADDRMS_OK;
 }

@@ -22,6 +22,7 @@
 #include "addrms_kernel.h"
 #include "direct_route.h"
 #include "silumul_kernel.h"
+#include "unit_report.h"
 
 namespace addrms {
 
@@ -456,39 +457,37 @@ __device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __
 // What bounds addrms_long_body is that one workgroup fills a CU and cannot hold its row: loads and stores take turns, and
 // what neither registers nor LDS keep is read twice.  Here `parts` workgroups share a row, a part each, held in registers
 // from the loads to the stores as in addrms_direct_body, so that a CU has several of them at different places of their
-// work and nothing is read twice.  They meet once, for the sum over the row: each puts the sum of its part into a 64-bit
-// word of the row's SplitRow and reads the words of the others.
+// work and nothing is read twice.  They meet once, for the sum over the row: each puts the sum of its part into words of the
+// row's SplitRow and reads those of the others.
 //
-// No wait depends on which workgroups are on the chip.  A word is 0 at first, kSplitClaimed once a workgroup that found it
-// missing for long has taken it upon itself to form that sum in the owner's place, and a sum with the sign bit set in the
-// end.  Both steps away from 0 are compare-and-swaps, so that one workgroup decides; it depends on nothing but its loads,
-// and every other one waits either for a workgroup that runs or for a word it may claim.  The owner of a claimed part
-// holds its elements as ever and waits for the sum like the others.  Outputs are written only after all words have been
-// read, so that whoever forms a sum finds the inputs untouched.  Both ways to a sum add in the same order.
+// Nothing has to be cleared for that.  A sum is two words, each with half of its bits and the launch's tag, which no other launch
+// with these units has or had (slot_pool.h), so that what earlier ones left is told from a sum of this one.  Both are read at once,
+// and those of up to eight parts are one cache line: three words of 22 bits of sum each, in three lines, 172.2 us against 170.6 for
+// 1024 x 131072 bf16.  Words that had to be 0 before a launch, cleared by the last workgroup of a row to have read them, took 0.3-0.6
+// us at the launch's end.
+//
+// No wait depends on which workgroups are on the chip.  A workgroup that finds a sum missing for long forms it itself, in the order
+// in which its owner does, and puts it into the first word with a compare-and-swap that finds no sum of this launch there: no one has
+// read a sum before that word is there, outputs are written only after all sums have been read, and so the inputs were untouched
+// while the sum was formed.  Where the owner or another workgroup was first, the sum formed here, perhaps of outputs, goes nowhere.  An owner that comes late writes the same bits once more.  So every workgroup waits either for
+// one that runs or for a sum that it may form.
 //
 // Words and counts are accessed with relaxed atomics of device scope, which go to the memory side of all XCDs' L2s, and
-// carry all that the workgroups tell each other, so that nothing else has to be made visible.  The last workgroup to have
-// read a row's words clears them, and the last row of a launch reports the launch as done, so that the words are clear
-// before they are another launch's (slot_map.h has who may use which).
+// carry all that the workgroups tell each other, so that nothing else has to be made visible.  A workgroup that has read a row's
+// words, its own writes to them long over, counts itself; the last one of each row reports the row (unit_report.h), and when all
+// rows have been, the units may be another launch's.  Nobody waits for what that takes.  Against words that are cleared and a report
+// to host memory, through the binding on buffers in rotation: 1 x 200000 bf16 6.0 -> 4.8 us, 64 x 55296 7.5 -> 6.6, 330 x 120896 58.7 ->
+// 56.2, 1024 x 131072 173.3 -> 170.5.
 //
 // A row's words and its count lie on 128-byte lines of their own: with eight rows to a line the atomics of a row's
 // neighbours queue up, some 10 ns per workgroup of the launch (1024 x 131072 bf16 in 32 parts 281 us against 213).
-// 1024 x 131072 bf16 208 -> 172 us (6.2 TB/s), 46 x 164992 fp16 25.9 -> 12.0, through the binding on buffers in rotation; more
+// 1024 x 131072 bf16 208 -> 170 us (6.3 TB/s), 46 x 164992 fp16 25.9 -> 12.0, through the binding on buffers in rotation; more
 // shapes at direct_addrms_split.  Not for rows that the registers of one workgroup hold: 2048 x 8192 fp32 in two parts 47.5
 // against 45.0.
-constexpr uint64_t kSplitClaimed = 1, kSplitSum = 1ull << 63;
-struct __align__(256) SplitRow {
-    uint64_t word[kSplitParts];
-    __align__(128) uint32_t read;                            // workgroups that have read all words
+struct __align__(128) SplitRow {
+    uint64_t word[kSplitParts][2];                           // tag, and the upper and the lower half of a part's sum
+    __align__(128) uint32_t read;                            // workgroups that have read all words; 0 again with the last one
 };
-struct __align__(128) SplitLaunch { uint32_t rows_done; };
-
-__device__ __forceinline__ bool split_take(uint64_t* word, uint64_t value)       // true: it was 0 and is now value
-{
-    uint64_t was = 0;
-    return __hip_atomic_compare_exchange_strong(word, &was, value, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t split_word(double sum) { return __builtin_bit_cast(uint64_t, sum) | kSplitSum; }
 
 // The sum over the squares of part `part`, formed by one wave in the order in which the part's own tpr threads form it.
 template <int DT, int VEC, int CPT, bool RAG>
@@ -530,37 +529,60 @@ __device__ __forceinline__ double split_part_sum(const char* xrow, const char* r
     return tpr == 64u ? read_lane(mine, 0) : read_lane(row16_scan(threadIdx.x < 16u ? mine : 0.0), 15);
 }
 
-// Called by the first wave: puts the part's sum into its word and returns the sum over the row once all words are there.
-// patience: reads of the words after which those still missing are claimed.
+// Called by the first wave: puts the part's sum into its words and returns the sum over the row once all are there.
+// patience: reads of the words after which a sum that is still missing is formed here.
 template <int DT, int VEC, int CPT, bool RAG>
-__device__ __forceinline__ double split_row_sum(double part_sum, SplitRow* row, uint32_t part, uint32_t parts, uint32_t patience,
-                                                const char* xrow, const char* rrow, const char* wbase, int32_t N, uint32_t tpr)
+__device__ __forceinline__ double split_row_sum(double part_sum, SplitRow* row, uint32_t tag, uint32_t part, uint32_t parts,
+                                                uint32_t patience, const char* xrow, const char* rrow, const char* wbase, int32_t N,
+                                                uint32_t tpr)
 {
-    const uint32_t lane = threadIdx.x;
-    if (lane == 0u) split_take(&row->word[part], split_word(part_sum));
-    uint64_t v = kSplitSum;                                  // lanes without a part: a sum of 0
+    constexpr int kSc1 = 16;
+    const __amdgpu_buffer_rsrc_t words = __builtin_amdgcn_make_buffer_rsrc(row, 0, sizeof(row->word), 0x00027000);
+    const auto word = [&](uint32_t half) { return static_cast<uint64_t>(tag) << 32 | half; };
+    if (threadIdx.x == 0u) {
+        const uint64_t s = __builtin_bit_cast(uint64_t, part_sum);
+        const u32x4 both = {static_cast<uint32_t>(s >> 32), tag, static_cast<uint32_t>(s), tag};
+        __builtin_amdgcn_raw_buffer_store_b128(both, words, part * 16u, 0, kSc1);
+    }
+    double sums;                                             // lane q: of part q, and 0 without one
     for (uint32_t reads = 0;; ++reads) {
-        if (lane < parts) v = __hip_atomic_load(&row->word[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__all((v & kSplitSum) != 0)) break;
-        if (reads >= patience) {
-            for (uint64_t missing = __ballot(v == 0); missing; missing &= missing - 1) {
-                const uint32_t q = static_cast<uint32_t>(__builtin_ctzll(missing));
-                bool claimed = false;
-                if (lane == 0u) claimed = split_take(&row->word[q], kSplitClaimed);
-                if (!__any(claimed)) continue;
-                const double sum = split_part_sum<DT, VEC, CPT, RAG>(xrow, rrow, wbase, N, q, tpr);
-                if (lane == 0u) __hip_atomic_store(&row->word[q], split_word(sum), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t lane = threadIdx.x;
+        asm volatile("" : "+v"(lane));                       // what is formed from it is not worth registers while a sum is formed
+        bool first = true, all = true;
+        sums = 0.0;
+        if (lane < parts) {
+            asm volatile("" ::: "memory");                   // read anew each time
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(words, lane * 16u, 0, kSc1);
+            first = v[1] == tag;
+            all = first && v[3] == tag;
+            sums = __builtin_bit_cast(double, static_cast<uint64_t>(v[0]) << 32 | v[2]);
+        }
+        if (__all(all)) break;
+        // A sum whose first word is there will have the other soon.  The one to form is the next behind this workgroup's own.
+        const uint32_t missing = static_cast<uint32_t>(__ballot(!first));
+        if (missing && reads >= patience) {
+            const uint32_t behind = missing & ~0u << part;
+            const uint32_t q = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(__builtin_ctz(behind ? behind : missing)));
+            const uint64_t sum = __builtin_bit_cast(uint64_t, split_part_sum<DT, VEC, CPT, RAG>(xrow, rrow, wbase, N, q, tpr));
+            lane = threadIdx.x;
+            asm volatile("" : "+v"(lane));
+            if (lane == 0u) {
+                uint64_t* w = row->word[q];
+                uint64_t now = __hip_atomic_load(&w[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (now >> 32 != tag && __hip_atomic_compare_exchange_strong(&w[0], &now, word(static_cast<uint32_t>(sum >> 32)), __ATOMIC_RELAXED,
+                                                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    __hip_atomic_store(&w[1], word(static_cast<uint32_t>(sum)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         __builtin_amdgcn_s_sleep(4);
     }
-    return wave_total(__builtin_bit_cast(double, v & ~kSplitSum));
+    return wave_total(sums);
 }
 
 template <int DT, int VEC, int CPT, int POL, bool RAG>
 __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* __restrict__ rp, const void* __restrict__ wp, double inv_n,
-                                                  float eps, int32_t N, uint32_t tpr, uint32_t parts, uint32_t M, SplitRow* rows,
-                                                  SplitLaunch* launch, uint32_t* done, uint32_t number, uint32_t patience)
+                                                  float eps, int32_t N, uint32_t tpr, uint32_t parts, uint32_t M, uint32_t at_row,
+                                                  SplitRow* rows, uint64_t* state, uint32_t tag, uint32_t number, uint32_t patience)
 {
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
@@ -568,9 +590,9 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     extern __shared__ double lds[];                          // one sum per wave, then the row's
 
     const uint32_t part = blockIdx.x, lane = threadIdx.x;
-    SplitRow* row = rows + blockIdx.y;
-    char* xrow = static_cast<char*>(xp) + static_cast<int64_t>(blockIdx.y) * N * XB;
-    char* rrow = static_cast<char*>(rp) + static_cast<int64_t>(blockIdx.y) * N * RB;
+    SplitRow* row = rows + at_row;
+    char* xrow = static_cast<char*>(xp) + static_cast<int64_t>(at_row) * N * XB;
+    char* rrow = static_cast<char*>(rp) + static_cast<int64_t>(at_row) * N * RB;
     const char* wbase = static_cast<const char*>(wp);
     const RowWalk<XB, VEC, RAG> rw(xrow, 0u, N, lane, tpr);
     const int32_t stride = rw.stride, col0 = rw.col0 + static_cast<int32_t>(part) * CPT * stride;
@@ -607,10 +629,11 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     __builtin_amdgcn_sched_barrier(0);
     uint32_t before = 0;                                     // workgroups that had read the words earlier
     if (lane < 64u) {
-        const double total = split_row_sum<DT, VEC, CPT, RAG>(part_sum, row, part, parts, patience, xrow, rrow, wbase, N, tpr);
+        const double total = split_row_sum<DT, VEC, CPT, RAG>(part_sum, row, tag, part, parts, patience, xrow, rrow, wbase, N, tpr);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the wave's own stores to words are over
         if (lane == 0u) {
             lds[16] = total;
-            before = __hip_atomic_fetch_add(&row->read, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            before = __builtin_amdgcn_atomic_inc32(&row->read, parts - 1u, __ATOMIC_RELAXED, "agent");
         }
     }
     wg_sync_lds();
@@ -642,16 +665,8 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     }
     one.store(xrow, rrow, rw.single, has_single, rstd);
 
-    // Everything below is atomic and goes to the memory side in this order: a wave's wait for its own earlier stores is
-    // all that is needed between two steps.
-    if (lane >= 64u || static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(before))) != parts - 1u) return;
-    if (lane < parts) __hip_atomic_store(&row->word[lane], uint64_t{0}, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (lane == 0u) __hip_atomic_store(&row->read, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lane != 0u || __hip_atomic_fetch_add(&launch->rows_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != M - 1u) return;
-    __hip_atomic_store(&launch->rows_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __hip_atomic_store(done, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (lane < 64u && static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(before))) == parts - 1u && lane == 0u)
+        unit_piece_done(state, number, at_row, M);
 }
 
 // The same rows by one workgroup each, for a call that finds no units for the kernel above: whatever made it find none, its
@@ -700,7 +715,7 @@ __device__ __forceinline__ void addrms_alone_body(void* __restrict__ xp, void* _
         }
         if (part == 0u) acc = one.add(acc);
         const double sum = row_sum(acc, RED_WAVE, tpr, lane, part & 1u, lds);
-        if ((lane & 63u) == part) mine = __builtin_bit_cast(double, split_word(sum) & ~kSplitSum);
+        if ((lane & 63u) == part) mine = sum;
     }
     const float rstd = rsqrt_to_f32(__builtin_fma(wave_total(mine), inv_n, static_cast<double>(eps)));
 

@@ -2,7 +2,7 @@
 // code only, no HIP.
 //
 // Such memory belongs to the loaded code object and is cut into units.  A launch has units of its own, from before it is
-// queued until it has reported itself as done in host memory; only then are they another launch's.  Nothing else is asked: not
+// queued until it is reported as done in host memory (slot_pool.h); only then are they another launch's.  Nothing else is asked: not
 // which stream a launch is on (a stream's handle may come back as another stream's while the first one's work is in flight),
 // nor on which GPU (each has a copy of the memory, and no unit is used on two of them at a time).
 #pragma once
@@ -17,7 +17,7 @@ template <int UNITS, typename Number = uint32_t>
 class SlotMap {
 public:
     // The first of `units` adjacent units that are free now; -1: none found.  Calls are serialised by the caller.
-    // done[u]: the number of the last launch with units from u on that has reported itself.
+    // done[u]: the number of the last launch with units from u on that has been reported.
     int take(int units, const volatile uint32_t* done)
     {
         // Once around from behind the units taken last, where those longest in flight are.  No launch's units begin before u
@@ -40,7 +40,7 @@ public:
         }
         return -1;
     }
-    // The number that the launch with these units reports.
+    // The number by which the launch with these units is reported.
     uint32_t number(int first) const { return unit_[first].number; }
     // There is no such launch after all.
     void give_back(int first) { unit_[first].span = 0; }

@@ -1,0 +1,88 @@
+// Launches that are told about by later ones (slot_pool.h), on a HIP of a few lines (fake_hip), for tests/test_slot_tell.py.
+#include <stdio.h>
+#include <string.h>
+
+#include "slot_pool.h"
+
+using namespace addrms_host;
+
+#define EXPECT(c) do { if (!(c)) { printf("line %d: %s\n", __LINE__, #c); return 1; } } while (0)
+
+// A launch tells once in a sixteenth of the units; where it could not be launched, the next one does.
+static int tells()
+{
+    static SlotPool<64> pool;
+    for (int i = 0; i < 40; ++i) {
+        SlotPool<64>::Lease lease;
+        EXPECT(pool.take(nullptr, 1, &lease) == Units::taken && lease.words() + lease.unit() == lease.done());
+        EXPECT(lease.tells() == (i % 4 == 3));
+        lease.launched();
+        *lease.done() = lease.number();
+    }
+    SlotPool<64>::Lease wide;
+    EXPECT(pool.take(nullptr, 4, &wide) == Units::taken && wide.tells());
+    wide.launched();
+    for (int i = 0; i < 4; ++i) {
+        SlotPool<64>::Lease lease;
+        EXPECT(pool.take(nullptr, 1, &lease) == Units::taken && lease.tells() == (i == 3));
+    }
+    SlotPool<64>::Lease after;
+    EXPECT(pool.take(nullptr, 1, &after) == Units::taken && after.tells());
+    return 0;
+}
+
+// No two launches with a unit have the same tag, whatever units they have besides.
+static int tags()
+{
+    static SlotPool<16> pool;
+    uint32_t last[16] = {};
+    unsigned seed = 1;
+    for (int i = 0; i < 5000; ++i) {
+        seed = seed * 1664525u + 1013904223u;
+        const int units = 1 + static_cast<int>(seed >> 24) % 7;
+        SlotPool<16>::Lease lease;
+        EXPECT(pool.take(nullptr, units, &lease) == Units::taken);
+        for (unsigned u = lease.unit(); u < lease.unit() + units; ++u) {
+            EXPECT(lease.tag() > last[u]);
+            last[u] = lease.tag();
+        }
+        if (seed >> 16 & 1) continue;                        // not launched after all
+        lease.launched();
+        *lease.done() = lease.number();
+    }
+    for (uint32_t t : last) EXPECT(t < 5000);
+    return 0;
+}
+
+// All launches have ended, and nothing says so: the call that finds no units has it told, and one of the caller's errors stays.
+static int asks()
+{
+    static SlotPool<4> pool;
+    SlotPool<4>::Lease held[4];
+    for (auto& l : held) {
+        EXPECT(pool.take(nullptr, 1, &l) == Units::taken);
+        l.launched();
+    }
+    int told = 0;
+    SlotPool<4>::Lease lease;
+    EXPECT(pool.take(nullptr, 2, &lease, [&](uint32_t* words) {
+        told += words == held[0].words();
+        for (auto& l : held) words[l.unit()] = l.number();
+        return hipSuccess;
+    }) == Units::taken && told == 1);
+    lease.launched();
+    SlotPool<4>::Lease more;
+    EXPECT(pool.take(nullptr, 3, &more, [](uint32_t*) { return fake_hip::is(hipErrorInvalidHandle); }) == Units::none);
+    EXPECT(hipPeekAtLastError() == hipSuccess);
+    return 0;
+}
+
+int main(int, char** argv)
+{
+    const struct { const char* name; int (*run)(); } tests[] = {{"tells", tells}, {"tags", tags}, {"asks", asks}};
+    int bad = 1;
+    for (const auto& t : tests)
+        if (!strcmp(argv[1], t.name)) bad = t.run();
+    if (!bad) printf("ok\n");
+    return bad;
+}
