@@ -476,8 +476,8 @@ __device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __
 // carry all that the workgroups tell each other, so that nothing else has to be made visible.  A workgroup that has read a row's
 // words, its own writes to them long over, counts itself; the last one of each row reports the row (unit_report.h), and when all
 // rows have been, the units may be another launch's.  Nobody waits for what that takes.  Against words that are cleared and a report
-// to host memory, through the binding on buffers in rotation: 1 x 200000 bf16 6.0 -> 4.8 us, 64 x 55296 7.5 -> 6.6, 330 x 120896 58.7 ->
-// 56.2, 1024 x 131072 173.3 -> 170.5.
+// to host memory, through the binding on buffers in rotation: 1 x 200000 bf16 6.0 -> 4.8 us, 64 x 55296 7.5 -> 6.2, 330 x 120896 58.7 ->
+// 56.0, 1024 x 131072 173.3 -> 170.4.
 //
 // A row's words and its count lie on 128-byte lines of their own: with eight rows to a line the atomics of a row's
 // neighbours queue up, some 10 ns per workgroup of the launch (1024 x 131072 bf16 in 32 parts 281 us against 213).
@@ -628,12 +628,14 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     for (int c = 0; c < CPT; ++c) ld_stream<POL_CACHED, XB * VEC, RAG ? XB : 16>(wbase, rw.clamped(col0 + c * stride) * XB, wv[c]);
     __builtin_amdgcn_sched_barrier(0);
     uint32_t before = 0;                                     // workgroups that had read the words earlier
+    uint64_t was = 0;
     if (lane < 64u) {
         const double total = split_row_sum<DT, VEC, CPT, RAG>(part_sum, row, tag, part, parts, patience, xrow, rrow, wbase, N, tpr);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the wave's own stores to words are over
         if (lane == 0u) {
             lds[16] = total;
             before = __builtin_amdgcn_atomic_inc32(&row->read, parts - 1u, __ATOMIC_RELAXED, "agent");
+            if (at_row == 0u) was = unit_state(state);
         }
     }
     wg_sync_lds();
@@ -666,7 +668,7 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     one.store(xrow, rrow, rw.single, has_single, rstd);
 
     if (lane < 64u && static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(before))) == parts - 1u && lane == 0u)
-        unit_piece_done(state, number, at_row, M);
+        unit_piece_done(state, was, number, at_row, M);
 }
 
 // The same rows by one workgroup each, for a call that finds no units for the kernel above: whatever made it find none, its

@@ -24,14 +24,19 @@ __device__ __forceinline__ void unit_done(uint64_t* state, uint32_t number)
 {
     __hip_atomic_store(state, static_cast<uint64_t>(number) << 32 | kUnitDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// One of `all` (up to 2^31) pieces of the launch is done; piece: which.  Two operations on one word, in that order, and nobody waits
-// for them: the first to come sets the count to 0, since numbers of a place only grow, and what is added is kUnitDone in all, but
-// short of it for less than all pieces.
-__device__ __forceinline__ void unit_piece_done(uint64_t* state, uint32_t number, uint32_t piece, uint32_t all)
+// One of `all` pieces of the launch is done; piece: which.  One addition each, which nobody waits for.  Piece 0 makes the last launch's
+// number this one's; what is added to the count beside it comes to kUnitDone (from that, or from 0 before the first launch) with all
+// pieces, and not before.  was, of piece 0: the state at any time of the launch before this.
+__device__ __forceinline__ uint64_t unit_state(const uint64_t* state) { return __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void unit_piece_done(uint64_t* state, uint64_t was, uint32_t number, uint32_t piece, uint32_t all)
 {
-    (void)__hip_atomic_fetch_max(state, static_cast<uint64_t>(number) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    (void)__hip_atomic_fetch_add(state, static_cast<uint64_t>(piece == 0u ? kUnitDone - (all - 1u) : 1u), __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
+    if (all == 1u) return unit_done(state, number);
+    uint64_t more = 1u;
+    if (piece == 0u) {
+        more = static_cast<uint64_t>(number - static_cast<uint32_t>(was >> 32)) << 32;
+        more += static_cast<uint64_t>(static_cast<uint32_t>(was) < kUnitDone ? kUnitDone : 0u) - (all - 1u);
+    }
+    (void)__hip_atomic_fetch_add(state, more, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // By a workgroup of `threads`: the numbers of launches that are done and not told yet go to the host's words.
 template <int UNITS>
