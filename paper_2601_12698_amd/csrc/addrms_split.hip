@@ -20,9 +20,8 @@ static __device__ UnitReports<kSplitUnits> split_reports;
 namespace {
 
 // tells: the first row of the grid is none of the tensors', and its first workgroup tells.
-// Six waves per SIMD asked for where one register more than 80 (fp16 without) takes a CU its third workgroup.
 template <int DT, int VEC, int CPT, int POL, bool RAG>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(VEC == 8 && CPT == 4 && RAG ? 6 : 4))) void addrms_split(addr_t x, addr_t r, addr_t w, double inv_n, float eps, int N, unsigned shape,
+__global__ __launch_bounds__(1024) void addrms_split(addr_t x, addr_t r, addr_t w, double inv_n, float eps, int N, unsigned shape,
                                                      unsigned rows, unsigned unit_tells, addr_t words, uint32_t number, uint32_t tag,
                                                      unsigned patience)
 {

@@ -501,11 +501,9 @@ __device__ __forceinline__ double split_part_sum(const char* xrow, const char* r
     for (uint32_t w = 0; w * 64u < tpr; ++w) {
         const RowWalk<XB, VEC, RAG> rw(xrow, 0u, N, w * 64u + threadIdx.x, tpr);
         double acc = 0.0;
-        // The wave holds its own part meanwhile, and what this needs on top decides how many workgroups a CU holds: not unrolled
-        // fp32 62 registers, unrolled 78 (500 x 200000 276 us against 307), bf16 87 and 102 (4096 x 32832 180 against 188); but
-        // 16-bit ragged rows 89 and 78 (1000 x 50001 79.5 against 77.1).
-        constexpr int kUnroll = RAG && VEC == 8 ? CPT : 1;
-#pragma unroll kUnroll
+        // The wave holds its own part meanwhile, and what this needs on top decides how many workgroups a CU holds (fp32 62 registers, unrolled
+        // 78: 500 x 200000 276 us against 307; 16-bit ragged rows 80, unrolled 79 or, for fp16, 81, which are one workgroup less).
+#pragma unroll 1
         for (int c = 0; c < CPT; ++c) {
             const int32_t col = rw.col0 + (static_cast<int32_t>(part) * CPT + c) * rw.stride;
             const uint32_t colc = rw.clamped(col);
@@ -628,14 +626,12 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     for (int c = 0; c < CPT; ++c) ld_stream<POL_CACHED, XB * VEC, RAG ? XB : 16>(wbase, rw.clamped(col0 + c * stride) * XB, wv[c]);
     __builtin_amdgcn_sched_barrier(0);
     uint32_t before = 0;                                     // workgroups that had read the words earlier
-    uint64_t was = 0;
     if (lane < 64u) {
         const double total = split_row_sum<DT, VEC, CPT, RAG>(part_sum, row, tag, part, parts, patience, xrow, rrow, wbase, N, tpr);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the wave's own stores to words are over
         if (lane == 0u) {
             lds[16] = total;
             before = __builtin_amdgcn_atomic_inc32(&row->read, parts - 1u, __ATOMIC_RELAXED, "agent");
-            if (at_row == 0u) was = unit_state(state);
         }
     }
     wg_sync_lds();
@@ -668,7 +664,7 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     one.store(xrow, rrow, rw.single, has_single, rstd);
 
     if (lane < 64u && static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(before))) == parts - 1u && lane == 0u)
-        unit_piece_done(state, was, number, at_row, M);
+        unit_piece_done(state, number, at_row, M);
 }
 
 // The same rows by one workgroup each, for a call that finds no units for the kernel above: whatever made it find none, its

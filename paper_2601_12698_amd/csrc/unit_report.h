@@ -24,17 +24,21 @@ __device__ __forceinline__ void unit_done(uint64_t* state, uint32_t number)
 {
     __hip_atomic_store(state, static_cast<uint64_t>(number) << 32 | kUnitDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// One of `all` pieces of the launch is done; piece: which.  One addition each, which nobody waits for.  Piece 0 makes the last launch's
-// number this one's; what is added to the count beside it comes to kUnitDone (from that, or from 0 before the first launch) with all
-// pieces, and not before.  was, of piece 0: the state at any time of the launch before this.
-__device__ __forceinline__ uint64_t unit_state(const uint64_t* state) { return __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void unit_piece_done(uint64_t* state, uint64_t was, uint32_t number, uint32_t piece, uint32_t all)
+// One of `all` pieces of the launch is done; piece: which.  With the number, the count of pieces comes to kUnitDone with the last one
+// and not before.  Nobody waits for the additions, but they are made one after the other, 10 ns each.  Few pieces each make sure first
+// that the number is this launch's (numbers of a place only grow, and the first to come starts the count at 0); of many, which would
+// take twice as long, piece 0 looks at what the launch before has left and adds the step to this one's.
+__device__ __forceinline__ void unit_piece_done(uint64_t* state, uint32_t number, uint32_t piece, uint32_t all)
 {
+    constexpr uint32_t kFew = 8;
     if (all == 1u) return unit_done(state, number);
-    uint64_t more = 1u;
-    if (piece == 0u) {
-        more = static_cast<uint64_t>(number - static_cast<uint32_t>(was >> 32)) << 32;
-        more += static_cast<uint64_t>(static_cast<uint32_t>(was) < kUnitDone ? kUnitDone : 0u) - (all - 1u);
+    uint64_t more = piece == 0u ? kUnitDone - (all - 1u) : 1u;
+    if (all <= kFew) {
+        (void)__hip_atomic_fetch_max(state, static_cast<uint64_t>(number) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (piece == 0u) {
+        const uint64_t was = __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // and pieces of this launch, if any
+        more += static_cast<uint64_t>(number - static_cast<uint32_t>(was >> 32)) << 32;
+        more -= static_cast<uint32_t>(was) & kUnitDone;      // 0 before the first launch
     }
     (void)__hip_atomic_fetch_add(state, more, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
