@@ -32,7 +32,7 @@ int64_t direct_launch_split(const DirectPlan& p, void* x, void* r, const void* w
                             unsigned patience, void* stream, int* status, bool* capturing);
 // The kernels for the same rows that need no units: the one of calls that find none, and the one of captured calls.
 int direct_launch_alone(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream);
-int direct_launch_long(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream);
+int direct_launch_whole(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream);
 int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream);
 int direct_launch_mergestates(const DirectPlan& p, const void* va, const float* sa, const void* vb, const float* sb, void* vo,
                               float* so, void* stream);

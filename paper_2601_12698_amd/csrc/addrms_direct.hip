@@ -130,9 +130,10 @@ namespace addrms_host {
 bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, uintptr_t w, DirectPlan* out)
 {
     if (!direct_addrms_route(M, N, dtype, default_vec, x, r, w, out)) return false;
+    if (!out->long_row) direct_addrms_split_few(M, N, dtype, out);
+    direct_split_kernels(dtype, out);
     if (out->long_row) {
         out->fn = addrms_long_fn(dtype, out->pol, out->rag);
-        direct_split_kernels(dtype, out);
         out->long_index = static_cast<unsigned>(dtype) * 4u + (out->pol == POL_NT ? 2u : 0u) + (out->rag ? 1u : 0u);
     } else {
         out->fn = addrms_fn(dtype, out->cpt, out->pol, out->rag, out->block_y > 1);
@@ -169,8 +170,18 @@ static int go(const DirectPlan& p, unsigned grid, void** args, void* stream)
                                             static_cast<hipStream_t>(stream)));
 }
 
-int direct_launch_long(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream)
+static int launch_rows(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream)
 {
+    double inv_n = 1.0 / static_cast<double>(N);
+    long long m = M;
+    int n = static_cast<int>(N);
+    unsigned tpr = p.block_x, rpw = p.block_y;
+    void* args[] = {&x, &r, &w, &inv_n, &eps, &n, &tpr, &rpw, &m};
+    return go(p, p.grid, args, stream);
+}
+int direct_launch_whole(const DirectPlan& p, void* x, void* r, const void* w, float eps, int64_t M, int64_t N, void* stream)
+{
+    if (!p.long_row) return launch_rows(p, x, r, w, eps, M, N, stream);
     if (const hipError_t e = prepare_long(p); e != hipSuccess) return static_cast<int>(e);
     double inv_n = 1.0 / static_cast<double>(N);
     int n = static_cast<int>(N);
@@ -182,7 +193,7 @@ int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, f
 {
     if (p.split_fn) {
         // Of the kernel that a capture of this call runs: a capture is no place for this.
-        if (const hipError_t e = prepare_long(p); e != hipSuccess) return static_cast<int>(e);
+        if (const hipError_t e = p.long_row ? prepare_long(p) : hipSuccess; e != hipSuccess) return static_cast<int>(e);
         int status;
         bool capturing;
         const int64_t split = direct_launch_split(p, x, r, w, eps, M, N, dtype, kSplitPatience, stream, &status, &capturing);
@@ -192,13 +203,7 @@ int direct_launch_addrms(const DirectPlan& p, void* x, void* r, const void* w, f
             return direct_launch_alone(p, static_cast<char*>(x) + split * N * x_bytes(dtype),
                                        static_cast<char*>(r) + split * N * r_bytes(dtype), w, eps, M - split, N, stream);
     }
-    if (p.long_row) return direct_launch_long(p, x, r, w, eps, M, N, stream);
-    double inv_n = 1.0 / static_cast<double>(N);
-    long long m = M;
-    int n = static_cast<int>(N);
-    unsigned tpr = p.block_x, rpw = p.block_y;
-    void* args[] = {&x, &r, &w, &inv_n, &eps, &n, &tpr, &rpw, &m};
-    return go(p, p.grid, args, stream);
+    return direct_launch_whole(p, x, r, w, eps, M, N, stream);
 }
 int direct_launch_silumul(const DirectPlan& p, const void* x, void* out, int64_t d, void* stream)
 {

@@ -1353,7 +1353,7 @@ int addrms_whole_rows_probe(void* x, void* residual, const void* weight, float e
     DirectPlan p;
     const int st = split_plan(x, residual, weight, M, N, dtype, &p);
     if (st != ADDRMS_OK || M == 0) return st;
-    HIP_TRY(static_cast<hipError_t>(captured ? direct_launch_long(p, x, residual, weight, eps, M, N, stream)
+    HIP_TRY(static_cast<hipError_t>(captured ? direct_launch_whole(p, x, residual, weight, eps, M, N, stream)
                                              : direct_launch_alone(p, x, residual, weight, eps, M, N, stream)));
     return ADDRMS_OK;
 }

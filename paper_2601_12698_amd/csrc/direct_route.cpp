@@ -142,6 +142,26 @@ static int64_t ragged_min(int vec, int default_vec, int64_t N)
     return vec == 8 && N < 32 * vec ? kMB : 0;
 }
 
+// Rows that the registers of one workgroup hold, up to so many at a time, are split like long ones: a CU that has a row of 100 to 260 KB
+// to itself takes 2 us and more to read and write it.  Formats of four elements per piece only; one workgroup / split, us on three
+// sets (fp16+fp32 gains a tenth less, with 80 rows of 16416 and 50 of 18000 nothing):
+//   fp32       1 row          8            16           32           64           80           96           128
+//   12288      3.62 / 3.44                 4.07 / 3.87  4.17 / 4.45  4.46 / 5.09
+//   14336      3.81 / 3.64    4.70 / 3.71  4.72 / 3.97  4.81 / 4.34  5.10 / 5.12  5.27 / 5.51  5.46 / 5.86  5.95 / 6.59
+//   16448      4.31 / 3.82    5.26 / 3.97  5.29 / 4.14  5.43 / 4.76  5.82 / 5.39  6.05 / 5.67  6.27 / 6.09  6.92 / 7.14
+//   20480      4.83 / 3.84    5.59 / 3.96  5.74 / 4.29  5.91 / 4.87  6.27 / 5.57  6.51 / 6.12  6.79 / 6.81  7.81 / 7.98
+//   24577      5.63 / 4.17    6.43 / 4.42  7.06 / 4.70  7.97 / 5.47  9.00 / 6.25  9.24 / 7.22  9.50 / 7.87  10.4 / 9.39
+//   28672      6.31 / 4.05    7.25 / 4.28  7.26 / 4.56  7.49 / 5.35  8.00 / 6.33  8.28 / 7.30  8.74 / 8.10  10.3 / 10.1
+//   32768      6.44 / 4.10    7.78 / 4.29  8.16 / 4.71  8.03 / 5.56  8.74 / 6.87  9.18 / 7.83  9.63 / 8.90  11.4 / 11.3
+// More rows than CUs gain up to 8 % split where they are ragged and lose up to 17 % otherwise (400 x 16448 17.5 / 21.1).
+void direct_addrms_split_few(int64_t M, int64_t N, int dtype, DirectRoute* out)
+{
+    const int64_t cus = hw().compute_units, pieces = (N + (out->rag ? kLineBytes / x_bytes(dtype) - 1 : 0) + 3) / 4;
+    const int64_t most = pieces > 7168 ? cus / 2 : pieces > 6144 ? cus / 8 * 3 : pieces > 5120 ? cus / 16 * 5 : pieces > 4096 ? cus / 32 * 5 :
+                         pieces > 3072 ? cus / 16 : 0;
+    if (direct_vec(dtype) == 4 && M <= most) direct_addrms_split(M, N, dtype, out);
+}
+
 // Threads per row: one per piece up to 1024, then as few pieces per thread as that allows, in equal shares: on 40 shapes
 // tried with 1 to 8 the fewest were the fastest, by 2-8 % against twice as many.  Written-through rows of more than 256
 // pieces take at least two, which then are stored in one go after the row sum (256 x 8192 bf16 4.0 / 4.2 against 4.2 / 5.3,

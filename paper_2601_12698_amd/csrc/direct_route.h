@@ -51,8 +51,8 @@ struct DirectRoute {
     bool long_row = false;                                  // rows beyond the registers: units = chunks parked in LDS
     unsigned grid = 0, block_x = 0, block_y = 1, lds = 0;   // block_y: rows of a workgroup
     unsigned units = 0, total = 0, mul = 0, shift = 0;      // flat operators: see direct_kernel.h
-    // Long rows that are split over workgroups where the launch can have units (slot_map.h); the rest of the route is
-    // what runs where it cannot.
+    // Rows that are split over workgroups where the launch can have units (slot_map.h): long ones, and few ones in registers; the rest
+    // of the route is what runs where it cannot.
     unsigned parts = 0, part_threads = 0;                   // 0: not split
     int part_cpt = 0, part_pol = 0;
 };
@@ -61,6 +61,8 @@ struct DirectRoute {
 // default_vec elements per access) asks for; *_align: bases or-ed together.
 bool direct_addrms_route(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, uintptr_t w,
                          DirectRoute* out);
+// For a route of rows in registers: splits them where they are few and wide.
+void direct_addrms_split_few(int64_t M, int64_t N, int dtype, DirectRoute* out);
 bool direct_silumul_route(int64_t M, int64_t d, int dtype, uintptr_t x_align, uintptr_t out_align, DirectRoute* out);
 bool direct_mergestates_route(int64_t rows, int64_t d, int dtype, uintptr_t v_align, DirectRoute* out);
 
