@@ -11,13 +11,13 @@ using namespace addrms;
 
 namespace {
 
-// MULTI: several rows per workgroup (rpw).  The launch shape travels as arguments: together with the rest they are preloaded
+// MULTI: several rows per workgroup (rpw).  KEEP: see SingleElement.  The launch shape travels as arguments: together with the rest they are preloaded
 // into scalar registers, where blockDim would be another load before the first address is known.
-template <int DT, int VEC, int CPT, int POL, bool RAG, bool MULTI>
+template <int DT, int VEC, int CPT, int POL, bool RAG, bool MULTI, bool KEEP>
 __global__ __launch_bounds__(1024) void addrms_direct(addr_t x, addr_t r, addr_t w, double inv_n, float eps, int N,
                                                       unsigned tpr, unsigned rpw, long long M)
 {
-    addrms_direct_body<DT, VEC, CPT, POL, RAG, (CPT > 1), MULTI>(at_global(x), at_global(r), at_global(w), eps, inv_n, N, tpr, rpw, M);
+    addrms_direct_body<DT, VEC, CPT, POL, RAG, (CPT > 1), MULTI, KEEP>(at_global(x), at_global(r), at_global(w), eps, inv_n, N, tpr, rpw, M);
 }
 template <int DT, int VEC, int POL, bool RAG>
 __global__ __launch_bounds__(kLongThreads) void addrms_long(addr_t x, addr_t r, addr_t w, float eps, double inv_n, int N,
@@ -39,45 +39,47 @@ __global__ __launch_bounds__(kFlatThreads) void mergestates_flat(addr_t va, addr
                                    at_global<char>(vo), at_global<float>(so), units, total, fd);
 }
 
-template <int DT, int CPT, int POL, bool RAG, bool MULTI> const void* addrms_fn3()
+template <int DT, int CPT, int POL, bool RAG, bool MULTI> const void* addrms_fn3(bool keep)
 {
     constexpr int VEC = direct_vec(DT);
-    if constexpr (direct_instance(VEC, CPT, POL, RAG, MULTI)) return reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL, RAG, MULTI>);
+    if constexpr (direct_instance(VEC, CPT, POL, RAG, MULTI))
+        return RAG && keep ? reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL, RAG, MULTI, RAG>)
+                           : reinterpret_cast<const void*>(&addrms_direct<DT, VEC, CPT, POL, RAG, MULTI, false>);
     else return nullptr;
 }
-template <int DT, int CPT, int POL> const void* addrms_fn2(bool rag, bool multi)
+template <int DT, int CPT, int POL> const void* addrms_fn2(bool rag, bool multi, bool keep)
 {
-    return rag ? (multi ? addrms_fn3<DT, CPT, POL, true, true>() : addrms_fn3<DT, CPT, POL, true, false>())
-               : (multi ? addrms_fn3<DT, CPT, POL, false, true>() : addrms_fn3<DT, CPT, POL, false, false>());
+    return rag ? (multi ? addrms_fn3<DT, CPT, POL, true, true>(keep) : addrms_fn3<DT, CPT, POL, true, false>(keep))
+               : (multi ? addrms_fn3<DT, CPT, POL, false, true>(keep) : addrms_fn3<DT, CPT, POL, false, false>(keep));
 }
-template <int DT, int CPT> const void* addrms_fn2(int pol, bool rag, bool multi)
+template <int DT, int CPT> const void* addrms_fn2(int pol, bool rag, bool multi, bool keep)
 {
     switch (pol) {
-    case POL_NT: return addrms_fn2<DT, CPT, POL_NT>(rag, multi);
-    case POL_WT: return addrms_fn2<DT, CPT, POL_WT>(rag, multi);
-    case POL_SHARED: return addrms_fn2<DT, CPT, POL_SHARED>(rag, multi);
+    case POL_NT: return addrms_fn2<DT, CPT, POL_NT>(rag, multi, keep);
+    case POL_WT: return addrms_fn2<DT, CPT, POL_WT>(rag, multi, keep);
+    case POL_SHARED: return addrms_fn2<DT, CPT, POL_SHARED>(rag, multi, keep);
     default: return nullptr;
     }
 }
-template <int DT> const void* addrms_fn1(int cpt, int pol, bool rag, bool multi)
+template <int DT> const void* addrms_fn1(int cpt, int pol, bool rag, bool multi, bool keep)
 {
     switch (cpt) {
-    case 1: return addrms_fn2<DT, 1>(pol, rag, multi);
-    case 2: return addrms_fn2<DT, 2>(pol, rag, multi);
-    case 3: return addrms_fn2<DT, 3>(pol, rag, multi);
-    case 4: return addrms_fn2<DT, 4>(pol, rag, multi);
-    case 6: return addrms_fn2<DT, 6>(pol, rag, multi);
-    case 8: return addrms_fn2<DT, 8>(pol, rag, multi);
+    case 1: return addrms_fn2<DT, 1>(pol, rag, multi, keep);
+    case 2: return addrms_fn2<DT, 2>(pol, rag, multi, keep);
+    case 3: return addrms_fn2<DT, 3>(pol, rag, multi, keep);
+    case 4: return addrms_fn2<DT, 4>(pol, rag, multi, keep);
+    case 6: return addrms_fn2<DT, 6>(pol, rag, multi, keep);
+    case 8: return addrms_fn2<DT, 8>(pol, rag, multi, keep);
     default: return nullptr;
     }
 }
-const void* addrms_fn(int dtype, int cpt, int pol, bool rag, bool multi)
+const void* addrms_fn(int dtype, int cpt, int pol, bool rag, bool multi, bool keep)
 {
     switch (dtype) {
-    case DT_BF16: return addrms_fn1<DT_BF16>(cpt, pol, rag, multi);
-    case DT_FP16: return addrms_fn1<DT_FP16>(cpt, pol, rag, multi);
-    case DT_FP16_RES32: return addrms_fn1<DT_FP16_RES32>(cpt, pol, rag, multi);
-    case DT_FP32: return addrms_fn1<DT_FP32>(cpt, pol, rag, multi);
+    case DT_BF16: return addrms_fn1<DT_BF16>(cpt, pol, rag, multi, keep);
+    case DT_FP16: return addrms_fn1<DT_FP16>(cpt, pol, rag, multi, keep);
+    case DT_FP16_RES32: return addrms_fn1<DT_FP16_RES32>(cpt, pol, rag, multi, keep);
+    case DT_FP32: return addrms_fn1<DT_FP32>(cpt, pol, rag, multi, keep);
     default: return nullptr;
     }
 }
@@ -136,7 +138,7 @@ bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintpt
         out->fn = addrms_long_fn(dtype, out->pol, out->rag);
         out->long_index = static_cast<unsigned>(dtype) * 4u + (out->pol == POL_NT ? 2u : 0u) + (out->rag ? 1u : 0u);
     } else {
-        out->fn = addrms_fn(dtype, out->cpt, out->pol, out->rag, out->block_y > 1);
+        out->fn = addrms_fn(dtype, out->cpt, out->pol, out->rag, out->block_y > 1, out->keep_shared);
     }
     return out->fn != nullptr;
 }

@@ -97,11 +97,14 @@ struct SingleElement {
     raw_t<XB> x{}, w{};
     raw_t<RB> r{};
     float h = 0.0f;
+    // KEEP: ordinary loads, which leave the line to the pieces beside the elements and to the next row; else non-temporal ones
+    // (direct_addrms_route has the rule).
+    template <bool KEEP>
     __device__ __forceinline__ void load(const char* xrow, const char* rrow, const char* wbase, uint32_t at, bool mine)
     {
         if (RAG && mine) {
-            ld_raw<XB, true>(xrow + static_cast<uint64_t>(at * XB), x);
-            ld_raw<RB, true>(rrow + static_cast<uint64_t>(at * RB), r);
+            ld_raw<XB, !KEEP>(xrow + static_cast<uint64_t>(at * XB), x);
+            ld_raw<RB, !KEEP>(rrow + static_cast<uint64_t>(at * RB), r);
             ld_raw<XB, false>(wbase + static_cast<uint64_t>(at * XB), w);
         }
     }
@@ -114,18 +117,19 @@ struct SingleElement {
         }
         return acc;
     }
+    template <bool NT = true>
     __device__ __forceinline__ void store(char* xrow, char* rrow, uint32_t at, bool mine, float rstd) const
     {
         if (RAG && mine) {
             float f[1] = {h};
             raw_t<RB> rout;
             pack_vec<RB, T::BF, 1>(f, rout);
-            st_raw<RB, true>(rrow + static_cast<uint64_t>(at * RB), rout);
+            st_raw<RB, NT>(rrow + static_cast<uint64_t>(at * RB), rout);
             const float t = h * rstd;
             f[0] = t * get_elem<XB, T::BF>(w, 0);
             raw_t<XB> yout;
             pack_vec<XB, T::BF, 1>(f, yout);
-            st_raw<XB, true>(xrow + static_cast<uint64_t>(at * XB), yout);
+            st_raw<XB, NT>(xrow + static_cast<uint64_t>(at * XB), yout);
         }
     }
 };
@@ -154,7 +158,7 @@ struct SingleElement {
 // Ragged: 2047 x 4095 fp16 18.0 -> 12.9 (from HBM 27.2 -> 13.3), 9000 x 6150 bf16 91 -> 73, 300 x
 // 10001 8.9 -> 6.7, 8192 x 1000 fp16+fp32 17.9 -> 15.5 (from HBM 23.1 -> 18.7); the single elements
 // cost the first 0.7 and weights at odd addresses 0.4 of what an aligned row would not.
-template <int DT, int VEC, int CPT, int POL, bool RAG, bool DEFER, bool MULTI>
+template <int DT, int VEC, int CPT, int POL, bool RAG, bool DEFER, bool MULTI, bool KEEP>
 __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* __restrict__ rp,
                                                    const void* __restrict__ wp, float eps, double inv_n, int32_t N,
                                                    uint32_t tpr, uint32_t rpw, int64_t M)
@@ -183,7 +187,7 @@ __device__ __forceinline__ void addrms_direct_body(void* __restrict__ xp, void* 
     float h[CPT][VEC];
     double acc = 0.0;
     SingleElement<DT, RAG> one;
-    one.load(xrow, rrow, wbase, rw.single, rw.has_single);
+    one.template load<KEEP>(xrow, rrow, wbase, rw.single, rw.has_single);
     raw_t<XB * VEC> wv[CPT];
     auto load_weights = [&] {
 #pragma unroll
@@ -340,7 +344,7 @@ __device__ __forceinline__ void addrms_long_body(void* __restrict__ xp, void* __
     };
 
     SingleElement<DT, RAG> one;
-    one.load(xbase, rbase, wbase, rw.single, rw.has_single);
+    one.template load<false>(xbase, rbase, wbase, rw.single, rw.has_single);
     // ---- register part
 #pragma unroll
     for (int g = 0; g < CPT; g += UNR) {
@@ -520,7 +524,7 @@ __device__ __forceinline__ double split_part_sum(const char* xrow, const char* r
             }
         }
         SingleElement<DT, RAG> one;
-        one.load(xrow, rrow, wbase, rw.single, rw.has_single && part == 0u);
+        one.template load<true>(xrow, rrow, wbase, rw.single, rw.has_single && part == 0u);
         const double sum = wave_total(one.add(acc));
         if (threadIdx.x == w) mine = sum;
     }
@@ -599,7 +603,7 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
     float h[CPT][VEC];
     double acc = 0.0;
     SingleElement<DT, RAG> one;
-    one.load(xrow, rrow, wbase, rw.single, has_single);
+    one.template load<true>(xrow, rrow, wbase, rw.single, has_single);
     raw_t<XB * VEC> xv[CPT];
     raw_t<RB * VEC> rv[CPT];
 #pragma unroll
@@ -661,7 +665,7 @@ __device__ __forceinline__ void addrms_split_body(void* __restrict__ xp, void* _
             st_stream<POL, XB * VEC>(xrow, static_cast<uint32_t>(col) * XB, out);
         }
     }
-    one.store(xrow, rrow, rw.single, has_single, rstd);
+    one.template store<false>(xrow, rrow, rw.single, has_single, rstd);
 
     if (lane < 64u && static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(before))) == parts - 1u && lane == 0u)
         unit_piece_done(state, number, at_row, M);
@@ -687,7 +691,7 @@ __device__ __forceinline__ void addrms_alone_body(void* __restrict__ xp, void* _
     const RowWalk<XB, VEC, RAG> rw(xrow, 0u, N, lane, tpr);
     const int32_t stride = rw.stride;
     SingleElement<DT, RAG> one;
-    one.load(xrow, rrow, wbase, rw.single, rw.has_single);
+    one.template load<true>(xrow, rrow, wbase, rw.single, rw.has_single);
 
     double mine = 0.0;                                       // lane p of a wave: sum of part p
     for (uint32_t part = 0; part < parts; ++part) {

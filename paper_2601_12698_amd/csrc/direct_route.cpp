@@ -200,9 +200,17 @@ void direct_addrms_split_few(int64_t M, int64_t N, int dtype, DirectRoute* out)
 // fp16+fp32 56.1 / 56.3 against 43.9 / 43.8; 31492 x 516 fp32 gains, 45.3 / 44.9 against 47.0 / 46.5).
 // A default configuration with narrower accesses than these admits bases that they do not (86912 fp32: two elements per
 // access): such rows take the ragged walk, whole vectors or not.
+// Single elements are read with ordinary loads, which leave their lines for the pieces beside them and for the row that shares the
+// line, but where x and residual have 16 to 36 MB and rows are longer than 3 KB of x, or 16 to 64 MB and 16 KB.  Non-temporal
+// against ordinary on three sets: 74751 x 301 fp16 45.6 / 34.7, 32467 x 693 bf16 38.9 / 32.2, 12000 x 501 12.0 / 10.8, 22522 x 999 fp16 35.8 /
+// 32.0, 513 x 4001 bf16 5.05 / 4.79, 488 x 4095 fp16 4.79 / 4.49, 244 x 4095 fp32 4.56 / 4.23; but 2014 x 4095 fp16 12.4 / 12.9, 1007 x 8191 12.9 /
+// 13.1, 503 x 16383 12.5 / 12.8, 2015 x 2047 fp32 12.0 / 12.2.  By size, 4095 fp16: 12 MB 1.03 times as fast, 16 MB 1.03, 20 MB 0.97, 24 MB
+// 0.96, 28 MB 0.99, 40 MB 1.01, 100 MB 1.02; 16383 fp16: 1.03, 1.03, 1.00, 0.99, 0.98, 0.99, and 64 MB 1.00.  Rows split over workgroups,
+// 300 x 33333 bf16: 17.5 / 16.8, and 16.5 with ordinary stores of them too, which change nothing in rows that are not split.
 bool direct_addrms_route(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, uintptr_t w, DirectRoute* out)
 {
     constexpr int64_t kWriteThroughMin = 512 << 10, kThreePiecesMin = 4 << 20, kLineWalkMin = 16 << 20, kSharedLinesRow = 3072;
+    constexpr int64_t kKeepMin = 36 << 20, kKeepLongRow = 16000, kKeepLongMin = 64 << 20;
     const int vec = direct_vec(dtype), xb = x_bytes(dtype), rb = r_bytes(dtype);
     const int64_t bytes = M * N * (xb + rb);
     const bool split = N % vec != 0 || x % (vec * xb) != 0 || r % (vec * rb) != 0 || w % (vec * xb) != 0;   // single elements
@@ -227,6 +235,7 @@ bool direct_addrms_route(int64_t M, int64_t N, int dtype, int default_vec, uintp
     out->cpt = static_cast<int>(cpt);
     out->pol = pol;
     out->rag = rag;
+    out->keep_shared = N * xb <= kSharedLinesRow || bytes <= kLineWalkMin || bytes > (N * xb >= kKeepLongRow ? kKeepLongMin : kKeepMin);
     if (!direct_instance(vec, out->cpt, pol, rag, out->block_y > 1)) return false;    // never: the tests walk the rules
     const int64_t workgroups = (M + out->block_y - 1) / out->block_y;
     if (!launchable(workgroups, tpr * out->block_y)) return false;

@@ -1,7 +1,10 @@
-// Which rows in registers are split over workgroups, for tests/test_few_rows.py.  Host code only.
+// Which rows in registers are split over workgroups, and how ragged ones read their single elements, for tests/test_few_rows.py and
+// tests/test_shared_lines.py.  Host code only.
 //   walk            every length in steps, and the numbers of rows around the limits: shapes; prints "ok"
-//   (no argument)   one problem per line: dtype M N; one split per line of output
+//   singles         one problem per line: dtype M N; how its single elements are read
+//   (no argument)   likewise; one split per line of output
 #include <stdio.h>
+#include <string.h>
 
 #include <initializer_list>
 
@@ -19,9 +22,10 @@ static bool route(int dtype, int64_t M, int64_t N, DirectRoute* p)
     return true;
 }
 
-int main(int argc, char**)
+int main(int argc, char** argv)
 {
-    if (argc > 1) {
+    const bool singles = argc > 1 && !strcmp(argv[1], "singles");
+    if (argc > 1 && !singles) {
         for (int dt : {ADDRMS_BF16, ADDRMS_FP16, ADDRMS_FP16_RES32, ADDRMS_FP32})
             for (int64_t N = 64; N <= 32768; N += N < 12000 ? 331 : 37)
                 for (int64_t M : {1, 2, 15, 16, 17, 40, 64, 80, 81, 127, 128, 129, 500, 5000}) {
@@ -47,7 +51,9 @@ int main(int argc, char**)
     long long M, N;
     while (scanf("%d %lld %lld", &dtype, &M, &N) == 3) {
         DirectRoute p;
-        if (!route(dtype, M, N, &p) || !p.parts) printf("whole\n");
+        const bool rows = route(dtype, M, N, &p);
+        if (singles) printf("%s\n", !rows || !p.rag ? "none" : p.keep_shared ? "ordinary" : "nontemporal");
+        else if (!rows || !p.parts) printf("whole\n");
         else printf("parts=%u threads=%u pieces=%d\n", p.parts, p.part_threads, p.part_cpt);
     }
     return 0;
