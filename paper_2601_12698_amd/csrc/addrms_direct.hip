@@ -103,19 +103,20 @@ const void* addrms_long_fn(int dtype, int pol, bool rag)
     }
 }
 
-template <int DT> const void* silumul_fn1(int pol, bool rag)
+template <int DT> const void* silumul_fn1(int pol, bool rag, bool keep)
 {
+    if (rag && keep) return reinterpret_cast<const void*>(&silumul_flat<DT, POL_SHARED, true>);       // written through, being small
     if (rag) return pol == POL_NT ? reinterpret_cast<const void*>(&silumul_flat<DT, POL_NT, true>)
                                   : reinterpret_cast<const void*>(&silumul_flat<DT, POL_WT, true>);
     return pol == POL_NT ? reinterpret_cast<const void*>(&silumul_flat<DT, POL_NT, false>)
                          : reinterpret_cast<const void*>(&silumul_flat<DT, POL_WT, false>);
 }
-const void* silumul_fn(int dtype, int pol, bool rag)
+const void* silumul_fn(int dtype, int pol, bool rag, bool keep)
 {
     switch (dtype) {
-    case DT_BF16: return silumul_fn1<DT_BF16>(pol, rag);
-    case DT_FP16: return silumul_fn1<DT_FP16>(pol, rag);
-    case DT_FP32: return silumul_fn1<DT_FP32>(pol, rag);
+    case DT_BF16: return silumul_fn1<DT_BF16>(pol, rag, keep);
+    case DT_FP16: return silumul_fn1<DT_FP16>(pol, rag, keep);
+    case DT_FP32: return silumul_fn1<DT_FP32>(pol, rag, keep);
     default: return nullptr;
     }
 }
@@ -145,7 +146,7 @@ bool direct_addrms_plan(int64_t M, int64_t N, int dtype, int default_vec, uintpt
 bool direct_silumul_plan(int64_t M, int64_t d, int dtype, uintptr_t x_align, uintptr_t out_align, DirectPlan* out)
 {
     if (!direct_silumul_route(M, d, dtype, x_align, out_align, out)) return false;
-    out->fn = silumul_fn(dtype, out->pol, out->rag);
+    out->fn = silumul_fn(dtype, out->pol, out->rag, out->keep_shared);
     return out->fn != nullptr;
 }
 bool direct_mergestates_plan(int64_t rows, int64_t d, int dtype, uintptr_t v_align, DirectPlan* out)

@@ -205,7 +205,8 @@ void direct_addrms_split_few(int64_t M, int64_t N, int dtype, DirectRoute* out)
 // against ordinary on three sets: 74751 x 301 fp16 45.6 / 34.7, 32467 x 693 bf16 38.9 / 32.2, 12000 x 501 12.0 / 10.8, 22522 x 999 fp16 35.8 /
 // 32.0, 513 x 4001 bf16 5.05 / 4.79, 488 x 4095 fp16 4.79 / 4.49, 244 x 4095 fp32 4.56 / 4.23; but 2014 x 4095 fp16 12.4 / 12.9, 1007 x 8191 12.9 /
 // 13.1, 503 x 16383 12.5 / 12.8, 2015 x 2047 fp32 12.0 / 12.2.  By size, 4095 fp16: 12 MB 1.03 times as fast, 16 MB 1.03, 20 MB 0.97, 24 MB
-// 0.96, 28 MB 0.99, 40 MB 1.01, 100 MB 1.02; 16383 fp16: 1.03, 1.03, 1.00, 0.99, 0.98, 0.99, and 64 MB 1.00.  Rows split over workgroups,
+// 0.96, 28 MB 0.99, 40 MB 1.01, 100 MB 1.02; 16383 fp16: 1.03, 1.03, 1.00, 0.99, 0.98, 0.99, and 64 MB 1.00.  From HBM the same from 24 MB
+// on (74751 x 301 46.3 / 35.1), 0.98 to 1.04 below.  Rows split over workgroups,
 // 300 x 33333 bf16: 17.5 / 16.8, and 16.5 with ordinary stores of them too, which change nothing in rows that are not split.
 bool direct_addrms_route(int64_t M, int64_t N, int dtype, int default_vec, uintptr_t x, uintptr_t r, uintptr_t w, DirectRoute* out)
 {
@@ -244,14 +245,20 @@ bool direct_addrms_route(int64_t M, int64_t N, int dtype, int default_vec, uintp
     return true;
 }
 
+// Ragged rows, whose waves share the lines at their ends, are read with ordinary loads up to 26 MB of output.  Non-temporal against
+// these on three sets / from HBM: 4073 x 1023 bf16 (25 MB of traffic) 5.6 / 6.6 against 5.2 / 6.5, 8146 x 1023 9.9 / 10.8 against 8.4 / 10.6, 1525 x 8191
+// 13.4 against 11.9, 2033 x 4099 9.7 / 10.6 against 8.4 / 10.6, 4073 x 1023 fp32 9.2 / 10.4 against 8.3 / 10.5; 16293 x 1023 bf16 (100 MB) 17.4
+// against 17.9.  (add+RMSNorm gains as much on three sets, and loses 10 to 20 % from HBM.)
 bool direct_silumul_route(int64_t M, int64_t d, int dtype, uintptr_t x_align, uintptr_t out_align, DirectRoute* out)
 {
+    constexpr int64_t kKeepMax = 26 << 20;
     const int es = x_bytes(dtype), vec = 16 / es;
     const bool rag = d % vec != 0;
     if (d < 2 * vec || M >= kFlatMax / d) return false;       // rows of one piece have no division; 32-bit positions
     if (out_align % 16 != 0 || (!rag && x_align % 16 != 0)) return false;
     out->pol = M * d * es <= write_through_max() ? POL_WT : POL_NT;
     out->rag = rag;
+    out->keep_shared = rag && M * d * es <= kKeepMax;
     if (rag) set_flat(out, (M * d + vec - 1) / vec, d, M * d);
     else set_flat(out, M * (d / vec), d / vec, M * (d / vec));
     return true;

@@ -48,7 +48,7 @@ struct DirectRoute {
     int pol = 0;                                            // as above
     int cpt = 0;                                            // pieces per thread (rows in registers)
     bool rag = false;                                       // ragged: see direct_kernel.h
-    bool keep_shared = false;                               // ragged rows in registers: ordinary loads of the single elements
+    bool keep_shared = false;                               // ragged rows: ordinary loads of single elements; silu_and_mul: of all
     bool long_row = false;                                  // rows beyond the registers: units = chunks parked in LDS
     unsigned grid = 0, block_x = 0, block_y = 1, lds = 0;   // block_y: rows of a workgroup
     unsigned units = 0, total = 0, mul = 0, shift = 0;      // flat operators: see direct_kernel.h

@@ -1,7 +1,7 @@
 // Which rows in registers are split over workgroups, and how ragged ones read their single elements, for tests/test_few_rows.py and
 // tests/test_shared_lines.py.  Host code only.
 //   walk            every length in steps, and the numbers of rows around the limits: shapes; prints "ok"
-//   singles         one problem per line: dtype M N; how its single elements are read
+//   singles [silu]  one problem per line: dtype M N; how its single elements, or all of a ragged activation, are read
 //   (no argument)   likewise; one split per line of output
 #include <stdio.h>
 #include <string.h>
@@ -51,6 +51,10 @@ int main(int argc, char** argv)
     long long M, N;
     while (scanf("%d %lld %lld", &dtype, &M, &N) == 3) {
         DirectRoute p;
+        if (argc > 2) {                                      // silu_and_mul
+            printf("%s\n", !direct_silumul_route(M, N, dtype, 0, 0, &p) || !p.rag ? "none" : p.keep_shared && p.pol == POL_WT ? "ordinary" : "nontemporal");
+            continue;
+        }
         const bool rows = route(dtype, M, N, &p);
         if (singles) printf("%s\n", !rows || !p.rag ? "none" : p.keep_shared ? "ordinary" : "nontemporal");
         else if (!rows || !p.parts) printf("whole\n");

@@ -1,5 +1,5 @@
-"""Single elements of ragged rows, which share a cache line with the row before or behind: ordinary loads or non-temporal ones (host
-code, on the CPU), and the bits of rows that are read either way (on the GPU)."""
+"""Ragged rows, which share cache lines with the row before and behind: ordinary loads or non-temporal ones, of their single elements
+in add+RMSNorm and of all in silu_and_mul (host code, on the CPU), and rows that are read either way (on the GPU)."""
 import subprocess
 
 import pytest
@@ -23,6 +23,18 @@ def test_both_sides_of_each_limit(driver):                  # noqa: F811
     r = subprocess.run([driver, "singles"], input=lines, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[-4000:]
     assert [(p, g) for (p, _), g in zip(CASES, r.stdout.split("\n"))] == CASES
+
+
+# 26 MB of output
+SILU = [(("bf16", 3325, 4099), "ordinary"), (("bf16", 3326, 4099), "nontemporal"), (("fp32", 6662, 1023), "ordinary"), (("fp32", 6663, 1023), "nontemporal"),
+        (("fp16", 1, 8191), "ordinary"), (("bf16", 3325, 4096), "none")]
+
+
+def test_both_sides_of_the_limit_of_activations(driver):    # noqa: F811
+    lines = "\n".join(f"{B.DTYPE_IDS[d]} {M} {N}" for (d, M, N), _ in SILU)
+    r = subprocess.run([driver, "singles", "silu"], input=lines, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-4000:]
+    assert [(p, g) for (p, _), g in zip(SILU, r.stdout.split("\n"))] == SILU
 
 
 @pytest.mark.gpu
