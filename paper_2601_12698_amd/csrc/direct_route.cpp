@@ -57,7 +57,8 @@ namespace addrms_host {
 // (1024 x 131072 bf16 in 4 / 8 / 16 parts 183 / 173 / 180; 500 x 200000 fp32 in 13 / 17 / 25 of four pieces 265 / 259 / 271).  Fewer rows
 // than that keeps the chip busy with are cut finer, down to 512 pieces, up to 512 workgroups in all, with as few pieces per
 // thread as 1024 threads allow (46 x 164992 fp16 in 6 / 11 / 21 parts 17.8 / 12.2 / 14.4; 1 x 200000 in 8 / 12 / 16 7.5 / 7.2 / 6.4).
-// Against one workgroup per row, on three sets / from HBM:
+// Against one workgroup per row, on three sets / from HBM (and the numbers of parts above: measured when meeting took 0.7 to 3 us
+// more than it does now, 1 x 200000 4.8, 1024 x 131072 170.5):
 //   1 x 200000 bf16   23.9 / 28.7  ->  6.4 / 6.3        2048 x 65536     195.7 / 195.5 -> 174.0 / 174.3
 //   8 x 123776        14.8 / 18.3  ->  6.4 / 6.4        4096 x 40960     228.4 / 227.8 -> 214.7 / 214.5
 //   60 x 131072       20.2 / 30.3  -> 12.5 / 12.7       500 x 200000 fp32 354 / 354 -> 274 / 274
