@@ -131,8 +131,8 @@ typedef struct addrms_cfg {
  * one such launch eagerly before capturing.  Long rows without a cfg are split over
  * workgroups that meet in device memory of the library (24 MiB per GPU, part of its
  * code object), a launch in a piece of its own until its end is reported in 4 KiB of
- * pinned host memory, allocated once by the first such call (by a later launch, one in
- * some dozens; a call that finds no piece free queues one that does no more).  A call that finds no piece
+ * pinned host memory per GPU, allocated once by the first such call there (by a later launch
+ * on that GPU, one in some dozens; a call that finds no piece free queues one that does no more).  A call that finds no piece
  * free, 2.7 ms or more of such work being in flight, waits for one as it would for room in a
  * full queue, at most 4 ms, and not again after a wait in vain until one has been free; then
  * it runs a kernel that needs none and gives the same bits.  A captured call runs a third
@@ -496,7 +496,7 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
  * the process ends), so this call allocates no device memory, frees nothing and does not wait: its kernels are only
  * enqueued on `stream`, and counts_out is valid once the stream has reached them.  They are one kernel, or two if the
  * stream is capturing.  (The end of one-kernel calls of more than one workgroup, 4096 elements of 16 bits or 2048 of 32, is
- * reported by later ones in 1 KiB of pinned host memory, allocated once by the first of them.  With 256 of them in flight a call waits for one to
+ * reported by later ones on the same GPU in 1 KiB of pinned host memory per GPU, allocated once by the first of them.  With 256 of them in flight a call waits for one to
  * end as it would for room in a full queue, at most 4 ms, and not again after a wait in vain until one has ended; then it
  * is two kernels.)  Nothing in it is a memset: a capturing caller records two kernel nodes, or one for a single workgroup.
  * n beyond 2^32-1 is INVALID_ARG as above (the arrays never limit n: a launch uses at most 512 workgroups whatever n is).

@@ -3,8 +3,8 @@
 //
 // Such memory belongs to the loaded code object and is cut into units.  A launch has units of its own, from before it is
 // queued until it is reported as done in host memory (slot_pool.h); only then are they another launch's.  Nothing else is asked: not
-// which stream a launch is on (a stream's handle may come back as another stream's while the first one's work is in flight),
-// nor on which GPU (each has a copy of the memory, and no unit is used on two of them at a time).
+// which stream a launch is on (a stream's handle may come back as another stream's while the first one's work is in flight).
+// Each GPU has a copy of the memory, and a map of its own.
 #pragma once
 #include <stdint.h>
 

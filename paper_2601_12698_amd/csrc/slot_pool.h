@@ -1,6 +1,9 @@
 // Units of device memory for launches whose workgroups meet in it (slot_map.h has the rule), and the host memory in which it is
 // reported that launches are done with theirs.  A launch says so in device memory (unit_report.h), and a later one, where it is
 // asked to, tells the host what it finds there when it begins: a write to host memory at the end of a launch costs 1 us of it.
+//
+// A launch can tell of launches on its own GPU only.  So each GPU has units, counts and words of its own, and what one of them has in
+// flight, or has not told yet, is nothing to the others.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -16,31 +19,34 @@ namespace addrms_host {
 
 enum class Units { taken, none, capturing };
 
-// One pool per kind of launch, for all GPUs.
+// One pool per kind of launch, with the units of each GPU.
 template <int UNITS>
 class SlotPool {
+    struct Gpu;
+
 public:
+    static constexpr int kMaxGpus = 64;                      // eight of them in eight partitions each; further ones have no units
     // A launch's units.  They go back where launched() is not called.
     class Lease {
     public:
         Lease() = default;
         Lease(const Lease&) = delete;
         Lease& operator=(const Lease&) = delete;
-        ~Lease() { if (pool_) pool_->give_back(*this); }
+        ~Lease() { if (gpu_) give_back(*this); }
         unsigned unit() const { return static_cast<unsigned>(unit_); }
         // What is to be written, and where, once the launch is done with its units (system scope).
         uint32_t number() const { return number_; }
         uint32_t* done() const { return done_; }
         // As number(), but of all launches with any of these units: no other one of them has it.
         uint32_t tag() const { return tag_; }
-        // Whether this launch is to tell what launches before it have said, and the words of all units for that.
+        // Whether this launch is to tell what launches before it on its GPU have said, and the words of all its units for that.
         bool tells() const { return tells_; }
         uint32_t* words() const { return done_ - unit_; }
-        void launched() { pool_ = nullptr; }
+        void launched() { gpu_ = nullptr; }
 
     private:
         friend class SlotPool;
-        SlotPool* pool_ = nullptr;
+        Gpu* gpu_ = nullptr;
         uint32_t* done_ = nullptr;
         uint32_t number_ = 0, tag_ = 0;
         int unit_ = -1;
@@ -64,34 +70,42 @@ public:
             return Units::none;
         }
         if (capture != hipStreamCaptureStatusNone) return Units::capturing;
-        uint32_t* done = reports(pending);
+        // A launch goes to its stream's GPU and meets in that GPU's memory, whichever GPU is the current one.
+        int device = -1;
+        if (device_of(stream, &device) != hipSuccess) {
+            forget_error(pending);
+            return Units::none;
+        }
+        if (device < 0 || device >= kMaxGpus) return Units::none;
+        Gpu& gpu = gpu_[device];
+        uint32_t* done = reports(gpu, pending);
         if (!done) return Units::none;
         using clock = std::chrono::steady_clock;
         for (clock::time_point began{};; std::this_thread::sleep_for(std::chrono::microseconds(20))) {
             const bool first = began == clock::time_point{};
             {
-                std::lock_guard<std::mutex> lock(mu_);
-                int u = map_.take(units, done);
-                uint32_t tag = u < 0 ? 0 : *std::max_element(tag_ + u, tag_ + u + units) + 1;
+                std::lock_guard<std::mutex> lock(gpu.mu);
+                int u = gpu.map.take(units, done);
+                uint32_t tag = u < 0 ? 0 : *std::max_element(gpu.tag + u, gpu.tag + u + units) + 1;
                 if (u >= 0 && tag == 0) {
-                    map_.give_back(u);
+                    gpu.map.give_back(u);
                     u = -1;
                 }
-                in_vain_ = in_vain_ && u < 0;
+                gpu.in_vain = gpu.in_vain && u < 0;
                 if (u >= 0) {
-                    std::fill_n(tag_ + u, units, tag);
-                    untold_ += units;
+                    std::fill_n(gpu.tag + u, units, tag);
+                    gpu.untold += units;
                     lease->tag_ = tag;
-                    lease->pool_ = this;
+                    lease->gpu_ = &gpu;
                     lease->done_ = done + u;
-                    lease->number_ = map_.number(u);
+                    lease->number_ = gpu.map.number(u);
                     lease->unit_ = u;
-                    lease->tells_ = untold_ >= kTellEvery;
-                    if (lease->tells_) untold_ = 0;
+                    lease->tells_ = gpu.untold >= kTellEvery;
+                    if (lease->tells_) gpu.untold = 0;
                     return Units::taken;
                 }
-                if (!first && clock::now() - began > std::chrono::milliseconds(4)) in_vain_ = true;
-                if (in_vain_ && !first) return Units::none;
+                if (!first && clock::now() - began > std::chrono::milliseconds(4)) gpu.in_vain = true;
+                if (gpu.in_vain && !first) return Units::none;
             }
             if (!first) continue;
             if (tell(done) != hipSuccess) forget_error(pending);
@@ -110,20 +124,26 @@ private:
     {
         if (!pending) (void)hipGetLastError();
     }
-    void give_back(const Lease& lease)
+    // The handles of the null streams and of the calling thread's are the same on every GPU: they are the current one's.
+    static hipError_t device_of(hipStream_t stream, int* device)
     {
-        std::lock_guard<std::mutex> lock(mu_);
-        map_.give_back(lease.unit_);
-        if (lease.tells_) untold_ = kTellEvery;              // the next one does
+        const bool current = stream == nullptr || stream == hipStreamLegacy || stream == hipStreamPerThread;
+        return current ? hipGetDevice(device) : hipStreamGetDevice(stream, device);
+    }
+    static void give_back(const Lease& lease)
+    {
+        std::lock_guard<std::mutex> lock(lease.gpu_->mu);
+        lease.gpu_->map.give_back(lease.unit_);
+        if (lease.tells_) lease.gpu_->untold = kTellEvery;   // the next one does
     }
     // A launch tells if so many units have been taken since the last one that does, itself included.
     static constexpr int kTellEvery = UNITS / 16;
-    // One word per unit, which every GPU can write, allocated once and kept until the process ends.  NULL: not there (yet: no
-    // thread waits for the one that allocates it).  Must not disturb a capture that another thread may be in.
-    uint32_t* reports(bool pending)
+    // One word per unit of the GPU, allocated once and kept until the process ends.  NULL: not there (yet: no thread waits for
+    // the one that allocates it).  Must not disturb a capture that another thread may be in.
+    static uint32_t* reports(Gpu& gpu, bool pending)
     {
-        uint32_t* done = done_.load(std::memory_order_acquire);
-        if (done || allocating_.exchange(true)) return done;
+        uint32_t* done = gpu.done.load(std::memory_order_acquire);
+        if (done || gpu.allocating.exchange(true)) return done;
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         if (hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
             void* p = nullptr;
@@ -134,21 +154,24 @@ private:
         }
         if (done) {
             std::fill_n(done, UNITS, 0u);
-            done_.store(done, std::memory_order_release);
+            gpu.done.store(done, std::memory_order_release);
         } else {
-            allocating_.store(false);
+            gpu.allocating.store(false);
         }
         return done;
     }
-    std::mutex mu_;
-    SlotMap<UNITS> map_;
-    // Tags of the last launches with each unit, from 1.  They grow by one while all units have been taken once, or 1 ms of launches, so
-    // that 2^32 of them take a month and more.  Units behind the last one are not taken any more.
-    uint32_t tag_[UNITS] = {};
-    bool in_vain_ = false;
-    int untold_ = 0;                                         // units taken since a launch was asked to tell
-    std::atomic<uint32_t*> done_{nullptr};
-    std::atomic<bool> allocating_{false};
+    struct Gpu {
+        std::mutex mu;
+        SlotMap<UNITS> map;
+        // Tags of the last launches with each unit, from 1.  They grow by one while all units have been taken once, or 1 ms of
+        // launches, so that 2^32 of them take a month and more.  Units behind the last one are not taken any more.
+        uint32_t tag[UNITS] = {};
+        bool in_vain = false;
+        int untold = 0;                                      // units taken since a launch was asked to tell
+        std::atomic<uint32_t*> done{nullptr};
+        std::atomic<bool> allocating{false};
+    };
+    Gpu gpu_[kMaxGpus];
 };
 
 }  // namespace addrms_host

@@ -5,8 +5,7 @@
 // by a workgroup of its own at its beginning, where the write is over long before the launch is.  As the last access of the launch
 // itself that write took 0.7-1.5 us, in which the next launch of the stream waits.
 //
-// Which GPU a launch ran on is not asked here either: each GPU tells a number once, the one that only it has found new, and a
-// place has its next launch, with another number, only after that has arrived.  So what was told never goes back.
+// A GPU tells of its own launches, into words of its own (slot_pool.h), and each number once.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -2,6 +2,9 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <utility>
+#include <vector>
+
 #include "slot_pool.h"
 
 using namespace addrms_host;
@@ -77,9 +80,61 @@ static int asks()
     return 0;
 }
 
+// Launches that end at once, on GPUs of their own; one that tells knows those of its GPU.  How many calls found no units at first.
+struct Gpus {
+    static SlotPool<64> pool;
+    std::vector<std::pair<uint32_t*, uint32_t>> ended[8];    // not told yet: where, and what
+    int without = 0;
+
+    explicit Gpus(int n)
+    {
+        for (int g = 0; g < n; ++g) fake_hip::device[stream(g)] = g;
+    }
+    static hipStream_t stream(int gpu) { return reinterpret_cast<hipStream_t>(static_cast<size_t>(0x1000 + gpu)); }
+    void tell(int gpu)
+    {
+        for (const auto& e : ended[gpu]) *e.first = e.second;
+        ended[gpu].clear();
+    }
+    bool launch(int gpu, int units)
+    {
+        SlotPool<64>::Lease lease;
+        const Units got = pool.take(stream(gpu), units, &lease, [&](uint32_t*) {
+            ++without;
+            tell(gpu);
+            return hipSuccess;
+        });
+        if (got != Units::taken) return false;
+        if (lease.tells()) tell(gpu);
+        lease.launched();
+        ended[gpu].push_back({lease.done(), lease.number()});
+        return true;
+    }
+};
+SlotPool<64> Gpus::pool;
+
+// GPUs in rotation: what is told of one of them does not depend on the others.
+static int rotation()
+{
+    Gpus gpus(8);
+    for (int i = 0; i < 20000; ++i) EXPECT(gpus.launch(i % 8, i < 10000 ? 1 : 4));
+    EXPECT(gpus.without == 0);
+    return 0;
+}
+
+// A GPU that is not used any more, with launches that nobody has told of, takes nothing from another one.
+static int quiet()
+{
+    Gpus gpus(2);
+    for (int i = 0; i < 2046; ++i) EXPECT(gpus.launch(i % 2, 1));
+    for (int i = 0; i < 554; ++i) EXPECT(gpus.launch(0, 1));
+    EXPECT(gpus.without == 0);
+    return 0;
+}
+
 int main(int, char** argv)
 {
-    const struct { const char* name; int (*run)(); } tests[] = {{"tells", tells}, {"tags", tags}, {"asks", asks}};
+    const struct { const char* name; int (*run)(); } tests[] = {{"tells", tells}, {"tags", tags}, {"asks", asks}, {"rotation", rotation}, {"quiet", quiet}};
     int bad = 1;
     for (const auto& t : tests)
         if (!strcmp(argv[1], t.name)) bad = t.run();
