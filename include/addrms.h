@@ -132,7 +132,8 @@ typedef struct addrms_cfg {
  * workgroups that meet in device memory of the library (24 MiB per GPU, part of its
  * code object), a launch in a piece of its own until its end is reported in 4 KiB of
  * pinned host memory per GPU, allocated once by the first such call there (by a later launch
- * on that GPU, one in some dozens; a call that finds no piece free queues one that does no more).  A call that finds no piece
+ * on that GPU, one in some dozens; a call that finds no piece free and waits queues one that does
+ * no more, and calls that do not wait one in 4 ms).  A call that finds no piece
  * free, 2.7 ms or more of such work being in flight, waits for one as it would for room in a
  * full queue, at most 4 ms, and not again after a wait in vain until one has been free; then
  * it runs a kernel that needs none and gives the same bits.  A captured call runs a third
@@ -498,7 +499,7 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
  * stream is capturing.  (The end of one-kernel calls of more than one workgroup, 4096 elements of 16 bits or 2048 of 32, is
  * reported by later ones on the same GPU in 1 KiB of pinned host memory per GPU, allocated once by the first of them.  With 256 of them in flight a call waits for one to
  * end as it would for room in a full queue, at most 4 ms, and not again after a wait in vain until one has ended; then it
- * is two kernels.)  Nothing in it is a memset: a capturing caller records two kernel nodes, or one for a single workgroup.
+ * is two kernels.  A call that waits queues a launch that only reports, and calls that do not wait one in 4 ms.)  Nothing in it is a memset: a capturing caller records two kernel nodes, or one for a single workgroup.
  * n beyond 2^32-1 is INVALID_ARG as above (the arrays never limit n: a launch uses at most 512 workgroups whatever n is).
  * Every call on a GPU may use that GPU's array: calls that may overlap in time on one GPU (different streams, concurrent
  * graphs) race on it and must be serialised by the caller; calls on one stream are ordered and safe. */

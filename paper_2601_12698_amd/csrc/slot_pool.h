@@ -59,7 +59,8 @@ public:
     // other kernel.  But what is in flight may depend on something that the caller has yet to do.  So the wait is bounded, and
     // after one in vain nobody waits until units have been found again.
     // tell(words): queues a launch on `stream` that does nothing but tell.  Where launches have ended, but none has begun after
-    // them that was to tell, it finds units for this call or for one after it.
+    // them that was to tell, it finds units for this call or for one after it.  A call that does not wait queues one only if none
+    // has been for as long as a call would wait: behind a stream that waits for something they would be added to its queue.
     template <class Tell>
     Units take(hipStream_t stream, int units, Lease* lease, Tell tell)
     {
@@ -80,9 +81,8 @@ public:
         Gpu& gpu = gpu_[device];
         uint32_t* done = reports(gpu, pending);
         if (!done) return Units::none;
-        using clock = std::chrono::steady_clock;
         for (clock::time_point began{};; std::this_thread::sleep_for(std::chrono::microseconds(20))) {
-            const bool first = began == clock::time_point{};
+            bool ask = false, waits = true;
             {
                 std::lock_guard<std::mutex> lock(gpu.mu);
                 int u = gpu.map.take(units, done);
@@ -91,8 +91,8 @@ public:
                     gpu.map.give_back(u);
                     u = -1;
                 }
-                gpu.in_vain = gpu.in_vain && u < 0;
                 if (u >= 0) {
+                    gpu.in_vain = false;
                     std::fill_n(gpu.tag + u, units, tag);
                     gpu.untold += units;
                     lease->tag_ = tag;
@@ -104,12 +104,19 @@ public:
                     if (lease->tells_) gpu.untold = 0;
                     return Units::taken;
                 }
-                if (!first && clock::now() - began > std::chrono::milliseconds(4)) gpu.in_vain = true;
-                if (gpu.in_vain && !first) return Units::none;
+                const clock::time_point now = clock::now();
+                if (began == clock::time_point{}) {
+                    began = now;
+                    waits = !gpu.in_vain;
+                    ask = waits || now - gpu.asked > kWait;
+                    if (ask) gpu.asked = now;
+                } else {
+                    if (now - began > kWait) gpu.in_vain = true;
+                    waits = !gpu.in_vain;
+                }
             }
-            if (!first) continue;
-            if (tell(done) != hipSuccess) forget_error(pending);
-            began = clock::now();
+            if (ask && tell(done) != hipSuccess) forget_error(pending);
+            if (!waits) return Units::none;
         }
     }
     Units take(hipStream_t stream, int units, Lease* lease)
@@ -118,6 +125,8 @@ public:
     }
 
 private:
+    using clock = std::chrono::steady_clock;
+    static constexpr std::chrono::milliseconds kWait{4};
     // A call above has failed, which is nothing to the caller: the thread's error goes, unless one was pending before, for
     // whoever caused that one to find.
     static void forget_error(bool pending)
@@ -167,6 +176,7 @@ private:
         // launches, so that 2^32 of them take a month and more.  Units behind the last one are not taken any more.
         uint32_t tag[UNITS] = {};
         bool in_vain = false;
+        clock::time_point asked{};                           // when the last launch that only tells was queued
         int untold = 0;                                      // units taken since a launch was asked to tell
         std::atomic<uint32_t*> done{nullptr};
         std::atomic<bool> allocating{false};

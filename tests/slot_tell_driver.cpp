@@ -80,6 +80,39 @@ static int asks()
     return 0;
 }
 
+// After a wait in vain: calls that neither wait nor queue a telling launch each.  One that is due finds the units.
+static int in_vain()
+{
+    static SlotPool<8> pool;
+    using clock = std::chrono::steady_clock;
+    const auto ms = [](clock::time_point since) { return std::chrono::duration<double, std::milli>(clock::now() - since).count(); };
+    SlotPool<8>::Lease all;
+    EXPECT(pool.take(nullptr, 8, &all) == Units::taken);
+    all.launched();
+    const clock::time_point began = clock::now();
+    int tells = 0;
+    const auto call = [&](bool ended) {
+        SlotPool<8>::Lease lease;
+        return pool.take(nullptr, 1, &lease, [&](uint32_t* words) {
+            ++tells;
+            if (ended) words[0] = all.number();
+            return hipSuccess;
+        });
+    };
+    EXPECT(call(false) == Units::none && ms(began) > 4.0 && tells == 1);
+    double best = 1e9;                                       // of 50 times 100 calls: the machine may be busy
+    for (int batch = 0; batch < 50; ++batch) {
+        const clock::time_point t = clock::now();
+        for (int i = 0; i < 100; ++i) EXPECT(call(false) == Units::none);
+        best = std::min(best, ms(t));
+    }
+    EXPECT(best < 100 * 0.02 / 2 && tells <= 2 + ms(began) / 4);
+    std::this_thread::sleep_for(std::chrono::milliseconds(5));
+    const int before = tells;
+    EXPECT(call(true) == Units::none && tells == before + 1 && call(false) == Units::taken && tells == before + 1);
+    return 0;
+}
+
 // Launches that end at once, on GPUs of their own; one that tells knows those of its GPU.  How many calls found no units at first.
 struct Gpus {
     static SlotPool<64> pool;
@@ -134,7 +167,7 @@ static int quiet()
 
 int main(int, char** argv)
 {
-    const struct { const char* name; int (*run)(); } tests[] = {{"tells", tells}, {"tags", tags}, {"asks", asks}, {"rotation", rotation}, {"quiet", quiet}};
+    const struct { const char* name; int (*run)(); } tests[] = {{"tells", tells}, {"tags", tags}, {"asks", asks}, {"in_vain", in_vain}, {"rotation", rotation}, {"quiet", quiet}};
     int bad = 1;
     for (const auto& t : tests)
         if (!strcmp(argv[1], t.name)) bad = t.run();

@@ -25,7 +25,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["tells", "tags", "asks", "rotation", "quiet"])
+@pytest.mark.parametrize("what", ["tells", "tags", "asks", "in_vain", "rotation", "quiet"])
 def test_units(driver, what):
     r = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300,
                        env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
