@@ -5,7 +5,8 @@
 // by a workgroup of its own at its beginning, where the write is over long before the launch is.  As the last access of the launch
 // itself that write took 0.7-1.5 us, in which the next launch of the stream waits.
 //
-// A GPU tells of its own launches, into words of its own (slot_pool.h), and each number once.
+// A GPU tells of its own launches, into words of its own (slot_pool.h), and each number once: by the workgroup that raised `told` to
+// it.  A place has its next launch, with a greater number, only after that has arrived.  So a word never goes back.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -16,7 +17,7 @@ constexpr uint32_t kUnitDone = 1u << 31;
 template <int UNITS>
 struct UnitReports {
     uint64_t state[UNITS];                                   // of the launch with units from here on: its number, then kUnitDone once it is done
-    uint32_t told[UNITS];                                    // number that this GPU has told last
+    uint32_t told[UNITS];                                    // greatest number that this GPU has told
 };
 // The launch is done.  By the one thread that knows.
 __device__ __forceinline__ void unit_done(uint64_t* state, uint32_t number)
@@ -49,7 +50,7 @@ __device__ __forceinline__ void unit_tell(UnitReports<UNITS>* r, uint32_t* words
         const uint64_t s = __hip_atomic_load(&r->state[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint32_t number = static_cast<uint32_t>(s >> 32);
         if (static_cast<uint32_t>(s) != kUnitDone) continue;
-        if (__hip_atomic_exchange(&r->told[u], number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != number)
+        if (__hip_atomic_fetch_max(&r->told[u], number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < number)
             __hip_atomic_store(&words[u], number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
