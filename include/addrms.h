@@ -506,6 +506,11 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
 int addrms_gate_probe_noalloc(const void* y, const void* y_ref, const void* residual, const void* residual_ref,
                               int64_t n, int dtype, uint32_t tol, addrms_gate_counts* counts_out, void* stream);
 
+/* addrms_gate_probe_noalloc as one kernel, or NO_RESULT where it cannot be.  looks: at the counts of a workgroup that are missing,
+ * before the one that adds them up compares that workgroup's elements itself; 0: it compares all elements. */
+int addrms_gate_looks_probe(const void* y, const void* y_ref, const void* residual, const void* residual_ref, int64_t n,
+                            int dtype, uint32_t tol, uint32_t looks, addrms_gate_counts* counts_out, void* stream);
+
 /* Calibration kernel with the operator's traffic and none of its arithmetic:
  * reads [M,N] of x and of residual and writes both back (bitwise complemented),
  * 16 bytes per lane, streaming cache policy, three 256-thread workgroups per CU

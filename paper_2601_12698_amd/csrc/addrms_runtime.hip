@@ -444,8 +444,11 @@ __device__ __forceinline__ void gate_block(unsigned& rbad, unsigned& ybad, unsig
         }
 }
 
-// One launch: the workgroups put their counts into words of their own and end; the last one in the grid, which is the last to be
-// dispatched, waits for the words of all others and folds them.  It is the only one that waits, and they need nothing of it.
+// One launch: the workgroups put their counts into words of their own and end; the last one in the grid looks for the words of all
+// others and folds them.  It is the only one that looks, and they need nothing of it.  Nor does it depend on them: each XCD takes
+// its share of a grid by itself, so that others may still wait for room where the last one has found some.  After a number of looks
+// the wave that misses a word compares that workgroup's slice itself.  Whoever comes later than that leaves its words in a unit that
+// may be another launch's by then: with a number that is not that launch's, whose last workgroup may have to compare a slice, too.
 // A word is a count and, in its upper half, the number of the launch, so that nothing has to be cleared and no arrival to be
 // counted: what a unit's earlier launches left has other numbers (a unit's numbers do not come round, slot_map.h).  Words are
 // accessed with relaxed atomics of device scope, which go to the memory side of the XCDs' L2s.
@@ -454,10 +457,13 @@ __device__ __forceinline__ void gate_block(unsigned& rbad, unsigned& ybad, unsig
 //   8 k elements of bf16 (2 workgroups)  4.5 -> 3.7    28 k  4.7 -> 3.9    384 k (96)  5.5 -> 4.4    860 k (209)  5.9 -> 4.3
 //   2 M (512)  6.8 -> 5.8    4 M  8.8 -> 7.9    16 M  23.2 -> 22.5    64 M  77.4 -> 76.7
 // (with a report to host memory at the end, as before; unit_report.h has what is written now)
+// Looks that are counted cost 0.07 us of each (60 sizes of 2 to 573 workgroups' work, 4.37 -> 4.44 on average).
 // Two launches with arguments instead of gridDim: 860 k 7.0 -> 6.2.  Arguments in scalar registers when a wave starts: 28 k 4.3 ->
 // 3.9, 860 k 4.6 -> 4.3.
 struct GateWords { uint64_t rbad, ybad, ymax; };
 constexpr int kGateUnits = 256;                          // launches in flight: 1 ms of them
+// Looks at a missing word, a microsecond and more each: some hundreds of them, and more than the whole comparison takes.
+unsigned gate_looks(long long n) { return 256u + static_cast<unsigned>(n >> 20); }
 static __device__ GateWords gate_words[kGateUnits][kGateMaxGrid];
 static __device__ addrms::UnitReports<kGateUnits> gate_reports;
 
@@ -466,33 +472,50 @@ __device__ __forceinline__ void gate_put(uint64_t* word, unsigned count, uint32_
     __hip_atomic_store(word, static_cast<uint64_t>(number) << 32 | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint64_t gate_look(const uint64_t* word) { return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// Thread 0's counts of workgroup `block` of n.
-__device__ __forceinline__ void gate_meet(unsigned rbad, unsigned ybad, unsigned ymax, unsigned block, unsigned n, GateWords* words,
-                                          unsigned* out, uint64_t* state, uint32_t number)
+// The counts that one workgroup leaves, added to those here once they are there.  True: they are not, after `looks` further looks.
+__device__ __forceinline__ bool gate_without(const GateWords* w, uint32_t number, unsigned looks, unsigned& rbad, unsigned& ybad, unsigned& ymax)
 {
-    if (block != n - 1u) {
-        if (threadIdx.x == 0) {
-            GateWords* w = &words[block];
-            gate_put(&w->rbad, rbad, number); gate_put(&w->ybad, ybad, number); gate_put(&w->ymax, ymax, number);
+    uint64_t a, b, c;
+    bool without = false;
+    for (unsigned k = looks;; --k, __builtin_amdgcn_s_sleep(1)) {
+        a = gate_look(&w->rbad); b = gate_look(&w->ybad); c = gate_look(&w->ymax);        // in one trip to memory
+        if ((a >> 32) == number && (b >> 32) == number && (c >> 32) == number) break;
+        if (k == 0u) {
+            a = b = c = 0;
+            without = true;
+            break;
         }
-        return;
     }
-    if (threadIdx.x != 0) rbad = ybad = ymax = 0u;
-    if (threadIdx.x < n - 1u) {
-        const GateWords* w = &words[threadIdx.x];
-        uint64_t a, b, c;
-        for (;; __builtin_amdgcn_s_sleep(1)) {               // three words in one trip to memory
-            a = gate_look(&w->rbad); b = gate_look(&w->ybad); c = gate_look(&w->ymax);
-            if ((a >> 32) == number && (b >> 32) == number && (c >> 32) == number) break;
-        }
-        rbad += static_cast<unsigned>(a);
-        ybad += static_cast<unsigned>(b);
-        ymax = static_cast<unsigned>(c) > ymax ? static_cast<unsigned>(c) : ymax;
+    rbad += static_cast<unsigned>(a);
+    ybad += static_cast<unsigned>(b);
+    ymax = static_cast<unsigned>(c) > ymax ? static_cast<unsigned>(c) : ymax;
+    return without;
+}
+// One element.
+template <int XB, int RB>
+__device__ __forceinline__ void gate_element(const char* y, const char* y_ref, const char* r, const char* r_ref, long long i, unsigned tol,
+                                             unsigned& rbad, unsigned& ybad, unsigned& ymax)
+{
+    if constexpr (XB == 4) gate_count_y<4>(reinterpret_cast<const uint32_t*>(y)[i], reinterpret_cast<const uint32_t*>(y_ref)[i], tol, ybad, ymax);
+    else gate_count_y<2>(reinterpret_cast<const uint16_t*>(y)[i], reinterpret_cast<const uint16_t*>(y_ref)[i], tol, ybad, ymax);
+    if constexpr (RB == 4) rbad += reinterpret_cast<const uint32_t*>(r)[i] != reinterpret_cast<const uint32_t*>(r_ref)[i];
+    else rbad += reinterpret_cast<const uint16_t*>(r)[i] != reinterpret_cast<const uint16_t*>(r_ref)[i];
+}
+// Adds workgroup `block`'s slice, as gate_slice counts it, to the counts of a wave.  Small rather than fast.
+template <int XB, int RB>
+__device__ __forceinline__ void gate_wave_slice(const char* y, const char* y_ref, const char* r, const char* r_ref, long long n, unsigned tol,
+                                                unsigned block, unsigned grid, unsigned& rbad, unsigned& ybad, unsigned& ymax)
+{
+    constexpr unsigned E = 16 / XB, kRun = kGateBlock * E;   // elements of a piece, and of a workgroup's pieces side by side
+    long long at = static_cast<long long>(block) * kRun, end = n / E * E;
+    for (bool rest = block == 0u;; rest = false, at = end, end = n) {
+#pragma unroll 1
+        for (; at < end; at += static_cast<long long>(grid) * kRun)
+#pragma unroll 1
+            for (unsigned i = threadIdx.x & 63u; i < kRun && at + i < end; i += 64u)
+                gate_element<XB, RB>(y, y_ref, r, r_ref, at + i, tol, rbad, ybad, ymax);
+        if (!rest) break;
     }
-    gate_block<1>(rbad, ybad, ymax);                         // its barrier: all words have been read
-    if (threadIdx.x != 0) return;
-    *reinterpret_cast<addrms::u32x4*>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
-    addrms::unit_done(state, number);
 }
 
 // The three counts of a workgroup's grid-stride slice, valid in thread 0.
@@ -533,12 +556,7 @@ __device__ __forceinline__ void gate_slice(const char* y, const char* y_ref, con
     }
     // the last n % E elements, one per thread of the first workgroup
     const long long i = static_cast<long long>(pieces) * E + threadIdx.x;
-    if (block == 0 && i < n) {
-        if constexpr (XB == 4) gate_count_y<4>(reinterpret_cast<const uint32_t*>(y)[i], reinterpret_cast<const uint32_t*>(y_ref)[i], tol, ybad, ymax);
-        else gate_count_y<2>(reinterpret_cast<const uint16_t*>(y)[i], reinterpret_cast<const uint16_t*>(y_ref)[i], tol, ybad, ymax);
-        if constexpr (RB == 4) rbad += reinterpret_cast<const uint32_t*>(r)[i] != reinterpret_cast<const uint32_t*>(r_ref)[i];
-        else rbad += reinterpret_cast<const uint16_t*>(r)[i] != reinterpret_cast<const uint16_t*>(r_ref)[i];
-    }
+    if (block == 0 && i < n) gate_element<XB, RB>(y, y_ref, r, r_ref, i, tol, rbad, ybad, ymax);
     gate_block<0>(rbad, ybad, ymax);
 }
 template <int XB, int RB>
@@ -553,19 +571,51 @@ __global__ __launch_bounds__(kGateBlock) void gate_partial_kernel(addr_t y, addr
 }
 // tells: the first workgroup compares nothing and tells.
 template <int XB, int RB>
-__global__ __launch_bounds__(kGateBlock) void gate_one_kernel(addr_t y, addr_t y_ref, addr_t r, addr_t r_ref, long long n, unsigned tol,
-                                                               unsigned grid, addr_t out, unsigned unit_tells, uint32_t number, addr_t words)
+__global__ __launch_bounds__(kGateBlock) void gate_one_kernel(addr_t y_at, addr_t y_ref_at, addr_t r_at, addr_t r_ref_at, long long n,
+                                                               unsigned tol, unsigned grid, addr_t out_at, unsigned unit_looks, uint32_t number,
+                                                               addr_t words)
 {
-    const unsigned unit = unit_tells >> 1, tells = unit_tells & 1u, block = blockIdx.x - tells;
+    const unsigned unit = unit_looks >> 1 & 0x7fffu, tells = unit_looks & 1u, block = blockIdx.x - tells;
     if (tells && blockIdx.x == 0u) {
         addrms::unit_tell(&gate_reports, at_global<uint32_t>(words), kGateBlock);
         return;
     }
+    const char *y = at_global<char>(y_at), *y_ref = at_global<char>(y_ref_at), *r = at_global<char>(r_at), *r_ref = at_global<char>(r_ref_at);
+    addrms::u32x4* out = at_global<addrms::u32x4>(out_at);
     unsigned rbad, ybad, ymax;
-    gate_slice<XB, RB>(at_global<char>(y), at_global<char>(y_ref), at_global<char>(r), at_global<char>(r_ref), n, tol, block, grid,
-                       rbad, ybad, ymax);
-    if (grid > 1u) gate_meet(rbad, ybad, ymax, block, grid, gate_words[unit], at_global<unsigned>(out), &gate_reports.state[unit], number);
-    else if (threadIdx.x == 0) *at_global<addrms::u32x4>(out) = addrms::u32x4{rbad, ybad, ymax, 0u};
+    gate_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, block, grid, rbad, ybad, ymax);
+    if (grid == 1u) {
+        if (threadIdx.x == 0) *out = addrms::u32x4{rbad, ybad, ymax, 0u};
+        return;
+    }
+    GateWords* all = gate_words[unit];
+    if (block != grid - 1u) {
+        if (threadIdx.x == 0) {
+            GateWords* w = &all[block];
+            gate_put(&w->rbad, rbad, number); gate_put(&w->ybad, ybad, number); gate_put(&w->ymax, ymax, number);
+        }
+        return;
+    }
+    if (threadIdx.x != 0) rbad = ybad = ymax = 0u;
+    const unsigned looks = unit_looks >> 16;
+    const uint32_t expected = looks ? number : ~number;      // not this launch's: nothing is found
+    bool without = false;                                    // the word of workgroup threadIdx.x is missing
+    if (threadIdx.x < grid - 1u) without = gate_without(&all[threadIdx.x], expected, looks, rbad, ybad, ymax);
+    uint64_t left = __ballot(without);
+    if (__builtin_expect(left != 0u, 0)) {                   // not expected: its instructions lie behind the kernel's end
+        do {
+            const unsigned first = (threadIdx.x & ~63u) + static_cast<unsigned>(__builtin_ctzll(left));
+            gate_wave_slice<XB, RB>(y, y_ref, r, r_ref, n, tol, static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(first))),
+                                    grid, rbad, ybad, ymax);
+            without = without && threadIdx.x != first;
+            if (without) without = gate_without(&all[threadIdx.x], expected, 0u, rbad, ybad, ymax);
+            left = __ballot(without);
+        } while (left);
+    }
+    gate_block<1>(rbad, ybad, ymax);                         // its barrier: all slices have been counted
+    if (threadIdx.x != 0) return;
+    *out = addrms::u32x4{rbad, ybad, ymax, 0u};
+    addrms::unit_done(&gate_reports.state[unit], number);
 }
 __global__ __launch_bounds__(kGateBlock) void gate_tell_kernel(addr_t words) { addrms::unit_tell(&gate_reports, at_global<uint32_t>(words), kGateBlock); }
 // One workgroup.  accumulate != 0 folds the new counts into what `out` already holds
@@ -622,7 +672,7 @@ SlotPool<kGateUnits> g_gate_slots;
 
 // The gate in one launch, where one workgroup does it or the launch can have a unit.  *launched: whether it was.
 int launch_gate_in_one(const void* y, const void* y_ref, const void* r, const void* r_ref, long long n, int xb, int rb, unsigned tol,
-                       unsigned* out, hipStream_t stream, bool* launched)
+                       unsigned looks, unsigned* out, hipStream_t stream, bool* launched)
 {
     unsigned workgroups = static_cast<unsigned>(gate_grid(n, xb));
     SlotPool<kGateUnits>::Lease lease;
@@ -633,12 +683,12 @@ int launch_gate_in_one(const void* y, const void* y_ref, const void* r, const vo
     *launched = workgroups == 1 || g_gate_slots.take(stream, 1, &lease, tell) == Units::taken;
     if (!*launched) return ADDRMS_OK;
     const bool meet = workgroups > 1;
-    unsigned tells = meet && lease.tells() ? 1u : 0u, unit_tells = meet ? lease.unit() << 1 | tells : 0u;
+    unsigned tells = meet && lease.tells() ? 1u : 0u, unit_looks = meet ? std::min(looks, 0xffffu) << 16 | lease.unit() << 1 | tells : 0u;
     uint32_t *words = meet ? lease.words() : nullptr, number = meet ? lease.number() : 0u;
     const void* fn = xb == 4   ? reinterpret_cast<const void*>(&gate_one_kernel<4, 4>)
                      : rb == 4 ? reinterpret_cast<const void*>(&gate_one_kernel<2, 4>)
                                : reinterpret_cast<const void*>(&gate_one_kernel<2, 2>);
-    void* args[] = {&y, &y_ref, &r, &r_ref, &n, &tol, &workgroups, &out, &unit_tells, &number, &words};
+    void* args[] = {&y, &y_ref, &r, &r_ref, &n, &tol, &workgroups, &out, &unit_looks, &number, &words};
     // The launch's own status: hipGetLastError may have an older error, of the caller's, for a launch that is queued.
     HIP_TRY(hipLaunchKernel(fn, dim3(workgroups + tells), dim3(kGateBlock), args, 0, stream));
     if (meet) lease.launched();
@@ -1480,14 +1530,26 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
     return ADDRMS_OK;
 }
 
+int addrms_gate_looks_probe(const void* y, const void* y_ref, const void* residual, const void* residual_ref, int64_t n,
+                            int dtype, uint32_t tol, uint32_t looks, addrms_gate_counts* counts_out, void* stream)
+{
+    int st = check_gate_args(y, y_ref, residual, residual_ref, n, dtype, counts_out);
+    if (st != ADDRMS_OK) return st;
+    bool launched = false;
+    st = launch_gate_in_one(y, y_ref, residual, residual_ref, n, x_bytes(dtype), r_bytes(dtype), tol, looks,
+                            reinterpret_cast<unsigned*>(counts_out), static_cast<hipStream_t>(stream), &launched);
+    if (st != ADDRMS_OK || launched) return st;
+    return fail(ADDRMS_ERR_NO_RESULT, "the comparison could not be one launch");
+}
+
 int addrms_gate_probe_noalloc(const void* y, const void* y_ref, const void* residual, const void* residual_ref, int64_t n,
                               int dtype, uint32_t tol, addrms_gate_counts* counts_out, void* stream)
 {
     int st = check_gate_args(y, y_ref, residual, residual_ref, n, dtype, counts_out);
     if (st != ADDRMS_OK) return st;
     bool launched = false;
-    st = launch_gate_in_one(y, y_ref, residual, residual_ref, n, x_bytes(dtype), r_bytes(dtype), tol, reinterpret_cast<unsigned*>(counts_out),
-                            static_cast<hipStream_t>(stream), &launched);
+    st = launch_gate_in_one(y, y_ref, residual, residual_ref, n, x_bytes(dtype), r_bytes(dtype), tol, gate_looks(n),
+                            reinterpret_cast<unsigned*>(counts_out), static_cast<hipStream_t>(stream), &launched);
     if (st != ADDRMS_OK || launched) return st;
     unsigned* partial = nullptr;
     st = gate_scratch_on_current_device(&partial);

@@ -18,6 +18,24 @@ def test_counts(dtype, workgroups, more):
         assert counts(B.addrms_gate_probe_noalloc, case, dtype, tol) == counts(B.addrms_gate_probe, case, dtype, tol)
 
 
+@pytest.mark.parametrize("looks", [0, 1, 1000])
+@pytest.mark.parametrize("dtype,n", [("bf16", 4097), ("fp16_res32", 64 * 4096), ("fp32", 65 * 2048 + 3), ("bf16", 512 * 4096 + 9)])
+def test_workgroups_that_are_not_there(dtype, n, looks):
+    """The one that adds up compares the elements of those whose counts it does not find."""
+    case = planted(dtype, n, 3, 40, 11, 2)
+    for tol in (0, 1):
+        want = counts(B.addrms_gate_probe, case, dtype, tol)
+        assert counts(lambda y, v, r, q, d, t, o: B.addrms_gate_looks_probe(y, v, r, q, d, t, looks, o), case, dtype, tol) == want
+
+
+def test_units_come_back():
+    """More comparisons than there are units, each over before the next: one whose end is lost would leave too few of them."""
+    case, out = planted("bf16", 20000, 1, 3, 5, 2), torch.zeros(4, dtype=torch.int32, device="cuda")
+    for _ in range(600):
+        B.addrms_gate_looks_probe(*case, "bf16", 1, 1000, out)
+        torch.cuda.synchronize()
+
+
 def test_more_launches_than_units():
     """600 launches in flight, of sizes in turn, so that every unit is used again with words of another launch in it."""
     per = 512 * 8
