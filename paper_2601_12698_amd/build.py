@@ -85,7 +85,7 @@ def _compile_kernel_unit(src: str, force: bool) -> str:
     rem = src[:-4] + ".remarks"
     if (not force and os.path.exists(rem) and
             _newer(obj, src, os.path.join(CSRC, "addrms_kernel.h"), os.path.join(CSRC, "silumul_kernel.h"),
-                   os.path.join(CSRC, "mergestates_kernel.h"))):
+                   os.path.join(CSRC, "mergestates_kernel.h"), os.path.join(CSRC, "write_through.h"))):
         return open(rem).read()
     preload = PRELOAD_FLAGS if os.path.basename(src).startswith(("kern_addrms_", "kern_silumul_")) else []
     r = _run(["hipcc", *DEVICE_FLAGS, *preload, *INCLUDES, "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj])
@@ -150,7 +150,7 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
 
     objs = [u[:-4] + ".o" for u in units]
     hdrs = [os.path.join(ROOT, "include", "addrms.h"), os.path.join(ROOT, "include", "silumul.h"), os.path.join(ROOT, "include", "mergestates.h"),
-            os.path.join(CSRC, "addrms_internal.h"), os.path.join(CSRC, "direct_route.h"),
+            os.path.join(CSRC, "addrms_internal.h"), os.path.join(CSRC, "direct_route.h"), os.path.join(CSRC, "write_through.h"),
             os.path.join(CSRC, "slot_map.h"), os.path.join(CSRC, "slot_pool.h")]
     gen = [os.path.join(BUILD, f) for f in ("gen_instances.inc", "gen_resources.inc",
                                              "gen_dispatch_decl.inc", "gen_dispatch_rows.inc")]
@@ -160,7 +160,7 @@ def build(force: bool = False, jobs: int = 8, verbose: bool = False) -> str:
         if force or not _newer(obj, src, *hdrs, *gen):
             _run(["hipcc", "-x", "c++", *HOST_FLAGS, *INCLUDES, "-c", src, "-o", obj])
         objs.append(obj)
-    dev_hdrs = [os.path.join(CSRC, f) for f in ("addrms_kernel.h", "silumul_kernel.h", "mergestates_kernel.h",
+    dev_hdrs = [os.path.join(CSRC, f) for f in ("addrms_kernel.h", "write_through.h", "silumul_kernel.h", "mergestates_kernel.h",
                                                  "direct_kernel.h", "addrms_direct.h", "unit_report.h")]
     for name in ("addrms_runtime.hip", "addrms_direct.hip", "addrms_split.hip"):
         src = os.path.join(CSRC, name)

@@ -16,6 +16,7 @@
 #include <unordered_map>
 
 #include "addrms_internal.h"
+#include "write_through.h"
 
 namespace addrms_host {
 
@@ -240,18 +241,22 @@ int64_t write_through_max() { return hw().last_level_cache_bytes / 8 * 3; }
 //       3 to 9 MB 0.96-1.18 / 0.94-1.27   13 to 18 MB 0.85-0.97 / 1.06-1.13   20 to 65 MB 0.76-0.87 / 1.004-1.05
 //       85 to 98 MB 0.87-0.98 / 1.02-1.05   160 MB 1.03 / 1.02
 //     PERSISTENT, 67 MB 1.02 / 1.06;  rows that are not whole lines 0.94-0.97 / 1.20-1.22 (as aligned spans 0.90 / 1.03);  two
-//     bytes per access, ragged, 1.36 / 1.49
+//     bytes per access, ragged, 1.36 / 1.49;  fp16+fp32 with eight elements per access, y alone written through (write_through_piece),
+//     0.95-0.99 / 1.03-1.06
 //   silu_and_mul, the same (d = 4096 to 14336)
 //       2 to 35 MB 0.95-1.007 / 1.00-1.06   44 to 88 MB 0.91-0.976 / 1.003-1.036   130 MB 1.02 / 1.02
 //   merge_attn_states, 2 and 13 MB 0.99-1.02 / 0.99-1.06
 // From HBM it gives away some percent of what the next kernel gets back, which finds its input in the memory-side cache.
 bool launch_write_through(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op)
 {
-    constexpr int64_t kMB = 1000 * 1000, kAddrmsMin = 20 * kMB, kSiluMin = 40 * kMB, kNarrowest = 4;
-    const int64_t row = N * x_bytes(dtype), out = M * (op == OP_ADDRMS ? row + N * r_bytes(dtype) : row);
-    if (op == OP_MERGE || !(c.flags & ADDRMS_FLAG_NONTEMPORAL) || (c.flags & ADDRMS_FLAG_PERSISTENT) || c.vec * x_bytes(dtype) < kNarrowest)
-        return false;
-    if (row % kLineBytes != 0 && !(c.flags & ADDRMS_FLAG_ALIGNED_SPAN)) return false;
+    constexpr int64_t kMB = 1000 * 1000, kAddrmsMin = 20 * kMB, kSiluMin = 40 * kMB;
+    constexpr int kNotWritten = ADDRMS_FLAG_PERSISTENT | ADDRMS_FLAG_TWO_PASS | ADDRMS_FLAG_LDS_CACHE;
+    if (op == OP_MERGE || !(c.flags & ADDRMS_FLAG_NONTEMPORAL) || (c.flags & kNotWritten)) return false;
+    const bool span = (c.flags & ADDRMS_FLAG_ALIGNED_SPAN) != 0, norm = op == OP_ADDRMS;
+    const int64_t pass = static_cast<int64_t>(c.vec) * c.threads_per_row, chunks = norm && !span ? (N + pass - 1) / pass : 0;
+    if (chunks > 16 || !write_through_instance(c.vec, static_cast<int>(chunks))) return false;
+    const int64_t row = N * x_bytes(dtype), out = M * (norm ? row + N * r_bytes(dtype) : row);
+    if (row % kLineBytes != 0 && !span) return false;
     return out >= (op == OP_ADDRMS ? kAddrmsMin : kSiluMin) && out <= write_through_max();
 }
 

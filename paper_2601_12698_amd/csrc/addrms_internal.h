@@ -108,7 +108,8 @@ int64_t n_row_blocks(const addrms_cfg& c, int64_t M);
 int64_t n_workgroups(const addrms_cfg& c, int64_t M, int wgs_per_cu);
 // Whether the waves of a launch with this cfg wait for one load before they ask for more (wait_one_load).
 bool launch_paced(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op);
-// Whether the outputs of a launch with this streaming cfg are written through to the memory-side cache (st_out).
+// Whether the outputs of a launch with this streaming cfg are written through to the memory-side cache (st_out; write_through.h has
+// which instances and which pieces).
 bool launch_write_through(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op);
 // Bytes of output up to which write-through stores leave it in the memory-side cache for the next kernel: three eighths of it.
 int64_t write_through_max();

@@ -44,6 +44,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "write_through.h"
+
 namespace addrms {
 
 enum : int { DT_BF16 = 0, DT_FP16 = 1, DT_FP16_RES32 = 2, DT_FP32 = 3 };
@@ -158,7 +160,7 @@ __device__ __forceinline__ void st_write_through(char* base, uint32_t off, const
 template <int BYTES, bool NT, bool WT>
 __device__ __forceinline__ void st_out(char* base, uint32_t off, const raw_t<BYTES>& v, uint32_t flags)
 {
-    if constexpr (NT && WT && BYTES <= 16) {
+    if constexpr (NT && WT && write_through_piece(BYTES)) {
         if (flags & LAUNCH_WRITE_THROUGH) {
             st_write_through<BYTES>(base, off, v);
             return;
@@ -436,9 +438,7 @@ __device__ __forceinline__ void addrms_body(void* __restrict__ xp, void* __restr
 {
     using T = dt_traits<DT>;
     constexpr int XB = T::XB, RB = T::RB;
-    // Beyond six chunks, and with one element per chunk, the second kind of store takes registers that some instances do not have
-    // without giving up a wave per SIMD.
-    constexpr bool BF = T::BF, WT = VEC > 1 && CPT <= 6;
+    constexpr bool BF = T::BF, WT = write_through_instance(VEC, CPT);
     extern __shared__ double lds[];
 
     const uint32_t lane = threadIdx.x, ry = threadIdx.y;
@@ -895,7 +895,7 @@ __device__ __forceinline__ void addrms_span_body(void* __restrict__ xp, void* __
 {
     using T_ = dt_traits<DT>;
     constexpr int XB = T_::XB, RB = T_::RB;
-    constexpr bool BF = T_::BF, WT = true;
+    constexpr bool BF = T_::BF, WT = write_through_instance(VEC, 0);
     static_assert(VEC * XB <= 16 && VEC * RB <= 16, "one access per stream and piece");
     extern __shared__ double lds[];
     (void)reduce; (void)nblocks;

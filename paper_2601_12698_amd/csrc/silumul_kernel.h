@@ -74,7 +74,7 @@ __device__ __forceinline__ void silumul_body(const void* __restrict__ xp, void* 
                     if (row_ok && col <= nlast) {
                         raw_t<ES * VEC> out;
                         pack_vec<ES, BF, VEC>(y, out);
-                        st_out<ES * VEC, NT, (VEC > 1)>(out_base, (out_off + col) * ES, out, flags);
+                        st_out<ES * VEC, NT, write_through_instance(VEC, 0)>(out_base, (out_off + col) * ES, out, flags);
                     }
                 }
             }

@@ -24,7 +24,10 @@ NEVER = [
     (NORM, "bf16", 4000, 4096, "8,512,1,0,1,0,0,0"), (NORM, "bf16", 4000, 4096, "8,512,1,0,1,6,0,0"),
     (NORM, "bf16", 4000, 4104, "8,576,1,0,1,2,0,0"), (NORM, "fp16", 4000, 4096, "1,1024,1,0,4,2,0,0"),
     (SILU, "bf16", 4000, 8192, "8,1024,1,0,1,0,0,0"), (SILU, "bf16", 4000, 8200, "8,1024,1,0,1,2,0,0"),
-    (MERGE, "bf16", 100000, 256, "8,32,8,0,1,2,0,0")]
+    (MERGE, "bf16", 100000, 256, "8,32,8,0,1,2,0,0"),
+    # instances without that kind of store: more than six chunks, one element per chunk, forms for long rows
+    (NORM, "bf16", 2000, 8192, "2,512,1,0,1,2,0,0"), (NORM, "fp32", 3000, 4096, "1,1024,1,0,4,2,0,0"),
+    (SILU, "fp32", 3000, 4096, "1,1024,1,0,4,2,0,0"), (NORM, "bf16", 400, 40960, "8,1024,1,0,2,18,0,0"), (NORM, "bf16", 400, 40960, "8,1024,1,0,2,10,0,0")]
 
 
 def test_which_launches_write_through(tmp_path):
