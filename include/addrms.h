@@ -58,7 +58,8 @@ enum { ADDRMS_REDUCE_WAVE = 0,   /* wave64 cross-lane (DPP) sums, one LDS hop ac
 enum { ADDRMS_FLAG_XCD_CONTIG = 1,    /* workgroups of one XCD cover a contiguous row range       */
        ADDRMS_FLAG_NONTEMPORAL = 2,   /* streaming cache policy on x/residual loads and stores; an
                                          output of a size that the memory-side cache keeps for
-                                         the next kernel is written through to it instead       */
+                                         the next kernel is written through to it instead, unless
+                                         ADDRMS_FLAG_STREAM_STORES says otherwise               */
        ADDRMS_FLAG_PERSISTENT = 4,    /* grid = resident workgroups only; each walks several row
                                          blocks and prefetches the next block before reducing   */
        ADDRMS_FLAG_TWO_PASS = 8,      /* rows too long for the register row cache: read the row
@@ -79,6 +80,10 @@ enum { ADDRMS_FLAG_XCD_CONTIG = 1,    /* workgroups of one XCD cover a contiguou
                                          by one instruction; row sums come from a segmented reduction
                                          in LDS.  threads_per_row x rows_per_wg threads share the span;
                                          vec x residual element size must be 16 bytes                */
+       ADDRMS_FLAG_STREAM_STORES = 128, /* with ADDRMS_FLAG_NONTEMPORAL (not for merges): outputs are
+                                         stored with the streaming policy at every size.  No knob
+                                         of the grid; a search sets it where that measured faster
+                                         for the configuration it returns                       */
        ADDRMS_FLAG_DEFER_STORE = 32 };/* the residual is written after the row reduction, the whole
                                          row at once and then the whole y row, instead of chunk by
                                          chunk while the row is still being read: a workgroup reads

@@ -246,11 +246,14 @@ int64_t write_through_max() { return hw().last_level_cache_bytes / 8 * 3; }
 //   silu_and_mul, the same (d = 4096 to 14336)
 //       2 to 35 MB 0.95-1.007 / 1.00-1.06   44 to 88 MB 0.91-0.976 / 1.003-1.036   130 MB 1.02 / 1.02
 //   merge_attn_states, 2 and 13 MB 0.99-1.02 / 0.99-1.06
-// From HBM it gives away some percent of what the next kernel gets back, which finds its input in the memory-side cache.
+// From HBM it gives away some percent of what the next kernel gets back, which finds its input in the memory-side cache.  A search,
+// whose buffers are beyond that cache, loses by it and would leave the configurations it suits best (8192 x 1000 fp16+fp32: aligned
+// spans, 17.65 us non-temporal and 18.4 written through, for partial lines in 18.3): it has the stores as part of what it chooses
+// (run_search).
 bool launch_write_through(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op)
 {
     constexpr int64_t kMB = 1000 * 1000, kAddrmsMin = 20 * kMB, kSiluMin = 40 * kMB;
-    constexpr int kNotWritten = ADDRMS_FLAG_PERSISTENT | ADDRMS_FLAG_TWO_PASS | ADDRMS_FLAG_LDS_CACHE;
+    constexpr int kNotWritten = ADDRMS_FLAG_STREAM_STORES | ADDRMS_FLAG_PERSISTENT | ADDRMS_FLAG_TWO_PASS | ADDRMS_FLAG_LDS_CACHE;
     if (op == OP_MERGE || !(c.flags & ADDRMS_FLAG_NONTEMPORAL) || (c.flags & kNotWritten)) return false;
     const bool span = (c.flags & ADDRMS_FLAG_ALIGNED_SPAN) != 0, norm = op == OP_ADDRMS;
     const int64_t pass = static_cast<int64_t>(c.vec) * c.threads_per_row, chunks = norm && !span ? (N + pass - 1) / pass : 0;
@@ -323,8 +326,11 @@ Feas check_cfg(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op, int
         return infeasible("grid", "reduce=%d: %s has no reduction; the knob must stay 0", c.reduce, op_name(op));
     if (!in_set(c.unroll, kUnrolls, 4)) return infeasible("grid", "unroll=%d: must be 1, 2, 4 or 8", c.unroll);
     if (c.flags & ~(ADDRMS_FLAG_XCD_CONTIG | ADDRMS_FLAG_NONTEMPORAL | ADDRMS_FLAG_PERSISTENT | ADDRMS_FLAG_TWO_PASS |
-                    ADDRMS_FLAG_LDS_CACHE | ADDRMS_FLAG_DEFER_STORE | ADDRMS_FLAG_ALIGNED_SPAN))
+                    ADDRMS_FLAG_LDS_CACHE | ADDRMS_FLAG_DEFER_STORE | ADDRMS_FLAG_ALIGNED_SPAN | ADDRMS_FLAG_STREAM_STORES))
         return infeasible("grid", "flags=0x%x: unknown bits set", c.flags);
+    if ((c.flags & ADDRMS_FLAG_STREAM_STORES) && (!(c.flags & ADDRMS_FLAG_NONTEMPORAL) || op == OP_MERGE))
+        return infeasible("grid", "flags=0x%x: ADDRMS_FLAG_STREAM_STORES says how ADDRMS_FLAG_NONTEMPORAL stores outputs that may be "
+                          "written through, which those of merges never are", c.flags);
     const bool span = (c.flags & ADDRMS_FLAG_ALIGNED_SPAN) != 0;
     if (span && op != OP_ADDRMS)
         return infeasible("grid", "flags=0x%x: only add+RMSNorm has the aligned-span form", c.flags);

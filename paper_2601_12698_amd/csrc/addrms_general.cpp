@@ -22,7 +22,7 @@ double knob_distance(const addrms_cfg& a, const addrms_cfg& b)
     auto l2 = [](int v) { return log2(static_cast<double>(std::max(1, v))); };
     return fabs(l2(a.vec) - l2(b.vec)) * 2.0 + fabs(l2(a.threads_per_row) - l2(b.threads_per_row)) +
            fabs(l2(a.rows_per_wg) - l2(b.rows_per_wg)) + fabs(l2(a.unroll) - l2(b.unroll)) * 0.5 +
-           (a.reduce != b.reduce ? 1.0 : 0.0) + __builtin_popcount(static_cast<unsigned>(a.flags ^ b.flags)) +
+           (a.reduce != b.reduce ? 1.0 : 0.0) + __builtin_popcount(static_cast<unsigned>((a.flags ^ b.flags) & ~ADDRMS_FLAG_STREAM_STORES)) +
            0.25 * abs(a.max_waves_per_simd - b.max_waves_per_simd);
 }
 
@@ -51,7 +51,7 @@ struct OpenBackend {
 
 int run_select_general(const addrms_shape* shapes, int n, int dtype, const addrms_budget* budget,
                        const addrms_backend_factory& factory, bool insert_in_table,
-                       addrms_cfg* out_general, addrms_general_report* report, int op)
+                       addrms_cfg* out_general, addrms_general_report* report, int op, bool store_kinds)
 {
     using Clock = std::chrono::steady_clock;
     const auto t0 = Clock::now();
@@ -79,7 +79,7 @@ int run_select_general(const addrms_shape* shapes, int n, int dtype, const addrm
                         (long long)shapes[i].M, (long long)shapes[i].N);
         addrms_cfg best{};
         addrms_tune_report tr{};
-        const int st = run_search(shapes[i].M, shapes[i].N, dtype, budget, ob.be, &best, &tr, op);
+        const int st = run_search(shapes[i].M, shapes[i].N, dtype, budget, ob.be, &best, &tr, op, store_kinds);
         if (st != ADDRMS_OK) return st;
         rep.specialized[i] = best;
         rep.specialized_us[i] = tr.best_us;
@@ -100,7 +100,11 @@ int run_select_general(const addrms_shape* shapes, int n, int dtype, const addrm
         enumerate(shapes[0].M, shapes[0].N, dtype, &all, nullptr, nullptr, op);
         std::vector<addrms_cfg> common;
         for (const addrms_cfg& c : all)
-            if (feasible_everywhere(c, shapes, n, dtype, op)) common.push_back(c);
+            if (feasible_everywhere(c, shapes, n, dtype, op)) {
+                common.push_back(c);
+                for (int i = 0; store_kinds && i < n; ++i)
+                    if (launch_write_through(c, shapes[i].M, shapes[i].N, dtype, op)) common.back().flags |= ADDRMS_FLAG_STREAM_STORES;
+            }
         if (common.empty() && cands.empty())
             return fail(ADDRMS_ERR_NO_RESULT, "no configuration is feasible on all %d shapes", n);
         std::unordered_set<uint64_t> have;
@@ -187,7 +191,7 @@ int run_select_general(const addrms_shape* shapes, int n, int dtype, const addrm
 // ---- the outer loop with a fixed strategy list ------------------------------------
 int run_tune_rounds(const addrms_shape* shapes, int n, int dtype, const addrms_budget* budget,
                     const addrms_backend_factory& factory, bool insert_in_table,
-                    addrms_cfg* out_general, addrms_rounds_report* report, int op)
+                    addrms_cfg* out_general, addrms_rounds_report* report, int op, bool store_kinds)
 {
     using Clock = std::chrono::steady_clock;
     const auto t0 = Clock::now();
@@ -234,7 +238,7 @@ int run_tune_rounds(const addrms_shape* shapes, int n, int dtype, const addrms_b
         addrms_general_report gr{};
         int st = ADDRMS_OK;
         if (r == 0 || info.pass) {
-            st = run_select_general(shapes, n, dtype, &rb, factory, false, &general, &gr, op);
+            st = run_select_general(shapes, n, dtype, &rb, factory, false, &general, &gr, op, store_kinds);
             if (st != ADDRMS_OK) return st;
             info.general = general;
             info.geomean_speedup_general = gr.geomean_speedup_general;

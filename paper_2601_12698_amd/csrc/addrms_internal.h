@@ -125,18 +125,20 @@ int table_insert(int64_t M, int64_t N, int dtype, const addrms_cfg& cfg, double 
 uint64_t table_generation();
 
 // ---- search ----------------------------------------------------------------
-int run_search(int64_t M, int64_t N, int dtype, const addrms_budget* budget,
-               const addrms_backend& be, addrms_cfg* out_cfg, addrms_tune_report* report, int op = OP_ADDRMS);
+// store_kinds (device runs): configurations whose launches would be written through are searched with ADDRMS_FLAG_STREAM_STORES, and the
+// leading one without it as well.
+int run_search(int64_t M, int64_t N, int dtype, const addrms_budget* budget, const addrms_backend& be, addrms_cfg* out_cfg,
+               addrms_tune_report* report, int op = OP_ADDRMS, bool store_kinds = false);
 
 // ---- general configuration ---------------------------------------------------
 // insert_in_table: store each shape's winner in the specialised table (device runs only).
 int run_select_general(const addrms_shape* shapes, int n, int dtype, const addrms_budget* budget,
-                       const addrms_backend_factory& factory, bool insert_in_table,
-                       addrms_cfg* out_general, addrms_general_report* report, int op = OP_ADDRMS);
+                       const addrms_backend_factory& factory, bool insert_in_table, addrms_cfg* out_general,
+                       addrms_general_report* report, int op = OP_ADDRMS, bool store_kinds = false);
 
 int run_tune_rounds(const addrms_shape* shapes, int n, int dtype, const addrms_budget* budget,
-                    const addrms_backend_factory& factory, bool insert_in_table,
-                    addrms_cfg* out_general, addrms_rounds_report* report, int op = OP_ADDRMS);
+                    const addrms_backend_factory& factory, bool insert_in_table, addrms_cfg* out_general,
+                    addrms_rounds_report* report, int op = OP_ADDRMS, bool store_kinds = false);
 // Measures what the efficiency rules of the deriver prune (see addrms_audit_rules).
 int run_audit_rules(int64_t M, int64_t N, int dtype, const addrms_budget* budget, const addrms_backend& be,
                     addrms_audit_report* report);

@@ -1182,7 +1182,7 @@ template <class H> int tune_on_device(int64_t M, int64_t N, int dtype, const add
     if (st != ADDRMS_OK) return st;
     addrms_backend be{&h, backend_validate<H>, backend_measure<H>};
     addrms_tune_report local{};
-    st = run_search(M, N, dtype, budget, be, out_cfg, &local, H::kOp);
+    st = run_search(M, N, dtype, budget, be, out_cfg, &local, H::kOp, true);
     if (st != ADDRMS_OK) return st;
     if (report) *report = local;
     return table_insert(M, N, dtype, *out_cfg, local.best_us, H::kOp);
@@ -1198,7 +1198,7 @@ template <class H> int select_general_on_device(const addrms_shape* shapes, int3
     std::lock_guard<std::mutex> lock(g_tune_mu);
     HarnessFactory hf{budget_eps(budget)};
     addrms_backend_factory fac{&hf, factory_open<H>, factory_close<H>};
-    return run_select_general(shapes, n, dtype, budget, fac, true, out_general, report, H::kOp);
+    return run_select_general(shapes, n, dtype, budget, fac, true, out_general, report, H::kOp, true);
 }
 template <class H> int tune_rounds_on_device(const addrms_shape* shapes, int32_t n, int dtype, const addrms_budget* budget,
                                              addrms_cfg* out_general, addrms_rounds_report* report)
@@ -1209,7 +1209,7 @@ template <class H> int tune_rounds_on_device(const addrms_shape* shapes, int32_t
     std::lock_guard<std::mutex> lock(g_tune_mu);
     HarnessFactory hf{budget_eps(budget)};
     addrms_backend_factory fac{&hf, factory_open<H>, factory_close<H>};
-    return run_tune_rounds(shapes, n, dtype, budget, fac, true, out_general, report, H::kOp);
+    return run_tune_rounds(shapes, n, dtype, budget, fac, true, out_general, report, H::kOp, true);
 }
 
 // Mean time of one cfg (NULL: table, else default) on library-allocated buffers.

@@ -79,9 +79,15 @@ struct Searcher {
         if (b.max_wall_ms > 0.0 && elapsed_ms() >= b.max_wall_ms) return false;
         return true;
     }
+    // Candidates have one kind of store each, which is not a knob that a step turns.
+    static uint64_t key(addrms_cfg c)
+    {
+        c.flags &= ~ADDRMS_FLAG_STREAM_STORES;
+        return cfg_key(c);
+    }
     int find(const addrms_cfg& c) const
     {
-        auto it = index.find(cfg_key(c));
+        auto it = index.find(key(c));
         return it == index.end() ? -1 : it->second;
     }
 
@@ -184,7 +190,7 @@ struct Searcher {
                 const int want_flags = mode == kPlain ? 0
                                        : mode == kDeferred ? (ADDRMS_FLAG_NONTEMPORAL | ADDRMS_FLAG_DEFER_STORE)
                                                            : ADDRMS_FLAG_NONTEMPORAL;
-                if ((c.flags & ~kFormBits) != want_flags) continue;
+                if ((c.flags & ~(kFormBits | ADDRMS_FLAG_STREAM_STORES)) != want_flags) continue;
                 const int want_unroll = std::min(2, cands[i].res.chunks_per_thread);
                 score = fabs(log2(threads / 256.0)) + 0.1 * fabs(log2((double)c.unroll) - log2((double)want_unroll));
                 if (mode == kCapped) score += 0.5 * fabs(static_cast<double>(c.max_waves_per_simd) - 4.0);
@@ -430,7 +436,7 @@ int verbosity()
 }
 
 int run_search(int64_t M, int64_t N, int dtype, const addrms_budget* budget, const addrms_backend& be,
-               addrms_cfg* out_cfg, addrms_tune_report* report, int op)
+               addrms_cfg* out_cfg, addrms_tune_report* report, int op, bool store_kinds)
 {
     if (!out_cfg) return fail(ADDRMS_ERR_INVALID_ARG, "out_cfg is NULL");
     if (!be.measure) return fail(ADDRMS_ERR_INVALID_ARG, "backend has no measure function");
@@ -472,8 +478,9 @@ int run_search(int64_t M, int64_t N, int dtype, const addrms_budget* budget, con
     for (const addrms_cfg& c : feasible) {
         Cand cd;
         cd.cfg = c;
-        cd.res = check_cfg(c, M, N, dtype, op).res;
-        s.index[cfg_key(c)] = static_cast<int>(s.cands.size());
+        if (store_kinds && launch_write_through(c, M, N, dtype, op)) cd.cfg.flags |= ADDRMS_FLAG_STREAM_STORES;
+        cd.res = check_cfg(cd.cfg, M, N, dtype, op).res;
+        s.index[Searcher::key(c)] = static_cast<int>(s.cands.size());
         s.cands.push_back(cd);
     }
     const int i_default = s.find(dflt);
@@ -569,6 +576,14 @@ int run_search(int64_t M, int64_t N, int dtype, const addrms_budget* budget, con
     std::vector<int> confirm = top;
     if (i_default >= 0 && !default_in_top && s.cands[i_default].tried && !s.cands[i_default].failed)
         confirm.push_back(i_default);
+    if (s.cands[top.front()].cfg.flags & ADDRMS_FLAG_STREAM_STORES) {        // the leading one, written through
+        Cand other = s.cands[top.front()];
+        other.cfg.flags &= ~ADDRMS_FLAG_STREAM_STORES;
+        if (b.skip_validation || !be.validate || be.validate(be.user, &other.cfg) == 0) {
+            confirm.push_back(static_cast<int>(s.cands.size()));
+            s.cands.push_back(other);
+        }
+    }
     std::vector<double> sum(confirm.size(), 0.0);
     std::vector<int> cnt(confirm.size(), 0);
     const int rounds = 2;

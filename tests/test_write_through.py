@@ -48,6 +48,54 @@ def test_which_launches_write_through(tmp_path):
     assert r.stdout.split() == ["0", "1", "1", "0"] * len(LIMITS) + ["0"] * len(NEVER)
 
 
+@pytest.mark.parametrize("what", ["chooses", "general", "accepted"])
+def test_store_kinds_in_a_search(what, tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    if not os.path.exists(os.path.join(BUILD, "gen_resources.inc")):
+        pytest.skip("the generated instance and resource tables are not present (build the library first)")
+    exe = str(tmp_path / "driver")
+    cmd = ["g++", "-std=c++17", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-Wall", "-Wextra",
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", BUILD, os.path.join(ROOT, "tests", "store_kinds_driver.cpp"),
+           *[os.path.join(CSRC, s) for s in HOST_SOURCES], "-o", exe]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout[-4000:]
+    r = subprocess.run([exe, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout[-4000:]
+
+
+def test_a_saved_kind_of_store_comes_back(tmp_path):
+    B.addrms_table_clear()
+    cfg = B.make_cfg(4, 64, 16, 0, 4, B.FLAG_NONTEMPORAL | B.FLAG_DEFER_STORE | B.FLAG_ALIGNED_SPAN | B.FLAG_STREAM_STORES)
+    B.addrms_table_insert(8192, 1000, "fp16_res32", cfg, 17.6)
+    B.addrms_table_save(str(tmp_path / "t"))
+    B.addrms_table_clear()
+    B.addrms_table_load(str(tmp_path / "t"))
+    assert B.addrms_table_lookup(8192, 1000, "fp16_res32").as_tuple() == cfg.as_tuple()
+    B.addrms_table_clear()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("op,dtype,M,N,plan", [(NORM, "fp16_res32", 8192, 1000, "4,64,16,0,4,98,0,0"), (NORM, "bf16", 2633, 7168, "8,448,1,0,1,34,6,0"),
+                                               (SILU, "bf16", 4000, 11008, "8,704,1,0,1,2,0,0")])
+def test_results_with_either_kind_of_store(op, dtype, M, N, plan):
+    through, stream = (B.Cfg(*map(int, plan.split(","))) for _ in range(2))
+    stream.flags |= B.FLAG_STREAM_STORES
+    x, xok, r, rok, w = norm_inputs(M, 2 * N if op == SILU else N, dtype, 5)
+    if op == NORM:
+        xw, rw = x.clone(), r.clone()
+        B.addrms_run(xw, rw, w, 1e-6, M, N, dtype, through)
+        B.addrms_run(x, r, w, 1e-6, M, N, dtype, stream)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(x), bits(xw)) and torch.equal(bits(r), bits(rw)) and xok() and rok()
+    else:
+        a, b = (torch.ones(M, N, dtype=x.dtype, device="cuda") for _ in range(2))
+        B.silumul_run(x, a, M, N, dtype, through)
+        B.silumul_run(x, b, M, N, dtype, stream)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(a), bits(b))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("at", ["below", "fewest", "most"])
 @pytest.mark.parametrize("op,dtype,N,plan,lo,hi", LIMITS)
