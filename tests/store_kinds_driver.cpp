@@ -55,6 +55,28 @@ static int chooses()
     return 0;
 }
 
+// Rows by themselves in shares of 256 to 320 threads lead a little, and the way to the fastest begins at a span that is behind them.
+static int measure_layouts(void*, const addrms_cfg* c, int, int, double* us)
+{
+    const bool deferred = c->flags & ADDRMS_FLAG_DEFER_STORE;
+    const int threads = c->threads_per_row * c->rows_per_wg;
+    if (c->flags & ADDRMS_FLAG_ALIGNED_SPAN) *us = threads == 1024 ? (c->rows_per_wg == 16 ? 17.4 : 18.8) : 19.4;
+    else *us = c->threads_per_row == 320 ? 18.7 : c->threads_per_row == 256 ? 18.5 : c->threads_per_row == 128 ? 18.6 : 19.5;
+    *us *= (c->flags & ADDRMS_FLAG_NONTEMPORAL ? 1.0 : 1.2) * (deferred ? 1.0 : 1.02) * (c->vec == 4 ? 1.0 : 1.5) * (c->max_waves_per_simd ? 1.1 : 1.0) *
+           (c->flags & ADDRMS_FLAG_PERSISTENT ? 1.3 : 1.0) * (c->flags & ADDRMS_FLAG_XCD_CONTIG ? 1.02 : 1.0);
+    return 0;
+}
+static int layouts()
+{
+    addrms_backend be{nullptr, nullptr, measure_layouts};
+    addrms_budget b{};
+    addrms_cfg best{};
+    addrms_tune_report rep{};
+    EXPECT(run_search(kM, kN, kDtype, &b, be, &best, &rep, OP_ADDRMS, true) == ADDRMS_OK);
+    EXPECT((best.flags & ADDRMS_FLAG_ALIGNED_SPAN) && best.rows_per_wg == 16);
+    return 0;
+}
+
 // One configuration for two shapes of which one writes through.
 static int general()
 {
@@ -100,7 +122,7 @@ static int accepted()
 
 int main(int, char** argv)
 {
-    const struct { const char* name; int (*run)(); } tests[] = {{"chooses", chooses}, {"general", general}, {"accepted", accepted}};
+    const struct { const char* name; int (*run)(); } tests[] = {{"chooses", chooses}, {"layouts", layouts}, {"general", general}, {"accepted", accepted}};
     int bad = 1;
     for (const auto& t : tests)
         if (!strcmp(argv[1], t.name)) bad = t.run();

@@ -48,7 +48,7 @@ def test_which_launches_write_through(tmp_path):
     assert r.stdout.split() == ["0", "1", "1", "0"] * len(LIMITS) + ["0"] * len(NEVER)
 
 
-@pytest.mark.parametrize("what", ["chooses", "general", "accepted"])
+@pytest.mark.parametrize("what", ["chooses", "layouts", "general", "accepted"])
 def test_store_kinds_in_a_search(what, tmp_path):
     if shutil.which("g++") is None:
         pytest.skip("no g++")
