@@ -133,17 +133,22 @@ typedef struct addrms_cfg {
  * graph (stream capture); the first launch of a kernel whose LDS allocation is
  * beyond 64 KiB (an occupancy cap that pads it, rows that continue in LDS, with or
  * without a cfg) raises that kernel's dynamic-LDS limit once per process, so issue
- * one such launch eagerly before capturing.  Long rows without a cfg are split over
- * workgroups that meet in device memory of the library (24 MiB per GPU, part of its
- * code object), a launch in a piece of its own until its end is reported in 4 KiB of
- * pinned host memory per GPU, allocated once by the first such call there (by a later launch
- * on that GPU, one in some dozens; a call that finds no piece free and waits queues one that does
- * no more, and calls that do not wait one in 4 ms).  A call that finds no piece
- * free, 2.7 ms or more of such work being in flight, waits for one as it would for room in a
- * full queue, at most 4 ms, and not again after a wait in vain until one has been free; then
- * it runs a kernel that needs none and gives the same bits.  A captured call runs a third
- * kernel, whose row sum is taken in another order: in some 1e-7 of rows rstd is rounded to
- * the fp32 value beside the one that an eager call takes.
+ * one such launch eagerly before capturing.
+ *
+ * Two kinds of rows without a cfg are split over workgroups: long ones, of more than some 32,700
+ * elements (but for numbers of them that keep all CUs busy whole), and few wide ones of ADDRMS_FP32
+ * and ADDRMS_FP16_RES32, which one workgroup could hold: up to 16 rows from about 12,300 elements,
+ * 40 from 16,400, 80 from 20,500, 96 from 24,600 and 128 from 28,700.  The workgroups of a row meet in device memory of the
+ * library (24 MiB per GPU, part of a code object that the first such call loads), a launch in a
+ * piece of its own until its end is reported in 4 KiB of pinned host memory per GPU, allocated once
+ * by the first such call there (by a later launch on that GPU, one in some dozens; a call that finds
+ * no piece free and waits queues one that does no more, and calls that do not wait one in 4 ms).  A
+ * call that finds no piece free, 2.7 ms or more of such work being in flight, waits for one as it
+ * would for room in a full queue, at most 4 ms, and not again after a wait in vain until one has
+ * been free; then it runs a kernel that needs none and gives the same bits.  A captured call runs a
+ * third kernel, as calls with more rows than the above do, whose row sum is taken in another order:
+ * in some 1e-7 of rows rstd is rounded to the fp32 value beside the one that an eager call with few
+ * rows takes.
  */
 int addrms_run(void* x, void* residual, const void* weight, float eps,
                int64_t M, int64_t N, int dtype, const addrms_cfg* cfg, void* stream);

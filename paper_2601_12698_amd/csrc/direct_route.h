@@ -32,8 +32,9 @@ constexpr bool direct_instance(int vec, int cpt, int pol, bool rag, bool multi)
 }
 
 constexpr int kSplitRows = 4096;                             // rows of one launch of split rows; more are several launches
-// The memory that they meet in: units of 64 rows (24 KB), 24 MB in all.  A row is at least 32769 elements long, 42 ns of
-// bf16 at 6.2 TB/s, so that all units are taken no sooner than 2.7 ms of such launches are in flight.
+// The memory that they meet in: units of 64 rows (24 KB), 24 MB in all.  A long row is at least 32769 elements long, 42 ns of
+// bf16 at 6.2 TB/s, so that all units are taken no sooner than 2.7 ms of such launches are in flight.  The same of few wide rows on one
+// stream: launches of one unit take 3.3 us and more, of two 5.4.
 constexpr int kSplitUnits = 1024, kSplitUnitRows = 64;
 constexpr int kSplitParts = 16;                              // workgroups a row may be split over
 // The kernels of split rows: pieces per thread and store policy.  With fewer than four pieces 512 workgroups are within 32 MB.
