@@ -504,7 +504,7 @@ int addrms_gate_probe(const void* y, const void* y_ref, const void* residual, co
 /* addrms_gate_probe for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments and the same verdict in counts_out, but the
  * per-workgroup partial counts live in arrays that are part of the library's device code (one copy per GPU, held until
- * the process ends), so this call allocates no device memory, frees nothing and does not wait: its kernels are only
+ * the process ends), so this call allocates no device memory, frees nothing and does not wait for its kernels: they are only
  * enqueued on `stream`, and counts_out is valid once the stream has reached them.  They are one kernel, or two if the
  * stream is capturing.  (The end of one-kernel calls of more than one workgroup, 4096 elements of 16 bits or 2048 of 32, is
  * reported by later ones on the same GPU in 1 KiB of pinned host memory per GPU, allocated once by the first of them.  With 256 of them in flight a call waits for one to

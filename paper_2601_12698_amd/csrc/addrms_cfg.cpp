@@ -240,15 +240,15 @@ int64_t write_through_max() { return hw().last_level_cache_bytes / 8 * 3; }
 //   and 8192; 64 to 1024 threads, with and without XCD_CONTIG, deferred stores and occupancy caps; 45 in all)
 //       3 to 9 MB 0.96-1.18 / 0.94-1.27   13 to 18 MB 0.85-0.97 / 1.06-1.13   20 to 65 MB 0.76-0.87 / 1.004-1.05
 //       85 to 98 MB 0.87-0.98 / 1.02-1.05   160 MB 1.03 / 1.02
-//     PERSISTENT, 67 MB 1.02 / 1.06;  rows that are not whole lines 0.94-0.97 / 1.20-1.22 (as aligned spans 0.90 / 1.03);  two
-//     bytes per access, ragged, 1.36 / 1.49;  fp16+fp32 with eight elements per access, y alone written through (write_through_piece),
+//     PERSISTENT, 67 MB 1.02 / 1.06;  rows that are not whole lines 0.94-0.97 / 1.20-1.22 (as aligned spans, 49 to 98 MB,
+//     0.84-0.90 / 1.03-1.07);  two bytes per access, ragged, 1.36 / 1.49;  fp16+fp32 with eight elements per access, y alone written through (write_through_piece),
 //     0.95-0.99 / 1.03-1.06
 //   silu_and_mul, the same (d = 4096 to 14336)
 //       2 to 35 MB 0.95-1.007 / 1.00-1.06   44 to 88 MB 0.91-0.976 / 1.003-1.036   130 MB 1.02 / 1.02
 //   merge_attn_states, 2 and 13 MB 0.99-1.02 / 0.99-1.06
 // From HBM it gives away some percent of what the next kernel gets back, which finds its input in the memory-side cache.  A search,
 // whose buffers are beyond that cache, loses by it and would leave the configurations it suits best (8192 x 1000 fp16+fp32: aligned
-// spans, 17.65 us non-temporal and 18.4 written through, for partial lines in 18.3): it has the stores as part of what it chooses
+// spans, 17.8 us non-temporal and 18.4 written through, for partial lines in 18.3): it has the stores as part of what it chooses
 // (run_search).
 bool launch_write_through(const addrms_cfg& c, int64_t M, int64_t N, int dtype, int op)
 {

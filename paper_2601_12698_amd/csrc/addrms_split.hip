@@ -26,7 +26,8 @@ __global__ __launch_bounds__(1024) void addrms_split(addr_t x, addr_t r, addr_t 
                                                      unsigned patience)
 {
     // 16-bit rows of whole pieces: so many registers that a CU takes two workgroups of 512 threads, not three (1024 x 131072 bf16 170.5 us
-    // against 176.2, 4096 x 40960 fp16 213.0 against 217.9).
+    // against 176.2, 4096 x 40960 fp16 213.0 against 217.9).  88 of them, v87 being the last, are five waves per SIMD, and so are up to 96
+    // that the compiler may come to need.
     if constexpr (VEC == 8 && CPT == 4 && !RAG) asm volatile("" ::: "v87");
     const uint32_t tpr = shape & 0xffffu, unit = unit_tells >> 1, tells = unit_tells & 1u;
     if (tells && blockIdx.y == 0u) {

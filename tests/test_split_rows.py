@@ -55,6 +55,16 @@ def test_registers_leave_room_for_workgroups():
     assert seen == 32
 
 
+def test_parts_of_whole_16_bit_rows_are_two_to_a_cu():
+    """Five waves per SIMD, no more: two workgroups of 512 threads, which is faster than three."""
+    path = os.path.join(BUILD, "addrms_split.remarks")
+    if not os.path.exists(path):
+        pytest.skip("the library is not built here")
+    with open(path) as f:
+        waves = [r["occupancy"] for name, r in build.parse_remarks(f.read()).items() if re.search(r"addrms_splitILi\dELi8ELi4ELi\dELb0E", name)]
+    assert waves and set(waves) == {5}
+
+
 SHAPES = [
     (("bf16", 8, 32832), "parts=9 threads=512 pieces=1 nontemporal"),
     (("bf16", 1024, 131072), "parts=8 threads=512 pieces=4 nontemporal"),

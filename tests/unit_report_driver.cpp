@@ -48,7 +48,7 @@ static int pieces()
         for (int launch = 0; launch < 4; ++launch) {
             static const uint32_t counts[] = {1, 2, 3, 8, 9, 10, 64};
             const uint32_t all = counts[random(7)];
-            number += 1 + random(3);                         // numbers may have gone to launches of another GPU, or to none
+            number += 1 + random(3);                         // a number may have gone to a launch that failed
             std::vector<uint32_t> left;
             for (uint32_t p = 0; p < all; ++p) left.push_back(p);
             uint32_t finished = 0;
